@@ -8,32 +8,32 @@
 // a token is written in 8-byte pieces that a wavefront's accumulator tiles complete to 128
 // contiguous bytes.
 //
-// Workgroup = 8 wavefronts = a 256-feature x BM-token tile (BM = 256; 128, 64 or 32 for small
-// batches; 128 x 128 for matrices too small to fill the chip with wide tiles), wavefront = 64 features
-// x BM/2 tokens of it (2 x 4 or 2 x 2 MFMA tiles; 32 x BM for the narrowest).  What bounds a tile
-// shape on this chip is the path global memory -> LDS (64 bytes per clock and compute unit): a
-// 128 x 128 tile needs 512 bytes of operands per MFMA, which is that path's whole bandwidth at
-// full MFMA rate (measured: 0.30 of the MFMA peak, 0.40 with half of the loads made redundant);
-// 256 x 256 needs half of it.  k advances in stages of 64, so that an LDS row is one full 128-byte
-// line of its matrix row; a stage (256 x 64 weights, BM x 64 tokens) goes from global memory
-// straight into LDS (global_load_lds_dwordx4: no staging registers) into a ring of two stages
-// (BM = 256: 128 KiB), three (BM = 128: 144 KiB) or four, one workgroup per compute unit, one
-// barrier per stage.  The eight 16-byte pieces of LDS row r are XOR-swizzled with (r >> 1) & 7 so that the
-// 16 lanes of a b128 operand read, which walk 16 rows at one logical piece, hit distinct banks.
-// Inside a stage the loop is skewed by one k16 step: the operands of step s+1 are read while the
-// MFMAs of step s issue, and the last step's operands are carried over the barrier.
+// Two kernels.  linear_phased_kernel (more than 64 tokens): four wavefronts, one per SIMD, each with up to 128 x 128
+// results in accumulation registers; linear_kernel (up to 64 tokens): eight wavefronts, narrow token tiles, bound by
+// fetching the weights.  Both bring k stages of 64 (an LDS row is one full 128-byte line of its matrix row; rows of half a
+// line fetch at less than half the rate: 43 against 95 GB/s per compute unit out of L2) from global memory straight into LDS
+// (global_load_lds_dwordx4: no staging registers).  The eight 16-byte pieces of LDS row r are XOR-swizzled with
+// (r >> 1) & 7 so that the 16 lanes of a b128 operand read, which walk 16 rows at one logical piece, hit distinct banks.
+//
+// The non-temporal hint goes on the weights where ONE token tile covers the batch: every weight byte is then fetched
+// once and the chip streams 7.0 TB/s with it against 6.2 without.  Where several token tiles share a weight tile it
+// must not: lines fetched with it do not stay in L2 for the other compute units of the XCD (58 GB/s per compute unit
+// against 95 for a tile shared by eight of them).
 //
 // Few tokens (a decode-heavy batch): one token tile covers the batch, the weights are read
 // once, and the layer is bound by fetching them (section 3.1); when the grid would leave
 // compute units idle the k range is cut into pieces (split-K) whose fp32 partial tiles a
 // second small kernel adds up in piece order (bitwise reproducible).
 //
-// Workgroup -> tile mapping: blockIdx % 8 selects the XCD; an XCD owns the feature tiles
-// n = xcd, xcd + 8, ... and runs all token tiles of a feature tile back to back, so that the
-// weight tile they share is fetched into that XCD's L2 once.
+// Workgroup -> tile mapping (lin_work_item): blockIdx % 8 selects the XCD; every XCD gets a contiguous run of work items
+// (equal runs, give or take one) in an order that walks groups of four feature tiles, so that the 32 workgroups an XCD
+// runs at a time share weight and token tiles in its L2.  (Dealing whole feature tiles to XCDs, n = xcd, xcd + 8, ...,
+// left ten feature tiles on eight XCDs with two rounds of work on two of them: 2048 x 2560 x 8192 took 161 us, now 81.)
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -52,6 +52,7 @@ constexpr int kLinBN = 256;      // features per workgroup tile
 constexpr int kLinStageK = 64;   // k per stage: one 128-byte line of every row
 constexpr int kLinXcds = 8;
 constexpr int kLinThreads = 512;
+constexpr int kLinSmallTokens = 64;  // up to this many: linear_kernel, beyond: linear_phased_kernel
 
 typedef void __attribute__((address_space(3))) *lin_lds_ptr;
 
@@ -65,8 +66,7 @@ __device__ __forceinline__ void lin_dma_load_16(const uint16_t *base, int byte_o
                  : "s"(lds_addr), "v"(byte_off), "s"(base)
                  : "memory");
 }
-// The same with the non-temporal hint, for the weights: every weight byte is fetched by one workgroup
-// of a token tile, and a layer's weights are far more than the caches hold (+1 to +6 %).
+// The same with the non-temporal hint (weights that one workgroup alone fetches).
 __device__ __forceinline__ void lin_dma_load_16_stream(const uint16_t *base, int byte_off, uint32_t lds_addr) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
                  :
@@ -86,6 +86,29 @@ struct LinearParams {
     int32_t n_tiles, t_tiles, splits;
     int32_t k_per_split;  // multiple of 64
 };
+
+struct LinearItem {
+    int32_t n_tile, t_tile, split;  // n_tile < 0: nothing to do
+};
+// Work item of this workgroup: the XCD's run of the items, which are ordered (group of four feature tiles, k piece,
+// token tile, feature tile of the group).
+constexpr int kLinGroup = 4;
+__device__ __forceinline__ LinearItem lin_work_item(const LinearParams &p) {
+    const int items = p.n_tiles * p.t_tiles * p.splits;
+    const int xcd = blockIdx.x % kLinXcds, j = blockIdx.x / kLinXcds;
+    const int run = items / kLinXcds, extra = items % kLinXcds;
+    if (j >= run + (xcd < extra ? 1 : 0)) return LinearItem{-1, 0, 0};
+    const int it = xcd * run + min(xcd, extra) + j;
+    const int per_group = kLinGroup * p.splits * p.t_tiles;
+    const int group = __builtin_amdgcn_readfirstlane(it / per_group);
+    int rest = it - group * per_group;
+    const int width = min(kLinGroup, p.n_tiles - group * kLinGroup);
+    // wave-uniform by construction; tell the compiler (its integer division goes through the vector unit)
+    const int split = __builtin_amdgcn_readfirstlane(rest / (width * p.t_tiles));
+    rest -= split * width * p.t_tiles;
+    const int t_tile = __builtin_amdgcn_readfirstlane(rest / width);
+    return LinearItem{group * kLinGroup + rest - t_tile * width, t_tile, split};
+}
 
 // BM tokens per tile; WT wavefronts side by side along the tokens (the other 8 / WT along the features);
 // RING stages of LDS; BN features per tile (256, or 128 for matrices too small to fill the chip with wide tiles).
@@ -107,14 +130,9 @@ __global__ __launch_bounds__(kLinThreads, 1) void linear_kernel(LinearParams p) 
     __shared__ __attribute__((aligned(16))) uint16_t smem[RING * STAGE];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // work item of this workgroup
-    const int xcd = blockIdx.x % kLinXcds;
-    int j = blockIdx.x / kLinXcds;
-    const int t_tile = j % p.t_tiles;
-    j /= p.t_tiles;
-    const int split = j % p.splits;
-    const int n_tile = xcd + kLinXcds * (j / p.splits);
-    if (n_tile >= p.n_tiles) return;
+    const LinearItem wi = lin_work_item(p);
+    if (wi.n_tile < 0) return;
+    const int n_tile = wi.n_tile, t_tile = wi.t_tile, split = wi.split;
     const int n0 = n_tile * BN;
     const int t0 = t_tile * BM;
     const int k_begin = split * p.k_per_split;
@@ -256,6 +274,271 @@ __global__ __launch_bounds__(kLinThreads, 1) void linear_kernel(LinearParams p) 
     }
 }
 
+// ---------------------------------------------------------------------------------------
+// More than 64 tokens: four wavefronts in a 2 x 2 grid, one per SIMD.  A wavefront owns (A0 + A1) x (B0 + B1) MFMA tiles
+// of 32 features x 32 tokens (4 x 4 in the largest shape: all 256 accumulation registers), so that a 256 x 256 tile reads
+// 8 operands from LDS per 16 MFMAs; eight wavefronts of 64 x 128 read 12, which together with the incoming stages is all
+// the LDS port delivers at full MFMA rate (384 + 128 of 512 clocks), and they were bound by it.
+//
+// A stage is worked off in phases: half A0 of the wavefront's weight rows x half B0 of its token rows, A0 x B1, A1 x B1,
+// A1 x B0, each over the stage's 64 k.  While a phase's MFMAs issue, the operands of the half that a later phase needs are
+// read into registers (8 reads per 16 MFMAs), and the barrier at the head of the next phase then frees that half's LDS for
+// the stage RING stages on.  So LDS is refilled half by half and a fetch has 1.75 stages (RING = 2) to land; waiting for
+// whole stages gives it less than one of the two that 128 KiB hold, and the loop then waits for memory: 2048 x 8192 x 7168
+// on all-zero data 158 us by whole stages, 121 us by halves.  On N(0,1) data the matrix pipes' power sets the clock:
+// 195-205 us before (eight wavefronts, whole stages), 174-182 us now = 1.3-1.38 PFLOP/s; its MFMAs alone take 146 us.
+// One wavefront per SIMD leaves nobody to cover a wait, so a phase is laid out by hand: slot m issues its share of reads and
+// fetches, then MFMA m, and a scheduling barrier keeps the compiler from moving them (343 instructions per 128 MFMAs).
+// Accumulators go out through LDS as whole rows (16-byte stores, 128 to 256 contiguous bytes per token and wavefront): 5 us
+// less per tile than 8-byte stores from the accumulator layout.
+// ---------------------------------------------------------------------------------------
+template <int A0, int A1, int B0, int B1, int RING, bool STREAM>
+__global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {
+    constexpr int KS = kLinStageK;
+    constexpr int NI = A0 + A1, NJ = B0 + B1;    // MFMA tiles of a wavefront along features, tokens
+    constexpr int BN = 64 * NI, BM = 64 * NJ;    // features, tokens of the workgroup's tile
+    constexpr int BLOCK = 32 * KS;               // elements of 32 rows of a stage
+    constexpr int STAGE = 2 * (NI + NJ) * BLOCK;
+    // halves in the order in which they are read; each holds its rows for both wavefronts along its side
+    constexpr int HA0 = 0, HB0 = 1, HB1 = 2, HA1 = 3;
+    constexpr int kBlocks[4] = {A0, B0, B1, A1};
+    constexpr int kOff[4] = {0, 2 * NI * BLOCK, 2 * (NI + B0) * BLOCK, 2 * A0 * BLOCK};
+    constexpr int LOADS = 2 * (NI + NJ);         // 1 KiB loads of a wavefront per stage: two per 32-row block
+    static_assert(A0 > 0 && A1 > 0 && B0 > 0 && RING >= 2, "two weight halves, one or two token halves");
+    static_assert(RING * LOADS < 64, "the vector-memory counter holds 63 loads");
+    static_assert(RING * STAGE * 2 <= 160 * 1024 && RING * STAGE * 2 >= 4 * 16384, "LDS of a compute unit; the output's transposition needs 16 KiB per wavefront");
+    __shared__ __attribute__((aligned(16))) uint16_t smem[RING * STAGE];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const LinearItem wi = lin_work_item(p);
+    if (wi.n_tile < 0) return;
+    const int n0 = wi.n_tile * BN, t0 = wi.t_tile * BM;
+    const int k_begin = wi.split * p.k_per_split;
+    const int n_stages = (min(p.K, k_begin + p.k_per_split) - k_begin) / KS;
+    auto row_key = [](int row) { return (row >> 1) & 7; };
+
+    // ---- global -> LDS.  LDS row l of a half of nb blocks is row l % 32 of block (l / 32) % nb of side-wavefront
+    // l / (32 nb); wavefront w moves rows 16 nb w .. as 2 nb loads of 8 rows.  Rows past the matrix re-read its last row.
+    const uint16_t *w_base = p.w + (int64_t)n0 * p.K + k_begin;
+    const uint16_t *x_base = p.x + (int64_t)t0 * p.K + k_begin;
+    const uint32_t smem_addr = (uint32_t)(uintptr_t)(lin_lds_ptr)(smem);
+    int off[LOADS];  // this lane's byte offsets: halves A0, B0, B1, A1 one after the other
+    auto half_loads = [&](int h) { return 2 * kBlocks[h]; };
+    auto first_load = [&](int h) { return 2 * ((h > 0 ? A0 : 0) + (h > 1 ? B0 : 0) + (h > 2 ? B1 : 0)); };
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        const bool weights = h == HA0 || h == HA1;
+        const int nb = kBlocks[h];
+        const int before = h == HA1 ? A0 : h == HB1 ? B0 : 0;  // blocks of the side's first half
+#pragma unroll
+        for (int i = 0; i < 2 * nb; ++i) {
+            const int l = wave * 16 * nb + i * 8 + lane / 8;
+            const int row = l / (32 * nb) * 32 * (weights ? NI : NJ) + (before + l / 32 % nb) * 32 + l % 32;
+            const int base = weights ? n0 : t0, limit = weights ? p.N : p.T;
+            off[first_load(h) + i] = ((min(base + row, limit - 1) - base) * p.K + ((lane % 8) ^ row_key(l % 32)) * 8) * 2;
+        }
+    }
+    // load i of half h of stage `stage` into ring slot `slot`; stages past the range re-read the last one, so that every
+    // phase issues the same loads and one wait count serves the whole loop
+    auto issue = [&](auto ht, int i, int stage, int slot) {
+        constexpr int h = decltype(ht)::value;
+        const int k = min(stage, n_stages - 1) * KS;
+        const uint32_t dst = smem_addr + (uint32_t)(slot * STAGE + kOff[h] + wave * kBlocks[h] * 16 * KS) * 2 + (uint32_t)i * 1024;
+        if (h == HB0 || h == HB1) lin_dma_load_16(x_base + k, off[first_load(h) + i], dst);
+        else if (STREAM) lin_dma_load_16_stream(w_base + k, off[first_load(h) + i], dst);
+        else lin_dma_load_16(w_base + k, off[first_load(h) + i], dst);
+    };
+
+    // ---- operands: wavefront (wn, wt) owns features 32 NI wn .. and tokens 32 NJ wt .. of the tile
+    const int wn = wave & 1, wt = wave >> 1;
+    const int r = lane & 31, g = lane >> 5;
+    int piece[4];  // element offset of k16 step s inside a 32-row block for this lane
+#pragma unroll
+    for (int s = 0; s < 4; ++s) piece[s] = r * KS + ((2 * s + g) ^ row_key(r)) * 8;
+    constexpr int BX = B0 > B1 ? B0 : B1;
+    lbf16x8 fa[2][A0 > A1 ? A0 : A1][4];  // weight operands of halves A0, A1
+    lbf16x8 fb[2][BX][4];                 // token operands: B0 and B1 swap sets from stage to stage
+    // read q (k16 step q / nb, block q % nb) of half h from ring slot `slot`; tokens go to set `set`
+    auto read = [&](auto ht, auto set, int q, int slot) {
+        constexpr int h = decltype(ht)::value;
+        constexpr int nb = kBlocks[h] > 0 ? kBlocks[h] : 1;
+        const int s = q / nb, b = q % nb;
+        const int side = (h == HA0 || h == HA1) ? wn : wt;
+        const lbf16x8 v = __builtin_bit_cast(lbf16x8, *reinterpret_cast<const lu32x4 *>(smem + slot * STAGE + kOff[h] + (side * nb + b) * BLOCK + piece[s]));
+        if (h == HA0 || h == HA1) fa[h == HA1 ? 1 : 0][b][s] = v;
+        else fb[decltype(set)::value][b][s] = v;
+    };
+    lf32x16 acc[NI][NJ];
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    auto mfma = [&](int a, int na, int nb, int b_first, const lbf16x8 (&b_ops)[BX][4], int m) {
+        const int s = m / (na * nb), e = m % (na * nb);
+        const int j = e / na, i = (j & 1) ? na - 1 - e % na : e % na;  // consecutive MFMAs share an operand
+        lf32x16 &c = acc[(a ? A0 : 0) + i][b_first + j];
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a][i][s], b_ops[j][s], c, 0, 0, 0);
+    };
+    using S0 = std::integral_constant<int, 0>;
+    using S1 = std::integral_constant<int, 1>;
+    using TA0 = std::integral_constant<int, HA0>;
+    using TB0 = std::integral_constant<int, HB0>;
+    using TB1 = std::integral_constant<int, HB1>;
+    using TA1 = std::integral_constant<int, HA1>;
+
+    // The head of a phase: at most `keep` loads in flight, so the half about to be read has landed; this wavefront's reads
+    // are in registers; and behind the barrier both hold for every wavefront.
+#define LIN_PHASE_HEAD(keep)            \
+    LIN_WAIT_VMCNT_AND_LDS(keep);       \
+    __builtin_amdgcn_s_barrier();       \
+    asm volatile("" ::: "memory")
+
+    // Prologue: RING stages on their way, A0 and B0 of the first one into registers.
+#pragma unroll
+    for (int st = 0; st < RING; ++st) {
+#pragma unroll
+        for (int i = 0; i < half_loads(HA0); ++i) issue(TA0{}, i, st, st);
+#pragma unroll
+        for (int i = 0; i < half_loads(HB0); ++i) issue(TB0{}, i, st, st);
+#pragma unroll
+        for (int i = 0; i < half_loads(HB1); ++i) issue(TB1{}, i, st, st);
+#pragma unroll
+        for (int i = 0; i < half_loads(HA1); ++i) issue(TA1{}, i, st, st);
+    }
+    LIN_PHASE_HEAD(RING * LOADS - 2 * A0);
+#pragma unroll
+    for (int q = 0; q < 4 * A0; ++q) read(TA0{}, S0{}, q, 0);
+    LIN_PHASE_HEAD(RING * LOADS - 2 * A0 - 2 * B0);
+    if constexpr (B1 > 0) {
+#pragma unroll
+        for (int i = 0; i < half_loads(HA0); ++i) issue(TA0{}, i, RING, 0);
+    }
+#pragma unroll
+    for (int q = 0; q < 4 * B0; ++q) read(TB0{}, S0{}, q, 0);
+
+    // One phase: weight half a x token half b (operand set bset).  Reads half rh from slot rslot (tokens into set rset) over
+    // the first three quarters of its MFMAs, and refills half ih, whose reads the barrier closes, with stage istage.
+    // Loads younger than half rh when the phase starts: RING stages less rh and less ih, which is issued next.
+    auto phase = [&](auto at, auto bt, auto bset, auto rht, auto rset, int rslot, auto iht, int istage, int islot) {
+        constexpr int a = decltype(at)::value, b = decltype(bt)::value, rh = decltype(rht)::value, ih = decltype(iht)::value;
+        constexpr int na = a ? A1 : A0, nb = b ? B1 : B0, NM = na * nb * 4;
+        constexpr int reads = 4 * kBlocks[rh], loads = 2 * kBlocks[ih];
+        constexpr int span = NM * 3 / 4;
+        LIN_PHASE_HEAD(RING * LOADS - 2 * kBlocks[rh] - 2 * kBlocks[ih]);
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+            const int q0 = reads * min(m, span) / span, q1 = reads * min(m + 1, span) / span;
+#pragma unroll
+            for (int q = 0; q < reads; ++q)
+                if (q >= q0 && q < q1) read(rht, rset, q, rslot);
+#pragma unroll
+            for (int l = 0; l < loads; ++l)
+                if (l >= loads * m / NM && l < loads * (m + 1) / NM) issue(iht, l, istage, islot);
+            mfma(a, na, nb, b ? B0 : 0, fb[decltype(bset)::value], m);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // The same without a second token half: A1 is read under A0 x B0, the next stage's B0 and A0 under A1 x B0, and a phase
+    // refills what the other one read.  Loads younger than what it reads: RING - 1 stages.
+    auto phase_one_half = [&](auto at, auto bset, auto rset, int rslot, int istage, int islot) {
+        constexpr int a = decltype(at)::value;
+        constexpr int na = a ? A1 : A0, NM = na * B0 * 4;
+        constexpr int reads = a ? 4 * (B0 + A0) : 4 * A1, loads = a ? 2 * A1 : 2 * (A0 + B0);
+        LIN_PHASE_HEAD((RING - 1) * LOADS);
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+#pragma unroll
+            for (int q = 0; q < reads; ++q)
+                if (q >= reads * m / NM && q < reads * (m + 1) / NM) {
+                    if (!a) read(TA1{}, S0{}, q, rslot);
+                    else if (q < 4 * B0) read(TB0{}, rset, q, rslot);
+                    else read(TA0{}, S0{}, q - 4 * B0, rslot);
+                }
+#pragma unroll
+            for (int l = 0; l < loads; ++l)
+                if (l >= loads * m / NM && l < loads * (m + 1) / NM) {
+                    if (a) issue(TA1{}, l, istage, islot);
+                    else if (l < 2 * A0) issue(TA0{}, l, istage, islot);
+                    else issue(TB0{}, l - 2 * A0, istage, islot);
+                }
+            mfma(a, na, B0, 0, fb[decltype(bset)::value], m);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    int slot = 0;
+    auto stage = [&](int st, auto par) {
+        constexpr int P = decltype(par)::value;           // B0 of this stage is in set P
+        using Own = std::integral_constant<int, P>;
+        using Other = std::integral_constant<int, P ^ 1>;
+        if (RING == 2) slot = P;                          // known when the code is generated
+        const int next = RING == 2 ? P ^ 1 : slot + 1 == RING ? 0 : slot + 1;
+        if constexpr (B1 > 0) {
+            phase(S0{}, S0{}, Own{}, TB1{}, Other{}, slot, TB0{}, st + RING, slot);
+            phase(S0{}, S1{}, Other{}, TA1{}, S0{}, slot, TB1{}, st + RING, slot);
+            phase(S1{}, S1{}, Other{}, TA0{}, S0{}, next, TA1{}, st + RING, slot);
+            phase(S1{}, S0{}, Own{}, TB0{}, Other{}, next, TA0{}, st + 1 + RING, next);
+        } else {
+            phase_one_half(S0{}, Own{}, S0{}, slot, st + RING, slot);
+            phase_one_half(S1{}, Own{}, Other{}, next, st + RING, slot);
+        }
+        slot = next;
+    };
+    int st = 0;
+    for (; st + 1 < n_stages; st += 2) {
+        stage(st, S0{});
+        stage(st + 1, S1{});
+    }
+    if (st < n_stages) stage(st, S0{});
+
+    // ---- output.  The padding loads have landed and every wavefront is done with the operands: LDS (16 KiB per wavefront)
+    // turns 32 tokens at a time into rows; 16-byte piece c of row r sits at c ^ (r & 15).  Accumulator element e of lane
+    // (r, g) of tile (i, j) is feature 32i + 8(e/4) + 4g + e%4, token 32j + r.
+    LIN_PHASE_HEAD(0);
+#undef LIN_PHASE_HEAD
+    const int f_wave = n0 + wn * 32 * NI, t_wave = t0 + wt * 32 * NJ;
+    char *const out = reinterpret_cast<char *>(smem) + wave * 16384;
+    const bool final_rows = p.splits == 1;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (final_rows) {
+            constexpr int PIECES = 4 * NI;                // of a token's row of this wavefront, bf16
+            char *const buf = out + (j & 1) * 8192;
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const lf32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+                    *reinterpret_cast<lu32x2 *>(buf + r * 256 + ((i * 4 + q) ^ (r & 15)) * 16 + g * 8) = __builtin_bit_cast(lu32x2, __builtin_convertvector(v, lbf16x4));
+                }
+#pragma unroll
+            for (int u = 0; u < PIECES / 2; ++u) {
+                const int row = (u * 64 + lane) / PIECES, c = (u * 64 + lane) % PIECES;
+                const lu32x4 v = *reinterpret_cast<const lu32x4 *>(buf + row * 256 + (c ^ (row & 15)) * 16);
+                const int t = t_wave + j * 32 + row, f = f_wave + c * 8;
+                if (t < p.T && f < p.N) *reinterpret_cast<lu32x4 *>(p.y + (int64_t)t * p.N + f) = v;
+            }
+        } else {
+            constexpr int PIECES = 8 * NI;                // the same, fp32
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<lf32x4 *>(out + r * 512 + ((i * 8 + 2 * q + g) ^ (r & 15)) * 16) =
+                        lf32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+#pragma unroll
+            for (int u = 0; u < PIECES / 2; ++u) {
+                const int row = (u * 64 + lane) / PIECES, c = (u * 64 + lane) % PIECES;
+                const lf32x4 v = *reinterpret_cast<const lf32x4 *>(out + row * 512 + (c ^ (row & 15)) * 16);
+                const int t = t_wave + j * 32 + row, f = f_wave + c * 4;
+                if (t < p.T && f < p.N) *reinterpret_cast<lf32x4 *>(p.part + ((int64_t)wi.split * p.T + t) * p.N + f) = v;
+            }
+        }
+    }
+}
+
 // Adds the split-K pieces of every output element in piece order and rounds once to bf16.
 __global__ __launch_bounds__(256) void linear_reduce_kernel(const float *part, uint16_t *y, int64_t elems, int splits) {
     const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
@@ -276,10 +559,66 @@ __global__ __launch_bounds__(256) void linear_reduce_kernel(const float *part, u
 
 }  // namespace
 
+// Tile shapes of linear_phased_kernel, with the microseconds of one 64-k stage when every compute unit runs one, for
+// batches of several token tiles and of one (weights straight from memory, with the non-temporal hint).
+struct PhasedShape {
+    int32_t features, tokens;
+    double stage_us, stage_us_one_tile;
+};
+constexpr PhasedShape kPhasedShapes[] = {
+    {256, 256, 0.654, 0.619}, {256, 192, 0.538, 0.588}, {192, 256, 0.547, 0.545}, {192, 192, 0.502, 0.573},
+    {256, 128, 0.530, 0.597}, {128, 256, 0.487, 0.502}, {192, 128, 0.465, 0.552}, {128, 192, 0.413, 0.476},
+    {128, 128, 0.377, 0.414}, {256, 64, 0.494, 0.630},  {192, 64, 0.403, 0.526},  {128, 64, 0.292, 0.346},
+};
+
+// More than 64 tokens.  Cost of a tiling in microseconds, fitted to 3,600 timings (the 13 layer shapes of four models, 15
+// token counts from 40 to 2048, every tile shape and piece count that could compete; a tiling's time is met within 7 % rms,
+// the chosen one is 2 % slower than the best measured on average): the largest of
+//   rounds of workgroups (one per compute unit) x (stages per piece x stage time + the tile's way out, 8.2 us for 256 x 256),
+//   the padded product at 2.26 PFLOP/s, and the weights at 8.05 TB/s,
+// plus 0.53 of the other two (none hides the others entirely), 4.3 us per launch, and for pieces of k their fp32 partial
+// tiles, written and read back at 6.2 TB/s, and 1.2 us for the second kernel.
+static LinearPlan plan_phased(int32_t T, int32_t N, int32_t K, size_t workspace_bytes) {
+    const int64_t k_stages = K / kLinStageK;
+    const int64_t per_split_bytes = (int64_t)T * N * 4;
+    const double memory_us = 2.0 * N * K / 8.05e6;
+    LinearPlan best{};
+    double best_cost = -1.0;
+    for (const PhasedShape &sh : kPhasedShapes) {
+        const int64_t n_tiles = (N + sh.features - 1) / sh.features;
+        const int64_t t_tiles = (T + sh.tokens - 1) / sh.tokens;
+        const int64_t tiles = n_tiles * t_tiles;
+        const double stage_us = t_tiles == 1 ? sh.stage_us_one_tile : sh.stage_us;
+        const double out_us = 8.2 * sh.features * sh.tokens / 65536.0;
+        const double product_us = 2.0 * (double)tiles * sh.features * sh.tokens * K / 2.26e9;
+        for (int64_t s = 1; s <= 16 && (s == 1 || (s * 4 <= k_stages && tiles * s <= 1024)); ++s) {
+            if (s > 1 && (size_t)(s * per_split_bytes) > workspace_bytes) break;
+            const int64_t stages = (k_stages + s - 1) / s;
+            const int64_t pieces = (k_stages + stages - 1) / stages;
+            if (pieces != s) continue;  // the same stages per piece in fewer pieces has been looked at
+            const double rounds = (double)((tiles * s + 255) / 256);
+            const double compute_us = rounds * ((double)stages * stage_us + out_us);
+            const double longest = std::max(compute_us, std::max(product_us, memory_us));
+            double c = 4.3 + longest + 0.53 * (compute_us + product_us + memory_us - longest);
+            if (s > 1) c += 1.2 + 2.0 * (double)s * (double)per_split_bytes / 6.2e6;
+            if (best_cost < 0.0 || c < best_cost) {
+                best_cost = c;
+                best.feature_tile = sh.features;
+                best.token_tile = sh.tokens;
+                best.n_tiles = (int32_t)n_tiles;
+                best.t_tiles = (int32_t)t_tiles;
+                best.splits = (int32_t)s;
+                best.k_per_split = s == 1 ? K : (int32_t)(stages * kLinStageK);
+            }
+        }
+    }
+    return best;
+}
+
 LinearPlan plan_linear(int32_t T, int32_t N, int32_t K, size_t workspace_bytes) {
+    if (T > kLinSmallTokens) return plan_phased(T, N, K, workspace_bytes);
     // Rough cost of a tiling, in microseconds: rounds of workgroups (one per compute unit) x stages per piece x
-    // the time of a stage (measured: ~1.95 us for a 256-token tile; ~1.3 us for the narrower ones, where
-    // fetching the weights bounds it), plus, when the k range is cut into s pieces so that a small grid
+    // the time of a stage (fetching the weights bounds it: ~1.3 us for 256 features, ~0.7 us for 128), plus, when the k range is cut into s pieces so that a small grid
     // fills the chip, the fp32 partial tiles (written, read back and added by a second kernel) at
     // ~3 TB/s and that kernel's launch.  Pieces keep at least 4 stages (256 k) and must fit the workspace.
     const int64_t k_stages = K / kLinStageK;
@@ -291,12 +630,7 @@ LinearPlan plan_linear(int32_t T, int32_t N, int32_t K, size_t workspace_bytes) 
         const int64_t n_tiles = (N + feature_tile - 1) / feature_tile;
         const int64_t t_tiles = (T + token_tile - 1) / token_tile;
         const int64_t tiles = n_tiles * t_tiles;
-        // a narrow tile next to others of its feature tile shares the weights and is bound by arithmetic (~15 % dearer
-        // per token than the 256-token tile); alone it is bound by fetching them.  The 128 x 128 tile is bound by
-        // the path global memory -> LDS: ~0.75 us for a quarter of the wide tile's arithmetic.
-        // The 128 x 64 tile of small batches moves half the weight bytes of the 256-feature tiles per stage.
-        const double stage_us = feature_tile == 128 ? (token_tile == 64 ? 0.7 : 0.75)
-                                                    : token_tile == 256 ? 1.95 : (t_tiles >= 2 ? 1.12 : 1.3);
+        const double stage_us = feature_tile == 128 ? 0.7 : 1.3;
         for (int64_t s = 1; s <= 16 && (s == 1 || s * 4 <= k_stages); ++s) {
             if (s > 1 && (size_t)(s * per_split_bytes) > workspace_bytes) break;
             const int64_t rounds = (tiles * s + slots - 1) / slots;
@@ -315,18 +649,10 @@ LinearPlan plan_linear(int32_t T, int32_t N, int32_t K, size_t workspace_bytes) 
             }
         }
     };
-    // Token tile: the smallest that holds a small batch; from 65 tokens on, 256 tokens per tile halve the
-    // operand traffic per MFMA, 128 waste less of a ragged batch and give twice the workgroups, and 128 x 128
-    // tiles give four times the workgroups to a matrix that is too small to fill the chip otherwise.
-    // Small batches are bound by fetching the weights: 128-feature tiles give a large matrix enough workgroups
-    // to fill the chip without cutting k (no partial tiles, no second kernel).
-    if (T <= 32) { consider(256, 32); consider(128, 64); }
-    else if (T <= 64) { consider(256, 64); consider(128, 64); }
-    else {
-        consider(256, 256);
-        consider(256, 128);
-        consider(128, 128);
-    }
+    // Token tile: the smallest that holds the batch.  128-feature tiles give a large matrix enough workgroups to fill the
+    // chip without cutting k (no partial tiles, no second kernel).
+    consider(256, T <= 32 ? 32 : 64);
+    consider(128, 64);
     return best_plan;
 }
 
@@ -339,23 +665,51 @@ int launch_linear(const LinearPlan &pl, const void *x, const void *w, void *y, i
     p.part = static_cast<float *>(workspace);
     p.T = T; p.N = N; p.K = K;
     p.n_tiles = pl.n_tiles; p.t_tiles = pl.t_tiles; p.splits = pl.splits; p.k_per_split = pl.k_per_split;
-    const int64_t n_rounds = (pl.n_tiles + kLinXcds - 1) / kLinXcds;
-    const int64_t blocks = kLinXcds * n_rounds * pl.t_tiles * pl.splits;
+    const int64_t items = (int64_t)pl.n_tiles * pl.t_tiles * pl.splits;
+    const int64_t blocks = (items + kLinXcds - 1) / kLinXcds * kLinXcds;
     if (blocks > 0x7FFFFFFF) return (int)hipErrorInvalidValue;  // more workgroups than a grid holds
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // LDS: 6 x 24 KiB, 4 x 32 KiB, 2 x 64 KiB, 3 x 48 KiB, 3 x 40 KiB, 4 x 36 KiB
-    if (pl.feature_tile == 128 && pl.token_tile == 64)
-        hipLaunchKernelGGL((linear_kernel<64, 2, 6, kLinStageK, 128>), dim3((unsigned)blocks), dim3(kLinThreads), 0, st, p);
-    else if (pl.feature_tile == 128)
-        hipLaunchKernelGGL((linear_kernel<128, 2, 4, kLinStageK, 128>), dim3((unsigned)blocks), dim3(kLinThreads), 0, st, p);
-    else if (pl.token_tile == 256)
-        hipLaunchKernelGGL((linear_kernel<256, 2, 2>), dim3((unsigned)blocks), dim3(kLinThreads), 0, st, p);
-    else if (pl.token_tile == 128)
-        hipLaunchKernelGGL((linear_kernel<128, 2, 3>), dim3((unsigned)blocks), dim3(kLinThreads), 0, st, p);
-    else if (pl.token_tile == 64)
-        hipLaunchKernelGGL((linear_kernel<64, 1, 3>), dim3((unsigned)blocks), dim3(kLinThreads), 0, st, p);
-    else
-        hipLaunchKernelGGL((linear_kernel<32, 1, 4>), dim3((unsigned)blocks), dim3(kLinThreads), 0, st, p);
+    const dim3 grid((unsigned)blocks);
+    if (T > kLinSmallTokens) {
+        const bool one_token_tile = pl.t_tiles == 1;
+        auto go = [&](auto a0, auto a1, auto b0, auto b1, auto ring) {
+            constexpr int A0 = decltype(a0)::value, A1 = decltype(a1)::value, B0 = decltype(b0)::value, B1 = decltype(b1)::value;
+            if (pl.feature_tile != 64 * (A0 + A1) || pl.token_tile != 64 * (B0 + B1)) return;
+            if constexpr (B1 > 0) {  // a 64-token tile never covers these batches alone
+                if (one_token_tile) {
+                    hipLaunchKernelGGL((linear_phased_kernel<A0, A1, B0, B1, decltype(ring)::value, true>), grid, dim3(256), 0, st, p);
+                    return;
+                }
+            }
+            hipLaunchKernelGGL((linear_phased_kernel<A0, A1, B0, B1, decltype(ring)::value, false>), grid, dim3(256), 0, st, p);
+        };
+        using I0 = std::integral_constant<int, 0>;
+        using I1 = std::integral_constant<int, 1>;
+        using I2 = std::integral_constant<int, 2>;
+        using I3 = std::integral_constant<int, 3>;
+        using I4 = std::integral_constant<int, 4>;
+        using I5 = std::integral_constant<int, 5>;
+        using I6 = std::integral_constant<int, 6>;
+        // LDS: RING x 128 x (features + tokens) bytes, 112 to 160 KiB
+        go(I2{}, I2{}, I2{}, I2{}, I2{});
+        go(I2{}, I2{}, I2{}, I1{}, I2{});
+        go(I2{}, I1{}, I2{}, I2{}, I2{});
+        go(I2{}, I1{}, I2{}, I1{}, I3{});
+        go(I2{}, I2{}, I1{}, I1{}, I3{});
+        go(I1{}, I1{}, I2{}, I2{}, I3{});
+        go(I2{}, I1{}, I1{}, I1{}, I4{});
+        go(I1{}, I1{}, I2{}, I1{}, I4{});
+        go(I1{}, I1{}, I1{}, I1{}, I5{});
+        go(I2{}, I2{}, I1{}, I0{}, I4{});
+        go(I2{}, I1{}, I1{}, I0{}, I5{});
+        go(I1{}, I1{}, I1{}, I0{}, I6{});
+    } else if (pl.feature_tile == 128) {  // LDS: 6 x 24 KiB, 3 x 40 KiB, 4 x 36 KiB
+        hipLaunchKernelGGL((linear_kernel<64, 2, 6, kLinStageK, 128>), grid, dim3(kLinThreads), 0, st, p);
+    } else if (pl.token_tile == 64) {
+        hipLaunchKernelGGL((linear_kernel<64, 1, 3>), grid, dim3(kLinThreads), 0, st, p);
+    } else {
+        hipLaunchKernelGGL((linear_kernel<32, 1, 4>), grid, dim3(kLinThreads), 0, st, p);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || pl.splits == 1) return (int)e;
     const int64_t elems = (int64_t)T * N;

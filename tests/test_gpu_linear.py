@@ -118,3 +118,42 @@ def test_model_shapes_sampled(hx):
         rows = sorted(set([0, T - 1, 127 % T, 128 % T] + rng.integers(0, T, 12).tolist()))
         cols = sorted(set([0, N - 1, 127, 128, 1023, 1024] + rng.integers(0, N, 40).tolist()))
         run(hx, T, N, K, seed=21, rows=rows, cols=cols)
+
+
+# Batches of more than 64 tokens: one shape per tile of that path (features x tokens), uncut and cut along k, with one
+# token tile and with several; ragged in tokens and (where it can be) in features, odd and even numbers of k stages.
+@pytest.mark.parametrize("T,N,K", [
+    (65, 128, 64), (300, 384, 704), (65, 384, 704),                            # 128 x 64, one stage, and in two pieces
+    (1025, 2176, 704), (129, 3968, 3008), (257, 12416, 704),                   # 192 x 64 uncut and cut, 256 x 64
+    (900, 3968, 704), (900, 1152, 2496), (65, 8320, 1984),                     # 128 x 128
+    (1025, 3968, 704), (1025, 1280, 4032), (129, 6272, 3008),                  # 128 x 192
+    (1025, 6272, 704), (1025, 2176, 8128), (193, 8320, 3008),                  # 128 x 256
+    (577, 8320, 704), (577, 1920, 8128), (65, 8320, 6080),                     # 192 x 128
+    (900, 8320, 704), (1025, 1920, 6080), (129, 8320, 8128),                   # 192 x 192
+    (1000, 12160, 64), (450, 6272, 6080), (193, 12416, 5056),                  # 192 x 256
+    (577, 12416, 704), (577, 2560, 8128), (65, 12416, 4032),                   # 256 x 128
+    (1025, 8320, 704), (577, 4992, 6080), (129, 12416, 5056),                  # 256 x 192
+    (1025, 12416, 704), (450, 8320, 8128)])                                    # 256 x 256
+def test_tiles_of_large_batches(hx, T, N, K):
+    binding, harness = hx
+    print("linear case T", T, "N", N, "K", K, flush=True)
+    rng = np.random.default_rng([T, N, K])
+    x_bits = wl.normal_bf16((T, 0x58), (T, K))
+    w = torch.randn(N, K, device="cuda", dtype=torch.bfloat16, generator=torch.Generator(device="cuda").manual_seed(N + K))
+    x = harness.bits_to_device(x_bits)
+    room = torch.full((T + 3, N), float("nan"), device="cuda", dtype=torch.bfloat16)   # rows behind y must stay as they are
+    scratch = torch.empty(max(binding.linear_workspace_bytes(T, N, K), 16), dtype=torch.uint8, device="cuda")
+    binding.linear(x, w, room[:T], scratch)
+    torch.cuda.synchronize()
+    assert torch.isnan(room[T:]).all() and torch.isfinite(room[:T]).all()
+    got = harness.bf16_tensor_to_f64(room[:T])
+    rows = sorted(set([0, T - 1, 63, 64] + rng.integers(0, T, 12).tolist()))
+    cols = sorted(set([0, N - 1, N - 128, 127] + rng.integers(0, N, 40).tolist()))
+    w_bits = harness.device_to_bits(w[torch.as_tensor(cols, device="cuda")])
+    ref = oracle.linear(x_bits, w_bits, rows=rows, cols=list(range(len(cols))))
+    check(got[np.ix_(rows, cols)], ref, x_bits, w_bits, rows, list(range(len(cols))), "T%d N%d K%d" % (T, N, K))
+    # ... and every element against a float32 product: both sides' errors are far below the one rounding to bf16
+    whole = x.float() @ w.float().t()
+    y = room[:T].float()
+    mag = 2.0 ** -18 * (K ** 0.5) * 8                                                   # 2^-20 sum |x w| of N(0,1) rows, generously
+    assert ((y - whole).abs() <= 2.0 ** -7 * whole.abs() + mag).all()
