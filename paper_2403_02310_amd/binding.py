@@ -86,13 +86,13 @@ lib.sarathi_set_option.argtypes = [_vp, ctypes.c_char_p, ctypes.c_int64]
 lib.sarathi_get_kernel_times.restype = ctypes.c_int
 lib.sarathi_get_kernel_times.argtypes = [_vp, ctypes.POINTER(KernelTimes)]
 lib.sarathi_kv_append.restype = ctypes.c_int
-lib.sarathi_kv_append.argtypes = [_vp, _vp, _vp, _vp, _vp, _vp, _i32p, _i32p, _i32p,
+lib.sarathi_kv_append.argtypes = [_vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp,  # length arrays: an address or an int32 pointer
                                   ctypes.c_int32, ctypes.c_int32, ctypes.c_int64, _vp, _vp]
 lib.sarathi_hybrid_attention.restype = ctypes.c_int
-lib.sarathi_hybrid_attention.argtypes = [_vp, _vp, _vp, _vp, _vp, _i32p, _i32p, _i32p,
+lib.sarathi_hybrid_attention.argtypes = [_vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp,
                                          ctypes.c_int32, ctypes.c_int32, ctypes.c_int64, ctypes.c_float, _vp, _vp, _vp]
 lib.sarathi_hybrid_attention_noalloc.restype = ctypes.c_int
-lib.sarathi_hybrid_attention_noalloc.argtypes = [_vp, _vp, _vp, _vp, _vp, _i32p, _i32p, _i32p,
+lib.sarathi_hybrid_attention_noalloc.argtypes = [_vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp,
                                                  ctypes.c_int32, ctypes.c_int32, ctypes.c_int64, ctypes.c_float, _vp, _vp]
 lib.sarathi_plan_hybrid_attention.restype = ctypes.c_int
 lib.sarathi_plan_hybrid_attention.argtypes = [_vp, _i32p, _i32p, _i32p, ctypes.c_int32, ctypes.c_int32,
@@ -115,6 +115,13 @@ def _i32(a) -> np.ndarray:
 
 def _ptr(a: Optional[np.ndarray]):
     return None if a is None else a.ctypes.data_as(_i32p)
+
+
+def _addr(a: np.ndarray) -> int:
+    """Address of a contiguous int32 array that the caller keeps alive for the call.  As a plain integer: building a
+    ctypes pointer from an array takes 2.4 us, and the three length arrays of the two calls of an iteration made up half
+    of the 28 us it kept the host busy (small batches are bound by that)."""
+    return a.__array_interface__["data"][0]
 
 
 def _dev(t) -> Optional[int]:
@@ -223,7 +230,7 @@ class Handle:
         ws = workspace if workspace is not None else self.ensure_workspace()
         self._check_block_table(block_table, len(ql))
         self._check(lib.sarathi_kv_append(self._h, _dev(k_new), _dev(v_new), _dev(k_cache), _dev(v_cache),
-                                          _dev(block_table), _ptr(qs), _ptr(ql), _ptr(cl), len(ql), n, pages,
+                                          _dev(block_table), _addr(qs), _addr(ql), _addr(cl), len(ql), n, pages,
                                           _dev(ws), _stream(stream)))
 
     def hybrid_attention(self, q, k_cache, v_cache, block_table, q_start, q_len, ctx_len, sm_scale: float, out,
@@ -235,7 +242,7 @@ class Handle:
         ws = workspace if workspace is not None else self.ensure_workspace()
         self._check_block_table(block_table, len(ql))
         self._check(lib.sarathi_hybrid_attention(self._h, _dev(q), _dev(k_cache), _dev(v_cache), _dev(block_table),
-                                                 _ptr(qs), _ptr(ql), _ptr(cl), len(ql), n, pages, float(sm_scale),
+                                                 _addr(qs), _addr(ql), _addr(cl), len(ql), n, pages, float(sm_scale),
                                                  _dev(out), _dev(ws), _stream(stream)))
         return out
 
@@ -247,7 +254,7 @@ class Handle:
         pages = int(k_cache.shape[0]) if num_pages is None else num_pages
         self._check_block_table(block_table, len(ql))
         self._check(lib.sarathi_hybrid_attention_noalloc(self._h, _dev(q), _dev(k_cache), _dev(v_cache), _dev(block_table),
-                                                         _ptr(qs), _ptr(ql), _ptr(cl), len(ql), n, pages, float(sm_scale),
+                                                         _addr(qs), _addr(ql), _addr(cl), len(ql), n, pages, float(sm_scale),
                                                          _dev(out), _stream(stream)))
         return out
 
