@@ -95,16 +95,16 @@ inline int32_t steps_of_split(const TileDesc &t, int32_t split) {
     return (int32_t)ceil_div(e - b, kTileKeys);
 }
 
-// Chooses the split of every tile in [first, last) for `split_keys`, assigns partial rows and
+// Chooses the split of every tile in [first, last) for `split_keys` (spans of up to `whole_keys` stay uncut), assigns partial rows and
 // counters, and appends the units sorted longest first (counting sort on 32-key steps).
-void emit_units(Plan &plan, size_t first, size_t last, int64_t split_keys, std::vector<uint32_t> &scratch,
+void emit_units(Plan &plan, size_t first, size_t last, int64_t split_keys, int64_t whole_keys, std::vector<uint32_t> &scratch,
                 std::vector<int32_t> &bucket) {
     scratch.clear();
     int32_t max_steps = 0;
     for (size_t ti = first; ti < last; ++ti) {
         TileDesc &t = plan.tiles[ti];
         const int64_t span = t.n_keys - t.key_lo;  // keys the tile reads
-        int32_t ns = (span <= split_keys + split_keys / 2) ? 1 : (int32_t)ceil_div(span, split_keys);
+        int32_t ns = (span <= std::max(split_keys + split_keys / 2, whole_keys)) ? 1 : (int32_t)ceil_div(span, split_keys);
         t.keys_per_split = (int32_t)(ceil_div(ceil_div(span, ns), kTileKeys) * kTileKeys);
         t.n_splits = (int32_t)ceil_div(span, t.keys_per_split);
         if (t.n_splits > 1) {
@@ -133,12 +133,12 @@ void emit_units(Plan &plan, size_t first, size_t last, int64_t split_keys, std::
 }
 
 // Split units, partial rows and split tiles a choice of split_keys would need for tiles [first, last).
-void count_splits(const Plan &plan, size_t first, size_t last, int64_t split_keys, int64_t &n_split_units,
+void count_splits(const Plan &plan, size_t first, size_t last, int64_t split_keys, int64_t whole_keys, int64_t &n_split_units,
                   int64_t &rows, int64_t &n_split_tiles) {
     for (size_t ti = first; ti < last; ++ti) {
         const TileDesc &t = plan.tiles[ti];
         const int64_t span = t.n_keys - t.key_lo;
-        if (span <= split_keys + split_keys / 2) continue;
+        if (span <= std::max(split_keys + split_keys / 2, whole_keys)) continue;
         const int64_t ns = ceil_div(span, split_keys);
         n_split_units += ns;
         rows += ns * t.n_cols;
@@ -230,7 +230,15 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
         const int64_t balanced = ceil_div(std::max<int64_t>(tile_floor, share * 42 / 100), kTileKeys) * kTileKeys;
         tile_split = std::min(tile_split, balanced);
     }
-    if (opt.tile_split_keys <= 0 && !has_wave_tiles && n_chunk_tiles > 0 && (int64_t)n_chunk_tiles * cfg.num_kv_heads < 512) {
+    // The same next to decodes that hardly count: chunk blocks on at most half of the compute units, and decodes that
+    // stream for less than a quarter of the time the longest chunk block takes uncut (512 tokens behind 1871 next to 4
+    // decodes: 48 + 6 us with whole chunk tiles, 40 + 9 cut in two; next to 16 decodes, 0.4 of that time, 54 + 6 against 58 + 10).
+    int64_t longest_span = 0;
+    for (size_t ti = 0; ti < n_chunk_tiles; ++ti)
+        longest_span = std::max<int64_t>(longest_span, plan.tiles[ti].n_keys - plan.tiles[ti].key_lo);
+    const bool few_decodes = (int64_t)n_chunk_tiles * cfg.num_kv_heads <= 128 &&
+                             wave_stream_us < 0.25 * 0.62 * (double)longest_span / kTileKeys;
+    if (opt.tile_split_keys <= 0 && (!has_wave_tiles || few_decodes) && n_chunk_tiles > 0 && (int64_t)n_chunk_tiles * cfg.num_kv_heads < 512) {
         // A chunk-only batch with fewer tiles than block slots (two per compute unit), e.g. one chunk of a prompt
         // that is prefilled in pieces: how many pieces per tile?  More pieces shorten the blocks and fill the chip,
         // but every piece writes a 64 KiB partial tile per KV head that the merge kernel reads back, and a second
@@ -240,9 +248,7 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
         // launch.  (8192-token prompt, LLaMA2-70B shape: chunks of 512 tokens 1,600 -> 1,45x us per pass, chunks of
         // 256 tokens 1,956 -> 1,7xx us, against one fixed rule of about a thousand keys per piece.)
         const int64_t blocks1 = (int64_t)n_chunk_tiles * cfg.num_kv_heads;
-        int64_t max_span = 1;
-        for (size_t ti = 0; ti < n_chunk_tiles; ++ti)
-            max_span = std::max<int64_t>(max_span, plan.tiles[ti].n_keys - plan.tiles[ti].key_lo);
+        const int64_t max_span = std::max<int64_t>(1, longest_span);
         const double avg_steps = (double)keys_of_kind[kKindTile] / (double)n_chunk_tiles / kTileKeys;
         double best = 0.0;
         int64_t best_n = 1;
@@ -264,10 +270,88 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
         }
         tile_split = ceil_div(ceil_div(max_span, best_n), kTileKeys) * kTileKeys;
     }
+    // Few decodes.  Uncut, a batch's wave blocks (tiles x KV heads) leave compute units idle or finish with the longest
+    // decode streaming alone, and one block pulls 40 GB/s at most where the chip streams 6,550.  Up to 512 blocks (two per
+    // compute unit, all resident at once) the keys per piece therefore come from an estimate, in microseconds, of
+    //   decodes: the larger of (all keys at the chip's rate, the longest piece at a block's) + a quarter of the smaller
+    //            + 3, and 2 for every further 512 blocks;
+    //   with prefill chunks in the launch: the longer of decodes and chunks + 0.3 of the shorter (they share the units);
+    //   merge, if anything is cut: 5.3 + 0.25 per piece of the tile with the most + its partial rows twice at 4.5 TB/s.
+    // Against timings of 20 decode-only and 17 hybrid batches (1 to 64 decodes of 256 to 32,768 keys, seven pieces each):
+    // the chosen piece is within 5 % of the best one at the median and 1.9 x (decodes only) and 1.17 x (hybrid) faster than
+    // whole decodes on average; 8 decodes of 256-4096 keys: 53 -> 19 + 6 us.  A cut has to promise 5 %, and
+    // below 28 us nothing is cut: two launches keep the host for about as long, and a merge would be a third.
+    // (A block's rate is its compute unit's: eight wavefronts instead of four pull the same 40 GB/s, so only more blocks help.)
+    // Where one decode holds half of the keys or more, it alone is cut, as such batches always were: 7000 and 3000 keys
+    // next to three short ones then end with the 3000-key block, at 38 us instead of about 20.
+    int64_t wave_whole = 0;
+    const int64_t n_wave_tiles = (int64_t)(plan.tiles.size() - n_chunk_tiles);
+    plan.short_decode_pieces = false;
+    if (opt.split_keys <= 0 && n_wave_tiles > 0 && n_wave_tiles * cfg.num_kv_heads <= 512) {
+        const double key_us = cfg.head_dim * 4.0;  // bytes of a key and its value, one KV head
+        double chunk_us = 0.0;
+        bool chunk_cut = false;
+        if (n_chunk_tiles > 0) {
+            int64_t steps = 0, longest = 0, chunk_units = 0;
+            for (size_t ti = 0; ti < n_chunk_tiles; ++ti) {
+                const int64_t span = plan.tiles[ti].n_keys - plan.tiles[ti].key_lo;
+                const int64_t ns = span <= tile_split + tile_split / 2 ? 1 : ceil_div(span, tile_split);
+                const int64_t piece = ceil_div(ceil_div(span, ns), kTileKeys);
+                steps += ceil_div(span, kTileKeys) + ns;
+                longest = std::max(longest, piece + 1);
+                chunk_units += ns;
+                chunk_cut |= ns > 1;
+            }
+            const double step_us = (chunk_units + n_wave_tiles) * cfg.num_kv_heads <= 256 ? 0.62 : 0.9;
+            chunk_us = 4.0 + std::max((double)longest * step_us, (double)steps * cfg.num_kv_heads * step_us / 512.0);
+        }
+        const double stream_us = (double)keys_of_kind[kKindWave] * cfg.num_kv_heads * key_us / 6.55e6;
+        int64_t longest_wave = 0;
+        for (size_t ti = n_chunk_tiles; ti < plan.tiles.size(); ++ti)
+            longest_wave = std::max<int64_t>(longest_wave, plan.tiles[ti].n_keys - plan.tiles[ti].key_lo);
+        const int64_t whole = 2 * longest_wave >= keys_of_kind[kKindWave] ? longest_wave / 2 : 0;
+        auto estimate = [&](int32_t keys) {
+            const float inverse = 1.0f / (float)keys;
+            int64_t longest = 0, pieces = 0, rows = 0, most = 1;
+            for (size_t ti = n_chunk_tiles; ti < plan.tiles.size(); ++ti) {
+                const int32_t span = plan.tiles[ti].n_keys - plan.tiles[ti].key_lo;
+                if (span <= std::max<int64_t>(keys + keys / 2, whole)) {
+                    longest = std::max<int64_t>(longest, span);
+                    pieces += 1;
+                } else {
+                    const int64_t ns = (int64_t)((float)(span - 1) * inverse) + 1;
+                    longest = std::max<int64_t>(longest, keys);
+                    pieces += ns;
+                    rows += ns * plan.tiles[ti].n_cols;
+                    most = std::max(most, ns);
+                }
+            }
+            const double block_us = (double)longest * key_us / 40.0e3;
+            const double decode_us = 3.0 + std::max(stream_us, block_us) + 0.25 * std::min(stream_us, block_us) +
+                                     2.0 * (double)((pieces * cfg.num_kv_heads - 1) / 512);
+            double c = std::max(decode_us, chunk_us) + 0.3 * std::min(decode_us, chunk_us);
+            if (most > 1) {
+                c += 0.25 * (double)most + 2.0 * (double)rows * cfg.num_kv_heads * (cfg.head_dim + 2) * 4.0 / 4.5e6;
+                if (!chunk_cut) c += 5.3;
+            }
+            return c;
+        };
+        const double as_is = estimate((int32_t)std::min<int64_t>(wave_split, INT32_MAX / 2));
+        double best = as_is < 28.0 ? 0.0 : 0.95 * as_is;
+        for (const int32_t keys : {4096, 3072, 2048, 1536, 1024, 768, 512, 384, 256}) {
+            const double c = estimate(keys);
+            if (c < best) {
+                best = c;
+                wave_split = keys;
+                wave_whole = whole;
+                plan.short_decode_pieces = true;
+            }
+        }
+    }
     for (;;) {
         int64_t n_split_units = 0, rows = 0, n_split_tiles = 0;
-        count_splits(plan, 0, n_chunk_tiles, tile_split, n_split_units, rows, n_split_tiles);
-        count_splits(plan, n_chunk_tiles, plan.tiles.size(), wave_split, n_split_units, rows, n_split_tiles);
+        count_splits(plan, 0, n_chunk_tiles, tile_split, 0, n_split_units, rows, n_split_tiles);
+        count_splits(plan, n_chunk_tiles, plan.tiles.size(), wave_split, wave_whole, n_split_units, rows, n_split_tiles);
         const int64_t max_splits_per_tile = (1 << (32 - kUnitTileBits)) - 1;
         bool fits = n_split_units <= kMaxSplitUnits && rows <= ws.max_part_rows && n_split_tiles <= kMaxSplitUnits / 2 &&
                     (int64_t)plan.tiles.size() + n_split_units <= ws.max_units;
@@ -282,7 +366,7 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
 
     static thread_local std::vector<uint32_t> scratch;
     static thread_local std::vector<int32_t> bucket;
-    emit_units(plan, 0, n_chunk_tiles, tile_split, scratch, bucket);
+    emit_units(plan, 0, n_chunk_tiles, tile_split, 0, scratch, bucket);
     plan.num_tile_units = (int32_t)plan.units.size();
     plan.num_tile_reduce_units = (int32_t)plan.reduce_units.size();
     plan.tile_unit_steps = 0;
@@ -294,7 +378,7 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
         plan.longest_tile_unit_steps = steps_of_split(plan.tiles[u & ((1u << kUnitTileBits) - 1)], (int32_t)(u >> kUnitTileBits));
     }
     plan.wave_keys = keys_of_kind[kKindWave];
-    emit_units(plan, n_chunk_tiles, plan.tiles.size(), wave_split, scratch, bucket);
+    emit_units(plan, n_chunk_tiles, plan.tiles.size(), wave_split, wave_whole, scratch, bucket);
 }
 
 }  // namespace sarathi

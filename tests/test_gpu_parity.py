@@ -482,3 +482,28 @@ def test_empty_batch_is_a_noop(hx):
     h.kv_append(q[:, :1], q[:, :1], k_cache, v_cache, bt, e, e, e, num_tokens=0)
     h.hybrid_attention(q, k_cache, v_cache, bt, e, e, e, 0.125, q, num_tokens=0)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("shape,q_len,ctx,opts", [
+    (wl.AttnShape(32, 8, 128), [1] * 4, [4096, 257, 385, 1], {}),                     # pieces of whole and of partial size
+    (wl.AttnShape(32, 8, 128), [1] * 3, [2049, 5023, 1537], {"window": 1900}),
+    (wl.AttnShape(58, 2, 64), [1] * 3, [6000, 5911, 770], {}),                        # 29 columns: two tiles per decode
+    (wl.AttnShape(8, 2, 128), [1] * 40, list(range(900, 900 + 40 * 37, 37)), {}),
+    (wl.AttnShape(16, 2, 128), [200, 1, 1], [1400, 3500, 3600], {}),                  # a chunk cut next to cut decodes
+    (wl.AttnShape(8, 1, 64), [90, 1, 1, 1], [90, 5000, 2500, 2600], {"interleave": 0})])
+def test_few_decodes_cut_to_fill_the_chip(hx, shape, q_len, ctx, opts):
+    """Batches whose decodes are cut although none is long: against the checker, and through both entry points."""
+    b = wl._make("few_decodes", shape, q_len, ctx, 91)
+    h = hx.make_handle(b)
+    for k, v in opts.items():
+        h.set_option(k, v)
+    print("case", shape, q_len[:4], ctx[:6], opts, flush=True)
+    info, _ = h.plan(b.q_start, b.q_len, b.ctx_len)
+    assert info.num_reduce_items >= 1
+    st = hx.setup_and_run(b, 0x7FC1, handle=h)
+    ref = oracle.attention_for_batch(b, window=opts.get("window", 0)) if "window" in opts else oracle.attention_for_batch(b)
+    compare(hx.bf16_tensor_to_f64(st["out"]), ref, str(opts))
+    out2 = torch.empty_like(st["out"])
+    h.hybrid_attention_noalloc(st["q"], st["k_cache"], st["v_cache"], st["bt"], b.q_start, b.q_len, b.ctx_len, b.sm_scale, out2)
+    torch.cuda.synchronize()
+    compare(hx.bf16_tensor_to_f64(out2), ref, "noalloc")

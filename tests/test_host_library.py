@@ -167,3 +167,28 @@ def test_linear_split_k_workspace_sizes():
     assert binding.linear_workspace_bytes(2048, 8192, 4096) == 0
     small = binding.linear_workspace_bytes(128, 4096, 14336)
     assert small > 0 and small % (128 * 4096 * 4) == 0 and small // (128 * 4096 * 4) <= 16
+
+
+FEW_DECODES = [  # shape, q_len, ctx, whether something has to be cut
+    (wl.AttnShape(32, 8, 128), [1] * 8, [4096] * 8, True),                             # equal, a multiple of every piece
+    (wl.AttnShape(32, 8, 128), [1] * 8, [257, 385, 513, 4095, 4096, 4097, 2049, 1], True),  # around the piece sizes
+    (wl.AttnShape(32, 8, 128), [1] * 65, [4096] * 65, False),                          # 520 blocks: not a few any more
+    (wl.AttnShape(32, 8, 128), [1], [300], False),                                     # one short decode
+    (wl.AttnShape(58, 2, 64), [1] * 5, [6000, 5900, 5800, 100, 5700], True),           # two column tiles per decode
+    (wl.AttnShape(8, 2, 128), [1, 1, 1], [9000, 2000, 3000], True),                    # one holds half of the keys
+    (wl.AttnShape(16, 2, 128), [512] + [1] * 4, [2383, 4000, 100, 300, 4000], True),   # next to a chunk, which is cut too
+    (wl.AttnShape(32, 8, 128), [700] + [1] * 16, [700] + [3000] * 16, True),
+]
+
+
+@pytest.mark.parametrize("case", range(len(FEW_DECODES)))
+@pytest.mark.parametrize("window", [0, 1000])
+def test_few_decodes_are_cut_and_covered(case, window):
+    """Small batches are cut until the chip is filled: every key is still covered once, pieces stay within two blocks
+    per compute unit's worth of rounding, and a decode that holds half of the batch's keys is cut alone."""
+    shape, q_len, ctx, cut = FEW_DECODES[case]
+    info = _coverage_check(wl._make("few%d" % case, shape, q_len, ctx, 90 + case), **({"window": window} if window else {}))
+    if not window:
+        assert (info.num_reduce_items > 0) == cut
+    if case == 5 and not window:
+        assert info.num_reduce_items == 1
