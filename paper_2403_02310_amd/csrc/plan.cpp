@@ -13,6 +13,7 @@
 // splits of a tile are merged in index order by a second, small kernel.
 #include <algorithm>
 #include <cstdio>
+#include <utility>
 
 #include "internal.h"
 
@@ -24,7 +25,7 @@ static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 constexpr int32_t kMaxSplitUnits = 8192;
 constexpr int32_t kMaxPartRows = 32768;
 constexpr int32_t kMinWaveKeys = 1024;   // automatic choice: keys per wavefront of a wave-tile block before the tile is split
-constexpr int32_t kMinTileSplitKeys = 1024;
+constexpr int32_t kMinTileSplitKeys = 1024;  // next to decodes
 
 WorkspaceLayout make_workspace_layout(const sarathi_config &cfg) {
     WorkspaceLayout w{};
@@ -146,6 +147,77 @@ void count_splits(const Plan &plan, size_t first, size_t last, int64_t split_key
     }
 }
 
+// Estimated time of a launch of chunk tiles alone whose keys are cut at `split_keys`, merge included, in microseconds; a
+// huge number if the cut does not fit the partial rows.  The launch is played through: units longest first over
+// 256 / Hkv groups of compute units (the KV heads of a unit start next to each other) with two block slots each.  From
+// measurements on this part: a block advances 32 keys in 0.62 us alone on its unit and in 0.92 us next to a second block
+// (0.72 of that with 64 channels), costs 1.2 us besides, the launch 5 us; a cut launch pays 2 us + 0.4 of the time its partial
+// rows take to merge for writing them, and the merge 5 us + 0.25 per piece + the rows twice at 5.5 TB/s.
+// Against 340 timings (36 batches of 1 to 4 chunks of 17-8192 tokens behind 0-12,117 keys, ten cuts each) the cheapest
+// cut by this estimate is 1 % slower than the best one.  The rules it replaces (0.42 of a block slot's share of the keys
+// from 512 blocks on, else rounds of average pieces) were 8 % off: 2048 tokens of two prompts, 64 heads: 159 + 17 us cut
+// into 1784 pieces, 140 us whole.
+double chunk_launch_us(const sarathi_config &cfg, const Plan &plan, size_t n_chunk_tiles, int64_t split_keys, int64_t max_rows) {
+    static thread_local std::vector<int32_t> count;                       // units by steps
+    static thread_local std::vector<std::pair<double, double>> busy;      // heap: (when the group's first slot falls free, steps its other block then has left)
+    const double scale = cfg.head_dim == 128 ? 1.0 : 0.72;
+    const double alone = 0.62 * scale, shared = 0.92 * scale, fixed_steps = 1.2 / alone;
+    int32_t max_steps = 0;
+    for (size_t ti = 0; ti < n_chunk_tiles; ++ti)
+        max_steps = std::max(max_steps, (int32_t)ceil_div(plan.tiles[ti].n_keys - plan.tiles[ti].key_lo, kTileKeys));
+    count.assign((size_t)max_steps + 1, 0);
+    int64_t rows = 0, most = 1;
+    for (size_t ti = 0; ti < n_chunk_tiles; ++ti) {
+        const int64_t span = plan.tiles[ti].n_keys - plan.tiles[ti].key_lo;
+        if (span <= split_keys + split_keys / 2) {
+            count[(size_t)ceil_div(span, kTileKeys)]++;
+            continue;
+        }
+        const int64_t steps = ceil_div(span, kTileKeys);
+        const int64_t piece = ceil_div(ceil_div(span, ceil_div(span, split_keys)), kTileKeys);
+        const int64_t pieces = ceil_div(steps, piece);
+        count[(size_t)piece] += (int32_t)(pieces - 1);
+        count[(size_t)(steps - (pieces - 1) * piece)]++;
+        rows += pieces * plan.tiles[ti].n_cols;
+        most = std::max(most, pieces);
+    }
+    if (rows > max_rows) return 1.0e12;
+    const size_t groups = (size_t)std::max(1, 256 / cfg.num_kv_heads);
+    busy.clear();
+    size_t started = 0;
+    double end = 0.0;
+    auto later = [](const std::pair<double, double> &a, const std::pair<double, double> &b) { return a.first > b.first; };
+    for (int32_t st = max_steps; st > 0; --st) {
+        for (int32_t i = 0; i < count[(size_t)st]; ++i) {
+            const double u = (double)st + fixed_steps;
+            if (started < groups) {
+                busy.emplace_back(0.0, u);                                // alone so far
+            } else {
+                if (started < 2 * groups) {                               // second slots, next to the longest units first
+                    auto &g = busy[started - groups];
+                    const double both = std::min(u, g.second);
+                    g = {shared * both, std::max(u, g.second) - both};
+                    if (started + 1 == 2 * groups) std::make_heap(busy.begin(), busy.end(), later);
+                } else {
+                    std::pop_heap(busy.begin(), busy.end(), later);
+                    auto &g = busy.back();
+                    const double both = std::min(u, g.second);
+                    g = {g.first + shared * both, std::max(u, g.second) - both};
+                    std::push_heap(busy.begin(), busy.end(), later);
+                }
+            }
+            ++started;
+        }
+    }
+    for (const auto &g : busy) end = std::max(end, g.first + alone * g.second);
+    double c = 5.0 + end;
+    if (most > 1) {
+        const double move_us = 2.0 * (double)rows * cfg.num_kv_heads * (cfg.head_dim + 2) * 4.0 / 5.5e6;
+        c += 2.0 + 0.4 * move_us + 5.0 + 0.25 * (double)most + move_us;
+    }
+    return c;
+}
+
 }  // namespace
 
 void plan_attention(const sarathi_config &cfg, const Options &opt, const WorkspaceLayout &ws,
@@ -222,53 +294,35 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
         tile_floor = std::max<int64_t>(2 * kMinTileSplitKeys, (int64_t)(wave_us / 1.2) * kTileKeys);
     }
     int64_t tile_split = pick(opt.tile_split_keys, keys_of_kind[kKindTile], tile_units_wanted, tile_floor);
-    if (opt.tile_split_keys <= 0 && !has_wave_tiles) {
-        // Balance: with few, long chunk tiles the longest unit must stay well below a block slot's
-        // share of the work (2 slots on each of 256 compute units), or the tail of the launch runs
-        // on a few units only.  0.42 of the share measured best on the long-context chunk batch.
-        const int64_t share = keys_of_kind[kKindTile] * cfg.num_kv_heads / 512;
-        const int64_t balanced = ceil_div(std::max<int64_t>(tile_floor, share * 42 / 100), kTileKeys) * kTileKeys;
-        tile_split = std::min(tile_split, balanced);
-    }
-    // The same next to decodes that hardly count: chunk blocks on at most half of the compute units, and decodes that
-    // stream for less than a quarter of the time the longest chunk block takes uncut (512 tokens behind 1871 next to 4
-    // decodes: 48 + 6 us with whole chunk tiles, 40 + 9 cut in two; next to 16 decodes, 0.4 of that time, 54 + 6 against 58 + 10).
-    int64_t longest_span = 0;
+    // Chunks alone, or next to decodes that hardly count (chunk blocks on at most half of the compute units, decodes that
+    // stream for less than a quarter of the time the longest chunk block takes uncut; 512 tokens behind 1871 next to 4
+    // decodes: 48 + 6 us with whole chunk tiles, 40 + 9 cut in two; next to 16 decodes, 0.4 of that time, 54 + 6 against
+    // 58 + 10): the cut that chunk_launch_us finds cheapest.  Pieces of fewer than eight key steps are all prologue, and the
+    // search ends where finer cuts have cost more twice in a row.
+    int64_t longest_span = 1;
     for (size_t ti = 0; ti < n_chunk_tiles; ++ti)
         longest_span = std::max<int64_t>(longest_span, plan.tiles[ti].n_keys - plan.tiles[ti].key_lo);
     const bool few_decodes = (int64_t)n_chunk_tiles * cfg.num_kv_heads <= 128 &&
                              wave_stream_us < 0.25 * 0.62 * (double)longest_span / kTileKeys;
-    if (opt.tile_split_keys <= 0 && (!has_wave_tiles || few_decodes) && n_chunk_tiles > 0 && (int64_t)n_chunk_tiles * cfg.num_kv_heads < 512) {
-        // A chunk-only batch with fewer tiles than block slots (two per compute unit), e.g. one chunk of a prompt
-        // that is prefilled in pieces: how many pieces per tile?  More pieces shorten the blocks and fill the chip,
-        // but every piece writes a 64 KiB partial tile per KV head that the merge kernel reads back, and a second
-        // kernel has to be launched at all.  Estimated cost in microseconds, from measurements on this part: a block
-        // advances 32 keys in ~0.62 us alone on its compute unit and in ~0.9 us next to a second block; blocks beyond
-        // the 512 slots run in further rounds; the merge moves the partial tiles twice at ~4.5 TB/s after ~5 us of
-        // launch.  (8192-token prompt, LLaMA2-70B shape: chunks of 512 tokens 1,600 -> 1,45x us per pass, chunks of
-        // 256 tokens 1,956 -> 1,7xx us, against one fixed rule of about a thousand keys per piece.)
-        const int64_t blocks1 = (int64_t)n_chunk_tiles * cfg.num_kv_heads;
-        const int64_t max_span = std::max<int64_t>(1, longest_span);
-        const double avg_steps = (double)keys_of_kind[kKindTile] / (double)n_chunk_tiles / kTileKeys;
-        double best = 0.0;
-        int64_t best_n = 1;
-        for (int64_t n = 1; n <= 16; ++n) {
-            if (n > 1 && max_span / n < 256) break;   // pieces of fewer than eight key steps are all prologue
-            const int64_t blocks = blocks1 * n;
-            const double steps = avg_steps / (double)n + 1.0;
-            const double rounds = blocks <= 512 ? 1.0 : (double)blocks / 512.0;
-            const double step_us = blocks <= 256 ? 0.62 : 0.9;
-            double cost = 4.0 + rounds * steps * step_us;
-            if (n > 1) {
-                const double partial_bytes = (double)blocks * kTileCols * (cfg.head_dim + 2) * 4.0;
-                cost += 5.0 + 2.0 * partial_bytes / 4.5e6;
-            }
-            if (n == 1 || cost < best) {
-                best = cost;
-                best_n = n;
+    if (opt.tile_split_keys <= 0 && n_chunk_tiles > 0 && (!has_wave_tiles || few_decodes)) {
+        tile_split = ceil_div(longest_span, kTileKeys) * kTileKeys;
+        if ((int64_t)n_chunk_tiles * cfg.num_kv_heads <= 8192) {
+            double best = chunk_launch_us(cfg, plan, n_chunk_tiles, tile_split, ws.max_part_rows);
+            // all slots busy to the end: no cut can gain what its merge costs
+            const double full_us = (double)keys_of_kind[kKindTile] / kTileKeys * cfg.num_kv_heads * (cfg.head_dim == 128 ? 0.92 : 0.66) / 512.0;
+            int worse = best < full_us + 15.0 ? 2 : 0;
+            for (int64_t n = 2; n <= 16 && longest_span / n >= 256 && worse < 2; ++n) {
+                const int64_t keys = ceil_div(ceil_div(longest_span, n), kTileKeys) * kTileKeys;
+                const double c = chunk_launch_us(cfg, plan, n_chunk_tiles, keys, ws.max_part_rows);
+                if (c < best) {
+                    best = c;
+                    tile_split = keys;
+                    worse = 0;
+                } else {
+                    ++worse;
+                }
             }
         }
-        tile_split = ceil_div(ceil_div(max_span, best_n), kTileKeys) * kTileKeys;
     }
     // Few decodes.  Uncut, a batch's wave blocks (tiles x KV heads) leave compute units idle or finish with the longest
     // decode streaming alone, and one block pulls 40 GB/s at most where the chip streams 6,550.  Up to 512 blocks (two per

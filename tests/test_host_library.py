@@ -192,3 +192,18 @@ def test_few_decodes_are_cut_and_covered(case, window):
         assert (info.num_reduce_items > 0) == cut
     if case == 5 and not window:
         assert info.num_reduce_items == 1
+
+
+@pytest.mark.parametrize("shape,chunks,cut", [
+    (wl.AttnShape(64, 8, 128), [(1299, 1299), (749, 4960)], False),   # two prompts that fill the chip whole
+    (wl.AttnShape(32, 8, 128), [(512, 2383)], True),                  # 128 blocks of 75 steps
+    (wl.AttnShape(32, 8, 128), [(1000, 1100), (400, 9400)], True),    # one long prefix among short ones
+    (wl.AttnShape(32, 8, 128), [(300, 300)], False),
+    (wl.AttnShape(4, 1, 64), [(278, 6572), (987, 987)], True),        # more groups than units
+    (wl.AttnShape(320, 320, 64), [(40, 3000), (3000, 3000)], False),  # more KV heads than compute units, more blocks than are played through
+    (wl.AttnShape(64, 8, 128), [(4096, 70000)], False)])              # every slot busy to the end
+def test_chunk_only_batches_are_cut_where_it_pays(shape, chunks, cut):
+    """The cut of a chunk-only launch comes from playing it through; whatever it says, every key is covered once."""
+    b = wl._make("chunks", shape, [q for q, _ in chunks], [c for _, c in chunks], 95)
+    info = _coverage_check(b)
+    assert (info.num_reduce_items > 0) == cut
