@@ -110,6 +110,15 @@ __device__ __forceinline__ LinearItem lin_work_item(const LinearParams &p) {
     return LinearItem{group * kLinGroup + rest - t_tile * width, t_tile, split};
 }
 
+// Where a workgroup starts in its k range, in stages; it wraps round at the end.  Workgroups of one token tile only meet in
+// memory: if all of them started at the front, every row of the weights would be read at the same k, and rows lie a power
+// of two (or a small multiple of one) apart, so that all reads of a moment would fall on a few memory channels.
+// 8 x 28672 x 4096: 49 us from the front, 38 staggered; 77 x 28672 x 4096: 53 and 44; 8 x 14336 x 8192: 51 and 42.  With
+// several token tiles the workgroups of an XCD have to stay at the same k to share tiles in L2 (no gain measured there).
+__device__ __forceinline__ int lin_first_stage(const LinearParams &p, int n_tile, int n_stages) {
+    return p.t_tiles == 1 ? __builtin_amdgcn_readfirstlane((n_tile * 3) % n_stages) : 0;
+}
+
 // BM tokens per tile; WT wavefronts side by side along the tokens (the other 8 / WT along the features);
 // RING stages of LDS; BN features per tile (256, or 128 for matrices too small to fill the chip with wide tiles).
 template <int BM, int WT, int RING, int KS = kLinStageK, int BN = kLinBN>
@@ -138,6 +147,7 @@ __global__ __launch_bounds__(kLinThreads, 1) void linear_kernel(LinearParams p) 
     const int k_begin = split * p.k_per_split;
     const int k_end = min(p.K, k_begin + p.k_per_split);
     const int n_stages = (k_end - k_begin) / KS;
+    const int first_stage = lin_first_stage(p, n_tile, n_stages);
     auto row_key = [](int row) { return KS == 64 ? (row >> 1) & 7 : (row >> 2) & 3; };
 
     // ---- global -> LDS: wavefront w moves rows 32w .. 32w+31 of the weight tile (four loads of 8 rows) and
@@ -164,7 +174,8 @@ __global__ __launch_bounds__(kLinThreads, 1) void linear_kernel(LinearParams p) 
     auto issue_stage = [&](int stage, int slot) {
         // stages past the range re-read the last one into a free slot: every step issues the same
         // number of loads, so one wait count serves the whole loop
-        const int s = min(stage, n_stages - 1);
+        const int at = min(stage, n_stages - 1) + first_stage;
+        const int s = at < n_stages ? at : at - n_stages;
         const uint32_t dst = smem_addr + (uint32_t)(slot * STAGE * 2);
         const uint16_t *wb = w_base + s * KS;
         const uint16_t *xb = x_base + s * KS;
@@ -315,6 +326,7 @@ __global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {
     const int n0 = wi.n_tile * BN, t0 = wi.t_tile * BM;
     const int k_begin = wi.split * p.k_per_split;
     const int n_stages = (min(p.K, k_begin + p.k_per_split) - k_begin) / KS;
+    const int first_stage = STREAM ? lin_first_stage(p, wi.n_tile, n_stages) : 0;
     auto row_key = [](int row) { return (row >> 1) & 7; };
 
     // ---- global -> LDS.  LDS row l of a half of nb blocks is row l % 32 of block (l / 32) % nb of side-wavefront
@@ -342,7 +354,8 @@ __global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {
     // phase issues the same loads and one wait count serves the whole loop
     auto issue = [&](auto ht, int i, int stage, int slot) {
         constexpr int h = decltype(ht)::value;
-        const int k = min(stage, n_stages - 1) * KS;
+        const int at = min(stage, n_stages - 1) + first_stage;
+        const int k = (at < n_stages ? at : at - n_stages) * KS;
         const uint32_t dst = smem_addr + (uint32_t)(slot * STAGE + kOff[h] + wave * kBlocks[h] * 16 * KS) * 2 + (uint32_t)i * 1024;
         if (h == HB0 || h == HB1) lin_dma_load_16(x_base + k, off[first_load(h) + i], dst);
         else if (STREAM) lin_dma_load_16_stream(w_base + k, off[first_load(h) + i], dst);
