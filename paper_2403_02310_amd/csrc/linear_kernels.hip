@@ -48,7 +48,6 @@ typedef __attribute__((ext_vector_type(16))) float lf32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t lu32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t lu32x2;
 
-constexpr int kLinBN = 256;      // features per workgroup tile
 constexpr int kLinStageK = 64;   // k per stage: one 128-byte line of every row
 constexpr int kLinXcds = 8;
 constexpr int kLinThreads = 512;
@@ -120,9 +119,10 @@ __device__ __forceinline__ int lin_first_stage(const LinearParams &p, int n_tile
 }
 
 // BM tokens per tile; WT wavefronts side by side along the tokens (the other 8 / WT along the features);
-// RING stages of LDS; BN features per tile (256, or 128 for matrices too small to fill the chip with wide tiles).
-template <int BM, int WT, int RING, int KS = kLinStageK, int BN = kLinBN>
+// RING stages of LDS; BN features per tile.
+template <int BM, int WT, int RING, int BN>
 __global__ __launch_bounds__(kLinThreads, 1) void linear_kernel(LinearParams p) {
+    constexpr int KS = kLinStageK;
     constexpr int PIECES = KS / 8;              // 16-byte pieces of an LDS row
     constexpr int DMA_ROWS = 64 / PIECES;       // rows one 1 KiB load covers
     constexpr int W_ELEMS = BN * KS;
@@ -130,7 +130,8 @@ __global__ __launch_bounds__(kLinThreads, 1) void linear_kernel(LinearParams p) 
     constexpr int STAGE = W_ELEMS + X_ELEMS;
     constexpr int W_ROWS = BN / 8;              // weight rows a wavefront moves per stage
     constexpr int W_LOADS = W_ROWS / DMA_ROWS;  // 1 KiB loads of weight rows per wavefront and stage
-    constexpr int X_LOADS = BM >= 8 * DMA_ROWS ? BM / (8 * DMA_ROWS) : 1;  // the same for token rows
+    constexpr int X_LOADS = BM / (8 * DMA_ROWS);  // the same for token rows
+    static_assert(BM % (8 * DMA_ROWS) == 0, "every wavefront moves the same number of token rows");
     constexpr int LOADS = W_LOADS + X_LOADS;    // all loads of a wavefront per stage
     constexpr int NI = BN * WT / 256;           // 32-feature MFMA tiles per wavefront: BN features / (8 / WT wavefronts) / 32
     constexpr int NJ = BM / WT / 32;            // 32-token MFMA tiles per wavefront
@@ -148,7 +149,7 @@ __global__ __launch_bounds__(kLinThreads, 1) void linear_kernel(LinearParams p) 
     const int k_end = min(p.K, k_begin + p.k_per_split);
     const int n_stages = (k_end - k_begin) / KS;
     const int first_stage = lin_first_stage(p, n_tile, n_stages);
-    auto row_key = [](int row) { return KS == 64 ? (row >> 1) & 7 : (row >> 2) & 3; };
+    auto row_key = [](int row) { return (row >> 1) & 7; };
 
     // ---- global -> LDS: wavefront w moves rows 32w .. 32w+31 of the weight tile (four loads of 8 rows) and
     // rows (BM/8)w .. of the token tile.  Lane l of a load fills physical piece l % 8 of row l / 8 and
@@ -162,9 +163,7 @@ __global__ __launch_bounds__(kLinThreads, 1) void linear_kernel(LinearParams p) 
     }
 #pragma unroll
     for (int i = 0; i < X_LOADS; ++i) {
-        // fewer than 64 tokens: several wavefronts move the same rows (identical bytes to the same place), so
-        // that every wavefront issues the same number of loads
-        const int row = (wave * DMA_ROWS * X_LOADS) % BM + i * DMA_ROWS + lane / PIECES;
+        const int row = (wave * X_LOADS + i) * DMA_ROWS + lane / PIECES;
         const int piece = (lane % PIECES) ^ row_key(row);
         x_off[i] = ((min(t0 + row, p.T - 1) - t0) * p.K + piece * 8) * 2;
     }
@@ -183,7 +182,7 @@ __global__ __launch_bounds__(kLinThreads, 1) void linear_kernel(LinearParams p) 
         for (int i = 0; i < W_LOADS; ++i) lin_dma_load_16_stream(wb, w_off[i], dst + (uint32_t)((wave * W_ROWS + i * DMA_ROWS) * KS * 2));
 #pragma unroll
         for (int i = 0; i < X_LOADS; ++i)
-            lin_dma_load_16(xb, x_off[i], dst + (uint32_t)(W_ELEMS * 2 + ((wave * DMA_ROWS * X_LOADS) % BM + i * DMA_ROWS) * KS * 2));
+            lin_dma_load_16(xb, x_off[i], dst + (uint32_t)(W_ELEMS * 2 + (wave * X_LOADS + i) * DMA_ROWS * KS * 2));
     };
 
     // ---- operands: wavefront (wn, wt) owns features 32 NI wn.. and tokens 32 NJ wt.. of the tile
@@ -628,45 +627,44 @@ static LinearPlan plan_phased(int32_t T, int32_t N, int32_t K, size_t workspace_
     return best;
 }
 
-LinearPlan plan_linear(int32_t T, int32_t N, int32_t K, size_t workspace_bytes) {
-    if (T > kLinSmallTokens) return plan_phased(T, N, K, workspace_bytes);
-    // Rough cost of a tiling, in microseconds: rounds of workgroups (one per compute unit) x stages per piece x
-    // the time of a stage (fetching the weights bounds it: ~1.3 us for 256 features, ~0.7 us for 128), plus, when the k range is cut into s pieces so that a small grid
-    // fills the chip, the fp32 partial tiles (written, read back and added by a second kernel) at
-    // ~3 TB/s and that kernel's launch.  Pieces keep at least 4 stages (256 k) and must fit the workspace.
+// Up to 64 tokens: 128 or 256 features x 64 tokens of linear_kernel, cut along k so that a small batch streams the weights
+// through every compute unit.  Cost in microseconds, fitted to 1,900 timings (16 layer shapes, 1 to 64 tokens, 1 to 16
+// pieces; 6 % rms, the chosen tiling 1 % slower than the best one): as above with the weights at 9.9 TB/s in a maximum that
+// is approached from above by 0.61 of the smaller term, 0.13 us per stage for a full 64 tokens, 3.6 us for the second kernel
+// and 3.7 TB/s for the partial tiles.  (128 features win nearly everywhere: 8 x 4096 x 4096 in 8 pieces 11.4 us, 256
+// features x 32 tokens in 16 pieces, the tile this range had besides, 14.9.)
+static LinearPlan plan_small(int32_t T, int32_t N, int32_t K, size_t workspace_bytes) {
     const int64_t k_stages = K / kLinStageK;
     const int64_t per_split_bytes = (int64_t)T * N * 4;
-    const int64_t slots = 256;
-    LinearPlan best_plan{};
+    const double memory_us = 2.0 * N * K / 9.94e6;
+    LinearPlan best{};
     double best_cost = -1.0;
-    auto consider = [&](int32_t feature_tile, int32_t token_tile) {
-        const int64_t n_tiles = (N + feature_tile - 1) / feature_tile;
-        const int64_t t_tiles = (T + token_tile - 1) / token_tile;
-        const int64_t tiles = n_tiles * t_tiles;
-        const double stage_us = feature_tile == 128 ? 0.7 : 1.3;
-        for (int64_t s = 1; s <= 16 && (s == 1 || s * 4 <= k_stages); ++s) {
+    for (const int32_t features : {128, 256}) {
+        const int64_t n_tiles = (N + features - 1) / features;
+        const double stage_us = (features == 128 ? 0.256 : 0.468) + 0.128 * T / 64.0;
+        for (int64_t s = 1; s <= 16 && (s == 1 || (s * 4 <= k_stages && n_tiles * s <= 1024)); ++s) {
             if (s > 1 && (size_t)(s * per_split_bytes) > workspace_bytes) break;
-            const int64_t rounds = (tiles * s + slots - 1) / slots;
-            double c = (double)rounds * (double)((k_stages + s - 1) / s) * stage_us;
-            if (s > 1) c += 8.0 * (double)s * T * N / 3.0e6 + 5.0;
-            if (best_cost < 0.0 || c < 0.95 * best_cost) {
+            const int64_t stages = (k_stages + s - 1) / s;
+            if ((k_stages + stages - 1) / stages != s) continue;  // the same stages per piece in fewer pieces has been looked at
+            const double compute_us = (double)((n_tiles * s + 255) / 256) * ((double)stages * stage_us + 2.03 * features / 256.0);
+            double c = 1.5 + std::max(compute_us, memory_us) + 0.61 * std::min(compute_us, memory_us);
+            if (s > 1) c += 3.6 + 2.0 * (double)s * (double)per_split_bytes / 3.7e6;
+            if (best_cost < 0.0 || c < best_cost) {
                 best_cost = c;
-                best_plan.feature_tile = feature_tile;
-                best_plan.token_tile = token_tile;
-                best_plan.n_tiles = (int32_t)n_tiles;
-                best_plan.t_tiles = (int32_t)t_tiles;
-                int32_t kps = (int32_t)((K + s - 1) / s);
-                kps = (kps + kLinStageK - 1) / kLinStageK * kLinStageK;
-                best_plan.k_per_split = s == 1 ? K : kps;
-                best_plan.splits = s == 1 ? 1 : (K + kps - 1) / kps;
+                best.feature_tile = features;
+                best.token_tile = kLinSmallTokens;
+                best.n_tiles = (int32_t)n_tiles;
+                best.t_tiles = 1;
+                best.splits = (int32_t)s;
+                best.k_per_split = s == 1 ? K : (int32_t)(stages * kLinStageK);
             }
         }
-    };
-    // Token tile: the smallest that holds the batch.  128-feature tiles give a large matrix enough workgroups to fill the
-    // chip without cutting k (no partial tiles, no second kernel).
-    consider(256, T <= 32 ? 32 : 64);
-    consider(128, 64);
-    return best_plan;
+    }
+    return best;
+}
+
+LinearPlan plan_linear(int32_t T, int32_t N, int32_t K, size_t workspace_bytes) {
+    return T > kLinSmallTokens ? plan_phased(T, N, K, workspace_bytes) : plan_small(T, N, K, workspace_bytes);
 }
 
 int launch_linear(const LinearPlan &pl, const void *x, const void *w, void *y, int32_t T, int32_t N, int32_t K,
@@ -716,12 +714,10 @@ int launch_linear(const LinearPlan &pl, const void *x, const void *w, void *y, i
         go(I2{}, I2{}, I1{}, I0{}, I4{});
         go(I2{}, I1{}, I1{}, I0{}, I5{});
         go(I1{}, I1{}, I1{}, I0{}, I6{});
-    } else if (pl.feature_tile == 128) {  // LDS: 6 x 24 KiB, 3 x 40 KiB, 4 x 36 KiB
-        hipLaunchKernelGGL((linear_kernel<64, 2, 6, kLinStageK, 128>), grid, dim3(kLinThreads), 0, st, p);
-    } else if (pl.token_tile == 64) {
-        hipLaunchKernelGGL((linear_kernel<64, 1, 3>), grid, dim3(kLinThreads), 0, st, p);
+    } else if (pl.feature_tile == 128) {  // LDS: 6 x 24 KiB, 3 x 40 KiB
+        hipLaunchKernelGGL((linear_kernel<64, 2, 6, 128>), grid, dim3(kLinThreads), 0, st, p);
     } else {
-        hipLaunchKernelGGL((linear_kernel<32, 1, 4>), grid, dim3(kLinThreads), 0, st, p);
+        hipLaunchKernelGGL((linear_kernel<64, 1, 3, 256>), grid, dim3(kLinThreads), 0, st, p);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || pl.splits == 1) return (int)e;

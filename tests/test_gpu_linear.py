@@ -157,3 +157,14 @@ def test_tiles_of_large_batches(hx, T, N, K):
     y = room[:T].float()
     mag = 2.0 ** -18 * (K ** 0.5) * 8                                                   # 2^-20 sum |x w| of N(0,1) rows, generously
     assert ((y - whole).abs() <= 2.0 ** -7 * whole.abs() + mag).all()
+
+
+@pytest.mark.parametrize("T,N,K", [
+    (1, 128, 64), (64, 384, 192),                  # one stage; a ragged last feature tile, three stages
+    (64, 4096, 4096), (7, 1280, 4096),             # 128 features in eight and in sixteen pieces
+    (64, 32896, 64), (9, 11136, 3008),             # 256 features, ragged last tile, uncut and in five pieces
+    (5, 28672, 320)])                              # 128 features uncut, workgroups start at all five stages
+def test_tiles_of_small_batches(hx, T, N, K):
+    rows = sorted(set([0, T - 1, T // 2])); cols = sorted(set([0, N - 1, N - 128, 127] + np.random.default_rng(N).integers(0, N, 30).tolist()))
+    got = run(hx, T, N, K, seed=31 + T, rows=rows, cols=cols)
+    assert np.isfinite(got).all()
