@@ -215,6 +215,7 @@ sarathi_status enqueue_attention(sarathi_handle *h, char *dev, float *part_ml, f
     m.reduce_units = reinterpret_cast<const uint32_t *>(dev + reduce_off);
     m.num_reduce_units = (int32_t)pl.reduce_units.size();
     m.num_tile_reduce_units = pl.num_tile_reduce_units;
+    m.most_pieces = pl.most_pieces;
     m.part_ml = part_ml;
     m.part_o = part_o;
     m.sched = sched;

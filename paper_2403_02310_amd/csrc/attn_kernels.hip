@@ -1101,7 +1101,10 @@ struct ReduceParams {
     int32_t group;
 };
 
-template <int D>
+// BATCH: pieces fetched at once.  Chunk tiles are cut into a few pieces of many rows and bound by their bytes: four (with
+// eight, a batch of 56 tiles in two pieces took 25 us instead of 20).  Decodes that are cut to fill the chip have up to 32
+// pieces of a few rows and are bound by latency: eight (32 pieces: 11.2 -> 6.8 us, 16 pieces 8.0 -> 6.5).
+template <int D, int BATCH>
 __global__ __launch_bounds__(kMergeCols * D / 4) void splitkv_reduce_kernel(ReduceParams p) {
     constexpr int TPC = D / 4;  // threads per column
     const int kvh = blockIdx.x % p.num_kv_heads;
@@ -1119,15 +1122,14 @@ __global__ __launch_bounds__(kMergeCols * D / 4) void splitkv_reduce_kernel(Redu
     const float *__restrict__ po = p.part_o;
     // Loads first, arithmetic after: the pieces' rows were written by the attention launch and come from memory,
     // so a loop that loads, waits and accumulates piece by piece costs one memory latency per piece (and one more
-    // per piece for the maxima).  Up to kBatch pieces are fetched at once (indices beyond the last piece are clamped
-    // to it: a valid, unused read); the sums still run in index order.
-    constexpr int kBatch = 4;
+    // per piece for the maxima).  BATCH pieces are fetched at once (indices beyond the last piece are clamped
+    // to it: a valid, unused read), and the maxima of the later pieces as well; the sums still run in index order.
     const int n = it.n_splits;
-    float m[kBatch], l[kBatch];
-    f32x4 o[kBatch];
+    float m[BATCH], l[BATCH];
+    f32x4 o[BATCH];
     auto fetch = [&](int base) {
 #pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
+        for (int j = 0; j < BATCH; ++j) {
             const int64_t prow = prow0 + (int64_t)min(base + j, n - 1) * split_stride;
             const f32x2 v = *reinterpret_cast<const f32x2 *>(ml + prow * 2);
             m[j] = v[0];
@@ -1138,20 +1140,26 @@ __global__ __launch_bounds__(kMergeCols * D / 4) void splitkv_reduce_kernel(Redu
     fetch(0);
     float m_max = kNegSentinel;
 #pragma unroll
-    for (int j = 0; j < kBatch; ++j) m_max = fmaxf(m_max, m[j]);  // clamped entries repeat a valid piece
-    for (int i = kBatch; i < n; ++i) m_max = fmaxf(m_max, ml[(prow0 + i * split_stride) * 2]);
+    for (int j = 0; j < BATCH; ++j) m_max = fmaxf(m_max, m[j]);  // clamped entries repeat a valid piece
+    for (int i = BATCH; i < n; i += BATCH) {
+        float later[BATCH];
+#pragma unroll
+        for (int j = 0; j < BATCH; ++j) later[j] = ml[(prow0 + min(i + j, n - 1) * split_stride) * 2];
+#pragma unroll
+        for (int j = 0; j < BATCH; ++j) m_max = fmaxf(m_max, later[j]);
+    }
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     float lsum = 0.f;
     for (int base = 0;;) {
 #pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
+        for (int j = 0; j < BATCH; ++j) {
             if (base + j < n) {
                 const float w = __builtin_amdgcn_exp2f(m[j] - m_max);
                 lsum += w * l[j];
                 acc += o[j] * w;
             }
         }
-        base += kBatch;
+        base += BATCH;
         if (base >= n) break;
         fetch(base);
     }
@@ -1394,10 +1402,16 @@ int launch_reduce(const sarathi_config &cfg, const AttnMeta &m, void *out, int32
     p.group = cfg.num_q_heads / cfg.num_kv_heads;
     const unsigned blocks = (unsigned)count * (unsigned)cfg.num_kv_heads;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (cfg.head_dim == 128)
-        hipLaunchKernelGGL(splitkv_reduce_kernel<128>, dim3(blocks), dim3(kMergeCols * 128 / 4), 0, st, p);
-    else
-        hipLaunchKernelGGL(splitkv_reduce_kernel<64>, dim3(blocks), dim3(kMergeCols * 64 / 4), 0, st, p);
+    auto launch = [&](auto d, auto batch) {
+        constexpr int D = decltype(d)::value;
+        hipLaunchKernelGGL((splitkv_reduce_kernel<D, decltype(batch)::value>), dim3(blocks), dim3(kMergeCols * D / 4), 0, st, p);
+    };
+    auto pick_batch = [&](auto d) {
+        if (m.most_pieces <= 4) launch(d, std::integral_constant<int, 4>{});
+        else launch(d, std::integral_constant<int, 8>{});
+    };
+    if (cfg.head_dim == 128) pick_batch(std::integral_constant<int, 128>{});
+    else pick_batch(std::integral_constant<int, 64>{});
     return (int)hipGetLastError();
 }
 

@@ -62,6 +62,7 @@ struct Plan {
     std::vector<uint32_t> reduce_units;  // (8-column group, tile) of every split tile, for the merge kernel; chunk tiles first
     int32_t num_tile_reduce_units = 0;   // how many of them belong to chunk tiles
     int32_t num_split_tiles = 0;      // tiles with n_splits > 1
+    int32_t most_pieces = 0;          // the largest n_splits
     int32_t num_part_rows = 0;
     int32_t split_keys = 0;
     int32_t tile_split_keys = 0;
@@ -162,6 +163,7 @@ struct AttnMeta {
     const uint32_t *reduce_units;  // dev
     int32_t num_reduce_units;
     int32_t num_tile_reduce_units;   // leading entries of reduce_units that belong to chunk tiles
+    int32_t most_pieces = 0;         // pieces of the tile that is cut finest
     float *part_ml;              // dev
     float *part_o;               // dev
     int32_t *sched;              // dev, kSchedBytes

@@ -112,6 +112,7 @@ void emit_units(Plan &plan, size_t first, size_t last, int64_t split_keys, int64
             t.part_row0 = plan.num_part_rows;
             plan.num_part_rows += t.n_splits * t.n_cols;
             plan.num_split_tiles++;
+            plan.most_pieces = std::max(plan.most_pieces, t.n_splits);
             for (int32_t c0 = 0, grp = 0; c0 < t.n_cols; c0 += kReduceCols, ++grp)
                 plan.reduce_units.push_back(pack_unit((uint32_t)ti, (uint32_t)grp));
         } else {
@@ -230,6 +231,7 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
     plan.num_tile_units = 0;
     plan.num_tile_reduce_units = 0;
     plan.num_split_tiles = 0;
+    plan.most_pieces = 0;
     const int32_t G = cfg.num_q_heads / cfg.num_kv_heads;
 
     // Tiles: chunk tiles first, then wave tiles (two passes keep each kind contiguous).
