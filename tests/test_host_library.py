@@ -207,3 +207,24 @@ def test_chunk_only_batches_are_cut_where_it_pays(shape, chunks, cut):
     b = wl._make("chunks", shape, [q for q, _ in chunks], [c for _, c in chunks], 95)
     info = _coverage_check(b)
     assert (info.num_reduce_items > 0) == cut
+
+
+@pytest.mark.parametrize("shape,q_len,meet", [(wl.AttnShape(58, 2, 64), [1] * 8, True),
+                                              (wl.AttnShape(58, 2, 64), [1] * 9, False),          # a last, short window
+                                              (wl.AttnShape(20, 1, 128), [1] * 7 + [3], False),   # two tiles and four
+                                              (wl.AttnShape(12, 3, 64), [6, 1, 5, 1, 6], False)])  # two tiles and one
+def test_column_tiles_of_a_sequence_meet_on_an_xcd(shape, q_len, meet):
+    """With fewer than eight KV heads the wave tiles of one sequence are spread so that block % 8 is the same for each;
+    every piece still appears once."""
+    b = wl._make("pairs", shape, q_len, [2000 + 300 * i for i in range(len(q_len))], 96)
+    _coverage_check(b)
+    _coverage_check(b, split_keys=100)
+    _coverage_check(b, split_keys=1 << 20)
+    h = binding.Handle(shape.num_q_heads, shape.num_kv_heads, shape.head_dim, max_tokens=2048, max_seqs=128,
+                       max_blocks_per_seq=b.max_blocks_per_seq)
+    h.set_option("split_keys", 1 << 20)
+    _, items = h.plan(b.q_start, b.q_len, b.ctx_len)
+    where = {(it.seq, it.col_begin): i for i, it in enumerate(items)}
+    assert len(where) == len(items) == sum(-(-q * shape.group // 16) for q in q_len)
+    if meet:
+        assert all((where[(s, 16)] - where[(s, 0)]) * shape.num_kv_heads % 8 == 0 for s in range(b.num_seqs))
