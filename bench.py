@@ -317,7 +317,7 @@ def run_linear(args) -> int:
         "data": "synthetic" if args.values == "normal" else "synthetic, ALL-ZERO values (clock diagnostic, not a reported figure)",
         "config": {"workload": "linear: QKV, attention-output, feed-forward up and down projections of the four models of "
                                "Table 1 at one GPU's tensor-parallel share, 16 ... 2048 tokens, N(0,1) values"},
-        "roofline": {"bound": "mfma", "kernel": "linear_kernel", "achieved": ach, "peak": MFMA_BF16_PEAK_TFLOPS,
+        "roofline": {"bound": "mfma", "kernel": "linear_phased_kernel", "achieved": ach, "peak": MFMA_BF16_PEAK_TFLOPS,
                      "unit": "TFLOP/s", "frac": ach / MFMA_BF16_PEAK_TFLOPS, "traffic": None},
         "small_batch_roofline": {"bound": "hbm", "tokens": 128, "achieved": head["weights_GBps"]["128"], "peak": HBM_PEAK_GBS,
                                  "unit": "GB/s", "frac": head["weights_GBps"]["128"] / HBM_PEAK_GBS},
