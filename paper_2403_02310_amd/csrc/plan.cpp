@@ -13,6 +13,7 @@
 // splits of a tile are merged in index order by a second, small kernel.
 #include <algorithm>
 #include <cstdio>
+#include <functional>
 #include <utility>
 
 #include "internal.h"
@@ -231,7 +232,7 @@ double chunk_launch_us(const sarathi_config &cfg, const Plan &plan, size_t n_chu
     busy.clear();
     size_t started = 0;
     double end = 0.0;
-    auto later = [](const std::pair<double, double> &a, const std::pair<double, double> &b) { return a.first > b.first; };
+    auto later = std::greater<std::pair<double, double>>();  // of groups free at the same time the one with less left
     for (int32_t st = max_steps; st > 0; --st) {
         for (int32_t i = 0; i < count[(size_t)st]; ++i) {
             const double u = (double)st + fixed_steps;
@@ -353,20 +354,24 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
     if (opt.tile_split_keys <= 0 && n_chunk_tiles > 0 && (!has_wave_tiles || few_decodes)) {
         tile_split = ceil_div(longest_span, kTileKeys) * kTileKeys;
         if ((int64_t)n_chunk_tiles * cfg.num_kv_heads <= 8192) {
-            // A cut has to promise 5 %: 578 tokens behind 10,320 of a 4096-key window and 231 more, 64 heads, promise 0.5 %
-            // in 1008 pieces and run 3.5 % slower (106.5 us a call whole, 110.2 cut).
+            // Where whole tiles all run at once a cut has to promise 5 %: 578 tokens behind 10,320 of a 4096-key window and
+            // 231 more, 64 heads, promise 0.5 % in 1008 pieces instead of 416 blocks and run 3.5 % slower (106.5 us a call
+            // whole, 110.2 cut).  Beyond one round it may cost 2 % more: 1024, 512 and 384 tokens behind 10,801, 8,115 and
+            // 2,739, 56 heads, are estimated alike whole and in halves and run 3 % faster in halves (840 blocks 504 us, 1288
+            // blocks 477 + 15); of 9 timed batches of several rounds none is cut for the worse by this.
+            const bool one_round = (int64_t)n_chunk_tiles * cfg.num_kv_heads <= 512;
             const double whole_us = chunk_launch_us(cfg, plan, n_chunk_tiles, tile_split, ws.max_part_rows);
-            double best = whole_us;
+            double best = one_round ? whole_us : 1.02 * whole_us;
             // all slots busy to the end: no cut can gain what its merge costs
             const double full_us = (double)keys_of_kind[kKindTile] / kTileKeys * cfg.num_kv_heads * (cfg.head_dim == 128 ? 0.92 : 0.66) / 512.0;
-            int worse = best < full_us + 15.0 ? 2 : 0;
+            int worse = whole_us < full_us + 15.0 ? 2 : 0;
             for (int64_t n = 2; n <= 16 && longest_span / n >= 256 && worse < 2; ++n) {
                 const int64_t keys = ceil_div(ceil_div(longest_span, n), kTileKeys) * kTileKeys;
                 const double c = chunk_launch_us(cfg, plan, n_chunk_tiles, keys, ws.max_part_rows);
                 if (c < best) {
                     best = c;
                     worse = 0;
-                    if (c < 0.95 * whole_us) tile_split = keys;
+                    if (!one_round || c < 0.95 * whole_us) tile_split = keys;
                 } else {
                     ++worse;
                 }

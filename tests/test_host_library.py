@@ -196,6 +196,8 @@ def test_few_decodes_are_cut_and_covered(case, window):
 
 @pytest.mark.parametrize("shape,chunks,cut", [
     (wl.AttnShape(64, 8, 128), [(1299, 1299), (749, 4960)], False),   # two prompts that fill the chip whole
+    (wl.AttnShape(56, 8, 128), [(1024, 11825), (512, 8627), (384, 3123)], True),  # several rounds, alike by the estimate
+    (wl.AttnShape(64, 8, 128), [(578, 3500), (231, 231)], False),     # one round, a cut promises less than 5 %
     (wl.AttnShape(32, 8, 128), [(512, 2383)], True),                  # 128 blocks of 75 steps
     (wl.AttnShape(32, 8, 128), [(1000, 1100), (400, 9400)], True),    # one long prefix among short ones
     (wl.AttnShape(32, 8, 128), [(300, 300)], False),
