@@ -76,6 +76,14 @@ __device__ __forceinline__ void lin_dma_load_16_stream(const uint16_t *base, int
 // 3:0 and 15:14, expcnt 6:4 left at its maximum, lgkmcnt 11:8)
 #define LIN_WAIT_VMCNT_AND_LDS(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (((n) >> 4) << 14) | 0x0070)
 
+// Orders a wavefront's LDS writes before the reads of other lanes that follow (and reads before later writes).  The LDS queue
+// of a wavefront is in order, so no instruction comes of it; it keeps the compiler from moving one across the other.
+__device__ __forceinline__ void lin_wavefront_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 struct LinearParams {
     const uint16_t *x;   // [T, K]
     const uint16_t *w;   // [N, K]
@@ -515,6 +523,7 @@ __global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
         __builtin_amdgcn_sched_barrier(0);
+        lin_wavefront_lds_order();  // the reads of the strip that the same LDS held before
         if (final_rows) {
             constexpr int PIECES = 4 * NI;                // of a token's row of this wavefront, bf16
             char *const buf = out + (j & 1) * 8192;
@@ -525,6 +534,7 @@ __global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {
                     const lf32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
                     *reinterpret_cast<lu32x2 *>(buf + r * 256 + ((i * 4 + q) ^ (r & 15)) * 16 + g * 8) = __builtin_bit_cast(lu32x2, __builtin_convertvector(v, lbf16x4));
                 }
+            lin_wavefront_lds_order();
 #pragma unroll
             for (int u = 0; u < PIECES / 2; ++u) {
                 const int row = (u * 64 + lane) / PIECES, c = (u * 64 + lane) % PIECES;
@@ -540,6 +550,7 @@ __global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {
                 for (int q = 0; q < 4; ++q)
                     *reinterpret_cast<lf32x4 *>(out + r * 512 + ((i * 8 + 2 * q + g) ^ (r & 15)) * 16) =
                         lf32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+            lin_wavefront_lds_order();
 #pragma unroll
             for (int u = 0; u < PIECES / 2; ++u) {
                 const int row = (u * 64 + lane) / PIECES, c = (u * 64 + lane) % PIECES;
