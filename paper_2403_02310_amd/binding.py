@@ -86,13 +86,13 @@ lib.sarathi_set_option.argtypes = [_vp, ctypes.c_char_p, ctypes.c_int64]
 lib.sarathi_get_kernel_times.restype = ctypes.c_int
 lib.sarathi_get_kernel_times.argtypes = [_vp, ctypes.POINTER(KernelTimes)]
 lib.sarathi_kv_append.restype = ctypes.c_int
-lib.sarathi_kv_append.argtypes = [_vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp,  # length arrays: an address or an int32 pointer
+lib.sarathi_kv_append.argtypes = [_vp, _vp, _vp, _vp, _vp, _vp, _i32p, _i32p, _i32p,
                                   ctypes.c_int32, ctypes.c_int32, ctypes.c_int64, _vp, _vp]
 lib.sarathi_hybrid_attention.restype = ctypes.c_int
-lib.sarathi_hybrid_attention.argtypes = [_vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp,
+lib.sarathi_hybrid_attention.argtypes = [_vp, _vp, _vp, _vp, _vp, _i32p, _i32p, _i32p,
                                          ctypes.c_int32, ctypes.c_int32, ctypes.c_int64, ctypes.c_float, _vp, _vp, _vp]
 lib.sarathi_hybrid_attention_noalloc.restype = ctypes.c_int
-lib.sarathi_hybrid_attention_noalloc.argtypes = [_vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp,
+lib.sarathi_hybrid_attention_noalloc.argtypes = [_vp, _vp, _vp, _vp, _vp, _i32p, _i32p, _i32p,
                                                  ctypes.c_int32, ctypes.c_int32, ctypes.c_int64, ctypes.c_float, _vp, _vp]
 lib.sarathi_plan_hybrid_attention.restype = ctypes.c_int
 lib.sarathi_plan_hybrid_attention.argtypes = [_vp, _i32p, _i32p, _i32p, ctypes.c_int32, ctypes.c_int32,
@@ -107,6 +107,20 @@ lib.sarathi_linear_workspace_bytes.restype = ctypes.c_size_t
 lib.sarathi_linear_workspace_bytes.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_int32]
 lib.sarathi_linear.restype = ctypes.c_int
 lib.sarathi_linear.argtypes = [_vp, _vp, _vp, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, _vp, ctypes.c_size_t, _vp]
+
+
+def _with_addresses(name: str):
+    """The same C function for ``Handle``'s own calls, whose length arrays arrive as addresses of int32 arrays (``_addr``).
+    A function object of its own: ``lib``'s keep taking int32 pointers and refuse anything else."""
+    f = lib[name]
+    f.restype = getattr(lib, name).restype
+    f.argtypes = [_vp if t is _i32p else t for t in getattr(lib, name).argtypes]
+    return f
+
+
+_kv_append = _with_addresses("sarathi_kv_append")
+_hybrid_attention = _with_addresses("sarathi_hybrid_attention")
+_hybrid_attention_noalloc = _with_addresses("sarathi_hybrid_attention_noalloc")
 
 
 def _i32(a) -> np.ndarray:
@@ -229,9 +243,9 @@ class Handle:
         pages = int(k_cache.shape[0]) if num_pages is None else num_pages
         ws = workspace if workspace is not None else self.ensure_workspace()
         self._check_block_table(block_table, len(ql))
-        self._check(lib.sarathi_kv_append(self._h, _dev(k_new), _dev(v_new), _dev(k_cache), _dev(v_cache),
-                                          _dev(block_table), _addr(qs), _addr(ql), _addr(cl), len(ql), n, pages,
-                                          _dev(ws), _stream(stream)))
+        self._check(_kv_append(self._h, _dev(k_new), _dev(v_new), _dev(k_cache), _dev(v_cache),
+                               _dev(block_table), _addr(qs), _addr(ql), _addr(cl), len(ql), n, pages,
+                               _dev(ws), _stream(stream)))
 
     def hybrid_attention(self, q, k_cache, v_cache, block_table, q_start, q_len, ctx_len, sm_scale: float, out,
                          num_pages: Optional[int] = None, num_tokens: Optional[int] = None, workspace=None,
@@ -241,9 +255,9 @@ class Handle:
         pages = int(k_cache.shape[0]) if num_pages is None else num_pages
         ws = workspace if workspace is not None else self.ensure_workspace()
         self._check_block_table(block_table, len(ql))
-        self._check(lib.sarathi_hybrid_attention(self._h, _dev(q), _dev(k_cache), _dev(v_cache), _dev(block_table),
-                                                 _addr(qs), _addr(ql), _addr(cl), len(ql), n, pages, float(sm_scale),
-                                                 _dev(out), _dev(ws), _stream(stream)))
+        self._check(_hybrid_attention(self._h, _dev(q), _dev(k_cache), _dev(v_cache), _dev(block_table),
+                                      _addr(qs), _addr(ql), _addr(cl), len(ql), n, pages, float(sm_scale),
+                                      _dev(out), _dev(ws), _stream(stream)))
         return out
 
     def hybrid_attention_noalloc(self, q, k_cache, v_cache, block_table, q_start, q_len, ctx_len, sm_scale: float, out,
@@ -253,9 +267,9 @@ class Handle:
         n = int(ql.sum()) if num_tokens is None else num_tokens
         pages = int(k_cache.shape[0]) if num_pages is None else num_pages
         self._check_block_table(block_table, len(ql))
-        self._check(lib.sarathi_hybrid_attention_noalloc(self._h, _dev(q), _dev(k_cache), _dev(v_cache), _dev(block_table),
-                                                         _addr(qs), _addr(ql), _addr(cl), len(ql), n, pages, float(sm_scale),
-                                                         _dev(out), _stream(stream)))
+        self._check(_hybrid_attention_noalloc(self._h, _dev(q), _dev(k_cache), _dev(v_cache), _dev(block_table),
+                                              _addr(qs), _addr(ql), _addr(cl), len(ql), n, pages, float(sm_scale),
+                                              _dev(out), _stream(stream)))
         return out
 
 

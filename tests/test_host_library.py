@@ -230,3 +230,15 @@ def test_column_tiles_of_a_sequence_meet_on_an_xcd(shape, q_len, meet):
     assert len(where) == len(items) == sum(-(-q * shape.group // 16) for q in q_len)
     if meet:
         assert all((where[(s, 16)] - where[(s, 0)]) * shape.num_kv_heads % 8 == 0 for s in range(b.num_seqs))
+
+
+def test_the_library_functions_refuse_length_arrays_of_another_type():
+    """``binding.lib``'s functions take int32 pointers: an address or an array of 64-bit lengths is refused, not read as it is."""
+    h = binding.Handle(8, 2, 128, max_tokens=64, max_seqs=4, max_blocks_per_seq=4)
+    good = (ctypes.c_int32 * 1)(5)
+    for bad in ((ctypes.c_int64 * 1)(5), ctypes.addressof(good), b"\5\0\0\0"):
+        for name, args in (("sarathi_kv_append", (h._h, 1, 1, 1, 1, 1, good, bad, good, 1, 5, 9, 256, None)),
+                           ("sarathi_hybrid_attention", (h._h, 1, 1, 1, 1, good, bad, good, 1, 5, 9, 0.1, 1, 256, None)),
+                           ("sarathi_hybrid_attention_noalloc", (h._h, 1, 1, 1, 1, good, good, bad, 1, 5, 9, 0.1, 1, None))):
+            with pytest.raises(ctypes.ArgumentError):
+                getattr(binding.lib, name)(*args)
