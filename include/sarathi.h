@@ -198,9 +198,9 @@ sarathi_status sarathi_hybrid_attention(sarathi_handle *handle,
  * nothing (no hipMalloc / hipHostMalloc / hipFree, no stream or event creation) and enqueues kernels only; it
  * records no timing events ("time_kernels" is ignored) and treats option "interleave" = 1 as 2.
  *
- * Limits: the packed plan (48 bytes per tile of 16 decode columns or 128 chunk columns, 4 bytes per work item)
- * must fit into 96 KiB, else SARATHI_ECAPACITY (roughly 1,800 sequences); 16 MiB of partial rows (4,096 rows at
- * 8 KV heads x 128 channels; key ranges are cut less finely when that is short, never refused);
+ * Limits: the packed plan of the uncut batch (48 bytes per tile of 16 decode columns or 128 chunk columns, 4 bytes
+ * per work item) must fit into 96 KiB, else SARATHI_ECAPACITY (roughly 1,800 sequences); 16 MiB of partial rows
+ * (4,096 rows at 8 KV heads x 128 channels); key ranges are cut less finely when either is short, never refused for it;
  * num_kv_heads * head_dim * 4 bytes per partial row must leave room for 256 rows, else SARATHI_ECAPACITY.
  * Every call on a GPU shares that GPU's array: two calls that overlap in time on one GPU (two streams, two
  * handles, two threads) race; calls ordered by one stream are safe.  What must start at zero (the scheduling

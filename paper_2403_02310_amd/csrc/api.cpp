@@ -172,7 +172,7 @@ AttnMetaOffsets attn_meta_offsets(const Plan &pl) {
     AttnMetaOffsets o;
     o.units = align_up(sizeof(TileDesc) * pl.tiles.size(), 16);
     o.reduce = o.units + sizeof(uint32_t) * pl.units.size();
-    o.total = align_up(o.reduce + sizeof(uint32_t) * pl.reduce_units.size(), 16);
+    o.total = attn_meta_bytes(pl.tiles.size(), pl.units.size(), pl.reduce_units.size());
     return o;
 }
 template <typename T>
@@ -608,12 +608,13 @@ extern "C" sarathi_status sarathi_hybrid_attention_noalloc(sarathi_handle *h, co
     if (num_seqs == 0) return SARATHI_OK;
     if (!q || !k_cache || !v_cache || !block_table || !out) return fail(h, SARATHI_EINVAL, "null tensor pointer");
     if (!(sm_scale > 0.0f) || sm_scale - sm_scale != 0.0f) return fail(h, SARATHI_EINVAL, "sm_scale must be positive and finite");
-    // Partial rows the built-in scratch holds for this shape; the planner coarsens its splits until they fit.
+    // Partial rows and metadata the built-in scratch holds; the planner coarsens its splits until both fit.
     const size_t row_bytes = sizeof(float) * (size_t)h->cfg.num_kv_heads * h->cfg.head_dim;
     WorkspaceLayout lay = h->ws;
     lay.max_part_rows = (int32_t)std::min<size_t>((size_t)lay.max_part_rows, kStaticPartOBytes / row_bytes);
     if (lay.max_part_rows < 2 * kTileCols || sizeof(float) * 2 * (size_t)lay.max_part_rows * h->cfg.num_kv_heads > kStaticPartMlBytes)
         return fail(h, SARATHI_ECAPACITY, "allocation-free entry point: num_kv_heads * head_dim is too large for the built-in scratch");
+    lay.max_attn_meta = kStaticMetaBytes;
     h->resident_ws = nullptr;  // h->plan is about to be overwritten
     plan_attention(h->cfg, h->opt, lay, q_start, q_len, ctx_len, num_seqs, h->plan);
     const AttnMetaOffsets o = attn_meta_offsets(h->plan);

@@ -54,6 +54,11 @@ static_assert(sizeof(TileDesc) == 48, "TileDesc is copied to the device as raw b
 constexpr int kUnitTileBits = 22;
 inline uint32_t pack_unit(uint32_t tile, uint32_t split) { return (split << kUnitTileBits) | tile; }
 
+// Packed attention metadata: tile descriptors, work units, merge units.
+inline size_t attn_meta_bytes(size_t tiles, size_t units, size_t reduce_units) {
+    return ((sizeof(TileDesc) * tiles + 15) / 16 * 16 + sizeof(uint32_t) * (units + reduce_units) + 15) / 16 * 16;
+}
+
 struct Plan {
     std::vector<TileDesc> tiles;
     std::vector<uint32_t> units;      // chunk-tile units first (num_tile_units), then wave-tile units; longest first in each group;
@@ -84,6 +89,7 @@ struct WorkspaceLayout {
     int32_t max_units;
     int32_t max_reduce_units;
     int32_t max_part_rows;
+    size_t max_attn_meta; // bytes the packed plan of one attention call may take (attn_meta_bytes)
 };
 
 struct Options {

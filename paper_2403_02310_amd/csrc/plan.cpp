@@ -41,6 +41,7 @@ WorkspaceLayout make_workspace_layout(const sarathi_config &cfg) {
     w.max_reduce_units = (int32_t)std::min<int64_t>(kMaxPartRows / (2 * kReduceCols) + kMaxSplitUnits / 2, INT32_MAX / 64);
     const size_t attn_meta = sizeof(TileDesc) * (size_t)w.max_tiles +
                              sizeof(uint32_t) * ((size_t)w.max_units + (size_t)w.max_reduce_units) + 64;
+    w.max_attn_meta = attn_meta;
     const size_t append_meta = sizeof(AppendUnit) * (size_t)max_append_units(cfg) + 64;
     size_t off = 0;
     w.meta = off;
@@ -179,18 +180,26 @@ void pair_column_tiles(Plan &plan, size_t base, int32_t num_kv_heads, std::vecto
     }
 }
 
-// Split units, partial rows and split tiles a choice of split_keys would need for tiles [first, last).
-void count_splits(const Plan &plan, size_t first, size_t last, int64_t split_keys, int64_t whole_keys, int64_t &n_split_units,
-                  int64_t &rows, int64_t &n_split_tiles) {
+// What a choice of split_keys would need for tiles [first, last).
+struct SplitCount {
+    int64_t units = 0;         // pieces of the split tiles
+    int64_t rows = 0;          // partial rows
+    int64_t tiles = 0;         // split tiles
+    int64_t reduce_units = 0;  // merge units
+};
+SplitCount count_splits(const Plan &plan, size_t first, size_t last, int64_t split_keys, int64_t whole_keys) {
+    SplitCount c;
     for (size_t ti = first; ti < last; ++ti) {
         const TileDesc &t = plan.tiles[ti];
         const int64_t span = t.n_keys - t.key_lo;
         if (span <= std::max(split_keys + split_keys / 2, whole_keys)) continue;
         const int64_t ns = ceil_div(span, split_keys);
-        n_split_units += ns;
-        rows += ns * t.n_cols;
-        n_split_tiles++;
+        c.units += ns;
+        c.rows += ns * t.n_cols;
+        c.tiles++;
+        c.reduce_units += ceil_div(t.n_cols, kReduceCols);
     }
+    return c;
 }
 
 // Estimated time of a launch of chunk tiles alone whose keys are cut at `split_keys`, merge included, in microseconds; a
@@ -457,12 +466,16 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
         }
     }
     for (;;) {
-        int64_t n_split_units = 0, rows = 0, n_split_tiles = 0;
-        count_splits(plan, 0, n_chunk_tiles, tile_split, 0, n_split_units, rows, n_split_tiles);
-        count_splits(plan, n_chunk_tiles, plan.tiles.size(), wave_split, wave_whole, n_split_units, rows, n_split_tiles);
+        const SplitCount chunk = count_splits(plan, 0, n_chunk_tiles, tile_split, 0);
+        const SplitCount wave = count_splits(plan, n_chunk_tiles, plan.tiles.size(), wave_split, wave_whole);
+        const int64_t n_split_units = chunk.units + wave.units, n_split_tiles = chunk.tiles + wave.tiles;
+        const int64_t n_units = (int64_t)plan.tiles.size() - n_split_tiles + n_split_units;
         const int64_t max_splits_per_tile = (1 << (32 - kUnitTileBits)) - 1;
-        bool fits = n_split_units <= kMaxSplitUnits && rows <= ws.max_part_rows && n_split_tiles <= kMaxSplitUnits / 2 &&
+        bool fits = n_split_units <= kMaxSplitUnits && chunk.rows + wave.rows <= ws.max_part_rows && n_split_tiles <= kMaxSplitUnits / 2 &&
                     (int64_t)plan.tiles.size() + n_split_units <= ws.max_units;
+        // a batch whose tiles fit whole is not refused for the pieces it would have been cut into
+        if (n_split_tiles > 0 && attn_meta_bytes(plan.tiles.size(), (size_t)n_units, (size_t)(chunk.reduce_units + wave.reduce_units)) > ws.max_attn_meta)
+            fits = false;
         for (const TileDesc &t : plan.tiles)
             if (ceil_div(t.n_keys - t.key_lo, t.kind == kKindTile ? tile_split : wave_split) > max_splits_per_tile) { fits = false; break; }
         if (fits) break;

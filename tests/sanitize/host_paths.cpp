@@ -248,6 +248,47 @@ static void drive_attention_host_paths(std::mt19937_64 &rng) {
     }
 }
 
+// Batches close to what the allocation-free entry point holds (96 KiB of metadata): one whose tiles fit whole is taken,
+// however finely its keys would be cut elsewhere, and one whose tiles do not is refused.
+static void drive_built_in_scratch_limits(std::mt19937_64 &rng) {
+    auto rnd = [&](int lo, int hi) { return (int)(lo + rng() % (uint64_t)(hi - lo + 1)); };
+    const int shapes[][3] = {{71, 1, 64}, {64, 1, 128}, {20, 1, 128}, {64, 8, 128}};
+    int taken = 0, refused = 0;
+    for (int it = 0; it < 400; ++it) {
+        const int *sh = shapes[it % 4];
+        const int G = sh[0] / sh[1], target = rnd(1650, 1900), decodes = it % 3 ? 0 : rnd(1, 200);
+        std::vector<int32_t> qs, ql, cl;
+        int64_t T = 0, tiles = 0;
+        auto add = [&](int q, int prefix) {
+            qs.push_back((int32_t)T);
+            ql.push_back(q);
+            cl.push_back(prefix + q);
+            const int64_t cols = (int64_t)q * G;
+            tiles += cols >= 64 ? (cols + sarathi::kTileCols - 1) / sarathi::kTileCols : (cols + sarathi::kWaveCols - 1) / sarathi::kWaveCols;
+            T += q;
+        };
+        for (int i = 0; i < decodes; ++i) add(1, rnd(100, 16000));
+        while (tiles < target) add(std::max(1, std::min(rnd(40, 1600), (int)((target - tiles) * sarathi::kTileCols / G))), rnd(0, 2) ? rnd(0, 3000) : rnd(0, 16000));
+        const int S = (int)ql.size();
+        int max_blocks = 1;
+        for (int32_t c : cl) max_blocks = std::max(max_blocks, (c + 15) / 16);
+        const sarathi_config cfg{sh[0], sh[1], sh[2], 16, 0, (int32_t)T, S, max_blocks};
+        sarathi_handle *h = nullptr;
+        CHECK(sarathi_create(&cfg, &h) == SARATHI_OK);
+        std::vector<int32_t> bt((size_t)S * max_blocks, 0);
+        char dummy[16];
+        sarathi::g_num_seqs = S;
+        sarathi::g_num_tokens = T;
+        const bool fits = sarathi::attn_meta_bytes((size_t)tiles, (size_t)tiles, 0) <= sarathi::kStaticMetaBytes;
+        const sarathi_status st = sarathi_hybrid_attention_noalloc(h, dummy, dummy, dummy, bt.data(), qs.data(), ql.data(), cl.data(), S,
+                                                                   (int32_t)T, 1, 0.1f, dummy, nullptr);
+        CHECK(st == (fits ? SARATHI_OK : SARATHI_ECAPACITY));
+        (fits ? taken : refused)++;
+        CHECK(sarathi_destroy(h) == SARATHI_OK);
+    }
+    CHECK(taken > 200 && refused > 5);
+}
+
 static void drive_checker() {
     // one chunk on a prefix and two decodes, GQA 4:2, d = 8; every buffer exactly as large as documented
     const int Hq = 4, Hkv = 2, d = 8;
@@ -287,6 +328,7 @@ int main() {
     std::mt19937_64 rng(20240302);
     drive_scheduler(rng);
     drive_attention_host_paths(rng);
+    drive_built_in_scratch_limits(rng);
     drive_checker();
     std::printf("host paths clean (sink %llu)\n", (unsigned long long)sarathi::g_sink);
     return 0;
