@@ -399,8 +399,10 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
     // whole decodes on average; 8 decodes of 256-4096 keys: 53 -> 19 + 6 us.  A cut has to promise 5 %, and
     // below 28 us nothing is cut: two launches keep the host for about as long, and a merge would be a third.
     // (A block's rate is its compute unit's: eight wavefronts instead of four pull the same 40 GB/s, so only more blocks help.)
-    // Where one decode holds half of the keys or more, it alone is cut, as such batches always were: 7000 and 3000 keys
-    // next to three short ones then end with the 3000-key block, at 38 us instead of about 20.
+    // Where one decode holds half of the keys or more, a plan that cuts it finer and leaves all of up to half its length whole
+    // is tried first and taken if it promises the 5 %, as such batches always were (7000 and 3000 keys next to three short
+    // ones then end with the 3000-key block, at 42 us).  Where it does not the general search follows: 14,000, 7000 and 6500
+    // keys 54 + 6 us in pieces of 4096, 23 + 6 in pieces of 1024; 16,000 keys next to three times 4000 60 + 6 and 23 + 6.
     int64_t wave_whole = 0;
     const int64_t n_wave_tiles = (int64_t)(plan.tiles.size() - n_chunk_tiles);
     plan.short_decode_pieces = false;
@@ -427,12 +429,12 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
         for (size_t ti = n_chunk_tiles; ti < plan.tiles.size(); ++ti)
             longest_wave = std::max<int64_t>(longest_wave, plan.tiles[ti].n_keys - plan.tiles[ti].key_lo);
         const int64_t whole = 2 * longest_wave >= keys_of_kind[kKindWave] ? longest_wave / 2 : 0;
-        auto estimate = [&](int32_t keys) {
+        auto estimate = [&](int32_t keys, int64_t uncut) {
             const float inverse = 1.0f / (float)keys;
             int64_t longest = 0, pieces = 0, rows = 0, most = 1;
             for (size_t ti = n_chunk_tiles; ti < plan.tiles.size(); ++ti) {
                 const int32_t span = plan.tiles[ti].n_keys - plan.tiles[ti].key_lo;
-                if (span <= std::max<int64_t>(keys + keys / 2, whole)) {
+                if (span <= std::max<int64_t>(keys + keys / 2, uncut)) {
                     longest = std::max<int64_t>(longest, span);
                     pieces += 1;
                 } else {
@@ -453,16 +455,22 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
             }
             return c;
         };
-        const double as_is = estimate((int32_t)std::min<int64_t>(wave_split, INT32_MAX / 2));
-        double best = as_is < 28.0 ? 0.0 : 0.95 * as_is;
-        for (const int32_t keys : {4096, 3072, 2048, 1536, 1024, 768, 512, 384, 256}) {
-            const double c = estimate(keys);
-            if (c < best) {
-                best = c;
-                wave_split = keys;
-                wave_whole = whole;
-                plan.short_decode_pieces = true;
+        const double as_is = estimate((int32_t)std::min<int64_t>(wave_split, INT32_MAX / 2), 0);
+        auto search = [&](int64_t uncut) {
+            double best = 0.95 * as_is;
+            for (const int32_t keys : {4096, 3072, 2048, 1536, 1024, 768, 512, 384, 256}) {
+                const double c = estimate(keys, uncut);
+                if (c < best) {
+                    best = c;
+                    wave_split = keys;
+                    wave_whole = uncut;
+                    plan.short_decode_pieces = true;
+                }
             }
+        };
+        if (as_is >= 28.0) {
+            if (whole > 0) search(whole);
+            if (!plan.short_decode_pieces) search(0);
         }
     }
     for (;;) {

@@ -242,3 +242,20 @@ def test_the_library_functions_refuse_length_arrays_of_another_type():
                            ("sarathi_hybrid_attention_noalloc", (h._h, 1, 1, 1, 1, good, good, bad, 1, 5, 9, 0.1, 1, None))):
             with pytest.raises(ctypes.ArgumentError):
                 getattr(binding.lib, name)(*args)
+
+
+@pytest.mark.parametrize("rest", [[7000, 6500], [10000, 8000], [3000, 3000, 100]])
+def test_decodes_around_half_of_the_keys_are_cut_alike(rest):
+    """A plan that cuts only the decode that holds half of the batch's keys is an offer, not a must: just above and just below
+    that half the longest piece is about the same, and no longer than what one block streams well within the launch."""
+    shape, half, longest = wl.AttnShape(32, 8, 128), sum(rest), []
+    for first in (half - 300, half, half + 300):
+        b = wl._make("half", shape, [1] * (1 + len(rest)), [first] + rest, 97)
+        _coverage_check(b)
+        h = binding.Handle(32, 8, 128, max_tokens=64, max_seqs=8, max_blocks_per_seq=b.max_blocks_per_seq)
+        _, items = h.plan(b.q_start, b.q_len, b.ctx_len)
+        longest.append(max(it.key_end - it.key_begin for it in items))
+    if rest[-1] > 100:
+        assert max(longest) <= 1.5 * min(longest) and max(longest) <= 2304
+    else:
+        assert max(longest) <= 3000   # the 3000-key decodes stay whole above the half
