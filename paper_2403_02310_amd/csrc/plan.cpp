@@ -273,6 +273,132 @@ double chunk_launch_us(const sarathi_config &cfg, const Plan &plan, size_t n_chu
     return c;
 }
 
+// The cut of a batch's chunk tiles that chunk_launch_us finds cheapest within `max_rows` partial rows, in keys per piece (the longest
+// tile's keys: whole).  Pieces of fewer than eight key steps are all prologue, and the search ends where finer cuts have cost
+// more twice in a row.
+int64_t cheapest_chunk_split(const sarathi_config &cfg, const Plan &plan, size_t n_chunk_tiles, int64_t chunk_keys, int64_t longest_span, int64_t max_rows) {
+    int64_t tile_split = ceil_div(longest_span, kTileKeys) * kTileKeys;
+    if ((int64_t)n_chunk_tiles * cfg.num_kv_heads > 8192) return tile_split;
+    // Where whole tiles all run at once a cut has to promise 5 %: 578 tokens behind 10,320 of a 4096-key window and
+    // 231 more, 64 heads, promise 0.5 % in 1008 pieces instead of 416 blocks and run 3.5 % slower (106.5 us a call
+    // whole, 110.2 cut).  Beyond one round it may cost 2 % more: 1024, 512 and 384 tokens behind 10,801, 8,115 and
+    // 2,739, 56 heads, are estimated alike whole and in halves and run 3 % faster in halves (840 blocks 504 us, 1288
+    // blocks 477 + 15); of 9 timed batches of several rounds none is cut for the worse by this.
+    const bool one_round = (int64_t)n_chunk_tiles * cfg.num_kv_heads <= 512;
+    const double whole_us = chunk_launch_us(cfg, plan, n_chunk_tiles, tile_split, max_rows);
+    double best = one_round ? whole_us : 1.02 * whole_us;
+    // all slots busy to the end: no cut can gain what its merge costs
+    const double full_us = (double)chunk_keys / kTileKeys * cfg.num_kv_heads * (cfg.head_dim == 128 ? 0.92 : 0.66) / 512.0;
+    int worse = whole_us < full_us + 15.0 ? 2 : 0;
+    for (int64_t n = 2; n <= 16 && longest_span / n >= 256 && worse < 2; ++n) {
+        const int64_t keys = ceil_div(ceil_div(longest_span, n), kTileKeys) * kTileKeys;
+        const double c = chunk_launch_us(cfg, plan, n_chunk_tiles, keys, max_rows);
+        if (c < best) {
+            best = c;
+            worse = 0;
+            if (!one_round || c < 0.95 * whole_us) tile_split = keys;
+        } else {
+            ++worse;
+        }
+    }
+    return tile_split;
+}
+
+// Few decodes.  Uncut, a batch's wave blocks (tiles x KV heads) leave compute units idle or finish with the longest
+// decode streaming alone, and one block pulls 40 GB/s at most where the chip streams 6,550.  Up to 512 blocks (two per
+// compute unit, all resident at once) the keys per piece therefore come from an estimate, in microseconds, of
+//   decodes: the larger of (all keys at the chip's rate, the longest piece at a block's) + a quarter of the smaller
+//            + 3, and 2 for every further 512 blocks;
+//   with prefill chunks in the launch: the longer of decodes and chunks + 0.3 of the shorter (they share the units);
+//   merge, if anything is cut: 5.3 + 0.25 per piece of the tile with the most + its partial rows twice at 4.5 TB/s.
+// Against timings of 20 decode-only and 17 hybrid batches (1 to 64 decodes of 256 to 32,768 keys, seven pieces each):
+// the chosen piece is within 5 % of the best one at the median and 1.9 x (decodes only) and 1.17 x (hybrid) faster than
+// whole decodes on average; 8 decodes of 256-4096 keys: 53 -> 19 + 6 us.  A cut has to promise 5 %, and
+// below 28 us nothing is cut: two launches keep the host for about as long, and a merge would be a third.
+// (A block's rate is its compute unit's: eight wavefronts instead of four pull the same 40 GB/s, so only more blocks help.)
+// Where one decode holds half of the keys or more, a plan that cuts it finer and leaves all of up to half its length whole
+// is tried first and taken if it promises the 5 %, as such batches always were (7000 and 3000 keys next to three short
+// ones then end with the 3000-key block, at 42 us).  Where it does not the general search follows: 14,000, 7000 and 6500
+// keys 54 + 6 us in pieces of 4096, 23 + 6 in pieces of 1024; 16,000 keys next to three times 4000 60 + 6 and 23 + 6.
+struct WaveCut {
+    int64_t keys;   // per piece
+    int64_t whole;  // spans of up to this many keys stay uncut
+    bool few;       // chosen by the estimate
+};
+WaveCut cheapest_wave_cut(const sarathi_config &cfg, const Plan &plan, size_t n_chunk_tiles, int64_t wave_keys, int64_t tile_split, int64_t wave_split,
+                          int64_t max_rows, bool chunks_made_do) {
+    const int64_t n_wave_tiles = (int64_t)(plan.tiles.size() - n_chunk_tiles);
+    const double key_us = cfg.head_dim * 4.0;  // bytes of a key and its value, one KV head
+    double chunk_steps = 0.0;
+    int64_t chunk_blocks = 0;
+    bool chunk_cut = false;
+    if (n_chunk_tiles > 0) {
+        int64_t steps = 0, longest = 0, chunk_units = 0;
+        for (size_t ti = 0; ti < n_chunk_tiles; ++ti) {
+            const int64_t span = plan.tiles[ti].n_keys - plan.tiles[ti].key_lo;
+            const int64_t ns = span <= tile_split + tile_split / 2 ? 1 : ceil_div(span, tile_split);
+            const int64_t piece = ceil_div(ceil_div(span, ns), kTileKeys);
+            steps += ceil_div(span, kTileKeys) + ns;
+            longest = std::max(longest, piece + 1);
+            chunk_units += ns;
+            chunk_cut |= ns > 1;
+        }
+        chunk_blocks = chunk_units;
+        chunk_steps = std::max((double)longest, (double)steps * cfg.num_kv_heads / 512.0);
+    }
+    const double stream_us = (double)wave_keys * cfg.num_kv_heads * key_us / 6.55e6;
+    int64_t longest_wave = 0;
+    for (size_t ti = n_chunk_tiles; ti < plan.tiles.size(); ++ti)
+        longest_wave = std::max<int64_t>(longest_wave, plan.tiles[ti].n_keys - plan.tiles[ti].key_lo);
+    const int64_t whole = 2 * longest_wave >= wave_keys ? longest_wave / 2 : 0;
+    auto estimate = [&](int32_t keys, int64_t uncut) {
+        int64_t longest = 0, pieces = 0, rows = 0, most = 1;
+        for (size_t ti = n_chunk_tiles; ti < plan.tiles.size(); ++ti) {
+            const int32_t span = plan.tiles[ti].n_keys - plan.tiles[ti].key_lo;
+            if (span <= std::max<int64_t>(keys + keys / 2, uncut)) {
+                longest = std::max<int64_t>(longest, span);
+                pieces += 1;
+            } else {
+                const int32_t ns = (span - 1) / keys + 1;
+                longest = std::max<int64_t>(longest, keys);
+                pieces += ns;
+                rows += ns * plan.tiles[ti].n_cols;
+                most = std::max<int64_t>(most, ns);
+            }
+        }
+        const double block_us = (double)longest * key_us / 40.0e3;
+        const double decode_us = 3.0 + std::max(stream_us, block_us) + 0.25 * std::min(stream_us, block_us) +
+                                 2.0 * (double)((pieces * cfg.num_kv_heads - 1) / 512);
+        if (rows > max_rows && most > 1) return 1.0e12;
+        // whole chunk tiles that were to be cut are the launch's tail: pieces that push a second block onto their units tell
+        const int64_t blocks = (chunk_blocks + (chunks_made_do ? pieces : n_wave_tiles)) * cfg.num_kv_heads;
+        const double chunk_us = n_chunk_tiles == 0 ? 0.0 : 4.0 + chunk_steps * (blocks <= 256 ? 0.62 : 0.9);
+        double c = std::max(decode_us, chunk_us) + 0.3 * std::min(decode_us, chunk_us);
+        if (most > 1) {
+            c += 0.25 * (double)most + 2.0 * (double)rows * cfg.num_kv_heads * (cfg.head_dim + 2) * 4.0 / 4.5e6;
+            if (!chunk_cut) c += 5.3;
+        }
+        return c;
+    };
+    const double as_is = estimate((int32_t)std::min<int64_t>(wave_split, INT32_MAX / 2), 0);
+    WaveCut best{wave_split, 0, false};
+    double best_us = 0.95 * as_is;
+    auto search = [&](int64_t uncut) {
+        for (const int32_t keys : {4096, 3072, 2048, 1536, 1024, 768, 512, 384, 256}) {
+            const double c = estimate(keys, uncut);
+            if (c < best_us) {
+                best = WaveCut{keys, uncut, true};
+                best_us = c;
+            }
+        }
+    };
+    if (as_is >= 28.0) {
+        if (whole > 0) search(whole);
+        if (!best.few) search(0);
+    }
+    return best;
+}
+
 }  // namespace
 
 void plan_attention(const sarathi_config &cfg, const Options &opt, const WorkspaceLayout &ws,
@@ -349,129 +475,41 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
         const double wave_us = wave_stream_us;
         tile_floor = std::max<int64_t>(2 * kMinTileSplitKeys, (int64_t)(wave_us / 1.2) * kTileKeys);
     }
-    int64_t tile_split = pick(opt.tile_split_keys, keys_of_kind[kKindTile], tile_units_wanted, tile_floor);
     // Chunks alone, or next to decodes that hardly count (chunk blocks on at most half of the compute units, decodes that
     // stream for less than a quarter of the time the longest chunk block takes uncut; 512 tokens behind 1871 next to 4
     // decodes: 48 + 6 us with whole chunk tiles, 40 + 9 cut in two; next to 16 decodes, 0.4 of that time, 54 + 6 against
-    // 58 + 10): the cut that chunk_launch_us finds cheapest.  Pieces of fewer than eight key steps are all prologue, and the
-    // search ends where finer cuts have cost more twice in a row.
+    // 58 + 10): the cheapest cut by playing the launch through.
     int64_t longest_span = 1;
     for (size_t ti = 0; ti < n_chunk_tiles; ++ti)
         longest_span = std::max<int64_t>(longest_span, plan.tiles[ti].n_keys - plan.tiles[ti].key_lo);
     const bool few_decodes = (int64_t)n_chunk_tiles * cfg.num_kv_heads <= 128 &&
                              wave_stream_us < 0.25 * 0.62 * (double)longest_span / kTileKeys;
-    if (opt.tile_split_keys <= 0 && n_chunk_tiles > 0 && (!has_wave_tiles || few_decodes)) {
-        tile_split = ceil_div(longest_span, kTileKeys) * kTileKeys;
-        if ((int64_t)n_chunk_tiles * cfg.num_kv_heads <= 8192) {
-            // Where whole tiles all run at once a cut has to promise 5 %: 578 tokens behind 10,320 of a 4096-key window and
-            // 231 more, 64 heads, promise 0.5 % in 1008 pieces instead of 416 blocks and run 3.5 % slower (106.5 us a call
-            // whole, 110.2 cut).  Beyond one round it may cost 2 % more: 1024, 512 and 384 tokens behind 10,801, 8,115 and
-            // 2,739, 56 heads, are estimated alike whole and in halves and run 3 % faster in halves (840 blocks 504 us, 1288
-            // blocks 477 + 15); of 9 timed batches of several rounds none is cut for the worse by this.
-            const bool one_round = (int64_t)n_chunk_tiles * cfg.num_kv_heads <= 512;
-            const double whole_us = chunk_launch_us(cfg, plan, n_chunk_tiles, tile_split, ws.max_part_rows);
-            double best = one_round ? whole_us : 1.02 * whole_us;
-            // all slots busy to the end: no cut can gain what its merge costs
-            const double full_us = (double)keys_of_kind[kKindTile] / kTileKeys * cfg.num_kv_heads * (cfg.head_dim == 128 ? 0.92 : 0.66) / 512.0;
-            int worse = whole_us < full_us + 15.0 ? 2 : 0;
-            for (int64_t n = 2; n <= 16 && longest_span / n >= 256 && worse < 2; ++n) {
-                const int64_t keys = ceil_div(ceil_div(longest_span, n), kTileKeys) * kTileKeys;
-                const double c = chunk_launch_us(cfg, plan, n_chunk_tiles, keys, ws.max_part_rows);
-                if (c < best) {
-                    best = c;
-                    worse = 0;
-                    if (!one_round || c < 0.95 * whole_us) tile_split = keys;
-                } else {
-                    ++worse;
-                }
-            }
-        }
-    }
-    // Few decodes.  Uncut, a batch's wave blocks (tiles x KV heads) leave compute units idle or finish with the longest
-    // decode streaming alone, and one block pulls 40 GB/s at most where the chip streams 6,550.  Up to 512 blocks (two per
-    // compute unit, all resident at once) the keys per piece therefore come from an estimate, in microseconds, of
-    //   decodes: the larger of (all keys at the chip's rate, the longest piece at a block's) + a quarter of the smaller
-    //            + 3, and 2 for every further 512 blocks;
-    //   with prefill chunks in the launch: the longer of decodes and chunks + 0.3 of the shorter (they share the units);
-    //   merge, if anything is cut: 5.3 + 0.25 per piece of the tile with the most + its partial rows twice at 4.5 TB/s.
-    // Against timings of 20 decode-only and 17 hybrid batches (1 to 64 decodes of 256 to 32,768 keys, seven pieces each):
-    // the chosen piece is within 5 % of the best one at the median and 1.9 x (decodes only) and 1.17 x (hybrid) faster than
-    // whole decodes on average; 8 decodes of 256-4096 keys: 53 -> 19 + 6 us.  A cut has to promise 5 %, and
-    // below 28 us nothing is cut: two launches keep the host for about as long, and a merge would be a third.
-    // (A block's rate is its compute unit's: eight wavefronts instead of four pull the same 40 GB/s, so only more blocks help.)
-    // Where one decode holds half of the keys or more, a plan that cuts it finer and leaves all of up to half its length whole
-    // is tried first and taken if it promises the 5 %, as such batches always were (7000 and 3000 keys next to three short
-    // ones then end with the 3000-key block, at 42 us).  Where it does not the general search follows: 14,000, 7000 and 6500
-    // keys 54 + 6 us in pieces of 4096, 23 + 6 in pieces of 1024; 16,000 keys next to three times 4000 60 + 6 and 23 + 6.
+    auto chunk_count = [&](int64_t keys) { return count_splits(plan, 0, n_chunk_tiles, keys, 0); };
+    auto cut_chunks = [&](int64_t max_rows) {
+        if (opt.tile_split_keys <= 0 && n_chunk_tiles > 0 && (!has_wave_tiles || few_decodes))
+            return cheapest_chunk_split(cfg, plan, n_chunk_tiles, keys_of_kind[kKindTile], longest_span, max_rows);
+        int64_t keys = pick(opt.tile_split_keys, keys_of_kind[kKindTile], tile_units_wanted, tile_floor);
+        while (opt.tile_split_keys <= 0 && chunk_count(keys).rows > max_rows) keys *= 2;
+        return keys;
+    };
+    int64_t tile_split = cut_chunks(ws.max_part_rows);
     int64_t wave_whole = 0;
-    const int64_t n_wave_tiles = (int64_t)(plan.tiles.size() - n_chunk_tiles);
     plan.short_decode_pieces = false;
-    if (opt.split_keys <= 0 && n_wave_tiles > 0 && n_wave_tiles * cfg.num_kv_heads <= 512) {
-        const double key_us = cfg.head_dim * 4.0;  // bytes of a key and its value, one KV head
-        double chunk_us = 0.0;
-        bool chunk_cut = false;
-        if (n_chunk_tiles > 0) {
-            int64_t steps = 0, longest = 0, chunk_units = 0;
-            for (size_t ti = 0; ti < n_chunk_tiles; ++ti) {
-                const int64_t span = plan.tiles[ti].n_keys - plan.tiles[ti].key_lo;
-                const int64_t ns = span <= tile_split + tile_split / 2 ? 1 : ceil_div(span, tile_split);
-                const int64_t piece = ceil_div(ceil_div(span, ns), kTileKeys);
-                steps += ceil_div(span, kTileKeys) + ns;
-                longest = std::max(longest, piece + 1);
-                chunk_units += ns;
-                chunk_cut |= ns > 1;
-            }
-            const double step_us = (chunk_units + n_wave_tiles) * cfg.num_kv_heads <= 256 ? 0.62 : 0.9;
-            chunk_us = 4.0 + std::max((double)longest * step_us, (double)steps * cfg.num_kv_heads * step_us / 512.0);
+    if (opt.split_keys <= 0 && has_wave_tiles && (int64_t)(plan.tiles.size() - n_chunk_tiles) * cfg.num_kv_heads <= 512) {
+        WaveCut w = cheapest_wave_cut(cfg, plan, n_chunk_tiles, keys_of_kind[kKindWave], tile_split, wave_split, ws.max_part_rows, false);
+        const int64_t wave_rows = count_splits(plan, n_chunk_tiles, plan.tiles.size(), w.keys, w.whole).rows;
+        if (w.few && wave_rows + chunk_count(tile_split).rows > ws.max_part_rows) {
+            // The partial rows do not suffice for both cuts.  The decodes need few and the chunks make do with the rest (512 tokens
+            // behind 3871 next to 4000 and 3000 keys, 32 and 8 heads, 4096 rows: 87 us a call with whole chunk tiles, 97 with
+            // halves and whole decodes, which next to chunk blocks stream at 25 GB/s); then the decodes are looked at again
+            // (512 tokens behind 3871 next to 9000 and 3000 keys: 89 us, 136 with both cuts doubled until they fit).
+            if (opt.tile_split_keys <= 0) tile_split = cut_chunks(ws.max_part_rows - wave_rows);
+            w = cheapest_wave_cut(cfg, plan, n_chunk_tiles, keys_of_kind[kKindWave], tile_split, wave_split,
+                                  std::max<int64_t>(0, ws.max_part_rows - chunk_count(tile_split).rows), true);
         }
-        const double stream_us = (double)keys_of_kind[kKindWave] * cfg.num_kv_heads * key_us / 6.55e6;
-        int64_t longest_wave = 0;
-        for (size_t ti = n_chunk_tiles; ti < plan.tiles.size(); ++ti)
-            longest_wave = std::max<int64_t>(longest_wave, plan.tiles[ti].n_keys - plan.tiles[ti].key_lo);
-        const int64_t whole = 2 * longest_wave >= keys_of_kind[kKindWave] ? longest_wave / 2 : 0;
-        auto estimate = [&](int32_t keys, int64_t uncut) {
-            const float inverse = 1.0f / (float)keys;
-            int64_t longest = 0, pieces = 0, rows = 0, most = 1;
-            for (size_t ti = n_chunk_tiles; ti < plan.tiles.size(); ++ti) {
-                const int32_t span = plan.tiles[ti].n_keys - plan.tiles[ti].key_lo;
-                if (span <= std::max<int64_t>(keys + keys / 2, uncut)) {
-                    longest = std::max<int64_t>(longest, span);
-                    pieces += 1;
-                } else {
-                    const int64_t ns = (int64_t)((float)(span - 1) * inverse) + 1;
-                    longest = std::max<int64_t>(longest, keys);
-                    pieces += ns;
-                    rows += ns * plan.tiles[ti].n_cols;
-                    most = std::max(most, ns);
-                }
-            }
-            const double block_us = (double)longest * key_us / 40.0e3;
-            const double decode_us = 3.0 + std::max(stream_us, block_us) + 0.25 * std::min(stream_us, block_us) +
-                                     2.0 * (double)((pieces * cfg.num_kv_heads - 1) / 512);
-            double c = std::max(decode_us, chunk_us) + 0.3 * std::min(decode_us, chunk_us);
-            if (most > 1) {
-                c += 0.25 * (double)most + 2.0 * (double)rows * cfg.num_kv_heads * (cfg.head_dim + 2) * 4.0 / 4.5e6;
-                if (!chunk_cut) c += 5.3;
-            }
-            return c;
-        };
-        const double as_is = estimate((int32_t)std::min<int64_t>(wave_split, INT32_MAX / 2), 0);
-        auto search = [&](int64_t uncut) {
-            double best = 0.95 * as_is;
-            for (const int32_t keys : {4096, 3072, 2048, 1536, 1024, 768, 512, 384, 256}) {
-                const double c = estimate(keys, uncut);
-                if (c < best) {
-                    best = c;
-                    wave_split = keys;
-                    wave_whole = uncut;
-                    plan.short_decode_pieces = true;
-                }
-            }
-        };
-        if (as_is >= 28.0) {
-            if (whole > 0) search(whole);
-            if (!plan.short_decode_pieces) search(0);
-        }
+        wave_split = w.keys;
+        wave_whole = w.whole;
+        plan.short_decode_pieces = w.few;
     }
     for (;;) {
         const SplitCount chunk = count_splits(plan, 0, n_chunk_tiles, tile_split, 0);
@@ -487,8 +525,10 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
         for (const TileDesc &t : plan.tiles)
             if (ceil_div(t.n_keys - t.key_lo, t.kind == kKindTile ? tile_split : wave_split) > max_splits_per_tile) { fits = false; break; }
         if (fits) break;
-        wave_split *= 2;
-        tile_split *= 2;
+        // partial rows: the kind that needs more of them makes do with less
+        const bool rows_only = chunk.rows + wave.rows > ws.max_part_rows;
+        if (!rows_only || wave.rows >= chunk.rows) wave_split *= 2;
+        if (!rows_only || chunk.rows >= wave.rows) tile_split *= 2;
     }
     plan.split_keys = (int32_t)std::min<int64_t>(wave_split / 4, INT32_MAX);  // per wavefront
     plan.tile_split_keys = (int32_t)std::min<int64_t>(tile_split, INT32_MAX);

@@ -289,6 +289,33 @@ static void drive_built_in_scratch_limits(std::mt19937_64 &rng) {
     CHECK(taken > 200 && refused > 5);
 }
 
+// Chunks and decodes that both want to be cut, with the 4096 partial rows that the built-in scratch holds at 8 x 128: the plan is
+// one that was looked at, not both cuts doubled until they fit (twice the pieces at least).
+static void drive_scarce_partial_rows() {
+    struct Batch {
+        int32_t hq, hkv, d, max_rows;
+        std::vector<int32_t> q_len, ctx_len;
+        int32_t longest_decode_piece;
+    };
+    const Batch batches[] = {{32, 8, 128, 4096, {512, 1, 1}, {4383, 9000, 3000}, 1024},
+                             {32, 8, 128, 4096, {512, 1, 1, 1, 1}, {2383, 4000, 3000, 2000, 1000}, 1536},
+                             {32, 8, 128, 4096, {512, 1, 1, 1}, {6000, 8000, 3000, 3000}, 2048},
+                             {32, 1, 128, 32768, {512, 1, 1}, {4383, 4000, 9000}, 1024}};
+    for (const Batch &b : batches) {
+        const sarathi_config cfg{b.hq, b.hkv, b.d, 16, 0, 4096, 64, 1024};
+        sarathi::WorkspaceLayout ws = sarathi::make_workspace_layout(cfg);
+        ws.max_part_rows = b.max_rows;
+        std::vector<int32_t> q_start;
+        int32_t run = 0;
+        for (int32_t q : b.q_len) { q_start.push_back(run); run += q; }
+        sarathi::Plan plan;
+        sarathi::plan_attention(cfg, sarathi::Options{}, ws, q_start.data(), b.q_len.data(), b.ctx_len.data(), (int32_t)b.q_len.size(), plan);
+        CHECK(plan.num_part_rows <= b.max_rows);
+        for (const sarathi::TileDesc &t : plan.tiles)
+            if (t.kind == sarathi::kKindWave) CHECK(t.keys_per_split <= b.longest_decode_piece);
+    }
+}
+
 static void drive_checker() {
     // one chunk on a prefix and two decodes, GQA 4:2, d = 8; every buffer exactly as large as documented
     const int Hq = 4, Hkv = 2, d = 8;
@@ -329,6 +356,7 @@ int main() {
     drive_scheduler(rng);
     drive_attention_host_paths(rng);
     drive_built_in_scratch_limits(rng);
+    drive_scarce_partial_rows();
     drive_checker();
     std::printf("host paths clean (sink %llu)\n", (unsigned long long)sarathi::g_sink);
     return 0;
