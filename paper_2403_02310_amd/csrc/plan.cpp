@@ -13,7 +13,6 @@
 // splits of a tile are merged in index order by a second, small kernel.
 #include <algorithm>
 #include <cstdio>
-#include <functional>
 #include <utility>
 
 #include "internal.h"
@@ -212,65 +211,91 @@ SplitCount count_splits(const Plan &plan, size_t first, size_t last, int64_t spl
 // cut by this estimate is 1 % slower than the best one.  The rules it replaces (0.42 of a block slot's share of the keys
 // from 512 blocks on, else rounds of average pieces) were 8 % off: 2048 tokens of two prompts, 64 heads: 159 + 17 us cut
 // into 1784 pieces, 140 us whole.
-double chunk_launch_us(const sarathi_config &cfg, const Plan &plan, size_t n_chunk_tiles, int64_t split_keys, int64_t max_rows) {
+// The estimate is asked for up to sixteen cuts before the launch can be enqueued, so it is kept short: tiles of equal length are
+// looked at together; a cut is not played through if all slots busy to the end, or its longest piece, already cost `limit`
+// (the best cut so far); and where a KV head's units run on more than 32 groups, every m-th unit is played on an m-th of
+// the groups (the longest of each m, so that a few long ones tell).  Planned, on the host, with every cut played in full, now,
+// and with the older rules: 58 and 2 heads, 2000 tokens of three prompts 117, 21, 13 us; 71 heads and one, 8192 tokens 470,
+// 109, 90; 64 and 8 heads, 8192 tokens 35, 21, 11; 600 random batches 12.0, 7.1, 5.6 on average.
+struct ChunkBin {  // tiles of equal length
+    int32_t steps, tiles;
+    int64_t cols;
+};
+double chunk_launch_us(const sarathi_config &cfg, const std::vector<ChunkBin> &bins, int64_t split_keys, int64_t max_rows, double limit) {
+    static thread_local std::vector<std::pair<int32_t, int32_t>> cuts;    // (steps of a piece, pieces) of the bins' tiles
     static thread_local std::vector<int32_t> count;                       // units by steps
     static thread_local std::vector<std::pair<double, double>> busy;      // heap: (when the group's first slot falls free, steps its other block then has left)
     const double scale = cfg.head_dim == 128 ? 1.0 : 0.72;
     const double alone = 0.62 * scale, shared = 0.92 * scale, fixed_steps = 1.2 / alone;
-    int32_t max_steps = 0;
-    for (size_t ti = 0; ti < n_chunk_tiles; ++ti)
-        max_steps = std::max(max_steps, (int32_t)ceil_div(plan.tiles[ti].n_keys - plan.tiles[ti].key_lo, kTileKeys));
-    count.assign((size_t)max_steps + 1, 0);
-    int64_t rows = 0, most = 1;
-    for (size_t ti = 0; ti < n_chunk_tiles; ++ti) {
-        const int64_t span = plan.tiles[ti].n_keys - plan.tiles[ti].key_lo;
-        if (span <= split_keys + split_keys / 2) {
-            count[(size_t)ceil_div(span, kTileKeys)]++;
-            continue;
+    const int32_t split_steps = (int32_t)std::min<int64_t>(split_keys / kTileKeys, INT32_MAX / 2);
+    int32_t max_steps = 0, most = 1;
+    int64_t rows = 0, units = 0, steps = 0;
+    cuts.clear();
+    for (const ChunkBin &b : bins) {
+        int32_t piece = b.steps, n = 1;
+        if (b.steps > split_steps + split_steps / 2) {
+            n = (b.steps - 1) / split_steps + 1;
+            piece = (b.steps - 1) / n + 1;
+            n = (b.steps - 1) / piece + 1;
+            rows += n * b.cols;
+            most = std::max(most, n);
         }
-        const int64_t steps = ceil_div(span, kTileKeys);
-        const int64_t piece = ceil_div(ceil_div(span, ceil_div(span, split_keys)), kTileKeys);
-        const int64_t pieces = ceil_div(steps, piece);
-        count[(size_t)piece] += (int32_t)(pieces - 1);
-        count[(size_t)(steps - (pieces - 1) * piece)]++;
-        rows += pieces * plan.tiles[ti].n_cols;
-        most = std::max(most, pieces);
+        max_steps = std::max(max_steps, piece);
+        units += (int64_t)n * b.tiles;
+        steps += (int64_t)b.steps * b.tiles;
+        cuts.emplace_back(piece, n);
     }
     if (rows > max_rows) return 1.0e12;
-    const size_t groups = (size_t)std::max(1, 256 / cfg.num_kv_heads);
-    busy.clear();
-    size_t started = 0;
-    double end = 0.0;
-    auto later = std::greater<std::pair<double, double>>();  // of groups free at the same time the one with less left
-    for (int32_t st = max_steps; st > 0; --st) {
-        for (int32_t i = 0; i < count[(size_t)st]; ++i) {
-            const double u = (double)st + fixed_steps;
-            if (started < groups) {
-                busy.emplace_back(0.0, u);                                // alone so far
-            } else {
-                if (started < 2 * groups) {                               // second slots, next to the longest units first
-                    auto &g = busy[started - groups];
-                    const double both = std::min(u, g.second);
-                    g = {shared * both, std::max(u, g.second) - both};
-                    if (started + 1 == 2 * groups) std::make_heap(busy.begin(), busy.end(), later);
-                } else {
-                    std::pop_heap(busy.begin(), busy.end(), later);
-                    auto &g = busy.back();
-                    const double both = std::min(u, g.second);
-                    g = {g.first + shared * both, std::max(u, g.second) - both};
-                    std::push_heap(busy.begin(), busy.end(), later);
-                }
-            }
-            ++started;
-        }
-    }
-    for (const auto &g : busy) end = std::max(end, g.first + alone * g.second);
-    double c = 5.0 + end;
+    double c = 5.0;
     if (most > 1) {
         const double move_us = 2.0 * (double)rows * cfg.num_kv_heads * (cfg.head_dim + 2) * 4.0 / 5.5e6;
         c += 2.0 + 0.4 * move_us + 5.0 + 0.25 * (double)most + move_us;
     }
-    return c;
+    const int64_t all_groups = std::max(1, 256 / cfg.num_kv_heads);
+    const double at_least = std::max(shared / 2.0 * ((double)steps + fixed_steps * (double)units) / (double)all_groups, alone * (max_steps + fixed_steps));
+    if (c + at_least >= limit) return c + at_least;
+
+    count.assign((size_t)max_steps + 1, 0);
+    for (size_t i = 0; i < bins.size(); ++i) {
+        const auto [piece, n] = cuts[i];
+        count[(size_t)piece] += (n - 1) * bins[i].tiles;
+        count[(size_t)(bins[i].steps - (n - 1) * piece)] += bins[i].tiles;
+    }
+    const int64_t every = std::max<int64_t>(1, std::min(all_groups / 32, units / 128));
+    const size_t groups = (size_t)(all_groups / every);
+    busy.clear();
+    size_t started = 0;
+    int64_t seen = every - 1;  // the longest unit of each m
+    auto earlier = [](const std::pair<double, double> &x, const std::pair<double, double> &y) { return y < x; };  // of groups free at the same time the one with less left
+    for (int32_t st = max_steps; st > 0; --st) {
+        seen += count[(size_t)st];
+        for (; seen >= every; seen -= every) {
+            const double u = (double)st + fixed_steps;
+            if (started < groups) {
+                busy.emplace_back(0.0, u);                                // alone so far
+            } else if (started < 2 * groups) {                            // second slots, next to the longest units first
+                auto &g = busy[started - groups];
+                const double both = std::min(u, g.second);
+                g = {shared * both, std::max(u, g.second) - both};
+                if (started + 1 == 2 * groups) std::make_heap(busy.begin(), busy.end(), earlier);
+            } else {                                                      // the first group to fall free, moved down to its new place
+                const double both = std::min(u, busy[0].second);
+                const std::pair<double, double> g = {busy[0].first + shared * both, std::max(u, busy[0].second) - both};
+                if (c + g.first >= limit) return c + g.first;
+                size_t at = 0;
+                for (size_t child; (child = 2 * at + 1) < groups; at = child) {
+                    if (child + 1 < groups && busy[child + 1] < busy[child]) ++child;
+                    if (!(busy[child] < g)) break;
+                    busy[at] = busy[child];
+                }
+                busy[at] = g;
+            }
+            ++started;
+        }
+    }
+    double end = 0.0;
+    for (const auto &g : busy) end = std::max(end, g.first + alone * g.second);
+    return c + end;
 }
 
 // The cut of a batch's chunk tiles that chunk_launch_us finds cheapest within `max_rows` partial rows, in keys per piece (the longest
@@ -279,20 +304,30 @@ double chunk_launch_us(const sarathi_config &cfg, const Plan &plan, size_t n_chu
 int64_t cheapest_chunk_split(const sarathi_config &cfg, const Plan &plan, size_t n_chunk_tiles, int64_t chunk_keys, int64_t longest_span, int64_t max_rows) {
     int64_t tile_split = ceil_div(longest_span, kTileKeys) * kTileKeys;
     if ((int64_t)n_chunk_tiles * cfg.num_kv_heads > 8192) return tile_split;
+    static thread_local std::vector<ChunkBin> by_steps, bins;
+    by_steps.assign((size_t)(tile_split / kTileKeys) + 1, ChunkBin{0, 0, 0});
+    for (size_t ti = 0; ti < n_chunk_tiles; ++ti) {
+        ChunkBin &b = by_steps[(size_t)((uint32_t)(plan.tiles[ti].n_keys - plan.tiles[ti].key_lo + kTileKeys - 1) / kTileKeys)];
+        b.tiles++;
+        b.cols += plan.tiles[ti].n_cols;
+    }
+    bins.clear();
+    for (size_t st = 1; st < by_steps.size(); ++st)
+        if (by_steps[st].tiles > 0) bins.push_back(ChunkBin{(int32_t)st, by_steps[st].tiles, by_steps[st].cols});
     // Where whole tiles all run at once a cut has to promise 5 %: 578 tokens behind 10,320 of a 4096-key window and
     // 231 more, 64 heads, promise 0.5 % in 1008 pieces instead of 416 blocks and run 3.5 % slower (106.5 us a call
     // whole, 110.2 cut).  Beyond one round it may cost 2 % more: 1024, 512 and 384 tokens behind 10,801, 8,115 and
     // 2,739, 56 heads, are estimated alike whole and in halves and run 3 % faster in halves (840 blocks 504 us, 1288
     // blocks 477 + 15); of 9 timed batches of several rounds none is cut for the worse by this.
     const bool one_round = (int64_t)n_chunk_tiles * cfg.num_kv_heads <= 512;
-    const double whole_us = chunk_launch_us(cfg, plan, n_chunk_tiles, tile_split, max_rows);
+    const double whole_us = chunk_launch_us(cfg, bins, tile_split, max_rows, 1.0e12);
     double best = one_round ? whole_us : 1.02 * whole_us;
     // all slots busy to the end: no cut can gain what its merge costs
     const double full_us = (double)chunk_keys / kTileKeys * cfg.num_kv_heads * (cfg.head_dim == 128 ? 0.92 : 0.66) / 512.0;
     int worse = whole_us < full_us + 15.0 ? 2 : 0;
     for (int64_t n = 2; n <= 16 && longest_span / n >= 256 && worse < 2; ++n) {
         const int64_t keys = ceil_div(ceil_div(longest_span, n), kTileKeys) * kTileKeys;
-        const double c = chunk_launch_us(cfg, plan, n_chunk_tiles, keys, max_rows);
+        const double c = chunk_launch_us(cfg, bins, keys, max_rows, best);
         if (c < best) {
             best = c;
             worse = 0;

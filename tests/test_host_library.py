@@ -259,3 +259,29 @@ def test_decodes_around_half_of_the_keys_are_cut_alike(rest):
         assert max(longest) <= 1.5 * min(longest) and max(longest) <= 2304
     else:
         assert max(longest) <= 3000   # the 3000-key decodes stay whole above the half
+
+
+@pytest.mark.parametrize("shape,chunks", [
+    (wl.AttnShape(58, 2, 64), [(1000, 1100), (800, 830), (200, 12200)]),
+    (wl.AttnShape(71, 1, 64), [(8192, 8192)]),
+    (wl.AttnShape(71, 1, 64), [(1080, 1085), (1868, 1868), (179, 179), (1, 2394), (1, 5761), (1, 3000)])])
+def test_choosing_the_cut_takes_no_longer_than_a_few_plans(shape, chunks):
+    """The cut of a chunk-only batch is searched before its launch can be enqueued.  Planning it takes at most three times what the
+    same plan takes with the cut given (both the fastest of many runs, on the same machine)."""
+    import time
+    b = wl._make("chunks", shape, [q for q, _ in chunks], [c for _, c in chunks], 98)
+    h = binding.Handle(shape.num_q_heads, shape.num_kv_heads, shape.head_dim, max_tokens=16384, max_seqs=64,
+                       max_blocks_per_seq=b.max_blocks_per_seq)
+
+    def fastest():
+        best = 1.0
+        for _ in range(60):
+            t = time.perf_counter()
+            info, _ = h.plan(b.q_start, b.q_len, b.ctx_len, with_items=False)
+            best = min(best, time.perf_counter() - t)
+        return best * 1e6, info
+    searched_us, searched = fastest()
+    h.set_option("tile_split_keys", searched.tile_split_keys)
+    given_us, given = fastest()
+    assert given.num_items == searched.num_items
+    assert searched_us <= 3 * given_us + 15, (searched_us, given_us)
