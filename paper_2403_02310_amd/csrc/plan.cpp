@@ -303,7 +303,6 @@ double chunk_launch_us(const sarathi_config &cfg, const std::vector<ChunkBin> &b
 // more twice in a row.
 int64_t cheapest_chunk_split(const sarathi_config &cfg, const Plan &plan, size_t n_chunk_tiles, int64_t chunk_keys, int64_t longest_span, int64_t max_rows) {
     int64_t tile_split = ceil_div(longest_span, kTileKeys) * kTileKeys;
-    if ((int64_t)n_chunk_tiles * cfg.num_kv_heads > 8192) return tile_split;
     static thread_local std::vector<ChunkBin> by_steps, bins;
     by_steps.assign((size_t)(tile_split / kTileKeys) + 1, ChunkBin{0, 0, 0});
     for (size_t ti = 0; ti < n_chunk_tiles; ++ti) {

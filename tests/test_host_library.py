@@ -202,7 +202,7 @@ def test_few_decodes_are_cut_and_covered(case, window):
     (wl.AttnShape(32, 8, 128), [(1000, 1100), (400, 9400)], True),    # one long prefix among short ones
     (wl.AttnShape(32, 8, 128), [(300, 300)], False),
     (wl.AttnShape(4, 1, 64), [(278, 6572), (987, 987)], True),        # more groups than units
-    (wl.AttnShape(320, 320, 64), [(40, 3000), (3000, 3000)], False),  # more KV heads than compute units, more blocks than are played through
+    (wl.AttnShape(320, 320, 64), [(40, 3000), (3000, 3000)], False),  # more KV heads than compute units, more than 8192 blocks
     (wl.AttnShape(64, 8, 128), [(4096, 70000)], False)])              # every slot busy to the end
 def test_chunk_only_batches_are_cut_where_it_pays(shape, chunks, cut):
     """The cut of a chunk-only launch comes from playing it through; whatever it says, every key is covered once."""
@@ -285,3 +285,13 @@ def test_choosing_the_cut_takes_no_longer_than_a_few_plans(shape, chunks):
     given_us, given = fastest()
     assert given.num_items == searched.num_items
     assert searched_us <= 3 * given_us + 15, (searched_us, given_us)
+
+
+@pytest.mark.parametrize("shape,short,long", [(wl.AttnShape(64, 8, 128), 32, (64, 60000)), (wl.AttnShape(32, 32, 128), 34, (100, 60000))])
+def test_a_long_chunk_among_very_many_short_ones_is_cut(shape, short, long):
+    """More than 8192 chunk blocks: a few tiles behind a long prefix are still cut, or they alone would set the launch's time."""
+    n = 512 if shape.num_kv_heads == 8 else 1000
+    b = wl._make("many", shape, [n] * short + [long[0]], [n] * short + [long[1]], 99)
+    info = _coverage_check(b)
+    assert 0 < info.num_reduce_items <= -(-long[0] * shape.group // 128)
+    assert info.tile_split_keys <= long[1] // 4
