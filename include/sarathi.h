@@ -119,7 +119,7 @@ const char *sarathi_last_error(const sarathi_handle *handle);
  * window of a sequence are never dereferenced),
  * "decode_blocks_per_cu" (launches that hold decodes / 16-column tiles only: 1 = one block per compute unit, so
  * that blocks start longest first as units fall free, which shortens the tail of small batches; 2 = as many as fit;
- * -1 = automatic: one for up to 1024 blocks, unless the decodes were cut into pieces that all run at once),
+ * -1 = automatic: one for up to 1024 blocks, unless few decodes were cut into pieces of nearly one length),
  * "inline_append" (0/1: sarathi_kv_append sends up to 224 page records in its kernel's arguments instead of
  * letting the blocks read them from the pinned buffer), "lds_pad_kb" (diagnostic: KiB of unused LDS per
  * attention block, which lowers the number of blocks a compute unit holds),

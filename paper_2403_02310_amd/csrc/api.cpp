@@ -227,11 +227,14 @@ sarathi_status enqueue_attention(sarathi_handle *h, char *dev, float *part_ml, f
         // one block can pull (~36 GB/s): a tail of 15-20 us on 64 decodes.  With one block per compute unit the blocks
         // start longest first as units fall free and each streams at twice the share; one block per unit already
         // reaches the chip's streaming rate (256 blocks x 25.5 GB/s).  Measured on 48 ... 128 decodes: -12 to -20 %;
-        // from ~192 decodes on the launch is long enough for two per unit to win by 2-4 %.  Pieces of few decodes are
-        // nearly equal and all resident at once: two per unit (8 decodes of 256-4096 keys 15.3 us against 16.9 with one).
+        // from ~192 decodes on the launch is long enough for two per unit to win by 2-4 %.  Few decodes
+        // cut into pieces of nearly one length need no balancing, and two per unit win; the line lies between (70 batches
+        // of 2 to 138 decodes, launch time; up to 256 blocks there is no difference) longest piece x pieces = 1.33 x all
+        // keys (41 decodes, 1000 blocks: 115.1 us with one, 110.6 with two; 15 decodes 20.5 and 18.9) and 1.38 x (30.0
+        // and 30.8; at 1.7 to 1.8 x, where short decodes stay whole next to the pieces, 31.1 and 34.1, 53.6 and 69.6).
         const int64_t wave_blocks = (int64_t)((int32_t)pl.units.size() - pl.num_tile_units) * h->cfg.num_kv_heads;
         const bool wave_only = pl.num_tile_units == 0;
-        const bool one = h->opt.decode_blocks_per_cu == 1 || (h->opt.decode_blocks_per_cu < 0 && wave_blocks <= 1024 && !pl.short_decode_pieces);
+        const bool one = h->opt.decode_blocks_per_cu == 1 || (h->opt.decode_blocks_per_cu < 0 && wave_blocks <= 1024 && !pl.even_decode_pieces);
         if (wave_only && one && m.lds_pad_bytes == 0) m.lds_pad_bytes = kOneBlockPerUnitLdsPad;
     }
     // Rough durations: chunk work with one block per compute unit (~0.65 us per 32-key step), and the time

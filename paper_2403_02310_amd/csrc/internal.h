@@ -74,7 +74,7 @@ struct Plan {
     int64_t tile_unit_steps = 0;      // 32-key steps summed over the chunk-tile units
     int32_t longest_tile_unit_steps = 0;  // 32-key steps of the longest chunk-tile unit
     int64_t wave_keys = 0;            // keys summed over the wave tiles
-    bool short_decode_pieces = false; // few decodes, cut into pieces that fill the chip all at once
+    bool even_decode_pieces = false;  // few decodes, cut into pieces of nearly one length
 };
 
 // Byte offsets of the regions inside the caller's workspace (all 256-byte aligned).
@@ -106,8 +106,8 @@ struct Options {
                                     // runs about as long as they do; 0 = never, 1 = always
     int64_t decode_blocks_per_cu = -1;  // launches of wave tiles only: 2 = as many blocks per compute unit as fit, 1 = one (unused LDS
                                     // keeps a second one out, so blocks start longest first as units fall free instead of
-                                    // all at once); -1 = one for up to 1024 blocks of whole decodes, two beyond and
-                                    // where few decodes were cut into pieces
+                                    // all at once); -1 = one for up to 1024 blocks, two beyond and where few
+                                    // decodes were cut into pieces of nearly one length
     int64_t inline_append = 1;      // KV append: up to 224 page records travel in the kernel's arguments (else all are read from the pinned buffer)
     int64_t lds_pad_kb = 0;         // diagnostic only: KiB of unused LDS added to every attention block
     int64_t resident_chunks = -1;   // one-launch mode: blocks take their role (chunk or wave tiles) when they start, so that

@@ -528,7 +528,7 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
     };
     int64_t tile_split = cut_chunks(ws.max_part_rows);
     int64_t wave_whole = 0;
-    plan.short_decode_pieces = false;
+    bool few_cut = false;
     if (opt.split_keys <= 0 && has_wave_tiles && (int64_t)(plan.tiles.size() - n_chunk_tiles) * cfg.num_kv_heads <= 512) {
         WaveCut w = cheapest_wave_cut(cfg, plan, n_chunk_tiles, keys_of_kind[kKindWave], tile_split, wave_split, ws.max_part_rows, false);
         const int64_t wave_rows = count_splits(plan, n_chunk_tiles, plan.tiles.size(), w.keys, w.whole).rows;
@@ -543,7 +543,7 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
         }
         wave_split = w.keys;
         wave_whole = w.whole;
-        plan.short_decode_pieces = w.few;
+        few_cut = w.few;
     }
     for (;;) {
         const SplitCount chunk = count_splits(plan, 0, n_chunk_tiles, tile_split, 0);
@@ -582,7 +582,17 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
     }
     plan.wave_keys = keys_of_kind[kKindWave];
     const size_t wave_base = plan.units.size();
+    const int32_t split_chunk_tiles = plan.num_split_tiles;
     emit_units(plan, n_chunk_tiles, plan.tiles.size(), wave_split, wave_whole, scratch, bucket);
+    // Few decodes in pieces of nearly one length: the longest piece (the first unit), were all as long as it, would be at most
+    // 1.35 times the keys there are.
+    plan.even_decode_pieces = false;
+    if (few_cut && plan.num_split_tiles > split_chunk_tiles) {
+        const uint32_t u = plan.units[wave_base];
+        const int64_t longest = steps_of_split(plan.tiles[u & ((1u << kUnitTileBits) - 1)], (int32_t)(u >> kUnitTileBits));
+        const int64_t n_units = (int64_t)(plan.units.size() - wave_base);
+        plan.even_decode_pieces = 20 * longest * kTileKeys * n_units <= 27 * keys_of_kind[kKindWave];
+    }
     pair_column_tiles(plan, wave_base, cfg.num_kv_heads, scratch);
 }
 

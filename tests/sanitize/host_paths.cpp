@@ -64,6 +64,7 @@ namespace sarathi {
 static int g_num_seqs = 0;          // shape of the call in flight, for the walkers below
 static int64_t g_num_tokens = 0;
 static uint64_t g_sink = 0;
+static int32_t g_lds_pad_bytes = 0; // of the last attention launch
 
 int launch_kv_append(const sarathi_config &cfg, const AppendMeta &m, const void *k_new, const void *v_new, void *k_cache,
                      void *v_cache, int64_t num_pages, void *) {
@@ -121,6 +122,7 @@ int static_scratch(StaticScratch *out) {
 int launch_attention(const sarathi_config &cfg, const AttnMeta &m, const void *, const void *, const void *, int64_t,
                      float, void *, int which, void *) {
     const int H = cfg.num_kv_heads, D = cfg.head_dim;
+    g_lds_pad_bytes = m.lds_pad_bytes;
     for (int u = 0; u < m.num_units; ++u) {
         const uint32_t unit = m.units[u];
         const TileDesc &t = m.tiles[unit & ((1u << kUnitTileBits) - 1)];
@@ -316,6 +318,38 @@ static void drive_scarce_partial_rows() {
     }
 }
 
+// A launch of decodes alone runs one block per compute unit (padded LDS) unless it was cut into pieces of nearly one length.
+static void drive_decode_blocks_per_unit() {
+    struct Batch {
+        std::vector<int32_t> ctx_len;
+        bool cut, one_per_unit;
+    };
+    const Batch batches[] = {{std::vector<int32_t>(8, 4096), true, false},    // equal pieces
+                             {std::vector<int32_t>(60, 300), false, true},    // whole decodes
+                             {std::vector<int32_t>(120, 200), true, true}};   // every sixth 3600 keys and cut, the others whole
+    for (const Batch &b : batches) {
+        std::vector<int32_t> ctx = b.ctx_len;
+        if (b.cut && b.one_per_unit)
+            for (size_t i = 0; i < ctx.size(); i += 6) ctx[i] = 3600;
+        const int32_t S = (int32_t)ctx.size();
+        const sarathi_config cfg{16, 2, 128, 16, 0, S, S, 256};
+        std::vector<int32_t> q_start((size_t)S), q_len((size_t)S, 1), bt((size_t)S * 256, 0);
+        for (int32_t i = 0; i < S; ++i) q_start[(size_t)i] = i;
+        sarathi_handle *h = nullptr;
+        CHECK(sarathi_create(&cfg, &h) == SARATHI_OK);
+        sarathi_plan_info info{};
+        CHECK(sarathi_plan_hybrid_attention(h, q_start.data(), q_len.data(), ctx.data(), S, S, &info, nullptr, 0) == SARATHI_OK);
+        CHECK((info.num_reduce_items > 0) == b.cut);
+        char dummy[16];
+        sarathi::g_num_seqs = S;
+        sarathi::g_num_tokens = S;
+        CHECK(sarathi_hybrid_attention_noalloc(h, dummy, dummy, dummy, bt.data(), q_start.data(), q_len.data(), ctx.data(), S, S, 1, 0.1f,
+                                               dummy, nullptr) == SARATHI_OK);
+        CHECK((sarathi::g_lds_pad_bytes > 0) == b.one_per_unit);
+        CHECK(sarathi_destroy(h) == SARATHI_OK);
+    }
+}
+
 static void drive_checker() {
     // one chunk on a prefix and two decodes, GQA 4:2, d = 8; every buffer exactly as large as documented
     const int Hq = 4, Hkv = 2, d = 8;
@@ -357,6 +391,7 @@ int main() {
     drive_attention_host_paths(rng);
     drive_built_in_scratch_limits(rng);
     drive_scarce_partial_rows();
+    drive_decode_blocks_per_unit();
     drive_checker();
     std::printf("host paths clean (sink %llu)\n", (unsigned long long)sarathi::g_sink);
     return 0;
