@@ -34,6 +34,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <type_traits>
+#include <utility>
 
 #include "internal.h"
 
@@ -582,17 +583,20 @@ __global__ __launch_bounds__(256) void linear_reduce_kernel(const float *part, u
 
 }  // namespace
 
-// Tile shapes of linear_phased_kernel, with the microseconds of one 64-k stage when every compute unit runs one, for
+// Tile shapes of linear_phased_kernel (its template arguments), with the microseconds of one 64-k stage when every compute unit runs one, for
 // batches of several token tiles and of one (weights straight from memory, with the non-temporal hint).
 struct PhasedShape {
-    int32_t features, tokens;
+    int a0, a1, b0, b1, ring;  // LDS: ring x 128 x (features + tokens) bytes, 112 to 160 KiB
     double stage_us, stage_us_one_tile;
+    constexpr int32_t features() const { return 64 * (a0 + a1); }
+    constexpr int32_t tokens() const { return 64 * (b0 + b1); }
 };
 constexpr PhasedShape kPhasedShapes[] = {
-    {256, 256, 0.654, 0.619}, {256, 192, 0.538, 0.588}, {192, 256, 0.547, 0.545}, {192, 192, 0.502, 0.573},
-    {256, 128, 0.530, 0.597}, {128, 256, 0.487, 0.502}, {192, 128, 0.465, 0.552}, {128, 192, 0.413, 0.476},
-    {128, 128, 0.377, 0.414}, {256, 64, 0.494, 0.630},  {192, 64, 0.403, 0.526},  {128, 64, 0.292, 0.346},
+    {2, 2, 2, 2, 2, 0.654, 0.619}, {2, 2, 2, 1, 2, 0.538, 0.588}, {2, 1, 2, 2, 2, 0.547, 0.545}, {2, 1, 2, 1, 3, 0.502, 0.573},
+    {2, 2, 1, 1, 3, 0.530, 0.597}, {1, 1, 2, 2, 3, 0.487, 0.502}, {2, 1, 1, 1, 4, 0.465, 0.552}, {1, 1, 2, 1, 4, 0.413, 0.476},
+    {1, 1, 1, 1, 5, 0.377, 0.414}, {2, 2, 1, 0, 4, 0.494, 0.630}, {2, 1, 1, 0, 5, 0.403, 0.526}, {1, 1, 1, 0, 6, 0.292, 0.346},
 };
+constexpr size_t kNumPhasedShapes = sizeof(kPhasedShapes) / sizeof(kPhasedShapes[0]);
 
 // More than 64 tokens.  Cost of a tiling in microseconds, fitted to 3,600 timings (the 13 layer shapes of four models, 15
 // token counts from 40 to 2048, every tile shape and piece count that could compete; a tiling's time is met within 7 % rms,
@@ -608,12 +612,12 @@ static LinearPlan plan_phased(int32_t T, int32_t N, int32_t K, size_t workspace_
     LinearPlan best{};
     double best_cost = -1.0;
     for (const PhasedShape &sh : kPhasedShapes) {
-        const int64_t n_tiles = (N + sh.features - 1) / sh.features;
-        const int64_t t_tiles = (T + sh.tokens - 1) / sh.tokens;
+        const int64_t n_tiles = (N + sh.features() - 1) / sh.features();
+        const int64_t t_tiles = (T + sh.tokens() - 1) / sh.tokens();
         const int64_t tiles = n_tiles * t_tiles;
         const double stage_us = t_tiles == 1 ? sh.stage_us_one_tile : sh.stage_us;
-        const double out_us = 8.2 * sh.features * sh.tokens / 65536.0;
-        const double product_us = 2.0 * (double)tiles * sh.features * sh.tokens * K / 2.26e9;
+        const double out_us = 8.2 * sh.features() * sh.tokens() / 65536.0;
+        const double product_us = 2.0 * (double)tiles * sh.features() * sh.tokens() * K / 2.26e9;
         for (int64_t s = 1; s <= 16 && (s == 1 || (s * 4 <= k_stages && tiles * s <= 1024)); ++s) {
             if (s > 1 && (size_t)(s * per_split_bytes) > workspace_bytes) break;
             const int64_t stages = (k_stages + s - 1) / s;
@@ -626,8 +630,8 @@ static LinearPlan plan_phased(int32_t T, int32_t N, int32_t K, size_t workspace_
             if (s > 1) c += 1.2 + 2.0 * (double)s * (double)per_split_bytes / 6.2e6;
             if (best_cost < 0.0 || c < best_cost) {
                 best_cost = c;
-                best.feature_tile = sh.features;
-                best.token_tile = sh.tokens;
+                best.feature_tile = sh.features();
+                best.token_tile = sh.tokens();
                 best.n_tiles = (int32_t)n_tiles;
                 best.t_tiles = (int32_t)t_tiles;
                 best.splits = (int32_t)s;
@@ -678,6 +682,25 @@ LinearPlan plan_linear(int32_t T, int32_t N, int32_t K, size_t workspace_bytes) 
     return T > kLinSmallTokens ? plan_phased(T, N, K, workspace_bytes) : plan_small(T, N, K, workspace_bytes);
 }
 
+// Launches the shape of the table that the plan names; false if it names none of them.
+template <size_t I>
+static bool launch_phased_shape(const LinearPlan &pl, const LinearParams &p, dim3 grid, hipStream_t st) {
+    constexpr PhasedShape sh = kPhasedShapes[I];
+    if (pl.feature_tile != sh.features() || pl.token_tile != sh.tokens()) return false;
+    if constexpr (sh.b1 > 0) {  // a 64-token tile never covers these batches alone
+        if (pl.t_tiles == 1) {
+            hipLaunchKernelGGL((linear_phased_kernel<sh.a0, sh.a1, sh.b0, sh.b1, sh.ring, true>), grid, dim3(256), 0, st, p);
+            return true;
+        }
+    }
+    hipLaunchKernelGGL((linear_phased_kernel<sh.a0, sh.a1, sh.b0, sh.b1, sh.ring, false>), grid, dim3(256), 0, st, p);
+    return true;
+}
+template <size_t... I>
+static bool launch_phased(const LinearPlan &pl, const LinearParams &p, dim3 grid, hipStream_t st, std::index_sequence<I...>) {
+    return (launch_phased_shape<I>(pl, p, grid, st) || ...);
+}
+
 int launch_linear(const LinearPlan &pl, const void *x, const void *w, void *y, int32_t T, int32_t N, int32_t K,
                   void *workspace, void *stream) {
     LinearParams p;
@@ -693,42 +716,13 @@ int launch_linear(const LinearPlan &pl, const void *x, const void *w, void *y, i
     hipStream_t st = static_cast<hipStream_t>(stream);
     const dim3 grid((unsigned)blocks);
     if (T > kLinSmallTokens) {
-        const bool one_token_tile = pl.t_tiles == 1;
-        auto go = [&](auto a0, auto a1, auto b0, auto b1, auto ring) {
-            constexpr int A0 = decltype(a0)::value, A1 = decltype(a1)::value, B0 = decltype(b0)::value, B1 = decltype(b1)::value;
-            if (pl.feature_tile != 64 * (A0 + A1) || pl.token_tile != 64 * (B0 + B1)) return;
-            if constexpr (B1 > 0) {  // a 64-token tile never covers these batches alone
-                if (one_token_tile) {
-                    hipLaunchKernelGGL((linear_phased_kernel<A0, A1, B0, B1, decltype(ring)::value, true>), grid, dim3(256), 0, st, p);
-                    return;
-                }
-            }
-            hipLaunchKernelGGL((linear_phased_kernel<A0, A1, B0, B1, decltype(ring)::value, false>), grid, dim3(256), 0, st, p);
-        };
-        using I0 = std::integral_constant<int, 0>;
-        using I1 = std::integral_constant<int, 1>;
-        using I2 = std::integral_constant<int, 2>;
-        using I3 = std::integral_constant<int, 3>;
-        using I4 = std::integral_constant<int, 4>;
-        using I5 = std::integral_constant<int, 5>;
-        using I6 = std::integral_constant<int, 6>;
-        // LDS: RING x 128 x (features + tokens) bytes, 112 to 160 KiB
-        go(I2{}, I2{}, I2{}, I2{}, I2{});
-        go(I2{}, I2{}, I2{}, I1{}, I2{});
-        go(I2{}, I1{}, I2{}, I2{}, I2{});
-        go(I2{}, I1{}, I2{}, I1{}, I3{});
-        go(I2{}, I2{}, I1{}, I1{}, I3{});
-        go(I1{}, I1{}, I2{}, I2{}, I3{});
-        go(I2{}, I1{}, I1{}, I1{}, I4{});
-        go(I1{}, I1{}, I2{}, I1{}, I4{});
-        go(I1{}, I1{}, I1{}, I1{}, I5{});
-        go(I2{}, I2{}, I1{}, I0{}, I4{});
-        go(I2{}, I1{}, I1{}, I0{}, I5{});
-        go(I1{}, I1{}, I1{}, I0{}, I6{});
+        if (!launch_phased(pl, p, grid, st, std::make_index_sequence<kNumPhasedShapes>{})) return (int)hipErrorInvalidConfiguration;
     } else if (pl.feature_tile == 128) {  // LDS: 6 x 24 KiB, 3 x 40 KiB
         hipLaunchKernelGGL((linear_kernel<64, 2, 6, 128>), grid, dim3(kLinThreads), 0, st, p);
-    } else {
+    } else if (pl.feature_tile == 256) {
         hipLaunchKernelGGL((linear_kernel<64, 1, 3, 256>), grid, dim3(kLinThreads), 0, st, p);
+    } else {
+        return (int)hipErrorInvalidConfiguration;
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || pl.splits == 1) return (int)e;

@@ -295,3 +295,14 @@ def test_a_long_chunk_among_very_many_short_ones_is_cut(shape, short, long):
     info = _coverage_check(b)
     assert 0 < info.num_reduce_items <= -(-long[0] * shape.group // 128)
     assert info.tile_split_keys <= long[1] // 4
+
+
+def test_a_tile_that_no_kernel_has_is_an_error():
+    """The launcher takes its kernels from the planner's table of tiles; a plan that names another tile is refused and not
+    answered with success and an untouched output.  (The refusal comes before any device call.)"""
+    launch = binding.lib["_ZN7sarathi13launch_linearERKNS_10LinearPlanEPKvS4_PviiiS5_S5_"]
+    launch.argtypes = [ctypes.POINTER(ctypes.c_int32 * 6), ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p,
+                       ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p]
+    for tokens, features, token_tile in [(100, 320, 128), (100, 128, 96), (100, 0, 0), (32, 192, 64)]:
+        plan = (ctypes.c_int32 * 6)(features, token_tile, 1, 1, 1, 64)   # feature and token tile, their numbers, pieces, k per piece
+        assert launch(ctypes.byref(plan), None, None, None, tokens, 128, 64, None, None) == 9   # hipErrorInvalidConfiguration
