@@ -304,6 +304,7 @@ sarathi_status sarathi_build_stall_free_batch(int32_t token_budget, int32_t chun
  *            is cut into pieces so that a small batch still streams the weights through every compute unit;
  *            sarathi_linear_workspace_bytes gives the size that allows every cut the planner would make;
  *            with less (or none) the call still computes the same y with fewer pieces.
+ * Alignment: x, w and workspace 16 bytes, y 8 bytes (any whole allocation has more; a view may begin inside one).
  * Shapes: out_features a multiple of 128, in_features a multiple of 64 and at most 2^20, num_tokens >= 0
  * (0 is a no-op), num_tokens * out_features below 2^40; anything else returns SARATHI_ESHAPE.  Null
  * pointers with num_tokens > 0 return SARATHI_EINVAL, a failed launch SARATHI_EHIP.  The work is enqueued on

@@ -48,6 +48,7 @@ typedef __attribute__((ext_vector_type(4))) float lf32x4;
 typedef __attribute__((ext_vector_type(16))) float lf32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t lu32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t lu32x2;
+typedef lu32x4 __attribute__((aligned(8))) lu32x4_at8;  // output rows: y is promised 8-byte alignment only
 
 constexpr int kLinStageK = 64;   // k per stage: one 128-byte line of every row
 constexpr int kLinXcds = 8;
@@ -541,7 +542,7 @@ __global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {
                 const int row = (u * 64 + lane) / PIECES, c = (u * 64 + lane) % PIECES;
                 const lu32x4 v = *reinterpret_cast<const lu32x4 *>(buf + row * 256 + (c ^ (row & 15)) * 16);
                 const int t = t_wave + j * 32 + row, f = f_wave + c * 8;
-                if (t < p.T && f < p.N) *reinterpret_cast<lu32x4 *>(p.y + (int64_t)t * p.N + f) = v;
+                if (t < p.T && f < p.N) *reinterpret_cast<lu32x4_at8 *>(p.y + (int64_t)t * p.N + f) = v;
             }
         } else {
             constexpr int PIECES = 8 * NI;                // the same, fp32

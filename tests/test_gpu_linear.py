@@ -168,3 +168,25 @@ def test_tiles_of_small_batches(hx, T, N, K):
     rows = sorted(set([0, T - 1, T // 2])); cols = sorted(set([0, N - 1, N - 128, 127] + np.random.default_rng(N).integers(0, N, 30).tolist()))
     got = run(hx, T, N, K, seed=31 + T, rows=rows, cols=cols)
     assert np.isfinite(got).all()
+
+
+@pytest.mark.parametrize("T,N,K", [(8, 1280, 704), (77, 384, 704), (300, 1152, 2496), (1025, 3968, 704)])
+def test_output_views_that_begin_at_eight_bytes(hx, T, N, K):
+    """y may be a view that begins eight bytes into its allocation: same bits as into an aligned one, nothing beside it touched."""
+    binding, _ = hx
+    g = torch.Generator(device="cuda").manual_seed(T + N + K)
+    x = torch.randn(T, K, device="cuda", dtype=torch.bfloat16, generator=g)
+    w = torch.randn(N, K, device="cuda", dtype=torch.bfloat16, generator=g)
+    scratch = torch.empty(max(binding.linear_workspace_bytes(T, N, K), 16), dtype=torch.uint8, device="cuda")
+    aligned = torch.empty(T, N, device="cuda", dtype=torch.bfloat16)
+    room = torch.full((T * N + 64,), float("nan"), device="cuda", dtype=torch.bfloat16)
+    for ws in (scratch, None):
+        print("view case T", T, "N", N, "K", K, "workspace", ws is not None, flush=True)
+        binding.linear(x, w, aligned, ws)
+        room.fill_(float("nan"))
+        y = room[4:4 + T * N].view(T, N)
+        assert y.data_ptr() % 16 == 8
+        binding.linear(x, w, y, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(y, aligned)
+        assert torch.isnan(room[:4]).all() and torch.isnan(room[4 + T * N:]).all()
