@@ -314,6 +314,17 @@ size_t sarathi_linear_workspace_bytes(int32_t num_tokens, int32_t out_features, 
 sarathi_status sarathi_linear(const void *x, const void *w, void *y, int32_t num_tokens, int32_t out_features,
                               int32_t in_features, void *workspace, size_t workspace_bytes, void *stream);
 
+/* Host-only view of the tiling sarathi_linear would launch with that much workspace (no device work).  For tests and for
+ * sizing studies. */
+typedef struct {
+    int32_t feature_tile, token_tile;    /* output features x tokens of a workgroup's tile */
+    int32_t feature_tiles, token_tiles;  /* how many of them */
+    int32_t pieces;                      /* of the k range; more than one: fp32 partial tiles and a second kernel */
+    int32_t k_per_piece;
+} sarathi_linear_plan;
+sarathi_status sarathi_plan_linear(int32_t num_tokens, int32_t out_features, int32_t in_features, size_t workspace_bytes,
+                                   sarathi_linear_plan *out);
+
 #ifdef __cplusplus
 }
 #endif

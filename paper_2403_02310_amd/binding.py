@@ -61,10 +61,16 @@ class KernelTimes(ctypes.Structure):
                 ("merge_launches", ctypes.c_int64)]
 
 
+class LinearPlan(ctypes.Structure):
+    _fields_ = [("feature_tile", ctypes.c_int32), ("token_tile", ctypes.c_int32), ("feature_tiles", ctypes.c_int32),
+                ("token_tiles", ctypes.c_int32), ("pieces", ctypes.c_int32), ("k_per_piece", ctypes.c_int32)]
+
+
 EXPORTED = ["sarathi_create", "sarathi_destroy", "sarathi_workspace_bytes", "sarathi_last_error",
             "sarathi_set_option", "sarathi_kv_append", "sarathi_hybrid_attention",
             "sarathi_plan_hybrid_attention", "sarathi_build_stall_free_batch", "sarathi_get_kernel_times",
-            "sarathi_linear", "sarathi_linear_workspace_bytes", "sarathi_hybrid_attention_noalloc"]
+            "sarathi_linear", "sarathi_linear_workspace_bytes", "sarathi_plan_linear",
+            "sarathi_hybrid_attention_noalloc"]
 
 if not os.path.exists(LIB_PATH):
     raise ImportError("libsarathi.so is not built: run `python -c 'import __graft_entry__ as g; g.build()'` "
@@ -105,6 +111,8 @@ lib.sarathi_build_stall_free_batch.argtypes = [ctypes.c_int32, ctypes.c_int32,
                                                ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.POINTER(Batch)]
 lib.sarathi_linear_workspace_bytes.restype = ctypes.c_size_t
 lib.sarathi_linear_workspace_bytes.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_int32]
+lib.sarathi_plan_linear.restype = ctypes.c_int
+lib.sarathi_plan_linear.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, ctypes.c_size_t, ctypes.POINTER(LinearPlan)]
 lib.sarathi_linear.restype = ctypes.c_int
 lib.sarathi_linear.argtypes = [_vp, _vp, _vp, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, _vp, ctypes.c_size_t, _vp]
 
@@ -327,6 +335,17 @@ def build_stall_free_batch(token_budget: int, chunk_size: int, running_decodes: 
 
 def linear_workspace_bytes(num_tokens: int, out_features: int, in_features: int) -> int:
     return int(lib.sarathi_linear_workspace_bytes(num_tokens, out_features, in_features))
+
+
+def plan_linear(num_tokens: int, out_features: int, in_features: int, workspace_bytes: Optional[int] = None) -> LinearPlan:
+    """Tiling ``linear`` would launch with that much workspace (None: as much as it asks for)."""
+    if workspace_bytes is None:
+        workspace_bytes = linear_workspace_bytes(num_tokens, out_features, in_features)
+    out = LinearPlan()
+    st = lib.sarathi_plan_linear(num_tokens, out_features, in_features, workspace_bytes, ctypes.byref(out))
+    if st != 0:
+        raise SarathiError(st, "sarathi_plan_linear(T=%d, N=%d, K=%d) failed" % (num_tokens, out_features, in_features))
+    return out
 
 
 def linear(x, w, y, workspace=None, stream=None) -> None:

@@ -13,6 +13,8 @@ torch = pytest.importorskip("torch")
 import oracle
 from paper_2403_02310_amd import workloads as wl
 
+from . import linear_tile_cases
+
 pytestmark = pytest.mark.gpu
 
 
@@ -120,20 +122,7 @@ def test_model_shapes_sampled(hx):
         run(hx, T, N, K, seed=21, rows=rows, cols=cols)
 
 
-# Batches of more than 64 tokens: one shape per tile of that path (features x tokens), uncut and cut along k, with one
-# token tile and with several; ragged in tokens and (where it can be) in features, odd and even numbers of k stages.
-@pytest.mark.parametrize("T,N,K", [
-    (65, 128, 64), (300, 384, 704), (65, 384, 704),                            # 128 x 64, one stage, and in two pieces
-    (1025, 2176, 704), (129, 3968, 3008), (257, 12416, 704),                   # 192 x 64 uncut and cut, 256 x 64
-    (900, 3968, 704), (900, 1152, 2496), (65, 8320, 1984),                     # 128 x 128
-    (1025, 3968, 704), (1025, 1280, 4032), (129, 6272, 3008),                  # 128 x 192
-    (1025, 6272, 704), (1025, 2176, 8128), (193, 8320, 3008),                  # 128 x 256
-    (577, 8320, 704), (577, 1920, 8128), (65, 8320, 6080),                     # 192 x 128
-    (900, 8320, 704), (1025, 1920, 6080), (129, 8320, 8128),                   # 192 x 192
-    (1000, 12160, 64), (450, 6272, 6080), (193, 12416, 5056),                  # 192 x 256
-    (577, 12416, 704), (577, 2560, 8128), (65, 12416, 4032),                   # 256 x 128
-    (1025, 8320, 704), (577, 4992, 6080), (129, 12416, 5056),                  # 256 x 192
-    (1025, 12416, 704), (450, 8320, 8128)])                                    # 256 x 256
+@pytest.mark.parametrize("T,N,K", list(linear_tile_cases.LARGE))
 def test_tiles_of_large_batches(hx, T, N, K):
     binding, harness = hx
     print("linear case T", T, "N", N, "K", K, flush=True)
@@ -159,11 +148,7 @@ def test_tiles_of_large_batches(hx, T, N, K):
     assert ((y - whole).abs() <= 2.0 ** -7 * whole.abs() + mag).all()
 
 
-@pytest.mark.parametrize("T,N,K", [
-    (1, 128, 64), (64, 384, 192),                  # one stage; a ragged last feature tile, three stages
-    (64, 4096, 4096), (7, 1280, 4096),             # 128 features in eight and in sixteen pieces
-    (64, 32896, 64), (9, 11136, 3008),             # 256 features, ragged last tile, uncut and in five pieces
-    (5, 28672, 320)])                              # 128 features uncut, workgroups start at all five stages
+@pytest.mark.parametrize("T,N,K", list(linear_tile_cases.SMALL))
 def test_tiles_of_small_batches(hx, T, N, K):
     rows = sorted(set([0, T - 1, T // 2])); cols = sorted(set([0, N - 1, N - 128, 127] + np.random.default_rng(N).integers(0, N, 30).tolist()))
     got = run(hx, T, N, K, seed=31 + T, rows=rows, cols=cols)

@@ -10,6 +10,8 @@ import pytest
 
 from paper_2403_02310_amd import binding, workloads as wl
 
+from . import linear_tile_cases
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -306,3 +308,33 @@ def test_a_tile_that_no_kernel_has_is_an_error():
     for tokens, features, token_tile in [(100, 320, 128), (100, 128, 96), (100, 0, 0), (32, 192, 64)]:
         plan = (ctypes.c_int32 * 6)(features, token_tile, 1, 1, 1, 64)   # feature and token tile, their numbers, pieces, k per piece
         assert launch(ctypes.byref(plan), None, None, None, tokens, 128, 64, None, None) == 9   # hipErrorInvalidConfiguration
+
+
+def test_linear_tile_cases_run_the_tiles_they_name():
+    """The parity tests of the linear layer's tiles cover what they say, whatever the planner's constants become."""
+    for cases in (linear_tile_cases.LARGE, linear_tile_cases.SMALL):
+        for (T, N, K), (features, tokens, one_tile, pieces) in cases.items():
+            p = binding.plan_linear(T, N, K)
+            assert (p.feature_tile, p.token_tile, p.token_tiles == 1, p.pieces) == (features, tokens, one_tile, pieces), (T, N, K)
+            assert p.feature_tiles == -(-N // features) and p.token_tiles == -(-T // tokens)
+            assert p.k_per_piece % 64 == 0 and (p.pieces - 1) * p.k_per_piece < K <= p.pieces * p.k_per_piece
+            assert binding.plan_linear(T, N, K, 0).pieces == 1                      # no workspace, no pieces
+
+
+def test_linear_tile_cases_cover_every_kernel_the_planner_chooses():
+    """Every tile that a sweep over tokens, features and k comes across is among the cases, with one token tile (which has a kernel
+    of its own) and with several, cut along k and uncut."""
+    covered = {(f, t, one, pieces > 1) for f, t, one, pieces in linear_tile_cases.LARGE.values()}
+    small = {(f, t, one, pieces > 1) for f, t, one, pieces in linear_tile_cases.SMALL.values()}
+    for T in (1, 20, 64, 65, 100, 129, 150, 193, 200, 256, 257, 300, 450, 577, 900, 1025):
+        for N in range(128, 20000, 640):
+            for K in (64, 704, 1984, 3008, 4032, 6144, 8128, 11776):
+                p = binding.plan_linear(T, N, K)
+                assert (p.feature_tile, p.token_tile, p.token_tiles == 1, p.pieces > 1) in (covered if T > 64 else small), (T, N, K)
+
+
+def test_plan_linear_refuses_what_linear_refuses():
+    out = binding.LinearPlan()
+    assert binding.lib.sarathi_plan_linear(0, 128, 64, 0, ctypes.byref(out)) == binding.EINVAL
+    assert binding.lib.sarathi_plan_linear(4, 100, 64, 0, ctypes.byref(out)) == binding.ESHAPE
+    assert binding.lib.sarathi_plan_linear(4, 128, 64, 0, None) == binding.EINVAL
