@@ -618,6 +618,7 @@ extern "C" sarathi_status sarathi_hybrid_attention_noalloc(sarathi_handle *h, co
     if (lay.max_part_rows < 2 * kTileCols || sizeof(float) * 2 * (size_t)lay.max_part_rows * h->cfg.num_kv_heads > kStaticPartMlBytes)
         return fail(h, SARATHI_ECAPACITY, "allocation-free entry point: num_kv_heads * head_dim is too large for the built-in scratch");
     lay.max_attn_meta = kStaticMetaBytes;
+    lay.meta_per_launch = kUploadArgBytes;
     h->resident_ws = nullptr;  // h->plan is about to be overwritten
     plan_attention(h->cfg, h->opt, lay, q_start, q_len, ctx_len, num_seqs, h->plan);
     const AttnMetaOffsets o = attn_meta_offsets(h->plan);

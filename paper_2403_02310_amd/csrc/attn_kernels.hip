@@ -1068,7 +1068,7 @@ __global__ __launch_bounds__(256) void upload_kernel(u32x4 *dst, const u32x4 *sr
 
 // The same for callers that own no pinned buffer: the bytes travel in the kernel's arguments (the runtime copies
 // the argument block when the launch is enqueued, so the source is free at once).  3,840 bytes per launch.
-constexpr uint32_t kArgPieceWords = 960;
+constexpr uint32_t kArgPieceWords = kUploadArgBytes / 4;
 struct ArgPiece {
     uint32_t w[kArgPieceWords];
 };

@@ -90,6 +90,7 @@ struct WorkspaceLayout {
     int32_t max_reduce_units;
     int32_t max_part_rows;
     size_t max_attn_meta; // bytes the packed plan of one attention call may take (attn_meta_bytes)
+    size_t meta_per_launch; // the plan travels in kernel arguments, this many bytes a launch; 0 = it does not
 };
 
 struct Options {
@@ -198,6 +199,7 @@ int launch_reduce(const sarathi_config &cfg, const AttnMeta &m, void *out, int32
 constexpr size_t kStaticMetaBytes = (size_t)96 << 10;     // packed plan of one call
 constexpr size_t kStaticPartMlBytes = (size_t)512 << 10;  // (maximum, sum) of the partial rows: part_o bytes * 2 / head_dim at most
 constexpr size_t kStaticPartOBytes = (size_t)16 << 20;    // unnormalised outputs of the partial rows
+constexpr size_t kUploadArgBytes = 3840;                  // of the plan, in the arguments of one launch
 struct StaticScratch {
     char *meta;
     int32_t *sched;

@@ -298,13 +298,26 @@ double chunk_launch_us(const sarathi_config &cfg, const std::vector<ChunkBin> &b
     return c + end;
 }
 
+// Microseconds for which an iteration keeps the host where its plan travels in kernel arguments (0 elsewhere).  From calls that the
+// host bounds: 26 us for a few tiles, 38 for 59 tiles in 264 pieces (two launches for the plan and a merge).
+double iteration_host_us(const WorkspaceLayout &ws, size_t tiles, const SplitCount &chunk, const SplitCount &wave) {
+    if (ws.meta_per_launch == 0) return 0.0;
+    const int64_t units = (int64_t)tiles - chunk.tiles - wave.tiles + chunk.units + wave.units, reduce = chunk.reduce_units + wave.reduce_units;
+    const int64_t launches = ceil_div((int64_t)attn_meta_bytes(tiles, (size_t)units, (size_t)reduce), (int64_t)ws.meta_per_launch);
+    return 22.5 + 3.2 * (double)launches + 0.015 * (double)units + (reduce > 0 ? 3.5 : 0.0);
+}
+
 // The cut of a batch's chunk tiles that chunk_launch_us finds cheapest within `max_rows` partial rows, in keys per piece (the longest
 // tile's keys: whole).  Pieces of fewer than eight key steps are all prologue, and the search ends where finer cuts have cost
 // more twice in a row.
-int64_t cheapest_chunk_split(const sarathi_config &cfg, const Plan &plan, size_t n_chunk_tiles, int64_t chunk_keys, int64_t longest_span, int64_t max_rows) {
-    int64_t tile_split = ceil_div(longest_span, kTileKeys) * kTileKeys;
+struct ChunkCut {
+    int64_t keys;          // per piece
+    double us, whole_us;   // of the launch by the estimate, cut and whole
+};
+ChunkCut cheapest_chunk_cut(const sarathi_config &cfg, const Plan &plan, size_t n_chunk_tiles, int64_t chunk_keys, int64_t longest_span, int64_t max_rows) {
+    ChunkCut cut{ceil_div(longest_span, kTileKeys) * kTileKeys, 0.0, 0.0};
     static thread_local std::vector<ChunkBin> by_steps, bins;
-    by_steps.assign((size_t)(tile_split / kTileKeys) + 1, ChunkBin{0, 0, 0});
+    by_steps.assign((size_t)(cut.keys / kTileKeys) + 1, ChunkBin{0, 0, 0});
     for (size_t ti = 0; ti < n_chunk_tiles; ++ti) {
         ChunkBin &b = by_steps[(size_t)((uint32_t)(plan.tiles[ti].n_keys - plan.tiles[ti].key_lo + kTileKeys - 1) / kTileKeys)];
         b.tiles++;
@@ -319,7 +332,8 @@ int64_t cheapest_chunk_split(const sarathi_config &cfg, const Plan &plan, size_t
     // 2,739, 56 heads, are estimated alike whole and in halves and run 3 % faster in halves (840 blocks 504 us, 1288
     // blocks 477 + 15); of 9 timed batches of several rounds none is cut for the worse by this.
     const bool one_round = (int64_t)n_chunk_tiles * cfg.num_kv_heads <= 512;
-    const double whole_us = chunk_launch_us(cfg, bins, tile_split, max_rows, 1.0e12);
+    const double whole_us = chunk_launch_us(cfg, bins, cut.keys, max_rows, 1.0e12);
+    cut.us = cut.whole_us = whole_us;
     double best = one_round ? whole_us : 1.02 * whole_us;
     // all slots busy to the end: no cut can gain what its merge costs
     const double full_us = (double)chunk_keys / kTileKeys * cfg.num_kv_heads * (cfg.head_dim == 128 ? 0.92 : 0.66) / 512.0;
@@ -330,12 +344,15 @@ int64_t cheapest_chunk_split(const sarathi_config &cfg, const Plan &plan, size_t
         if (c < best) {
             best = c;
             worse = 0;
-            if (!one_round || c < 0.95 * whole_us) tile_split = keys;
+            if (!one_round || c < 0.95 * whole_us) {
+                cut.keys = keys;
+                cut.us = c;
+            }
         } else {
             ++worse;
         }
     }
-    return tile_split;
+    return cut;
 }
 
 // Few decodes.  Uncut, a batch's wave blocks (tiles x KV heads) leave compute units idle or finish with the longest
@@ -358,6 +375,7 @@ struct WaveCut {
     int64_t keys;   // per piece
     int64_t whole;  // spans of up to this many keys stay uncut
     bool few;       // chosen by the estimate
+    double us, as_is_us;  // of the launch and its merge by the estimate, cut so and by the rule for many decodes
 };
 WaveCut cheapest_wave_cut(const sarathi_config &cfg, const Plan &plan, size_t n_chunk_tiles, int64_t wave_keys, int64_t tile_split, int64_t wave_split,
                           int64_t max_rows, bool chunks_made_do) {
@@ -415,15 +433,11 @@ WaveCut cheapest_wave_cut(const sarathi_config &cfg, const Plan &plan, size_t n_
         return c;
     };
     const double as_is = estimate((int32_t)std::min<int64_t>(wave_split, INT32_MAX / 2), 0);
-    WaveCut best{wave_split, 0, false};
-    double best_us = 0.95 * as_is;
+    WaveCut best{wave_split, 0, false, as_is, as_is};
     auto search = [&](int64_t uncut) {
         for (const int32_t keys : {4096, 3072, 2048, 1536, 1024, 768, 512, 384, 256}) {
             const double c = estimate(keys, uncut);
-            if (c < best_us) {
-                best = WaveCut{keys, uncut, true};
-                best_us = c;
-            }
+            if (c < std::min(0.95 * as_is, best.us)) best = WaveCut{keys, uncut, true, c, as_is};
         }
     };
     if (as_is >= 28.0) {
@@ -519,9 +533,19 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
     const bool few_decodes = (int64_t)n_chunk_tiles * cfg.num_kv_heads <= 128 &&
                              wave_stream_us < 0.25 * 0.62 * (double)longest_span / kTileKeys;
     auto chunk_count = [&](int64_t keys) { return count_splits(plan, 0, n_chunk_tiles, keys, 0); };
+    // A cut whose units and merge keep the host longer than they spare the GPU is not made: 130 tokens next to 54 decodes of
+    // 125-3863 keys, 4 heads and one, 34 us a call whole and 38 in 264 pieces.
+    auto host_pays = [&](double us, double whole_us, const SplitCount &chunk, const SplitCount &wave, const SplitCount &whole_chunk) {
+        const double host_us = iteration_host_us(ws, plan.tiles.size(), chunk, wave);
+        return host_us <= us || host_us < 0.95 * std::max(whole_us, iteration_host_us(ws, plan.tiles.size(), whole_chunk, SplitCount{}));
+    };
     auto cut_chunks = [&](int64_t max_rows) {
-        if (opt.tile_split_keys <= 0 && n_chunk_tiles > 0 && (!has_wave_tiles || few_decodes))
-            return cheapest_chunk_split(cfg, plan, n_chunk_tiles, keys_of_kind[kKindTile], longest_span, max_rows);
+        if (opt.tile_split_keys <= 0 && n_chunk_tiles > 0 && (!has_wave_tiles || few_decodes)) {
+            const ChunkCut cut = cheapest_chunk_cut(cfg, plan, n_chunk_tiles, keys_of_kind[kKindTile], longest_span, max_rows);
+            if (!host_pays(cut.us, cut.whole_us, chunk_count(cut.keys), SplitCount{}, SplitCount{}))
+                return ceil_div(longest_span, kTileKeys) * kTileKeys;
+            return cut.keys;
+        }
         int64_t keys = pick(opt.tile_split_keys, keys_of_kind[kKindTile], tile_units_wanted, tile_floor);
         while (opt.tile_split_keys <= 0 && chunk_count(keys).rows > max_rows) keys *= 2;
         return keys;
@@ -531,7 +555,8 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
     bool few_cut = false;
     if (opt.split_keys <= 0 && has_wave_tiles && (int64_t)(plan.tiles.size() - n_chunk_tiles) * cfg.num_kv_heads <= 512) {
         WaveCut w = cheapest_wave_cut(cfg, plan, n_chunk_tiles, keys_of_kind[kKindWave], tile_split, wave_split, ws.max_part_rows, false);
-        const int64_t wave_rows = count_splits(plan, n_chunk_tiles, plan.tiles.size(), w.keys, w.whole).rows;
+        auto wave_count = [&]() { return count_splits(plan, n_chunk_tiles, plan.tiles.size(), w.keys, w.whole); };
+        const int64_t wave_rows = wave_count().rows;
         if (w.few && wave_rows + chunk_count(tile_split).rows > ws.max_part_rows) {
             // The partial rows do not suffice for both cuts.  The decodes need few and the chunks make do with the rest (512 tokens
             // behind 3871 next to 4000 and 3000 keys, 32 and 8 heads, 4096 rows: 87 us a call with whole chunk tiles, 97 with
@@ -541,9 +566,11 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
             w = cheapest_wave_cut(cfg, plan, n_chunk_tiles, keys_of_kind[kKindWave], tile_split, wave_split,
                                   std::max<int64_t>(0, ws.max_part_rows - chunk_count(tile_split).rows), true);
         }
-        wave_split = w.keys;
-        wave_whole = w.whole;
-        few_cut = w.few;
+        if (w.few && host_pays(w.us, w.as_is_us, chunk_count(tile_split), wave_count(), chunk_count(tile_split))) {
+            wave_split = w.keys;
+            wave_whole = w.whole;
+            few_cut = true;
+        }
     }
     for (;;) {
         const SplitCount chunk = count_splits(plan, 0, n_chunk_tiles, tile_split, 0);

@@ -350,6 +350,32 @@ static void drive_decode_blocks_per_unit() {
     }
 }
 
+// Allocation-free calls that the host bounds are not cut for the GPU's sake: their units travel in further launches and a merge is
+// one more.  The same batches are cut with a workspace, and ones that the GPU bounds are cut either way.
+static void drive_host_bound_cuts() {
+    struct Batch {
+        int32_t hq, hkv, d, chunk, decodes, low, step;
+        bool cut;
+    };
+    const Batch batches[] = {{4, 1, 64, 130, 54, 125, 69, false}, {32, 8, 128, 0, 8, 500, 500, true}, {64, 8, 128, 625, 2, 3400, 40, true}};
+    for (const Batch &b : batches) {
+        std::vector<int32_t> q_start, q_len, ctx;
+        int32_t run = 0;
+        if (b.chunk > 0) { q_len.push_back(b.chunk); ctx.push_back(b.chunk); }
+        for (int32_t i = 0; i < b.decodes; ++i) { q_len.push_back(1); ctx.push_back(b.low + i * b.step); }
+        for (int32_t q : q_len) { q_start.push_back(run); run += q; }
+        const sarathi_config cfg{b.hq, b.hkv, b.d, 16, 0, 1024, 64, 512};
+        const sarathi::WorkspaceLayout ws = sarathi::make_workspace_layout(cfg);
+        sarathi::WorkspaceLayout in_arguments = ws;
+        in_arguments.meta_per_launch = sarathi::kUploadArgBytes;
+        sarathi::Plan plan;
+        sarathi::plan_attention(cfg, sarathi::Options{}, ws, q_start.data(), q_len.data(), ctx.data(), (int32_t)q_len.size(), plan);
+        CHECK(plan.num_split_tiles > 0);
+        sarathi::plan_attention(cfg, sarathi::Options{}, in_arguments, q_start.data(), q_len.data(), ctx.data(), (int32_t)q_len.size(), plan);
+        CHECK((plan.num_split_tiles > 0) == b.cut);
+    }
+}
+
 static void drive_checker() {
     // one chunk on a prefix and two decodes, GQA 4:2, d = 8; every buffer exactly as large as documented
     const int Hq = 4, Hkv = 2, d = 8;
@@ -392,6 +418,7 @@ int main() {
     drive_built_in_scratch_limits(rng);
     drive_scarce_partial_rows();
     drive_decode_blocks_per_unit();
+    drive_host_bound_cuts();
     drive_checker();
     std::printf("host paths clean (sink %llu)\n", (unsigned long long)sarathi::g_sink);
     return 0;
