@@ -1103,7 +1103,9 @@ struct ReduceParams {
 
 // BATCH: pieces fetched at once.  Chunk tiles are cut into a few pieces of many rows and bound by their bytes: four (with
 // eight, a batch of 56 tiles in two pieces took 25 us instead of 20).  Decodes that are cut to fill the chip have up to 32
-// pieces of a few rows and are bound by latency: eight (32 pieces: 11.2 -> 6.8 us, 16 pieces 8.0 -> 6.5).
+// pieces of a few rows and are bound by latency: eight (32 pieces: 11.2 -> 6.8 us, 16 pieces 8.0 -> 6.5).  A launch has one
+// size, by its finest cut: where both kinds are merged together eights and fours take the same time (14.2 and 14.5 us, 9.2
+// and 8.1, 11.1 and 11.4, 8.3 and 8.5), and a launch per kind 2.5 to 3 us more.
 template <int D, int BATCH>
 __global__ __launch_bounds__(kMergeCols * D / 4) void splitkv_reduce_kernel(ReduceParams p) {
     constexpr int TPC = D / 4;  // threads per column

@@ -61,7 +61,8 @@ inline size_t attn_meta_bytes(size_t tiles, size_t units, size_t reduce_units) {
 
 struct Plan {
     std::vector<TileDesc> tiles;
-    std::vector<uint32_t> units;      // chunk-tile units first (num_tile_units), then wave-tile units; longest first in each group;
+    std::vector<uint32_t> units;      // chunk-tile units first (num_tile_units), then wave-tile units; longest first in each group
+                                      // (wave units that share keys may be re-ordered in windows, pair_column_tiles);
                                       // every unit is one block per KV head (a wave-tile block quarters its keys among its wavefronts)
     int32_t num_tile_units = 0;
     std::vector<uint32_t> reduce_units;  // (8-column group, tile) of every split tile, for the merge kernel; chunk tiles first
@@ -214,8 +215,8 @@ int launch_upload_args(void *dst, const void *host_src, size_t bytes, void *stre
 
 // ---- linear layer (linear_kernels.hip) ----
 struct LinearPlan {
-    int32_t feature_tile; // output features per workgroup tile: 256 or 128
-    int32_t token_tile;   // tokens per workgroup tile: 256, 128, 64 or 32
+    int32_t feature_tile; // output features per workgroup tile: 256, 192 or 128
+    int32_t token_tile;   // tokens per workgroup tile: 256, 192, 128 or 64
     int32_t n_tiles;      // feature tiles
     int32_t t_tiles;      // token tiles
     int32_t splits;       // pieces of the k range (1 = none); pieces write fp32 partial tiles

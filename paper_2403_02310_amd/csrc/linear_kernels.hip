@@ -4,9 +4,9 @@
 // Both operands are contiguous along the contraction index k, which is the per-lane operand
 // shape of v_mfma_f32_32x32x16_bf16 (a lane holds one row and 8 consecutive k).  The weight tile
 // is the A operand (rows = output features) and the token tile the B operand (columns = tokens),
-// so an accumulator lane holds ONE token and runs of 4 consecutive features: the output row of
-// a token is written in 8-byte pieces that a wavefront's accumulator tiles complete to 128
-// contiguous bytes.
+// so an accumulator lane holds ONE token and runs of 4 consecutive features.  Small batches write
+// these as 8-byte pieces that a wavefront's accumulator tiles complete to 128 contiguous bytes;
+// larger ones turn them into whole rows in LDS first.
 //
 // Two kernels.  linear_phased_kernel (more than 64 tokens): four wavefronts, one per SIMD, each with up to 128 x 128
 // results in accumulation registers; linear_kernel (up to 64 tokens): eight wavefronts, narrow token tiles, bound by
@@ -161,8 +161,8 @@ __global__ __launch_bounds__(kLinThreads, 1) void linear_kernel(LinearParams p) 
     const int first_stage = lin_first_stage(p, n_tile, n_stages);
     auto row_key = [](int row) { return (row >> 1) & 7; };
 
-    // ---- global -> LDS: wavefront w moves rows 32w .. 32w+31 of the weight tile (four loads of 8 rows) and
-    // rows (BM/8)w .. of the token tile.  Lane l of a load fills physical piece l % 8 of row l / 8 and
+    // ---- global -> LDS: wavefront w moves rows (BN/8)w .. of the weight tile and rows (BM/8)w .. of the token tile, 8 rows
+    // a load.  Lane l of a load fills physical piece l % 8 of row l / 8 and
     // therefore fetches the logical piece that lives there.  Rows past the matrix re-read its last row.
     int w_off[W_LOADS], x_off[X_LOADS];
 #pragma unroll
@@ -275,7 +275,7 @@ __global__ __launch_bounds__(kLinThreads, 1) void linear_kernel(LinearParams p) 
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             const int f0 = n0 + wn * (32 * NI) + i * 32 + 4 * g;
-            if (f0 >= p.N) continue;  // N is a multiple of 128, the tile 256 wide
+            if (f0 >= p.N) continue;  // N is a multiple of 128, the tile may reach past it
             if (p.splits == 1) {
                 uint16_t *yp = p.y + (int64_t)t * p.N + f0;
 #pragma unroll
@@ -310,7 +310,9 @@ __global__ __launch_bounds__(kLinThreads, 1) void linear_kernel(LinearParams p) 
 // One wavefront per SIMD leaves nobody to cover a wait, so a phase is laid out by hand: slot m issues its share of reads and
 // fetches, then MFMA m, and a scheduling barrier keeps the compiler from moving them (343 instructions per 128 MFMAs).
 // Accumulators go out through LDS as whole rows (16-byte stores, 128 to 256 contiguous bytes per token and wavefront): 5 us
-// less per tile than 8-byte stores from the accumulator layout.
+// less per tile than 8-byte stores from the accumulator layout.  The way out still takes 8.2 us for 256 x 256: each piece is
+// a predicated read, a wait and a store in a row, and that shape (256 + 256 registers) spills 43 registers there, none in
+// the key loop; the other shapes spill none.
 // ---------------------------------------------------------------------------------------
 template <int A0, int A1, int B0, int B1, int RING, bool STREAM>
 __global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {

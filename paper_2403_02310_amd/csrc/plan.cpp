@@ -298,13 +298,17 @@ double chunk_launch_us(const sarathi_config &cfg, const std::vector<ChunkBin> &b
     return c + end;
 }
 
-// Microseconds for which an iteration keeps the host where its plan travels in kernel arguments (0 elsewhere).  From calls that the
-// host bounds: 26 us for a few tiles, 38 for 59 tiles in 264 pieces (two launches for the plan and a merge).
-double iteration_host_us(const WorkspaceLayout &ws, size_t tiles, const SplitCount &chunk, const SplitCount &wave) {
-    if (ws.meta_per_launch == 0) return 0.0;
+// Where the plan travels in kernel arguments: how many launches it takes, and for how many microseconds an iteration keeps the
+// host.  From calls that the host bounds: 26 us for a few tiles, 38 for 59 tiles in 264 pieces (two launches for the plan and a
+// merge).
+struct ArgumentLaunches {
+    int64_t launches;
+    double host_us;
+};
+ArgumentLaunches argument_launches(const WorkspaceLayout &ws, size_t tiles, const SplitCount &chunk, const SplitCount &wave) {
     const int64_t units = (int64_t)tiles - chunk.tiles - wave.tiles + chunk.units + wave.units, reduce = chunk.reduce_units + wave.reduce_units;
     const int64_t launches = ceil_div((int64_t)attn_meta_bytes(tiles, (size_t)units, (size_t)reduce), (int64_t)ws.meta_per_launch);
-    return 22.5 + 3.2 * (double)launches + 0.015 * (double)units + (reduce > 0 ? 3.5 : 0.0);
+    return {launches, 22.5 + 3.2 * (double)launches + 0.015 * (double)units + (reduce > 0 ? 3.5 : 0.0)};
 }
 
 // The cut of a batch's chunk tiles that chunk_launch_us finds cheapest within `max_rows` partial rows, in keys per piece (the longest
@@ -533,11 +537,14 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
     const bool few_decodes = (int64_t)n_chunk_tiles * cfg.num_kv_heads <= 128 &&
                              wave_stream_us < 0.25 * 0.62 * (double)longest_span / kTileKeys;
     auto chunk_count = [&](int64_t keys) { return count_splits(plan, 0, n_chunk_tiles, keys, 0); };
-    // A cut whose units and merge keep the host longer than they spare the GPU is not made: 130 tokens next to 54 decodes of
-    // 125-3863 keys, 4 heads and one, 34 us a call whole and 38 in 264 pieces.
+    // Where the plan travels in kernel arguments, a cut that needs further launches for it and keeps the host longer than it
+    // spares the GPU is not made: 130 tokens next to 54 decodes of 125-3863 keys, 4 heads and one, 34 us a call whole and 38
+    // in 264 pieces.  A cut that fits the launches the uncut plan takes anyway is the same as with a workspace.
     auto host_pays = [&](double us, double whole_us, const SplitCount &chunk, const SplitCount &wave, const SplitCount &whole_chunk) {
-        const double host_us = iteration_host_us(ws, plan.tiles.size(), chunk, wave);
-        return host_us <= us || host_us < 0.95 * std::max(whole_us, iteration_host_us(ws, plan.tiles.size(), whole_chunk, SplitCount{}));
+        if (ws.meta_per_launch == 0) return true;
+        const ArgumentLaunches cut = argument_launches(ws, plan.tiles.size(), chunk, wave);
+        const ArgumentLaunches whole = argument_launches(ws, plan.tiles.size(), whole_chunk, SplitCount{});
+        return cut.launches == whole.launches || cut.host_us <= us || cut.host_us < 0.95 * std::max(whole_us, whole.host_us);
     };
     auto cut_chunks = [&](int64_t max_rows) {
         if (opt.tile_split_keys <= 0 && n_chunk_tiles > 0 && (!has_wave_tiles || few_decodes)) {

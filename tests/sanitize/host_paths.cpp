@@ -350,29 +350,36 @@ static void drive_decode_blocks_per_unit() {
     }
 }
 
-// Allocation-free calls that the host bounds are not cut for the GPU's sake: their units travel in further launches and a merge is
-// one more.  The same batches are cut with a workspace, and ones that the GPU bounds are cut either way.
+// Allocation-free calls that the host bounds are not cut for the GPU's sake where the units take further launches.  The same batches
+// are cut with a workspace; ones that the GPU bounds, and ones whose plan takes no more launches cut than whole, either way
+// and alike.
 static void drive_host_bound_cuts() {
     struct Batch {
-        int32_t hq, hkv, d, chunk, decodes, low, step;
+        int32_t hq, hkv, d;
+        std::vector<int32_t> q_len, ctx_len;
         bool cut;
     };
-    const Batch batches[] = {{4, 1, 64, 130, 54, 125, 69, false}, {32, 8, 128, 0, 8, 500, 500, true}, {64, 8, 128, 625, 2, 3400, 40, true}};
+    Batch batches[] = {{4, 1, 64, {130}, {130}, false},
+                       {32, 8, 128, std::vector<int32_t>(8, 1), {500, 1000, 1500, 2000, 2500, 3000, 3500, 4000}, true},
+                       {64, 8, 128, {625, 1, 1}, {912, 3403, 3440}, true},
+                       {8, 2, 128, {300, 1, 37, 1, 1, 200}, {1300, 555, 37, 1, 7000, 900}, true}};
+    for (int32_t i = 0; i < 54; ++i) {
+        batches[0].q_len.push_back(1);
+        batches[0].ctx_len.push_back(125 + 69 * i);
+    }
     for (const Batch &b : batches) {
-        std::vector<int32_t> q_start, q_len, ctx;
+        std::vector<int32_t> q_start;
         int32_t run = 0;
-        if (b.chunk > 0) { q_len.push_back(b.chunk); ctx.push_back(b.chunk); }
-        for (int32_t i = 0; i < b.decodes; ++i) { q_len.push_back(1); ctx.push_back(b.low + i * b.step); }
-        for (int32_t q : q_len) { q_start.push_back(run); run += q; }
+        for (int32_t q : b.q_len) { q_start.push_back(run); run += q; }
         const sarathi_config cfg{b.hq, b.hkv, b.d, 16, 0, 1024, 64, 512};
         const sarathi::WorkspaceLayout ws = sarathi::make_workspace_layout(cfg);
         sarathi::WorkspaceLayout in_arguments = ws;
         in_arguments.meta_per_launch = sarathi::kUploadArgBytes;
-        sarathi::Plan plan;
-        sarathi::plan_attention(cfg, sarathi::Options{}, ws, q_start.data(), q_len.data(), ctx.data(), (int32_t)q_len.size(), plan);
+        sarathi::Plan plan, other;
+        sarathi::plan_attention(cfg, sarathi::Options{}, ws, q_start.data(), b.q_len.data(), b.ctx_len.data(), (int32_t)b.q_len.size(), plan);
+        sarathi::plan_attention(cfg, sarathi::Options{}, in_arguments, q_start.data(), b.q_len.data(), b.ctx_len.data(), (int32_t)b.q_len.size(), other);
         CHECK(plan.num_split_tiles > 0);
-        sarathi::plan_attention(cfg, sarathi::Options{}, in_arguments, q_start.data(), q_len.data(), ctx.data(), (int32_t)q_len.size(), plan);
-        CHECK((plan.num_split_tiles > 0) == b.cut);
+        CHECK((other.num_split_tiles > 0) == b.cut && (other.units == plan.units) == b.cut);
     }
 }
 
