@@ -241,14 +241,13 @@ sarathi_status enqueue_attention(sarathi_handle *h, char *dev, float *part_ml, f
     // the decodes need to stream their keys and values (~5 bytes/ps).
     const double chunk_us = (double)pl.tile_unit_steps * h->cfg.num_kv_heads * 0.65 / kChunkBlocksForRoles;
     const double wave_us = (double)pl.wave_keys * h->cfg.num_kv_heads * h->cfg.head_dim * 4.0 / 5.0e6;
-    // The streaming hint pays on decode streams (+2 to +7 % without chunk work) and where the batch's longest
-    // chunk unit runs about as long as the decodes stream, because the chunk blocks, whose K/V tiles then stay in
-    // L2, are what the launch waits for (+1 to +3 % on a 512-token chunk behind a 3000-token prefix next to 64
-    // decodes); it costs 2 to 3 % where the decodes are the last to finish next to chunk work that matters (the
-    // same batch with a 1400-token prefix; the long-context batch).  A chunk block's 32-key step takes ~0.9 us
-    // next to streaming decodes.
-    const double chunk_tail_us = (double)pl.longest_tile_unit_steps * 0.9;
-    const bool stream_auto = chunk_us < 0.1 * wave_us || chunk_tail_us > 0.7 * wave_us;
+    // The streaming hint pays where a decode's K/V is read once: 6.7 against 5.9 TB/s with every compute unit streaming, and next
+    // to chunk blocks their K/V tiles stay in L2 (us a call, with and without: 512 tokens behind 1871 next to 64 decodes 107.6 and
+    // 121.5; three chunks next to 128 decodes of up to 16,384 keys 912 and 955; two next to 1024 decodes 1640 and 1721).
+    // Sequences of several wave tiles (more than 16 query heads per KV head, chunks of a few rows) read their keys once per
+    // tile, and the hint would have the second one find nothing in L2: 512 decodes, 58 and 2 heads, 138 and 122 us; with a
+    // 512-token chunk and 64 decodes 44.4 and 42.2 (but 200 decodes of up to 8192 keys 101 and 106).
+    const bool stream_auto = 2 * pl.shared_wave_keys <= pl.wave_keys;
     m.stream_kv = h->opt.stream_kv >= 0 ? (int32_t)h->opt.stream_kv : (stream_auto ? 1 : 0);
     // Chunk tiles (compute-bound) and wave tiles (memory-bound) are two kernels; when the batch
     // has both they run side by side: the chunk kernel is forked onto a second stream, where the

@@ -17,9 +17,14 @@
 // tile assigned as  row 4g'+i of MFMA b  <->  key 8g'+4b+i,  lane (g, n) ends up with the eight
 // scores of column n for keys 8g..8g+7 of the tile: exactly the B operand (P^T) of the second
 // contraction, and V^T for those eight keys is one 16-byte run of the channel-major V page.
-// So K, V and Q go from global memory straight into MFMA operands: no LDS, no transposes, no
-// barriers in the key loop; the softmax is per-lane work plus two cross-lane steps (lanes n, n+16,
-// n+32, n+48).
+// The softmax is per-lane work plus two cross-lane steps (lanes n, n+16, n+32, n+48); there are no barriers in the key loop.
+// K and V reach the operands through LDS: direct global -> LDS loads of whole pages into a ring that each wavefront has for
+// itself.  Loaded straight into operands, sixteen neighbouring lanes touch sixteen K rows (or 32-byte V^T rows) at once, and
+// the vector-memory path of a compute unit handles such a load at half the rate of one that reads 1 KiB front to back: 57
+// against 90 to 106 GB/s for one compute unit out of its caches, 36 against 52 from memory while 64 of them stream.  That path
+// is what decodes share with the chunk tiles of the same launch.  Straight into operands, and through LDS: 512 tokens behind
+// 1871 next to 64 decodes, 32 and 8 heads, 124.1 and 107.6 us a call; 256 decodes 224.0 and 216.7; 512 decodes of 64 channels, 58
+// and 2 heads, 173 and 123.  (The first two figures include the streaming hint's new rule, the last one is without the hint.)
 //
 // Chunk-tile path (prefill chunks).  A workgroup of four wavefronts owns 128 columns of one
 // sequence (32 per wave) and walks the key range in 32-key tiles staged once per workgroup in
@@ -57,6 +62,7 @@
 // ctx_len is zeroed so that stale cache contents (possibly NaN) cannot reach an accumulator.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <cstring>
 #include <mutex>
@@ -117,73 +123,140 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 __device__ __forceinline__ bf16x8 load_bf16x8(const uint16_t *p) {
     return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(p));
 }
-__device__ __forceinline__ bf16x8 load_bf16x8_stream(const uint16_t *p) {
-    return __builtin_bit_cast(bf16x8, __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p)));
-}
-
-template <int D>
-struct TileRegs {
-    bf16x8 k[2][D / 32];  // A operands of the two score MFMAs, per 32-channel step
-    bf16x8 v[D / 16];     // A operands of the output MFMAs, per 16-channel tile
-};
 
 // Read-only int32 data fetched with scalar loads (the block table: wave-uniform indices).
 typedef const int32_t __attribute__((address_space(4))) *const_i32_ptr;
 
+// One direct global -> LDS load moves 16 bytes per lane (1 KiB per wavefront): lane l fetches base + byte_off(l) and the
+// wavefront's data lands at LDS byte address lds_addr + 16 l.
+// Written as inline assembly on purpose: the compiler's wait-count bookkeeping treats the builtin form as a flat access
+// that may return out of order with LDS reads, and from then on turns every wait for an LDS operand into a full drain of
+// the LDS queue (in the chunk loop one pipeline bubble per four MFMAs).  The loads issued here are waited for by hand
+// (SARATHI_WAIT_VMCNT), they are the only vector-memory accesses of the key loops.
+// A whole page of one KV head (N loads of 1 KiB) behind ONE write of the LDS base register: the instruction's immediate
+// offset is added to the global address and to the LDS address alike, so load j uses offset 1024 j and a lane offset that
+// has 1024 j taken off (rel_off[j] = byte offset inside the page minus 1024 j, which is never negative: load j fetches the
+// page's j-th KiB).  STREAM: with the non-temporal hint (K/V read once, far more than the caches hold).
+template <int N, bool STREAM = false>
+__device__ __forceinline__ void dma_load_page(const uint16_t *base, const int (&rel_off)[N], uint32_t lds_addr) {
+    static_assert(N == 2 || N == 4, "pages of 2 KiB (d = 64) or 4 KiB (d = 128) per KV head");
+    if constexpr (N == 4 && !STREAM) {
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                     "global_load_lds_dwordx4 %1, %5\n\t"
+                     "global_load_lds_dwordx4 %2, %5 offset:1024\n\t"
+                     "global_load_lds_dwordx4 %3, %5 offset:2048\n\t"
+                     "global_load_lds_dwordx4 %4, %5 offset:3072"
+                     :
+                     : "s"(lds_addr), "v"(rel_off[0]), "v"(rel_off[1]), "v"(rel_off[2]), "v"(rel_off[3]), "s"(base)
+                     : "memory");
+    } else if constexpr (N == 4) {
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                     "global_load_lds_dwordx4 %1, %5 nt\n\t"
+                     "global_load_lds_dwordx4 %2, %5 offset:1024 nt\n\t"
+                     "global_load_lds_dwordx4 %3, %5 offset:2048 nt\n\t"
+                     "global_load_lds_dwordx4 %4, %5 offset:3072 nt"
+                     :
+                     : "s"(lds_addr), "v"(rel_off[0]), "v"(rel_off[1]), "v"(rel_off[2]), "v"(rel_off[3]), "s"(base)
+                     : "memory");
+    } else if constexpr (!STREAM) {
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                     "global_load_lds_dwordx4 %1, %3\n\t"
+                     "global_load_lds_dwordx4 %2, %3 offset:1024"
+                     :
+                     : "s"(lds_addr), "v"(rel_off[0]), "v"(rel_off[1]), "s"(base)
+                     : "memory");
+    } else {
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                     "global_load_lds_dwordx4 %1, %3 nt\n\t"
+                     "global_load_lds_dwordx4 %2, %3 offset:1024 nt"
+                     :
+                     : "s"(lds_addr), "v"(rel_off[0]), "v"(rel_off[1]), "s"(base)
+                     : "memory");
+    }
+}
+typedef void __attribute__((address_space(3))) *lds_ptr;
+__device__ __forceinline__ uint32_t lds_address(const uint16_t *p) {
+    return (uint32_t)(uintptr_t)(lds_ptr)(p);
+}
+__device__ __forceinline__ bf16x8 lds_bf16x8(const uint16_t *p) {
+    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(p));
+}
+
+// s_waitcnt with only the vector-memory counter constrained (gfx9 encoding: vmcnt in bits
+// 3:0 and 15:14, expcnt 6:4 and lgkmcnt 11:8 left at their maxima).
+#define SARATHI_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (((n) >> 4) << 14) | 0x0F70)
+// the same for the LDS (and scalar-load) counter at zero
+#define SARATHI_WAIT_LDS() __builtin_amdgcn_s_waitcnt(0xC07F)
+
+// K rows sit unpadded in LDS (a direct global->LDS load writes 1 KiB of consecutive bytes per
+// wavefront); the 16-byte chunks of row r are XOR-swizzled with this key so that the 16 lanes
+// of a b128 read, which walk 16 different rows at the same logical chunk, hit distinct banks.
 template <int D>
-struct LaneGeom {
-    const uint16_t *k_cache;
-    const uint16_t *v_cache;
-    const_i32_ptr bt;      // this sequence's block-table row (scalar loads)
-    int64_t page_stride;   // elements per page (all KV heads)
-    int64_t k_lane_off;    // element offset of this lane's K row start inside a page
-    int64_t v_lane_off;    // element offset of this lane's V^T run inside a page
-    int64_t last_page_id;  // num_pages - 1 (page ids are clamped: a corrupt table cannot fault)
-    int32_t n_pages_seq;   // pages that hold positions < ctx_len
-    int32_t k_pg_sel;      // which of the tile's two pages this lane's K rows come from
-    int32_t v_pg_sel;
+__device__ __forceinline__ int k_swizzle(int r) {
+    return D == 128 ? (r & 15) : ((r >> 1) & 7);
+}
+// LDS element offset of the 8-slot half `hh` of V^T row `d` of page `u`: the two halves of a
+// row are swapped on every other group of eight channels (conflict-free reads).
+template <int D>
+__device__ __forceinline__ int v_lds_off(int u, int d, int hh) {
+    return ((u * D + d) * 2 + (hh ^ ((d >> 3) & 1))) * 8;
+}
+
+// LDS of a wave-tile block: every wavefront has a ring of kRingTiles tiles of 32 keys of its own (K pages 0 and 1, V pages
+// 0 and 1); at the end the same bytes hold its 16 columns x (D + 4) floats of unnormalised output (the pad spreads the
+// columns over the banks) and 16 x (maximum, sum) for the merge.
+template <int D>
+struct WaveSmem {
+    static constexpr int kPageElems = kPageSize * D;
+    static constexpr int kTileElems = 4 * kPageElems;
+    static constexpr int kRingTiles = D == 128 ? 1 : 2;
+    static constexpr int kWaveElems = kRingTiles * kTileElems;
+    static constexpr int kTotalElems = 4 * kWaveElems;
+    static constexpr int kColStride = D + 4;
+    static constexpr int kOutFloats = kWaveCols * kColStride;
+    static_assert((kOutFloats + 2 * kWaveCols) * 4 <= kWaveElems * 2, "the merge data fits the wavefront's ring");
 };
 
-// The two block-table entries of a 32-key tile.  They are wave-uniform and come by scalar loads, which the
-// vector-memory counter does not see.  (As vector loads they were the youngest loads in flight when their
-// values were needed, and loads return in order: waiting for them meant waiting for the previous tile's K/V
-// too, so only one tile was ever in flight.)
+// What a wavefront needs to move its K/V pages from global memory to its ring.
+template <int D>
+struct WaveLoads {
+    static constexpr int kLoads = kPageSize * D / 512;  // 1 KiB loads per page of one KV head
+    const uint16_t *k_head;  // page 0 of this KV head
+    const uint16_t *v_head;
+    const_i32_ptr bt;      // this sequence's block-table row (scalar loads)
+    int64_t page_stride;   // elements per page (all KV heads)
+    int64_t last_page_id;  // num_pages - 1 (page ids are clamped: a corrupt table cannot fault)
+    int32_t n_pages_seq;   // pages that hold positions < ctx_len
+    uint32_t lds_addr;     // of this wavefront's ring
+    int k_off[2][kLoads];  // this lane's byte offsets (see dma_load_page) for a tile's K pages 0 and 1
+    int v_off[kLoads];
+};
+
+// The two block-table entries of a 32-key tile: wave-uniform, by scalar loads, which the vector-memory counter does not see.
 struct TilePages {
     int32_t e0, e1;
 };
 template <int D>
-__device__ __forceinline__ TilePages tile_pages(const LaneGeom<D> &ge, int tile) {
+__device__ __forceinline__ TilePages tile_pages(const WaveLoads<D> &ge, int tile) {
     // Pages at or beyond ceil(ctx_len/16) are never dereferenced: the index is clamped to the
-    // sequence's last page and whatever is loaded for such keys is masked in compute_tile.
+    // sequence's last page and whatever is loaded for such keys is masked.
     return TilePages{ge.bt[min(tile * 2, ge.n_pages_seq - 1)], ge.bt[min(tile * 2 + 1, ge.n_pages_seq - 1)]};
 }
-
-// Requests the K/V of `tile`, whose table entries arrive in `pages` (fetched a tile earlier), and fetches the
-// entries of the tile after it into `pages`.  The page bases are formed on the scalar unit; a lane only picks
-// one of the two.  STREAM: the loads carry the non-temporal hint (K/V read once, far more than the caches hold).
+template <int D>
+__device__ __forceinline__ int64_t page_offset(const WaveLoads<D> &ge, int32_t entry) {
+    return (entry < 0 ? 0 : (entry > ge.last_page_id ? ge.last_page_id : (int64_t)entry)) * ge.page_stride;
+}
 template <int D, bool STREAM>
-__device__ __forceinline__ void load_tile(const LaneGeom<D> &ge, int tile, TileRegs<D> &r, TilePages &pages) {
-    const int64_t p0 = pages.e0 < 0 ? 0 : (pages.e0 > ge.last_page_id ? ge.last_page_id : (int64_t)pages.e0);
-    const int64_t p1 = pages.e1 < 0 ? 0 : (pages.e1 > ge.last_page_id ? ge.last_page_id : (int64_t)pages.e1);
-    pages = tile_pages(ge, tile + 1);
-    const int64_t o0 = p0 * ge.page_stride, o1 = p1 * ge.page_stride;
-    const uint16_t *kp = ge.k_cache + (ge.k_pg_sel ? o1 : o0) + ge.k_lane_off;
-    const uint16_t *vp = ge.v_cache + (ge.v_pg_sel ? o1 : o0) + ge.v_lane_off;
-    if (STREAM) {
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int s = 0; s < D / 32; ++s) r.k[b][s] = load_bf16x8_stream(kp + b * 4 * D + s * 32);
-#pragma unroll
-        for (int t = 0; t < D / 16; ++t) r.v[t] = load_bf16x8_stream(vp + t * 16 * kPageSize);
-    } else {
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int s = 0; s < D / 32; ++s) r.k[b][s] = load_bf16x8(kp + b * 4 * D + s * 32);
-#pragma unroll
-        for (int t = 0; t < D / 16; ++t) r.v[t] = load_bf16x8(vp + t * 16 * kPageSize);
-    }
+__device__ __forceinline__ void issue_k(const WaveLoads<D> &ge, const TilePages &pages, int slot) {
+    const uint32_t dst = ge.lds_addr + (uint32_t)(slot * WaveSmem<D>::kTileElems * 2);
+    dma_load_page<WaveLoads<D>::kLoads, STREAM>(ge.k_head + page_offset(ge, pages.e0), ge.k_off[0], dst);
+    dma_load_page<WaveLoads<D>::kLoads, STREAM>(ge.k_head + page_offset(ge, pages.e1), ge.k_off[1], dst + WaveSmem<D>::kPageElems * 2);
+}
+template <int D, bool STREAM>
+__device__ __forceinline__ void issue_v(const WaveLoads<D> &ge, const TilePages &pages, int slot) {
+    const uint32_t dst = ge.lds_addr + (uint32_t)((slot * WaveSmem<D>::kTileElems + 2 * WaveSmem<D>::kPageElems) * 2);
+    dma_load_page<WaveLoads<D>::kLoads, STREAM>(ge.v_head + page_offset(ge, pages.e0), ge.v_off, dst);
+    dma_load_page<WaveLoads<D>::kLoads, STREAM>(ge.v_head + page_offset(ge, pages.e1), ge.v_off, dst + WaveSmem<D>::kPageElems * 2);
 }
 
 template <int D>
@@ -193,15 +266,15 @@ struct SoftmaxState {
     float l;          // this lane's share of the running sum (summed over g at the end)
 };
 
+// Scores of a tile from its K operands, masked, and their softmax weights as the B operand of the second contraction.
 template <int D>
-__device__ __forceinline__ void compute_tile(TileRegs<D> &r, const bf16x8 (&qreg)[D / 32], SoftmaxState<D> &st,
-                                             int tile, int g, int pos_eff, int min_pos_eff, int lo, int max_lo, int ctx,
-                                             float scale_log2) {
+__device__ __forceinline__ bf16x8 tile_weights(const bf16x8 (&k)[2][D / 32], const bf16x8 (&qreg)[D / 32], SoftmaxState<D> &st,
+                                               int tile, int g, int pos_eff, int min_pos_eff, int lo, int max_lo, float scale_log2) {
     f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < D / 32; ++s) {
-        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(r.k[0][s], qreg[s], s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(r.k[1][s], qreg[s], s1, 0, 0, 0);
+        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k[0][s], qreg[s], s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k[1][s], qreg[s], s1, 0, 0, 0);
     }
     const int key0 = tile * kTileKeys + g * 8;  // this lane's eight keys: key0 .. key0+7
     float t[8];
@@ -217,14 +290,6 @@ __device__ __forceinline__ void compute_tile(TileRegs<D> &r, const bf16x8 (&qreg
     if (tile * kTileKeys < max_lo) {  // wave-uniform: some lane's sliding window starts inside or after this tile
 #pragma unroll
         for (int j = 0; j < 8; ++j) t[j] = (key0 + j >= lo) ? t[j] : -INFINITY;
-    }
-    if (tile * kTileKeys + kTileKeys > ctx) {  // wave-uniform: tile holds slots at or beyond ctx_len
-        u32x4 keep;
-#pragma unroll
-        for (int w = 0; w < 4; ++w)
-            keep[w] = ((key0 + 2 * w < ctx) ? 0x0000FFFFu : 0u) | ((key0 + 2 * w + 1 < ctx) ? 0xFFFF0000u : 0u);
-#pragma unroll
-        for (int c = 0; c < D / 16; ++c) r.v[c] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, r.v[c]) & keep);
     }
     float tmax = fmaxf(fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3])), fmaxf(fmaxf(t[4], t[5]), fmaxf(t[6], t[7])));
     tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
@@ -245,27 +310,20 @@ __device__ __forceinline__ void compute_tile(TileRegs<D> &r, const bf16x8 (&qreg
         psum += p[j];
     }
     st.l += psum;
-    const bf16x8 pT = __builtin_convertvector(p, bf16x8);
-#pragma unroll
-    for (int c = 0; c < D / 16; ++c)
-        st.o[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(r.v[c], pT, st.o[c], 0, 0, 0);
+    return __builtin_convertvector(p, bf16x8);
 }
-
-// LDS a wave-tile block needs to merge its four wavefronts: per wave 16 columns x (D + 4) floats of
-// unnormalised output (the pad spreads the columns over the banks) and 16 x (maximum, sum).
-template <int D>
-struct WaveMergeSmem {
-    static constexpr int kColStride = D + 4;
-    static constexpr int kOutFloats = 4 * kWaveCols * kColStride;
-    static constexpr int kTotalFloats = kOutFloats + 4 * kWaveCols * 2;
-};
 
 // One wave-tile unit = one block.  The unit's key range is quartered (in multiples of 32 keys) among
 // the block's four wavefronts, which run the same loop as independent split-KV pieces and then merge
 // their (maximum, sum, unnormalised output) through LDS in wavefront order: the block writes the final
 // rows, or one set of partial rows if the tile is split further across blocks.
+//
+// A wavefront's ring holds 16 KiB (one tile of 128 channels, two of 64): a tile's K operands are read into registers, its K
+// pages' slots filled with those of the tile kRingTiles on, then the same with V, so 8 to 16 KiB of a wavefront are always
+// on their way.  Two blocks to a compute unit reach the chip's rate so (6.7 TB/s; rings twice as deep are no faster: a unit
+// needs 64 KiB in flight at 26 GB/s).  With 64 channels one tile instead of two is 1 to 6 % slower.
 template <int D, bool STREAM>
-__device__ __forceinline__ void wave16_path(const AttnParams &p, const TileDesc &it, int split, int kvh, float *merge_lds) {
+__device__ __forceinline__ void wave16_path(const AttnParams &p, const TileDesc &it, int split, int kvh, uint16_t *smem) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15;
@@ -302,19 +360,42 @@ __device__ __forceinline__ void wave16_path(const AttnParams &p, const TileDesc 
         for (int s = 0; s < D / 32; ++s) qreg[s] = load_bf16x8(qp + s * 32);
     }
 
-    LaneGeom<D> ge;
-    ge.k_cache = p.k_cache;
-    ge.v_cache = p.v_cache;
+    using WS = WaveSmem<D>;
+    using WL = WaveLoads<D>;
+    constexpr int kRing = WS::kRingTiles;
+    constexpr int kPair = 2 * WL::kLoads;  // loads of a tile's K pages, and of its V pages
+    uint16_t *const ring = smem + wave * WS::kWaveElems;
+    WL ge;
+    ge.k_head = p.k_cache + (int64_t)kvh * WS::kPageElems;
+    ge.v_head = p.v_cache + (int64_t)kvh * WS::kPageElems;
     ge.bt = (const_i32_ptr)(p.block_table + (int64_t)seq * p.max_blocks);
-    ge.page_stride = (int64_t)p.num_kv_heads * kPageSize * D;
+    ge.page_stride = (int64_t)p.num_kv_heads * WS::kPageElems;
     ge.last_page_id = p.num_pages - 1;
     ge.n_pages_seq = (ctx + kPageSize - 1) / kPageSize;
-    ge.k_pg_sel = n >> 3;
-    ge.v_pg_sel = g >> 1;
-    // K row of MFMA b, A-row n:  page n/8, slot ((n/4)&1)*8 + 4b + n%4 ; this lane reads channels 8g.. of each 32-step
-    ge.k_lane_off = (int64_t)kvh * kPageSize * D + (((n >> 2) & 1) * 8 + (n & 3)) * D + g * 8;
-    // V^T run of output tile t, A-row n: channel 16t+n, slots 8*(g&1) .. +7 of page g/2
-    ge.v_lane_off = (int64_t)kvh * D * kPageSize + n * kPageSize + (g & 1) * 8;
+    ge.lds_addr = lds_address(ring);
+    // Page 1's K rows take part in the same reads as page 0's rows of the same slots: its swizzle key is moved by as many
+    // chunks as four rows move it, which those reads leave out.
+    constexpr int kPageKey = D == 128 ? 4 : 2;
+    constexpr int kChunks = D / 8;  // 16-byte chunks of a K row
+#pragma unroll
+    for (int j = 0; j < WL::kLoads; ++j) {
+        const int q = j * 64 + lane, slot = q / kChunks, d = q >> 1;
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            ge.k_off[u][j] = slot * D * 2 + ((q % kChunks) ^ k_swizzle<D>(slot) ^ (u * kPageKey)) * 16 - j * 1024;
+        ge.v_off[j] = (d * 2 + ((q & 1) ^ ((d >> 3) & 1))) * 16 - j * 1024;
+    }
+    // K operand: A-row n of MFMA b is page n/8, slot ((n/4)&1)*8 + 4b + n%4; contraction step s: chunk 4s + g of that row
+    int k_rd[2][D / 32];
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int s = 0; s < D / 32; ++s) {
+            const int slot = ((n >> 2) & 1) * 8 + 4 * b + (n & 3);
+            k_rd[b][s] = (n >> 3) * WS::kPageElems + slot * D + ((4 * s + g) ^ k_swizzle<D>(slot) ^ ((n >> 3) * kPageKey)) * 8;
+        }
+    // V operand of output tile c: A-row n is channel 16c + n, contraction indices 8g .. are slots 8*(g&1) .. of page g/2
+    const int v_rd = 2 * WS::kPageElems + v_lds_off<D>(g >> 1, n, g & 1);
 
     SoftmaxState<D> st;
 #pragma unroll
@@ -325,30 +406,76 @@ __device__ __forceinline__ void wave16_path(const AttnParams &p, const TileDesc 
     const int tile_begin = ur.key_begin / kTileKeys;
     const int tile_end = piece_empty ? tile_begin : (ur.key_end + kTileKeys - 1) / kTileKeys;
 
-    // Two register sets, ping-pong: the loads of tile i+1 are in flight while tile i computes.
-    TileRegs<D> ra, rb;
     TilePages pages = tile_pages(ge, tile_begin);
-    load_tile<D, STREAM>(ge, tile_begin, ra, pages);
-    int tile = tile_begin;
-    for (; tile + 1 < tile_end; tile += 2) {
-        load_tile<D, STREAM>(ge, tile + 1, rb, pages);
-        compute_tile<D>(ra, qreg, st, tile, g, pos_eff, min_pos_eff, lo, max_lo, ctx, p.scale_log2);
-        if (tile + 2 < tile_end) load_tile<D, STREAM>(ge, tile + 2, ra, pages);
-        compute_tile<D>(rb, qreg, st, tile + 1, g, pos_eff, min_pos_eff, lo, max_lo, ctx, p.scale_log2);
+    SARATHI_WAIT_VMCNT(0);  // the queries, so that from here on the counter counts the direct loads only
+#pragma unroll
+    for (int i = 0; i < kRing; ++i)
+        if (tile_begin + i < tile_end) {
+            issue_k<D, STREAM>(ge, pages, i);
+            issue_v<D, STREAM>(ge, pages, i);
+            pages = tile_pages(ge, tile_begin + i + 1);
+        }
+    // One tile.  `left`: tiles still in the ring or, if `more`, all of it: how many loads are younger than the tile's.
+    auto step = [&](int tile, int slot, auto left, auto more) {
+        constexpr int kYounger = 2 * decltype(left)::value - 1;
+        constexpr bool kMore = decltype(more)::value;
+        const uint16_t *t_lds = ring + slot * WS::kTileElems;
+        SARATHI_WAIT_VMCNT(kYounger * kPair);
+        asm volatile("" ::: "memory");
+        bf16x8 k[2][D / 32];
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int s = 0; s < D / 32; ++s) k[b][s] = lds_bf16x8(t_lds + k_rd[b][s]);
+        SARATHI_WAIT_LDS();  // the operands are in registers: their slots may be filled again
+        asm volatile("" ::: "memory");
+        if (kMore) issue_k<D, STREAM>(ge, pages, slot);
+        const bf16x8 pT = tile_weights<D>(k, qreg, st, tile, g, pos_eff, min_pos_eff, lo, max_lo, p.scale_log2);
+        SARATHI_WAIT_VMCNT((kMore ? kYounger : kYounger - 1) * kPair);
+        asm volatile("" ::: "memory");
+        bf16x8 v[D / 16];
+#pragma unroll
+        for (int c = 0; c < D / 16; ++c) v[c] = lds_bf16x8(t_lds + v_rd + c * 16 * kPageSize);
+        SARATHI_WAIT_LDS();
+        asm volatile("" ::: "memory");
+        if (kMore) {
+            issue_v<D, STREAM>(ge, pages, slot);
+            pages = tile_pages(ge, tile + kRing + 1);
+        }
+        if (tile * kTileKeys + kTileKeys > ctx) {  // wave-uniform: tile holds slots at or beyond ctx_len
+            u32x4 keep;
+            const int key0 = tile * kTileKeys + g * 8;
+#pragma unroll
+            for (int w = 0; w < 4; ++w)
+                keep[w] = ((key0 + 2 * w < ctx) ? 0x0000FFFFu : 0u) | ((key0 + 2 * w + 1 < ctx) ? 0xFFFF0000u : 0u);
+#pragma unroll
+            for (int c = 0; c < D / 16; ++c) v[c] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, v[c]) & keep);
+        }
+#pragma unroll
+        for (int c = 0; c < D / 16; ++c) st.o[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v[c], pT, st.o[c], 0, 0, 0);
+    };
+    int tile = tile_begin, slot = 0;
+    for (; tile + kRing < tile_end; ++tile) {
+        step(tile, slot, std::integral_constant<int, kRing>{}, std::true_type{});
+        slot = slot + 1 == kRing ? 0 : slot + 1;
     }
-    if (tile < tile_end) compute_tile<D>(ra, qreg, st, tile, g, pos_eff, min_pos_eff, lo, max_lo, ctx, p.scale_log2);
+    if (kRing == 2 && tile + 1 < tile_end) {
+        step(tile, slot, std::integral_constant<int, 2>{}, std::false_type{});
+        ++tile;
+        slot ^= 1;
+    }
+    if (tile < tile_end) step(tile, slot, std::integral_constant<int, 1>{}, std::false_type{});
 
     float l = st.l + __shfl_xor(st.l, 16);
     l += __shfl_xor(l, 32);
 
-    // Publish this wavefront's piece: lane (n, g) holds channels 16c + 4g + i of column n.
-    using MS = WaveMergeSmem<D>;
+    // Publish this wavefront's piece where its ring was: lane (n, g) holds channels 16c + 4g + i of column n.
     {
-        float *o_w = merge_lds + (wave * kWaveCols + n) * MS::kColStride + g * 4;
+        float *o_w = reinterpret_cast<float *>(ring) + n * WS::kColStride + g * 4;
 #pragma unroll
         for (int c = 0; c < D / 16; ++c) *reinterpret_cast<f32x4 *>(o_w + c * 16) = st.o[c];
         if (g == 0) {
-            float *ml = merge_lds + MS::kOutFloats + (wave * kWaveCols + n) * 2;
+            float *ml = reinterpret_cast<float *>(ring) + WS::kOutFloats + n * 2;
             ml[0] = st.m;
             ml[1] = l;
         }
@@ -362,7 +489,7 @@ __device__ __forceinline__ void wave16_path(const AttnParams &p, const TileDesc 
     float m_w[4], m_max = kNegSentinel;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-        m_w[w] = merge_lds[MS::kOutFloats + (w * kWaveCols + mc) * 2];
+        m_w[w] = reinterpret_cast<const float *>(smem + w * WS::kWaveElems)[WS::kOutFloats + mc * 2];
         m_max = fmaxf(m_max, m_w[w]);
     }
     float acc[CH];
@@ -372,8 +499,9 @@ __device__ __forceinline__ void wave16_path(const AttnParams &p, const TileDesc 
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
         const float wt = __builtin_amdgcn_exp2f(m_w[w] - m_max);
-        l_tot += wt * merge_lds[MS::kOutFloats + (w * kWaveCols + mc) * 2 + 1];
-        const float *o_w = merge_lds + (w * kWaveCols + mc) * MS::kColStride + ch0;
+        const float *merge = reinterpret_cast<const float *>(smem + w * WS::kWaveElems);
+        l_tot += wt * merge[WS::kOutFloats + mc * 2 + 1];
+        const float *o_w = merge + mc * WS::kColStride + ch0;
 #pragma unroll
         for (int j = 0; j < CH; j += 4) {
             const f32x4 o4 = *reinterpret_cast<const f32x4 *>(o_w + j);
@@ -422,65 +550,6 @@ struct ChunkSmem {
     static constexpr int kTotalElems = 2 * kRing * kTileElems;
 };
 
-// K rows sit unpadded in LDS (a direct global->LDS load writes 1 KiB of consecutive bytes per
-// wavefront); the 16-byte chunks of row r are XOR-swizzled with this key so that the 16 lanes
-// of a b128 read, which walk 16 different rows at the same logical chunk, hit distinct banks.
-template <int D>
-__device__ __forceinline__ int k_swizzle(int r) {
-    return D == 128 ? (r & 15) : ((r >> 1) & 7);
-}
-// LDS element offset of the 8-slot half `hh` of V^T row `d` of page `u`: the two halves of a
-// row are swapped on every other group of eight channels (conflict-free reads).
-template <int D>
-__device__ __forceinline__ int v_lds_off(int u, int d, int hh) {
-    return ((u * D + d) * 2 + (hh ^ ((d >> 3) & 1))) * 8;
-}
-
-__device__ __forceinline__ bf16x8 lds_bf16x8(const uint16_t *p) {
-    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(p));
-}
-
-typedef void __attribute__((address_space(3))) *lds_ptr;
-
-// A direct global -> LDS load moves 16 bytes per lane (1 KiB per wavefront): lane l fetches
-// base + byte_off(l) and the wavefront's data lands at LDS byte address lds_addr + 16 l.
-// Written as inline assembly on purpose: the compiler's wait-count bookkeeping treats the
-// builtin form as a flat access that may return out of order with LDS reads, and from then on
-// turns every wait for an LDS operand into a full drain of the LDS queue (one pipeline bubble
-// per four MFMAs in the loop below).  The loads issued here are waited for by hand
-// (SARATHI_WAIT_VMCNT), the only vector-memory accesses of the chunk loop.
-// A whole page of one KV head (N loads of 1 KiB) behind ONE write of the LDS base register: the
-// instruction's immediate offset is added to the global address and to the LDS address alike, so
-// load j uses offset 1024 j and a lane offset that has 1024 j taken off (rel_off[j] = byte offset
-// inside the page minus 1024 j, which is never negative: load j fetches the page's j-th KiB).
-template <int N>
-__device__ __forceinline__ void dma_load_page(const uint16_t *base, const int (&rel_off)[N], uint32_t lds_addr) {
-    static_assert(N == 2 || N == 4, "pages of 2 KiB (d = 64) or 4 KiB (d = 128) per KV head");
-    if constexpr (N == 4) {
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
-                     "global_load_lds_dwordx4 %1, %5\n\t"
-                     "global_load_lds_dwordx4 %2, %5 offset:1024\n\t"
-                     "global_load_lds_dwordx4 %3, %5 offset:2048\n\t"
-                     "global_load_lds_dwordx4 %4, %5 offset:3072"
-                     :
-                     : "s"(lds_addr), "v"(rel_off[0]), "v"(rel_off[1]), "v"(rel_off[2]), "v"(rel_off[3]), "s"(base)
-                     : "memory");
-    } else {
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
-                     "global_load_lds_dwordx4 %1, %3\n\t"
-                     "global_load_lds_dwordx4 %2, %3 offset:1024"
-                     :
-                     : "s"(lds_addr), "v"(rel_off[0]), "v"(rel_off[1]), "s"(base)
-                     : "memory");
-    }
-}
-__device__ __forceinline__ uint32_t lds_address(const uint16_t *p) {
-    return (uint32_t)(uintptr_t)(lds_ptr)(p);
-}
-
-// s_waitcnt with only the vector-memory counter constrained (gfx9 encoding: vmcnt in bits
-// 3:0 and 15:14, expcnt 6:4 and lgkmcnt 11:8 left at their maxima).
-#define SARATHI_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (((n) >> 4) << 14) | 0x0F70)
 
 constexpr int kCarry = 3;  // output-MFMA operands read one step ahead
 
@@ -970,7 +1039,8 @@ __global__ __launch_bounds__(256, 2) void attn_chunk_kernel(AttnParams p) {
     const int blk = blockIdx.x / p.num_kv_heads;
     constexpr uint32_t kTileMask = (1u << kUnitTileBits) - 1;
     const uint32_t u = p.units[blk];
-    chunk_tile_path<D>(p, p.tiles[u & kTileMask], (int)(u >> kUnitTileBits), kvh, smem);
+    const TileDesc it = p.tiles[u & kTileMask];
+    chunk_tile_path<D>(p, it, (int)(u >> kUnitTileBits), kvh, smem);
 }
 
 // Wave tiles (decodes, tiny chunks): one unit per block, its keys quartered among the four wavefronts.
@@ -980,13 +1050,13 @@ __global__ __launch_bounds__(256, 2) void attn_chunk_kernel(AttnParams p) {
 // column tiles of one sequence keep sharing an XCD, and chunk tiles, whose tiles share K/V in its L2, are not rotated.
 template <int D, bool STREAM>
 __global__ __launch_bounds__(256, 2) void attn_wave_kernel(AttnParams p) {
-    __shared__ __attribute__((aligned(16))) float merge_lds[WaveMergeSmem<D>::kTotalFloats];
+    __shared__ __attribute__((aligned(16))) uint16_t smem[WaveSmem<D>::kTotalElems];
     const int kvh = blockIdx.x % p.num_kv_heads;
     const int blk = blockIdx.x / p.num_kv_heads;
     constexpr uint32_t kTileMask = (1u << kUnitTileBits) - 1;
     const uint32_t u = p.units[p.num_tile_units + blk];
-    const TileDesc &it = p.tiles[u & kTileMask];
-    wave16_path<D, STREAM>(p, it, (int)(u >> kUnitTileBits), (kvh + it.seq) % p.num_kv_heads, merge_lds);
+    const TileDesc it = p.tiles[u & kTileMask];  // a copy: the key loop's clobbers would have it read again at the end
+    wave16_path<D, STREAM>(p, it, (int)(u >> kUnitTileBits), (kvh + it.seq) % p.num_kv_heads, smem);
 }
 
 // Both kinds of unit in ONE launch (saves the second stream's fork and join).
@@ -1005,7 +1075,8 @@ __global__ __launch_bounds__(256, 2) void attn_wave_kernel(AttnParams p) {
 // an earlier launch (or anybody else) left in them.
 template <int D, bool ROLES, bool STREAM>
 __global__ __launch_bounds__(256, 2) void attn_hybrid_kernel(AttnParams p) {
-    __shared__ __attribute__((aligned(16))) uint16_t smem[ChunkSmem<D>::kTotalElems];
+    constexpr int kSmemElems = ChunkSmem<D>::kTotalElems > WaveSmem<D>::kTotalElems ? ChunkSmem<D>::kTotalElems : WaveSmem<D>::kTotalElems;
+    __shared__ __attribute__((aligned(16))) uint16_t smem[kSmemElems];
     const int kvh = blockIdx.x % p.num_kv_heads;
     int blk = blockIdx.x / p.num_kv_heads;
     constexpr uint32_t kTileMask = (1u << kUnitTileBits) - 1;
@@ -1044,13 +1115,12 @@ __global__ __launch_bounds__(256, 2) void attn_hybrid_kernel(AttnParams p) {
     if (blk >= 0) {
         if (chunk_role) {
             const uint32_t u = p.units[blk];
-            chunk_tile_path<D>(p, p.tiles[u & kTileMask], (int)(u >> kUnitTileBits), kvh, smem);
+            const TileDesc it = p.tiles[u & kTileMask];
+            chunk_tile_path<D>(p, it, (int)(u >> kUnitTileBits), kvh, smem);
         } else {
-            static_assert(sizeof(float) * WaveMergeSmem<D>::kTotalFloats <= sizeof(uint16_t) * ChunkSmem<D>::kTotalElems,
-                          "the wave blocks' merge buffer lives in the chunk blocks' LDS");
             const uint32_t u = p.units[blk];
-            const TileDesc &it = p.tiles[u & kTileMask];
-            wave16_path<D, STREAM>(p, it, (int)(u >> kUnitTileBits), (kvh + it.seq) % p.num_kv_heads, reinterpret_cast<float *>(smem));
+            const TileDesc it = p.tiles[u & kTileMask];
+            wave16_path<D, STREAM>(p, it, (int)(u >> kUnitTileBits), (kvh + it.seq) % p.num_kv_heads, smem);
         }
     }
     // the compute unit is free for another chunk block
@@ -1441,7 +1511,8 @@ int launch_attention(const sarathi_config &cfg, const AttnMeta &m, const void *q
     p.sched = nullptr;
     p.window = m.window;
     const bool stream_kv = m.stream_kv != 0;
-    const unsigned dyn_lds = (unsigned)m.lds_pad_bytes;  // diagnostic: unused LDS that lowers the blocks per compute unit
+    // unused LDS that lowers the blocks per compute unit; all it can take next to the blocks' own 64 KiB already leaves one
+    const unsigned dyn_lds = (unsigned)std::min<int32_t>(m.lds_pad_bytes, 95 * 1024);
     hipStream_t st = static_cast<hipStream_t>(stream);
     const unsigned chunk_blocks = (unsigned)m.num_tile_units * (unsigned)cfg.num_kv_heads;
     const unsigned wave_blocks = (unsigned)(m.num_units - m.num_tile_units) * (unsigned)cfg.num_kv_heads;

@@ -75,6 +75,7 @@ struct Plan {
     int64_t tile_unit_steps = 0;      // 32-key steps summed over the chunk-tile units
     int32_t longest_tile_unit_steps = 0;  // 32-key steps of the longest chunk-tile unit
     int64_t wave_keys = 0;            // keys summed over the wave tiles
+    int64_t shared_wave_keys = 0;     // those of sequences with several wave tiles, which read the same keys
     bool even_decode_pieces = false;  // few decodes, cut into pieces of nearly one length
 };
 
@@ -103,9 +104,8 @@ struct Options {
     int64_t interleave = 2;         // batches with both kinds of tile: 0 = two launches in sequence, 1 = chunk kernel on a
                                     // second stream next to the wave kernel, 2 = one launch holding both kinds of block
     int64_t window = 0;             // sliding-window attention: a query sees its last `window` keys (itself included); 0 = all
-    int64_t stream_kv = -1;         // decode K/V loads carry the streaming (non-temporal) hint: -1 = when the batch's chunk
-                                    // work is absent or small next to its decode streams, or its longest chunk unit
-                                    // runs about as long as they do; 0 = never, 1 = always
+    int64_t stream_kv = -1;         // decode K/V loads carry the streaming (non-temporal) hint: -1 = unless most of the keys
+                                    // are read by several wave tiles; 0 = never, 1 = always
     int64_t decode_blocks_per_cu = -1;  // launches of wave tiles only: 2 = as many blocks per compute unit as fit, 1 = one (unused LDS
                                     // keeps a second one out, so blocks start longest first as units fall free instead of
                                     // all at once); -1 = one for up to 1024 blocks, two beyond and where few

@@ -464,6 +464,7 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
     plan.num_tile_reduce_units = 0;
     plan.num_split_tiles = 0;
     plan.most_pieces = 0;
+    plan.shared_wave_keys = 0;
     const int32_t G = cfg.num_q_heads / cfg.num_kv_heads;
 
     // Tiles: chunk tiles first, then wave tiles (two passes keep each kind contiguous).
@@ -493,6 +494,7 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
                 t.ctx_len = ctx_len[s];
                 plan.tiles.push_back(t);
                 keys_of_kind[kind] += t.n_keys - t.key_lo;
+                if (!chunk && n_cols > kWaveCols) plan.shared_wave_keys += t.n_keys - t.key_lo;
             }
         }
         if (pass == 0) n_chunk_tiles = plan.tiles.size();

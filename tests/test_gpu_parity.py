@@ -169,6 +169,22 @@ def test_many_kv_heads(hx, heads):
         compare(hx.bf16_tensor_to_f64(hx.setup_and_run(b, 0x7FC1, handle=h)["out"]), ref, str(opts))
 
 
+@pytest.mark.parametrize("shape", ["gqa4_d128", "mqa4_d64"])
+@pytest.mark.parametrize("hint", [0, 1])
+def test_decodes_around_the_edges_of_a_wavefronts_ring(hx, shape, hint):
+    """Decodes whose wavefronts get no tile, one, as many as their ring holds, one more and several more, with ragged last
+    tiles (unused slots are poisoned); uncut and in blocks of 128 keys, where every wavefront has one tile at most."""
+    ctx = [1, 31, 32, 33, 64, 96, 97, 128, 129, 160, 255, 256, 257, 290, 383, 384, 385, 512, 513, 769, 1025, 1601]
+    b = wl._make("ring_" + shape, SHAPES[shape], [1] * len(ctx), ctx, 91)
+    ref = oracle.attention_for_batch(b)
+    for opts in ({}, {"split_keys": 32}):
+        h = hx.make_handle(b)
+        h.set_option("stream_kv", hint)
+        for k, v in opts.items():
+            h.set_option(k, v)
+        compare(hx.bf16_tensor_to_f64(hx.setup_and_run(b, 0x7FC1, handle=h)["out"]), ref, "%s hint %d %s" % (shape, hint, opts))
+
+
 RANDOM_SHAPES = [wl.AttnShape(4, 1, 64), wl.AttnShape(8, 2, 128), wl.AttnShape(14, 2, 128), wl.AttnShape(3, 3, 64),
                  wl.AttnShape(20, 1, 128), wl.AttnShape(32, 8, 128), wl.AttnShape(8, 8, 64), wl.AttnShape(56, 8, 128),
                  wl.AttnShape(12, 4, 64)]
