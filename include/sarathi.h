@@ -120,6 +120,8 @@ const char *sarathi_last_error(const sarathi_handle *handle);
  * "decode_blocks_per_cu" (launches that hold decodes / 16-column tiles only: 1 = one block per compute unit, so
  * that blocks start longest first as units fall free, which shortens the tail of small batches; 2 = as many as fit;
  * -1 = automatic: one for up to 1024 blocks, unless few decodes were cut into pieces of nearly one length),
+ * "item_queue" (blocks take decodes / 16-column tiles from a queue instead of one block per tile: -1 = automatic, in long
+ * launches, 0 = only where "resident_chunks" has them do so, 1 = always),
  * "inline_append" (0/1: sarathi_kv_append sends up to 224 page records in its kernel's arguments instead of
  * letting the blocks read them from the pinned buffer), "lds_pad_kb" (diagnostic: KiB of unused LDS per
  * attention block, which lowers the number of blocks a compute unit holds),

@@ -51,6 +51,7 @@ struct sarathi_handle {
     uint64_t resident_opt_version = 0;
     uint64_t opt_version = 1;
     size_t resident_attn_off = 0;        // byte offset of the attention metadata inside the region
+    bool resident_sched_clear = false;   // no attention launch has used the scheduling words since that append cleared them
     // Second stream (default priority) on which the chunk-tile kernel runs next to the wave-tile
     // kernel, and the events that fork it from / join it into the caller's stream.
     hipStream_t side_stream = nullptr;
@@ -193,12 +194,59 @@ bool resident_plan_matches(const sarathi_handle *h, const int32_t *q_len, const 
            std::memcmp(h->resident_desc.data() + n, ctx_len, sizeof(int32_t) * (size_t)n) == 0;
 }
 
+// How the attention launch of h->plan hands out its work.
+struct Schedule {
+    bool roles;         // batches of both kinds: blocks take their role at run time
+    int32_t lds_pad;    // unused LDS per block
+    int32_t queue_blocks;  // so many blocks take their items from queues, whose counters are zero when the launch starts; 0 = a block per item
+};
+Schedule schedule_of(const sarathi_handle *h) {
+    const Plan &pl = h->plan;
+    Schedule s{false, (int32_t)h->opt.lds_pad_kb * 1024, 0};
+    const int64_t chunk_blocks = (int64_t)pl.num_tile_units * h->cfg.num_kv_heads;
+    const int64_t wave_blocks = (int64_t)((int32_t)pl.units.size() - pl.num_tile_units) * h->cfg.num_kv_heads;
+    if (chunk_blocks == 0) {
+        // A small decode-only batch whose blocks are all resident at once shares the memory system evenly among
+        // them, so the longest decode runs at a 512th of the bandwidth for most of its life and then alone at what
+        // one block can pull (~36 GB/s): a tail of 15-20 us on 64 decodes.  With one block per compute unit the blocks
+        // start longest first as units fall free and each streams at twice the share; one block per unit already
+        // reaches the chip's streaming rate (256 blocks x 25.5 GB/s).  Measured on 48 ... 128 decodes: -12 to -20 %;
+        // from ~192 decodes on the launch is long enough for two per unit to win by 2-4 %.  Few decodes
+        // cut into pieces of nearly one length need no balancing, and two per unit win; the line lies between (70 batches
+        // of 2 to 138 decodes, launch time; up to 256 blocks there is no difference) longest piece x pieces = 1.33 x all
+        // keys (41 decodes, 1000 blocks: 115.1 us with one, 110.6 with two; 15 decodes 20.5 and 18.9) and 1.38 x (30.0
+        // and 30.8; at 1.7 to 1.8 x, where short decodes stay whole next to the pieces, 31.1 and 34.1, 53.6 and 69.6).
+        const bool one = h->opt.decode_blocks_per_cu == 1 || (h->opt.decode_blocks_per_cu < 0 && wave_blocks <= 1024 && !pl.even_decode_pieces);
+        if (one && s.lds_pad == 0) s.lds_pad = kOneBlockPerUnitLdsPad;
+    }
+    const bool one_launch = chunk_blocks > 0 && wave_blocks > 0 && h->opt.interleave != 0;
+    // The time the decodes need to stream their keys and values.
+    const double wave_us = (double)pl.wave_keys * h->cfg.num_kv_heads * h->cfg.head_dim * 4.0 / 6.5e6;
+    // Roles pay where chunk blocks would otherwise pile up two to a compute unit for a part of the launch, and the launch is long
+    // enough for what blocks then wait for counters (3 to 8 us).  us, static and with roles: 512 chunk blocks next to 1024 decodes
+    // 1645 and 1626, 608 next to 300 decodes (420 us) 539 and 504, 504 next to 300 decodes 592 and 524, 840 next to 128
+    // decodes (700 us) 1074 and 910; but 264 blocks next to 150 decodes (150 us) 196 and 205, 272 blocks next to 13 decodes (20 us)
+    // 57 and 71, 256 next to 300 short ones (19 us) 196 and 228.
+    if (one_launch)
+        s.roles = h->opt.resident_chunks == 1 || (h->opt.resident_chunks < 0 && chunk_blocks > kChunkBlocksForRoles && wave_us > 80.0);
+    // A queue evens out the XCDs (3.5 % of a long launch) and costs an item's block 1.5 us, of two on a compute unit.  us, a
+    // block per item and queued: 1024 decodes, 8192 items, 1546 and 1518; 512 decodes, 4096 items, 759 and 748; 100 long
+    // ones 1240 and 1218; but 256 decodes, 2048 items, 216.5 and 219.5; 1024 short ones, 8192 items, 157 and 162.
+    const bool queue_pays = 0.035 * wave_us > 0.003 * (double)wave_blocks + 3.0;
+    const bool queue = h->opt.item_queue == 1 || (h->opt.item_queue < 0 && queue_pays);
+    if (s.roles || (queue && wave_blocks > 0 && (!one_launch || chunk_blocks <= kQueueBlocks)))
+        s.queue_blocks = s.lds_pad > kTwoBlocksLdsPad ? kQueueBlocks / 2 : kQueueBlocks;
+    if (!s.roles && one_launch && s.queue_blocks < chunk_blocks) s.queue_blocks = 0;  // every chunk tile has a block of its own
+    return s;
+}
+
 // Enqueues the attention launch (and the merge of split tiles) for h->plan, whose packed metadata is at `dev`.
+// `sched_clear`: the scheduling words are zero already.
 // `instrumented` = false: the allocation-free entry point, which records no timing events and never forks a
 // second stream (both create runtime objects on first use).
 sarathi_status enqueue_attention(sarathi_handle *h, char *dev, float *part_ml, float *part_o, int32_t *sched,
                                  const int32_t *block_table, const void *q, const void *k_cache, const void *v_cache,
-                                 int64_t num_pages, float sm_scale, void *out, hipStream_t s, bool instrumented) {
+                                 int64_t num_pages, float sm_scale, void *out, hipStream_t s, bool instrumented, bool sched_clear) {
     const Plan &pl = h->plan;
     const AttnMetaOffsets mo = attn_meta_offsets(pl);
     const size_t units_off = mo.units, reduce_off = mo.reduce;
@@ -220,27 +268,13 @@ sarathi_status enqueue_attention(sarathi_handle *h, char *dev, float *part_ml, f
     m.part_o = part_o;
     m.sched = sched;
     m.window = (int32_t)h->opt.window;
-    m.lds_pad_bytes = (int32_t)h->opt.lds_pad_kb * 1024;
-    {
-        // A small decode-only batch whose blocks are all resident at once shares the memory system evenly among
-        // them, so the longest decode runs at a 512th of the bandwidth for most of its life and then alone at what
-        // one block can pull (~36 GB/s): a tail of 15-20 us on 64 decodes.  With one block per compute unit the blocks
-        // start longest first as units fall free and each streams at twice the share; one block per unit already
-        // reaches the chip's streaming rate (256 blocks x 25.5 GB/s).  Measured on 48 ... 128 decodes: -12 to -20 %;
-        // from ~192 decodes on the launch is long enough for two per unit to win by 2-4 %.  Few decodes
-        // cut into pieces of nearly one length need no balancing, and two per unit win; the line lies between (70 batches
-        // of 2 to 138 decodes, launch time; up to 256 blocks there is no difference) longest piece x pieces = 1.33 x all
-        // keys (41 decodes, 1000 blocks: 115.1 us with one, 110.6 with two; 15 decodes 20.5 and 18.9) and 1.38 x (30.0
-        // and 30.8; at 1.7 to 1.8 x, where short decodes stay whole next to the pieces, 31.1 and 34.1, 53.6 and 69.6).
-        const int64_t wave_blocks = (int64_t)((int32_t)pl.units.size() - pl.num_tile_units) * h->cfg.num_kv_heads;
-        const bool wave_only = pl.num_tile_units == 0;
-        const bool one = h->opt.decode_blocks_per_cu == 1 || (h->opt.decode_blocks_per_cu < 0 && wave_blocks <= 1024 && !pl.even_decode_pieces);
-        if (wave_only && one && m.lds_pad_bytes == 0) m.lds_pad_bytes = kOneBlockPerUnitLdsPad;
+    const Schedule sched_plan = schedule_of(h);
+    m.lds_pad_bytes = sched_plan.lds_pad;
+    m.queue_blocks = sched_plan.queue_blocks;
+    if (sched_plan.queue_blocks > 0 && !sched_clear) {
+        e = (hipError_t)launch_zero(m.sched, kSchedBytes, stream);
+        if (e != hipSuccess) return hip_fail(h, "launch zero fill", e);
     }
-    // Rough durations: chunk work with one block per compute unit (~0.65 us per 32-key step), and the time
-    // the decodes need to stream their keys and values (~5 bytes/ps).
-    const double chunk_us = (double)pl.tile_unit_steps * h->cfg.num_kv_heads * 0.65 / kChunkBlocksForRoles;
-    const double wave_us = (double)pl.wave_keys * h->cfg.num_kv_heads * h->cfg.head_dim * 4.0 / 5.0e6;
     // The streaming hint pays where a decode's K/V is read once: 6.7 against 5.9 TB/s with every compute unit streaming, and next
     // to chunk blocks their K/V tiles stay in L2 (us a call, with and without: 512 tokens behind 1871 next to 64 decodes 107.6 and
     // 121.5; three chunks next to 128 decodes of up to 16,384 keys 912 and 955; two next to 1024 decodes 1640 and 1721).
@@ -274,18 +308,7 @@ sarathi_status enqueue_attention(sarathi_handle *h, char *dev, float *part_ml, f
         if (e == hipSuccess) e = (hipError_t)launch_attention(h->cfg, m, q, k_cache, v_cache, num_pages, sm_scale, out, 2, stream);
         if (e == hipSuccess) e = hipStreamWaitEvent(s, h->join_event, 0);
     } else if (both && h->opt.interleave != 0) {  // one launch (also where the second stream is not to be used)
-        // Run-time roles pay (a few atomics per block) when chunk blocks would otherwise pile up two
-        // to a compute unit for a good part of the launch: more chunk blocks than units, and chunk
-        // work that is not small next to the time the decodes need to stream.
-        const bool many_chunk_blocks = (int64_t)pl.num_tile_units * h->cfg.num_kv_heads > kChunkBlocksForRoles &&
-                                       chunk_us > 0.25 * wave_us;
-        const bool roles = h->cfg.num_kv_heads <= kSchedMaxKvHeads &&
-                           (h->opt.resident_chunks == 1 || (h->opt.resident_chunks < 0 && many_chunk_blocks));
-        if (roles) {  // the scheduling words start at zero, whatever the last user of the memory left there
-            e = (hipError_t)launch_zero(m.sched, kSchedBytes, stream);
-            if (e != hipSuccess) return hip_fail(h, "launch zero fill", e);
-        }
-        e = (hipError_t)launch_attention(h->cfg, m, q, k_cache, v_cache, num_pages, sm_scale, out, roles ? 5 : 4, stream);
+        e = (hipError_t)launch_attention(h->cfg, m, q, k_cache, v_cache, num_pages, sm_scale, out, sched_plan.roles ? 5 : 4, stream);
     } else {
         e = (hipError_t)launch_attention(h->cfg, m, q, k_cache, v_cache, num_pages, sm_scale, out, 3, stream);
     }
@@ -382,6 +405,11 @@ extern "C" sarathi_status sarathi_set_option(sarathi_handle *h, const char *name
     if (std::strcmp(name, "decode_blocks_per_cu") == 0) {
         if (value != -1 && value != 1 && value != 2) return fail(h, SARATHI_EINVAL, "decode_blocks_per_cu must be -1, 1 or 2");
         h->opt.decode_blocks_per_cu = value;
+        return SARATHI_OK;
+    }
+    if (std::strcmp(name, "item_queue") == 0) {
+        if (value < -1 || value > 1) return fail(h, SARATHI_EINVAL, "item_queue must be -1, 0 or 1");
+        h->opt.item_queue = value;
         return SARATHI_OK;
     }
     if (std::strcmp(name, "inline_append") == 0) {
@@ -548,6 +576,9 @@ extern "C" sarathi_status sarathi_kv_append(sarathi_handle *h, const void *k_new
         m.copy_dst = dev + h->resident_attn_off;
         m.copy_src = static_cast<const char *>(h->staging_dev[slot]) + h->resident_attn_off;
         m.copy_bytes = used - h->resident_attn_off;
+        m.zero_dst = static_cast<char *>(workspace) + h->ws.sched;
+        m.zero_bytes = schedule_of(h).queue_blocks > 0 ? kSchedBytes : 0;
+        h->resident_sched_clear = true;
     }
     const int t0 = timing_begin(h, 0, s);
     hipError_t e = (hipError_t)launch_kv_append(h->cfg, m, k_new, v_new, k_cache, v_cache, num_pages, stream);
@@ -575,9 +606,12 @@ extern "C" sarathi_status sarathi_hybrid_attention(sarathi_handle *h, const void
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e;
     char *dev;
+    bool sched_clear = false;
     if (resident_plan_matches(h, q_len, ctx_len, num_seqs, workspace, stream)) {
         // planned and uploaded by the sarathi_kv_append of this iteration (h->plan is that plan)
         dev = ws + h->ws.meta + h->resident_attn_off;
+        sched_clear = h->resident_sched_clear;
+        h->resident_sched_clear = false;
     } else {
         plan_attention(h->cfg, h->opt, h->ws, q_start, q_len, ctx_len, num_seqs, h->plan);
         if ((st = ensure_staging(h)) != SARATHI_OK) return st;
@@ -596,7 +630,7 @@ extern "C" sarathi_status sarathi_hybrid_attention(sarathi_handle *h, const void
     }
     return enqueue_attention(h, dev, reinterpret_cast<float *>(ws + h->ws.part_ml), reinterpret_cast<float *>(ws + h->ws.part_o),
                              reinterpret_cast<int32_t *>(ws + h->ws.sched), block_table, q, k_cache, v_cache, num_pages, sm_scale,
-                             out, s, /*instrumented=*/true);
+                             out, s, /*instrumented=*/true, sched_clear);
 }
 
 extern "C" sarathi_status sarathi_hybrid_attention_noalloc(sarathi_handle *h, const void *q, const void *k_cache,
@@ -635,5 +669,5 @@ extern "C" sarathi_status sarathi_hybrid_attention_noalloc(sarathi_handle *h, co
     e = (hipError_t)launch_upload_args(sc.meta, h->noalloc_meta.data(), o.total, stream);
     if (e != hipSuccess) return hip_fail(h, "launch upload(metadata in kernel arguments)", e);
     return enqueue_attention(h, sc.meta, sc.part_ml, sc.part_o, sc.sched, block_table, q, k_cache, v_cache, num_pages, sm_scale,
-                             out, static_cast<hipStream_t>(stream), /*instrumented=*/false);
+                             out, static_cast<hipStream_t>(stream), /*instrumented=*/false, /*sched_clear=*/false);
 }

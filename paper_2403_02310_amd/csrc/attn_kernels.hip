@@ -98,7 +98,7 @@ struct AttnParams {
     int32_t num_tile_units;  // units [0, num_tile_units) are 128-column chunk tiles (one block each)
     int32_t num_units;       // the rest are 16-column wave tiles (one block each as well)
     float scale_log2;        // sm_scale * log2(e): the softmax runs in base 2
-    int32_t *sched;          // scheduling words of the run-time role assignment (else unused)
+    int32_t *sched;          // scheduling words (see internal.h)
     int32_t window;          // sliding window: a query at position p sees keys p-window+1 .. p; 0 = all keys up to p
 };
 
@@ -116,6 +116,69 @@ __device__ __forceinline__ UnitRange unit_range(const TileDesc &t, int split) {
     return r;
 }
 
+// Read-only int32 data fetched with scalar loads (wave-uniform indices): the block table and the plan.
+typedef const int32_t __attribute__((address_space(4))) *const_i32_ptr;
+
+__device__ __forceinline__ uint32_t load_unit(const AttnParams &p, int i) {
+    return (uint32_t)((const_i32_ptr)p.units)[__builtin_amdgcn_readfirstlane(i)];
+}
+__device__ __forceinline__ TileDesc load_tile_desc(const AttnParams &p, uint32_t unit) {
+    const const_i32_ptr t = (const_i32_ptr)(p.tiles + (unit & ((1u << kUnitTileBits) - 1)));
+    return TileDesc{t[0], t[1], t[2], t[3], t[4], t[5], t[6], t[7], t[8], t[9], t[10], t[11]};
+}
+
+// Queues of work items.  An item is a unit for one KV head, number unit * Hkv + head; list x of a queue holds the items that
+// are x modulo 8, in order, behind one counter.  A block's home list is its index modulo 8 and thereby its XCD: items whose
+// K/V meet in one L2 stay together.  Whoever finds a list empty goes on with the next, so that no XCD waits for another:
+// with every compute unit streaming, the XCDs differ by up to 10 % in speed, and with the items dealt out evenly the slowest
+// decides (1024 decodes and two chunks: XCDs ended between 1459 and 1632 us).  The counters are relaxed atomics: they hand out
+// indices into the read-only plan.  They start at zero; the first `taken` items are the blocks' first ones.
+constexpr int kNoItem = 0x7FFFFFFF;
+constexpr int kOneEach = 0, kQueued = 1, kRoles = 2;  // how a launch of both kinds of tile hands them out
+struct Queue {
+    int32_t *counters;
+    int n_items, taken, list;
+    __device__ __forceinline__ int number(int x, int count) const {
+        return ((taken - x + kSchedLists - 1) / kSchedLists + count) * kSchedLists + x;
+    }
+    __device__ __forceinline__ int bump() const {
+        return __hip_atomic_fetch_add(counters + list * kSchedStride, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // the item at count `got` of the list, or kNoItem
+    __device__ __forceinline__ int item(int got) const {
+        const int i = number(list, got);
+        return i < n_items ? i : kNoItem;
+    }
+    // Moves to the list that has most left; false if all are empty.  All counters are read at once: going round by
+    // fetch-and-add would cost a block eight round trips to memory at its end.
+    __device__ __forceinline__ bool move_on() {
+        int counts[kSchedLists], most = 0;
+#pragma unroll
+        for (int x = 0; x < kSchedLists; ++x)
+            counts[x] = __hip_atomic_load(counters + x * kSchedStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int x = 0; x < kSchedLists; ++x) {
+            const int left = n_items - number(x, counts[x]);
+            if (left > most) most = left, list = x;
+        }
+        return most > 0;
+    }
+    // the item at count `got`, or where the list is at its end one of another list, or kNoItem
+    __device__ __forceinline__ int take(int got) {
+        int i = item(got);
+        while (i == kNoItem && move_on()) i = item(bump());
+        return i;
+    }
+};
+
+// The thread's index, as a value the compiler cannot follow: the per-lane offsets made from it are then formed anew for every item
+// a block takes instead of being kept in registers across items (28 more registers, and 15 spilled).
+__device__ __forceinline__ int thread_of_item() {
+    int t = (int)threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
 constexpr float kNegSentinel = -1.0e30f;  // finite "no key seen yet" running maximum
 constexpr float kRescaleSlack = 8.0f;     // raise the softmax reference only when exceeded by 2^8
 typedef __attribute__((ext_vector_type(16))) float f32x16;
@@ -123,9 +186,6 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 __device__ __forceinline__ bf16x8 load_bf16x8(const uint16_t *p) {
     return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(p));
 }
-
-// Read-only int32 data fetched with scalar loads (the block table: wave-uniform indices).
-typedef const int32_t __attribute__((address_space(4))) *const_i32_ptr;
 
 // One direct global -> LDS load moves 16 bytes per lane (1 KiB per wavefront): lane l fetches base + byte_off(l) and the
 // wavefront's data lands at LDS byte address lds_addr + 16 l.
@@ -322,10 +382,14 @@ __device__ __forceinline__ bf16x8 tile_weights(const bf16x8 (&k)[2][D / 32], con
 // pages' slots filled with those of the tile kRingTiles on, then the same with V, so 8 to 16 KiB of a wavefront are always
 // on their way.  Two blocks to a compute unit reach the chip's rate so (6.7 TB/s; rings twice as deep are no faster: a unit
 // needs 64 KiB in flight at 26 GB/s).  With 64 channels one tile instead of two is 1 to 6 % slower.
-template <int D, bool STREAM>
-__device__ __forceinline__ void wave16_path(const AttnParams &p, const TileDesc &it, int split, int kvh, uint16_t *smem) {
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+//
+// claim() is called by the block's first thread while its last tiles are on their way: the next item's counter is read
+// under the last loads, and not so early that a block sits on an item that another could have begun.  Returns what it returned.
+template <int D, bool STREAM, typename Claim>
+__device__ __forceinline__ int wave16_path(const AttnParams &p, const TileDesc &it, int split, int kvh, uint16_t *smem, Claim claim) {
+    const int tid = thread_of_item();
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15;
     const int g = lane >> 4;
     const int seq = it.seq;
@@ -455,8 +519,15 @@ __device__ __forceinline__ void wave16_path(const AttnParams &p, const TileDesc 
         for (int c = 0; c < D / 16; ++c) st.o[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v[c], pT, st.o[c], 0, 0, 0);
     };
     int tile = tile_begin, slot = 0;
-    for (; tile + kRing < tile_end; ++tile) {
+    for (; tile + kRing + 1 < tile_end; ++tile) {
         step(tile, slot, std::integral_constant<int, kRing>{}, std::true_type{});
+        slot = slot + 1 == kRing ? 0 : slot + 1;
+    }
+    int claimed = 0;
+    if (tid == 0) claimed = claim();  // in front of the last tile's loads: results come back in order
+    if (tile + kRing < tile_end) {
+        step(tile, slot, std::integral_constant<int, kRing>{}, std::true_type{});
+        ++tile;
         slot = slot + 1 == kRing ? 0 : slot + 1;
     }
     if (kRing == 2 && tile + 1 < tile_end) {
@@ -483,9 +554,9 @@ __device__ __forceinline__ void wave16_path(const AttnParams &p, const TileDesc 
     __syncthreads();
     // Merge: thread t owns column t / 16 and D / 16 consecutive channels of it.
     constexpr int CH = D / 16;
-    const int mc = threadIdx.x >> 4;
-    const int ch0 = (threadIdx.x & 15) * CH;
-    if (mc >= it.n_cols) return;
+    const int mc = tid >> 4;
+    const int ch0 = (tid & 15) * CH;
+    if (mc >= it.n_cols) return claimed;
     float m_w[4], m_max = kNegSentinel;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
@@ -521,17 +592,18 @@ __device__ __forceinline__ void wave16_path(const AttnParams &p, const TileDesc 
             const f32x4 o = {acc[j] * inv, acc[j + 1] * inv, acc[j + 2] * inv, acc[j + 3] * inv};
             *reinterpret_cast<u32x2 *>(op + j) = __builtin_bit_cast(u32x2, __builtin_convertvector(o, bf16x4));
         }
-        return;
+        return claimed;
     }
     // Tile split across blocks: this block's (reference maximum, sum, unnormalised output).
     const int64_t prow = ((int64_t)(whole.part_row + mc) * p.num_kv_heads + kvh);
     float *po = p.part_o + prow * D + ch0;
 #pragma unroll
     for (int j = 0; j < CH; j += 4) *reinterpret_cast<f32x4 *>(po + j) = f32x4{acc[j], acc[j + 1], acc[j + 2], acc[j + 3]};
-    if ((threadIdx.x & 15) == 0) {
+    if ((tid & 15) == 0) {
         p.part_ml[prow * 2 + 0] = m_max;
         p.part_ml[prow * 2 + 1] = l_tot;
     }
+    return claimed;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -759,7 +831,7 @@ __device__ __forceinline__ void chunk_tile_path(const AttnParams &p, const TileD
     constexpr int LOADS_PER_PAGE = PAGE_ELEMS / 512;  // 1 KiB wavefront loads per page of one KV head
     using SM = ChunkSmem<D>;
     constexpr int TE = SM::kTileElems;
-    const int tid = threadIdx.x;
+    const int tid = thread_of_item();
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform by construction; tell the compiler
     const int n = lane & 31;
@@ -1030,101 +1102,117 @@ __device__ __forceinline__ void chunk_tile_path(const AttnParams &p, const TileD
     }
 }
 
+// Item `item` of the wave tiles.  An item's KV head is rotated by its sequence: with 8 heads item % 8 is also the XCD, the
+// pages of one head lie 8 x 4 KiB apart, and an XCD that runs the same head of every sequence reads addresses of one residue
+// only.  (1024 decodes + 2 chunks 1677 -> 1662 us, the long-context hybrid batch 978 -> 974, 256 decodes 224.7 -> 224.3.)  The
+// column tiles of one sequence keep sharing an XCD, and chunk tiles, whose tiles share K/V in its L2, are not rotated.
+template <int D, bool STREAM, typename Claim>
+__device__ __forceinline__ int wave_item(const AttnParams &p, int item, uint16_t *smem, Claim claim) {
+    const int blk = item / p.num_kv_heads, kvh = item - blk * p.num_kv_heads;
+    const uint32_t u = load_unit(p, p.num_tile_units + blk);
+    const TileDesc it = load_tile_desc(p, u);
+    return wave16_path<D, STREAM>(p, it, (int)(u >> kUnitTileBits), (kvh + it.seq) % p.num_kv_heads, smem, claim);
+}
+template <int D>
+__device__ __forceinline__ void chunk_item(const AttnParams &p, int item, uint16_t *smem) {
+    const int blk = item / p.num_kv_heads, kvh = item - blk * p.num_kv_heads;  // consecutive items = the KV heads of one unit
+    const uint32_t u = load_unit(p, blk);
+    chunk_tile_path<D>(p, load_tile_desc(p, u), (int)(u >> kUnitTileBits), kvh, smem);
+}
+
 // Chunk tiles: one block per (unit, KV head); one wavefront per SIMD so that the pipelined
 // loop has the registers it needs, the matrix pipe / vector ALU overlap comes from inside the wave.
 template <int D>
 __global__ __launch_bounds__(256, 2) void attn_chunk_kernel(AttnParams p) {
     __shared__ __attribute__((aligned(16))) uint16_t smem[ChunkSmem<D>::kTotalElems];
-    const int kvh = blockIdx.x % p.num_kv_heads;  // consecutive blocks = the KV heads of one unit
-    const int blk = blockIdx.x / p.num_kv_heads;
-    constexpr uint32_t kTileMask = (1u << kUnitTileBits) - 1;
-    const uint32_t u = p.units[blk];
-    const TileDesc it = p.tiles[u & kTileMask];
-    chunk_tile_path<D>(p, it, (int)(u >> kUnitTileBits), kvh, smem);
+    chunk_item<D>(p, (int)blockIdx.x, smem);
 }
 
-// Wave tiles (decodes, tiny chunks): one unit per block, its keys quartered among the four wavefronts.
-// The blocks of a unit run its KV heads rotated by the sequence: with 8 heads block % 8 is also the XCD, the pages of one
-// head lie 8 x 4 KiB apart, and an XCD that runs the same head of every sequence reads addresses of one residue only.
-// (1024 decodes + 2 chunks 1677 -> 1662 us, the long-context hybrid batch 978 -> 974, 256 decodes 224.7 -> 224.3.)  The
-// column tiles of one sequence keep sharing an XCD, and chunk tiles, whose tiles share K/V in its L2, are not rotated.
-template <int D, bool STREAM>
+// Wave tiles (decodes, tiny chunks): one item per block or, QUEUED, the first gridDim.x items by the blocks in order and the
+// others from the queue.
+template <int D, bool STREAM, bool QUEUED>
 __global__ __launch_bounds__(256, 2) void attn_wave_kernel(AttnParams p) {
     __shared__ __attribute__((aligned(16))) uint16_t smem[WaveSmem<D>::kTotalElems];
-    const int kvh = blockIdx.x % p.num_kv_heads;
-    const int blk = blockIdx.x / p.num_kv_heads;
-    constexpr uint32_t kTileMask = (1u << kUnitTileBits) - 1;
-    const uint32_t u = p.units[p.num_tile_units + blk];
-    const TileDesc it = p.tiles[u & kTileMask];  // a copy: the key loop's clobbers would have it read again at the end
-    wave16_path<D, STREAM>(p, it, (int)(u >> kUnitTileBits), (kvh + it.seq) % p.num_kv_heads, smem);
+    const int block = (int)blockIdx.x;
+    if constexpr (!QUEUED) {
+        wave_item<D, STREAM>(p, block, smem, [] { return 0; });
+    } else {
+        __shared__ int32_t next_item;
+        Queue q{p.sched, (p.num_units - p.num_tile_units) * p.num_kv_heads, (int)gridDim.x, block % kSchedLists};
+        for (int item = block; item != kNoItem;) {
+            const int got = wave_item<D, STREAM>(p, item, smem, [&] { return q.bump(); });
+            if (threadIdx.x == 0) next_item = q.take(got);
+            __syncthreads();  // (and everyone is done with the ring's bytes; the next write is behind the next item's barrier)
+            item = __builtin_amdgcn_readfirstlane(next_item);
+        }
+    }
 }
 
 // Both kinds of unit in ONE launch (saves the second stream's fork and join).
 //
-// ROLES == false: the first num_tile_units * Hkv blocks run chunk tiles, the rest wave tiles.
-//
-// ROLES == true: a block decides what it runs when it starts.  Chunk blocks are compute-bound and
-// wave blocks memory-bound, and they overlap only when they share a compute unit; two chunk blocks
-// on one unit leave it without a memory stream.  So each block looks up its compute unit (hardware
-// id registers), tries to become that unit's one chunk block (compare-and-swap on the unit's flag)
-// and otherwise takes wave tiles; work is handed out by per-KV-head queue heads (atomic adds), each
-// kind longest first, and a block whose preferred queue is empty takes from the other one.  The grid
-// has exactly one block per work item and KV head, so the second queue cannot be empty too.  All
-// atomics are relaxed: they only hand out indices into the read-only plan.  The host clears the
-// scheduling words with a small fill kernel in front of every such launch, so nothing depends on what
-// an earlier launch (or anybody else) left in them.
-template <int D, bool ROLES, bool STREAM>
+// kOneEach: a block per item, the chunk tiles in front.
+// kQueued: the first blocks run a chunk tile each and the others begin with a wave tile; then all take wave tiles from the queue.
+// kRoles: chunk blocks are compute-bound and wave blocks memory-bound, and they overlap only when they share a compute
+// unit; two chunk blocks on one unit leave it without a memory stream.  So one block per compute unit (the first
+// half of the grid, which the hardware spreads over the units before it gives any of them a second block) works off the chunk
+// tiles and the other the wave tiles, each kind longest first, and a block whose queue is empty takes from the other one.
+template <int D, int MODE, bool STREAM>
 __global__ __launch_bounds__(256, 2) void attn_hybrid_kernel(AttnParams p) {
     constexpr int kSmemElems = ChunkSmem<D>::kTotalElems > WaveSmem<D>::kTotalElems ? ChunkSmem<D>::kTotalElems : WaveSmem<D>::kTotalElems;
     __shared__ __attribute__((aligned(16))) uint16_t smem[kSmemElems];
-    const int kvh = blockIdx.x % p.num_kv_heads;
-    int blk = blockIdx.x / p.num_kv_heads;
-    constexpr uint32_t kTileMask = (1u << kUnitTileBits) - 1;
-    const int n_wave_blocks = p.num_units - p.num_tile_units;
-    bool chunk_role = blk < p.num_tile_units;
-    __shared__ int32_t role[3];  // kind, index, "this block set its compute unit's flag"
-    // compute unit, shader array and shader engine ids (bits 8..15 of HW_ID) and the XCC id
-    auto my_cu_flag = [&]() -> int32_t * {
-        const uint32_t hw = __builtin_amdgcn_s_getreg((7 << 11) | (8 << 6) | 4);
-        const uint32_t xcc = __builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20);
-        return p.sched + (((xcc << 8) | hw) & (kSchedCuSlots - 1));
-    };
-    if (ROLES) {
-        if (threadIdx.x == 0) {
-            int32_t *flag = my_cu_flag();
-            int32_t *heads = p.sched + kSchedCuSlots;
-            int32_t expected = 0;
-            const bool own = __hip_atomic_compare_exchange_strong(flag, &expected, 1, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                                  __HIP_MEMORY_SCOPE_AGENT);
-            role[2] = own ? 1 : 0;
-            int kind = own ? 1 : 0;  // 1 = chunk tiles, 0 = wave tiles
-            int idx = __hip_atomic_fetch_add(heads + kind * kSchedMaxKvHeads + kvh, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (idx >= (kind ? p.num_tile_units : n_wave_blocks)) {
-                kind ^= 1;
-                idx = __hip_atomic_fetch_add(heads + kind * kSchedMaxKvHeads + kvh, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (idx >= (kind ? p.num_tile_units : n_wave_blocks)) idx = -1;  // cannot happen: one block per item
+    const int n_chunk = p.num_tile_units * p.num_kv_heads;
+    const int block = (int)blockIdx.x;
+    if constexpr (MODE == kOneEach) {
+        if (block < n_chunk) chunk_item<D>(p, block, smem);
+        else wave_item<D, STREAM>(p, block - n_chunk, smem, [] { return 0; });
+    } else {
+        __shared__ int32_t next_item;  // of the wave tiles; chunk tiles are numbered behind them
+        const int n_wave = (p.num_units - p.num_tile_units) * p.num_kv_heads, blocks = (int)gridDim.x;
+        const int chunk_blocks = MODE == kRoles ? blocks / 2 : n_chunk;
+        Queue waves{p.sched, n_wave, min(n_wave, blocks - chunk_blocks), block % kSchedLists};
+        Queue chunks{p.sched + kSchedLists * kSchedStride, n_chunk, min(n_chunk, chunk_blocks), block % kSchedLists};
+        // the first thread's choice of the next item, after a wave tile whose claim returned `got` or after a chunk tile
+        auto next = [&](bool after_wave, int got) -> int {
+            if (MODE == kQueued) return waves.take(after_wave ? got : waves.bump());
+            if (after_wave) {
+                const int w = waves.item(got);
+                if (w != kNoItem) return w;
+            } else {
+                const int c = chunks.item(chunks.bump());
+                if (c != kNoItem) return n_wave + c;
             }
-            role[0] = kind;
-            role[1] = idx;
+            for (;;) {  // the own list is at its end
+                const bool more_waves = waves.move_on(), more_chunks = chunks.move_on();
+                if (!more_waves && !more_chunks) return kNoItem;
+                if (more_waves && (after_wave || !more_chunks)) {
+                    const int w = waves.item(waves.bump());
+                    if (w != kNoItem) return w;
+                } else {
+                    const int c = chunks.item(chunks.bump());
+                    if (c != kNoItem) return n_wave + c;
+                }
+            }
+        };
+        int item;
+        if (block < chunk_blocks && block < n_chunk) item = n_wave + block;
+        else if (block >= chunk_blocks && block - chunk_blocks < n_wave) item = block - chunk_blocks;
+        else {  // fewer items of the preferred kind than blocks that prefer it
+            if (threadIdx.x == 0) next_item = next(block >= chunk_blocks, n_wave / kSchedLists + 1);
+            __syncthreads();
+            item = __builtin_amdgcn_readfirstlane(next_item);
+            __syncthreads();
         }
-        __syncthreads();
-        chunk_role = role[0] != 0;
-        blk = role[1];
-        if (blk >= 0 && !chunk_role) blk += p.num_tile_units;  // same numbering as the static split below
-    }
-    if (blk >= 0) {
-        if (chunk_role) {
-            const uint32_t u = p.units[blk];
-            const TileDesc it = p.tiles[u & kTileMask];
-            chunk_tile_path<D>(p, it, (int)(u >> kUnitTileBits), kvh, smem);
-        } else {
-            const uint32_t u = p.units[blk];
-            const TileDesc it = p.tiles[u & kTileMask];
-            wave16_path<D, STREAM>(p, it, (int)(u >> kUnitTileBits), (kvh + it.seq) % p.num_kv_heads, smem);
+        while (item != kNoItem) {
+            const bool wave = item < n_wave;
+            int got = 0;
+            if (wave) got = wave_item<D, STREAM>(p, item, smem, [&] { return waves.bump(); });
+            else chunk_item<D>(p, item - n_wave, smem);
+            if (threadIdx.x == 0) next_item = next(wave, got);
+            __syncthreads();  // (and everyone is done with the rings)
+            item = __builtin_amdgcn_readfirstlane(next_item);
+            __syncthreads();
         }
     }
-    // the compute unit is free for another chunk block
-    if (ROLES && threadIdx.x == 0 && role[2]) __hip_atomic_store(my_cu_flag(), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Per-call metadata, host -> device: a kernel that reads the pinned host buffer itself.  The runtime's copy
@@ -1262,10 +1350,14 @@ struct AppendParams {
     int32_t num_kv_heads;
     // The first copy_blocks blocks move copy_n16 16-byte words from copy_src to copy_dst instead (the attention
     // metadata of the same iteration, pinned host memory -> workspace, riding in this launch).
+    // The next zero_blocks clear zero_n16 words at zero_dst (scheduling words of the attention launch that follows).
     u32x4 *copy_dst;
     const u32x4 *copy_src;
     uint32_t copy_n16;
     uint32_t copy_blocks;
+    u32x4 *zero_dst;
+    uint32_t zero_n16;
+    uint32_t zero_blocks;
 };
 
 // Small batches carry their records in the kernel's arguments (the argument block is on the device when the
@@ -1286,7 +1378,12 @@ __device__ __forceinline__ void kv_append_block(const AppendParams &p, const App
         if (i < p.copy_n16) p.copy_dst[i] = p.copy_src[i];
         return;
     }
-    const unsigned blk = blockIdx.x - p.copy_blocks;
+    if (blockIdx.x < p.copy_blocks + p.zero_blocks) {
+        const uint32_t i = (blockIdx.x - p.copy_blocks) * D + threadIdx.x;
+        if (i < p.zero_n16) p.zero_dst[i] = u32x4{0, 0, 0, 0};
+        return;
+    }
+    const unsigned blk = blockIdx.x - p.copy_blocks - p.zero_blocks;
     const int unit = (int)(blk / (unsigned)p.num_kv_heads);
     const int h = (int)(blk % (unsigned)p.num_kv_heads);
     const u32x4 rec = *reinterpret_cast<const u32x4 *>(units + unit);
@@ -1373,7 +1470,10 @@ int launch_kv_append(const sarathi_config &cfg, const AppendMeta &m, const void 
     p.copy_src = static_cast<const u32x4 *>(m.copy_src);
     p.copy_n16 = (uint32_t)((m.copy_bytes + 15) / 16);
     p.copy_blocks = (p.copy_n16 + (uint32_t)cfg.head_dim - 1) / (uint32_t)cfg.head_dim;
-    const unsigned blocks = p.copy_blocks + (unsigned)m.num_units * (unsigned)cfg.num_kv_heads;
+    p.zero_dst = static_cast<u32x4 *>(m.zero_dst);
+    p.zero_n16 = (uint32_t)((m.zero_bytes + 15) / 16);
+    p.zero_blocks = (p.zero_n16 + (uint32_t)cfg.head_dim - 1) / (uint32_t)cfg.head_dim;
+    const unsigned blocks = p.copy_blocks + p.zero_blocks + (unsigned)m.num_units * (unsigned)cfg.num_kv_heads;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (m.units_host && m.num_units <= kInlineAppendUnits) {
         AppendParamsInline pi;
@@ -1508,7 +1608,7 @@ int launch_attention(const sarathi_config &cfg, const AttnMeta &m, const void *q
     p.num_tile_units = m.num_tile_units;
     p.num_units = m.num_units;
     p.scale_log2 = sm_scale * 1.4426950408889634f;
-    p.sched = nullptr;
+    p.sched = m.sched;
     p.window = m.window;
     const bool stream_kv = m.stream_kv != 0;
     // unused LDS that lowers the blocks per compute unit; all it can take next to the blocks' own 64 KiB already leaves one
@@ -1516,21 +1616,24 @@ int launch_attention(const sarathi_config &cfg, const AttnMeta &m, const void *q
     hipStream_t st = static_cast<hipStream_t>(stream);
     const unsigned chunk_blocks = (unsigned)m.num_tile_units * (unsigned)cfg.num_kv_heads;
     const unsigned wave_blocks = (unsigned)(m.num_units - m.num_tile_units) * (unsigned)cfg.num_kv_heads;
+    const unsigned in_flight = m.queue_blocks > 0 ? (unsigned)m.queue_blocks : 0xFFFFFFFFu;
+    auto with_stream = [&](auto launch) {
+        if (stream_kv) launch(std::true_type{}); else launch(std::false_type{});
+    };
     if (which == 4 || which == 5) {
-        p.sched = m.sched;
-        const dim3 grid(chunk_blocks + wave_blocks);
-        auto launch = [&](auto d, auto roles, auto stream_hint) {
-            hipLaunchKernelGGL((attn_hybrid_kernel<decltype(d)::value, decltype(roles)::value, decltype(stream_hint)::value>),
-                               grid, dim3(256), dyn_lds, st, p);
+        const dim3 grid(std::min(chunk_blocks + wave_blocks, in_flight));
+        auto launch = [&](auto d, auto mode) {
+            with_stream([&](auto hint) {
+                hipLaunchKernelGGL((attn_hybrid_kernel<decltype(d)::value, decltype(mode)::value, decltype(hint)::value>), grid, dim3(256), dyn_lds, st, p);
+            });
         };
-        auto pick_stream = [&](auto d, auto roles) {
-            if (stream_kv) launch(d, roles, std::true_type{}); else launch(d, roles, std::false_type{});
+        auto pick_mode = [&](auto d) {
+            if (which == 5) launch(d, std::integral_constant<int, kRoles>{});
+            else if (m.queue_blocks > 0) launch(d, std::integral_constant<int, kQueued>{});
+            else launch(d, std::integral_constant<int, kOneEach>{});
         };
-        auto pick_roles = [&](auto d) {
-            if (which == 5) pick_stream(d, std::true_type{}); else pick_stream(d, std::false_type{});
-        };
-        if (cfg.head_dim == 128) pick_roles(std::integral_constant<int, 128>{});
-        else pick_roles(std::integral_constant<int, 64>{});
+        if (cfg.head_dim == 128) pick_mode(std::integral_constant<int, 128>{});
+        else pick_mode(std::integral_constant<int, 64>{});
         return (int)hipGetLastError();
     }
     if (chunk_blocks && (which & 1)) {
@@ -1540,13 +1643,17 @@ int launch_attention(const sarathi_config &cfg, const AttnMeta &m, const void *q
             hipLaunchKernelGGL(attn_chunk_kernel<64>, dim3(chunk_blocks), dim3(256), dyn_lds, st, p);
     }
     if (wave_blocks && (which & 2)) {
-        if (cfg.head_dim == 128) {
-            if (stream_kv) hipLaunchKernelGGL((attn_wave_kernel<128, true>), dim3(wave_blocks), dim3(256), dyn_lds, st, p);
-            else hipLaunchKernelGGL((attn_wave_kernel<128, false>), dim3(wave_blocks), dim3(256), dyn_lds, st, p);
-        } else {
-            if (stream_kv) hipLaunchKernelGGL((attn_wave_kernel<64, true>), dim3(wave_blocks), dim3(256), dyn_lds, st, p);
-            else hipLaunchKernelGGL((attn_wave_kernel<64, false>), dim3(wave_blocks), dim3(256), dyn_lds, st, p);
-        }
+        const dim3 grid(std::min(wave_blocks, in_flight));
+        auto launch = [&](auto d, auto queued) {
+            with_stream([&](auto hint) {
+                hipLaunchKernelGGL((attn_wave_kernel<decltype(d)::value, decltype(hint)::value, decltype(queued)::value>), grid, dim3(256), dyn_lds, st, p);
+            });
+        };
+        auto pick_queued = [&](auto d) {
+            if (m.queue_blocks > 0) launch(d, std::true_type{}); else launch(d, std::false_type{});
+        };
+        if (cfg.head_dim == 128) pick_queued(std::integral_constant<int, 128>{});
+        else pick_queued(std::integral_constant<int, 64>{});
     }
     return (int)hipGetLastError();
 }

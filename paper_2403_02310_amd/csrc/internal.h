@@ -18,14 +18,17 @@ constexpr int kTileCols = 128;    // query columns a chunk tile carries (4 waves
 constexpr int kReduceCols = 8;    // columns one block of the merge kernel handles
 constexpr int kKindWave = 0;
 constexpr int kKindTile = 1;
-// Scheduling words of the one-launch hybrid kernel when blocks pick their role at run time:
-// one "a chunk block lives here" flag per compute unit (indexed by hardware ids), then per-KV-head
-// queue heads [kind][kv head].  The host zeroes them (fill kernel) in front of every launch that uses them.
-constexpr int kSchedCuSlots = 4096;
-constexpr int kSchedMaxKvHeads = 128;
-constexpr size_t kSchedBytes = sizeof(int32_t) * (kSchedCuSlots + 2 * kSchedMaxKvHeads);
-constexpr int kChunkBlocksForRoles = 256;   // one per compute unit
-// Dynamic LDS that, added to a wave-tile block's own 17-34 KiB, leaves room for one such block per compute unit (160 KiB).
+// Scheduling words of an attention launch whose blocks take their items from queues: eight counters of the wave tiles' queue
+// and eight of the chunk tiles', a 64-byte line apart.  They are zero when a launch that uses them starts; the append
+// launch of the iteration clears them, or a small kernel of its own.
+constexpr int kSchedLists = 8;    // one per XCD
+constexpr int kSchedStride = 16;
+constexpr int kSchedWords = 2 * kSchedLists * kSchedStride;
+constexpr size_t kSchedBytes = sizeof(int32_t) * kSchedWords;
+constexpr int kQueueBlocks = 512;           // two per compute unit
+constexpr int kChunkBlocksForRoles = 320;   // a quarter more than one per compute unit
+// Dynamic LDS next to a block's own 64 KiB: up to the first a compute unit (160 KiB) holds two blocks; with the second, one.
+constexpr int kTwoBlocksLdsPad = 15 * 1024;
 constexpr int kOneBlockPerUnitLdsPad = 64 * 1024;
 
 // One tile of query columns of one sequence.  A "column" is one (query row, query head inside
@@ -83,7 +86,7 @@ struct Plan {
 struct WorkspaceLayout {
     size_t meta;          // per-call metadata, packed: sequence arrays + hints (append) or tile descriptors + units (attention)
     size_t meta_bytes;
-    size_t sched;         // int32 [kSchedCuSlots + 2*kSchedMaxKvHeads], zeroed by the host before each launch that uses it
+    size_t sched;         // kSchedBytes of scheduling words, cleared in front of each launch that uses them
     size_t part_ml;       // float [max_part_rows][Hkv][2]
     size_t part_o;        // float [max_part_rows][Hkv][head_dim]
     size_t total;
@@ -110,6 +113,7 @@ struct Options {
                                     // keeps a second one out, so blocks start longest first as units fall free instead of
                                     // all at once); -1 = one for up to 1024 blocks, two beyond and where few
                                     // decodes were cut into pieces of nearly one length
+    int64_t item_queue = -1;        // blocks take wave tiles from a queue: -1 = in long launches, 0 = never (unless roles do), 1 = always
     int64_t inline_append = 1;      // KV append: up to 224 page records travel in the kernel's arguments (else all are read from the pinned buffer)
     int64_t lds_pad_kb = 0;         // diagnostic only: KiB of unused LDS added to every attention block
     int64_t resident_chunks = -1;   // one-launch mode: blocks take their role (chunk or wave tiles) when they start, so that
@@ -156,6 +160,9 @@ struct AppendMeta {
     void *copy_dst = nullptr;
     const void *copy_src = nullptr;
     size_t copy_bytes = 0;
+    // bytes the launch also clears (a multiple of 16, 16-byte aligned)
+    void *zero_dst = nullptr;
+    size_t zero_bytes = 0;
 };
 
 int launch_kv_append(const sarathi_config &cfg, const AppendMeta &m, const void *k_new, const void *v_new,
@@ -175,13 +182,14 @@ struct AttnMeta {
     float *part_ml;              // dev
     float *part_o;               // dev
     int32_t *sched;              // dev, kSchedBytes
+    int32_t queue_blocks = 0;    // so many blocks take their items from queues (sched is then zero at the start); 0 = a block per item
     int32_t window;              // sliding window in keys, 0 = none
     int32_t stream_kv;           // 1: the wave tiles' K/V loads carry the streaming hint
     int32_t lds_pad_bytes = 0;   // diagnostic: dynamic LDS added to the attention launches (fewer blocks per compute unit)
 };
 
-// which: bit 0 = the chunk-tile kernel, bit 1 = the wave-tile kernel, 4 = both kinds in one launch,
-// 5 = one launch whose blocks take their role at run time (needs m.sched zeroed, see launch_zero)
+// which: bit 0 = the chunk-tile kernel, bit 1 = the wave-tile kernel, 4 = both kinds in one launch (with queue_blocks at least
+// the chunk tiles' items), 5 = one launch in which one block per compute unit prefers chunk tiles (with queue_blocks)
 int launch_attention(const sarathi_config &cfg, const AttnMeta &m, const void *q, const void *k_cache,
                      const void *v_cache, int64_t num_pages, float sm_scale, void *out, int which, void *stream);
 

@@ -149,7 +149,7 @@ int launch_attention(const sarathi_config &cfg, const AttnMeta &m, const void *,
         const TileDesc &t = m.tiles[ru & ((1u << kUnitTileBits) - 1)];
         CHECK(t.n_splits > 1 && (int)(ru >> kUnitTileBits) * kReduceCols < t.n_cols);
     }
-    if (which == 5) g_sink += (uint64_t)m.sched[kSchedCuSlots + 2 * kSchedMaxKvHeads - 1];
+    if (which == 5) g_sink += (uint64_t)m.sched[kSchedWords - 1];
     return 0;
 }
 int launch_reduce(const sarathi_config &, const AttnMeta &m, void *, int32_t first, int32_t count, void *) {

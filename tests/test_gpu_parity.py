@@ -185,6 +185,32 @@ def test_decodes_around_the_edges_of_a_wavefronts_ring(hx, shape, hint):
         compare(hx.bf16_tensor_to_f64(hx.setup_and_run(b, 0x7FC1, handle=h)["out"]), ref, "%s hint %d %s" % (shape, hint, opts))
 
 
+@pytest.mark.parametrize("shape", ["gqa4_d128", "mqa4_d64", "mqa20_d128"])
+@pytest.mark.parametrize("mix", ["decodes", "few_items", "mostly_chunks", "mostly_decodes"])
+def test_blocks_that_take_their_items_from_queues(hx, shape, mix):
+    """More items than the 512 blocks of a queued launch and fewer, more and fewer chunk tiles than blocks that prefer them,
+    with the scheduling words cleared by the append (first call) and by the attention call itself (second call)."""
+    s = SHAPES[shape]
+    rng = np.random.default_rng(92)
+    dec = {"decodes": 700, "few_items": 20, "mostly_chunks": 9, "mostly_decodes": 600}[mix]
+    chunks = {"decodes": [], "few_items": [40, 90], "mostly_chunks": [170, 60, 333], "mostly_decodes": [70, 130]}[mix]
+    q = chunks + [1] * dec
+    ctx = [c + int(p) for c, p in zip(chunks, rng.integers(0, 900, len(chunks)))] + [int(c) for c in rng.integers(1, 300, dec)]
+    b = wl._make("queue_%s_%s" % (mix, shape), s, q, ctx, 92)
+    ref = oracle.attention_for_batch(b)
+    for opts in ({"item_queue": 1}, {"item_queue": 1, "resident_chunks": 0, "split_keys": 32, "tile_split_keys": 64},
+                 {"resident_chunks": 1, "tile_split_keys": 32, "split_keys": 32}, {"item_queue": 1, "decode_blocks_per_cu": 1}):
+        h = hx.make_handle(b)
+        for k, v in opts.items():
+            h.set_option(k, v)
+        st = hx.setup_and_run(b, 0x7FC1, handle=h)
+        compare(hx.bf16_tensor_to_f64(st["out"]), ref, "%s %s" % (mix, opts))
+        first = st["out"].clone()
+        st["out"].zero_()
+        h.hybrid_attention(st["q"], st["k_cache"], st["v_cache"], st["bt"], b.q_start, b.q_len, b.ctx_len, b.sm_scale, st["out"])
+        assert torch.equal(first.view(torch.int16), st["out"].view(torch.int16)), (mix, opts)
+
+
 RANDOM_SHAPES = [wl.AttnShape(4, 1, 64), wl.AttnShape(8, 2, 128), wl.AttnShape(14, 2, 128), wl.AttnShape(3, 3, 64),
                  wl.AttnShape(20, 1, 128), wl.AttnShape(32, 8, 128), wl.AttnShape(8, 8, 64), wl.AttnShape(56, 8, 128),
                  wl.AttnShape(12, 4, 64)]
