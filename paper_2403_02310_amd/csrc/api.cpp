@@ -228,7 +228,7 @@ Schedule schedule_of(const sarathi_handle *h) {
     // decodes (700 us) 1074 and 910; but 264 blocks next to 150 decodes (150 us) 196 and 205, 272 blocks next to 13 decodes (20 us)
     // 57 and 71, 256 next to 300 short ones (19 us) 196 and 228.
     if (one_launch)
-        s.roles = h->opt.resident_chunks == 1 || (h->opt.resident_chunks < 0 && chunk_blocks > kChunkBlocksForRoles && wave_us > 80.0);
+        s.roles = h->opt.resident_chunks == 1 || (h->opt.resident_chunks < 0 && chunk_blocks > kChunkBlocksForRoles && wave_us > kMinStreamUsForRoles);
     // A queue evens out the XCDs (3.5 % of a long launch) and costs an item's block 1.5 us, of two on a compute unit.  us, a
     // block per item and queued: 1024 decodes, 8192 items, 1546 and 1518; 512 decodes, 4096 items, 759 and 748; 100 long
     // ones 1240 and 1218; but 256 decodes, 2048 items, 216.5 and 219.5; 1024 short ones, 8192 items, 157 and 162.

@@ -26,7 +26,9 @@ constexpr int kSchedStride = 16;
 constexpr int kSchedWords = 2 * kSchedLists * kSchedStride;
 constexpr size_t kSchedBytes = sizeof(int32_t) * kSchedWords;
 constexpr int kQueueBlocks = 512;           // two per compute unit
-constexpr int kChunkBlocksForRoles = 320;   // a quarter more than one per compute unit
+// Run-time roles: beyond this many chunk blocks (a quarter more than one per compute unit) next to decodes that stream longer
+constexpr int kChunkBlocksForRoles = 320;
+constexpr double kMinStreamUsForRoles = 80.0;
 // Dynamic LDS next to a block's own 64 KiB: up to the first a compute unit (160 KiB) holds two blocks; with the second, one.
 constexpr int kTwoBlocksLdsPad = 15 * 1024;
 constexpr int kOneBlockPerUnitLdsPad = 64 * 1024;

@@ -318,10 +318,9 @@ struct ChunkCut {
     int64_t keys;          // per piece
     double us, whole_us;   // of the launch by the estimate, cut and whole
 };
-ChunkCut cheapest_chunk_cut(const sarathi_config &cfg, const Plan &plan, size_t n_chunk_tiles, int64_t chunk_keys, int64_t longest_span, int64_t max_rows) {
-    ChunkCut cut{ceil_div(longest_span, kTileKeys) * kTileKeys, 0.0, 0.0};
+const std::vector<ChunkBin> &chunk_bins(const Plan &plan, size_t n_chunk_tiles, int64_t longest_span) {
     static thread_local std::vector<ChunkBin> by_steps, bins;
-    by_steps.assign((size_t)(cut.keys / kTileKeys) + 1, ChunkBin{0, 0, 0});
+    by_steps.assign((size_t)ceil_div(longest_span, kTileKeys) + 1, ChunkBin{0, 0, 0});
     for (size_t ti = 0; ti < n_chunk_tiles; ++ti) {
         ChunkBin &b = by_steps[(size_t)((uint32_t)(plan.tiles[ti].n_keys - plan.tiles[ti].key_lo + kTileKeys - 1) / kTileKeys)];
         b.tiles++;
@@ -330,6 +329,11 @@ ChunkCut cheapest_chunk_cut(const sarathi_config &cfg, const Plan &plan, size_t 
     bins.clear();
     for (size_t st = 1; st < by_steps.size(); ++st)
         if (by_steps[st].tiles > 0) bins.push_back(ChunkBin{(int32_t)st, by_steps[st].tiles, by_steps[st].cols});
+    return bins;
+}
+ChunkCut cheapest_chunk_cut(const sarathi_config &cfg, const Plan &plan, size_t n_chunk_tiles, int64_t chunk_keys, int64_t longest_span, int64_t max_rows) {
+    ChunkCut cut{ceil_div(longest_span, kTileKeys) * kTileKeys, 0.0, 0.0};
+    const std::vector<ChunkBin> &bins = chunk_bins(plan, n_chunk_tiles, longest_span);
     // Where whole tiles all run at once a cut has to promise 5 %: 578 tokens behind 10,320 of a 4096-key window and
     // 231 more, 64 heads, promise 0.5 % in 1008 pieces instead of 416 blocks and run 3.5 % slower (106.5 us a call
     // whole, 110.2 cut).  Beyond one round it may cost 2 % more: 1024, 512 and 384 tokens behind 10,801, 8,115 and
@@ -357,6 +361,63 @@ ChunkCut cheapest_chunk_cut(const sarathi_config &cfg, const Plan &plan, size_t 
         }
     }
     return cut;
+}
+
+// Chunk tiles next to decodes: estimated microseconds of the launch and its merge with the chunks' keys cut at `split_keys`.  From
+// timings of 290 batches (1 to 3 chunks of 64-1024 tokens behind 0-12,288 keys next to 1-600 decodes of up to 16,384 keys,
+// five head shapes, seven cuts each; the estimate errs by 10 % rms):
+//   the decodes take 2.3 + the larger of (their bytes at 6.5 TB/s, the longest block's at 68 GB/s) + a quarter of the
+//   smaller + 0.15 of the chunks' work spread over the compute units;
+//   a chunk block takes 0.91 us per 32-key step next to a decode block and 0.55 once they have ended, between that and 0.67 and
+//   0.76 where there are 256 to 512 chunk blocks, and 1.4 steps besides (0.69 of all that with 64 channels); beyond
+//   512 blocks, or one per compute unit where blocks take roles, the launch is as long as the work dealt out evenly + 0.55 of
+//   the longest block; decodes that wait for slots of chunk blocks add up to 0.38 of the chunks' time;
+//   together: 7.1 + the longer of the two + 0.04 of the shorter + for a merge 2.5 + the partial rows twice at 3.4 TB/s.
+struct HybridBatch {
+    double wave_us;       // all decode keys at 6.5 TB/s
+    double wave_block_us; // the longest decode block's
+    int64_t wave_blocks;
+};
+double hybrid_launch_us(const sarathi_config &cfg, const std::vector<ChunkBin> &bins, const HybridBatch &b, int64_t split_keys, int64_t max_rows) {
+    const double scale = cfg.head_dim == 128 ? 1.0 : 0.69;
+    const int32_t split_steps = (int32_t)std::min<int64_t>(split_keys / kTileKeys, INT32_MAX / 2);
+    int64_t units = 0, steps = 0, longest = 0, rows = 0;
+    for (const ChunkBin &t : bins) {
+        int32_t piece = t.steps, n = 1;
+        if (t.steps > split_steps + split_steps / 2) {
+            n = (t.steps - 1) / split_steps + 1;
+            piece = (t.steps - 1) / n + 1;
+            n = (t.steps - 1) / piece + 1;
+            rows += n * t.cols;
+        }
+        longest = std::max<int64_t>(longest, piece);
+        units += (int64_t)n * t.tiles;
+        steps += (int64_t)t.steps * t.tiles;
+    }
+    if (rows > max_rows) return 1.0e12;
+    const int64_t blocks = units * cfg.num_kv_heads;
+    const double work = ((double)steps + 1.37 * (double)units) * cfg.num_kv_heads, block_steps = (double)longest + 1.37;
+    double decode_us = 2.3 + std::max(b.wave_us, b.wave_block_us) + 0.25 * std::min(b.wave_us, b.wave_block_us);
+    decode_us += 0.15 * std::min(work / 256.0 * scale, decode_us);
+    auto two_phases = [&](double x, double next_to_decodes, double after) {
+        const double us = x * next_to_decodes * scale;
+        return us <= decode_us ? us : decode_us + (us - decode_us) / next_to_decodes * after;
+    };
+    double chunk_us;
+    const bool roles = blocks > kChunkBlocksForRoles && b.wave_us > kMinStreamUsForRoles;
+    if (roles) {
+        chunk_us = std::max(two_phases(block_steps, 0.91, 0.76), two_phases(work / 256.0, 0.91, 0.38) + 0.55 * 0.76 * scale * block_steps);
+    } else if (blocks <= 512) {
+        const double second = std::max(0.0, (double)(blocks - 256) / 256.0);
+        chunk_us = two_phases(block_steps, 0.91 - 0.24 * second, 0.55 + 0.21 * second);
+        if (blocks + b.wave_blocks > 512) decode_us += 0.38 * second * std::min(chunk_us, decode_us);
+    } else {
+        chunk_us = std::max(two_phases(block_steps, 0.67, 0.76), (work / 512.0 + 0.55 * block_steps) * 0.76 * scale);
+        decode_us += 0.38 * std::min(chunk_us, decode_us);
+    }
+    double us = 7.1 + std::max(chunk_us, decode_us) + 0.04 * std::min(chunk_us, decode_us);
+    if (rows > 0) us += 2.5 + 2.0 * (double)rows * cfg.num_kv_heads * (cfg.head_dim + 2) * 4.0 / 3.4e6;
+    return us;
 }
 
 // Few decodes.  Uncut, a batch's wave blocks (tiles x KV heads) leave compute units idle or finish with the longest
@@ -548,15 +609,42 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
         const ArgumentLaunches whole = argument_launches(ws, plan.tiles.size(), whole_chunk, SplitCount{});
         return cut.launches == whole.launches || cut.host_us <= us || cut.host_us < 0.95 * std::max(whole_us, whole.host_us);
     };
+    int64_t longest_wave_span = 0;
+    for (size_t ti = n_chunk_tiles; ti < plan.tiles.size(); ++ti)
+        longest_wave_span = std::max<int64_t>(longest_wave_span, plan.tiles[ti].n_keys - plan.tiles[ti].key_lo);
+    // What the rules below chose, or a cut that hybrid_launch_us finds 6 % cheaper.  (220 batches beyond 32 us: 0.955 x the
+    // time on average, none more than 1.09 x; 512 tokens behind 9000 next to 64 decodes, 32 and 8 heads: 177 us in pieces
+    // of 3072 keys, 142 in halves.)
+    auto cheaper_next_to_decodes = [&](int64_t keys, int64_t max_rows) {
+        const double key_us = cfg.head_dim * 4.0;
+        const int64_t wave_block_keys = std::min(longest_wave_span, wave_split + wave_split / 2);
+        HybridBatch b{(double)keys_of_kind[kKindWave] * cfg.num_kv_heads * key_us / 6.5e6, (double)wave_block_keys * key_us / 68.0e3,
+                      (int64_t)(plan.tiles.size() - n_chunk_tiles) * cfg.num_kv_heads};
+        if (b.wave_blocks <= 512) b.wave_block_us = std::min(b.wave_block_us, std::max(b.wave_us, 10.0));  // few decodes are cut below
+        const std::vector<ChunkBin> &bins = chunk_bins(plan, n_chunk_tiles, longest_span);
+        const double as_is = hybrid_launch_us(cfg, bins, b, keys, max_rows);
+        if (as_is < 32.0) return keys;  // the host takes as long
+        double best = 0.94 * as_is;
+        int64_t best_keys = keys;
+        for (int64_t n = 1; n <= 16 && (n == 1 || longest_span / n >= 256); ++n) {
+            const int64_t k = ceil_div(ceil_div(longest_span, n), kTileKeys) * kTileKeys;
+            const double us = hybrid_launch_us(cfg, bins, b, k, max_rows);
+            if (us < best) best = us, best_keys = k;
+        }
+        if (best_keys != keys && !host_pays(best, as_is, chunk_count(best_keys), SplitCount{}, chunk_count(keys))) return keys;
+        return best_keys;
+    };
     auto cut_chunks = [&](int64_t max_rows) {
         if (opt.tile_split_keys <= 0 && n_chunk_tiles > 0 && (!has_wave_tiles || few_decodes)) {
             const ChunkCut cut = cheapest_chunk_cut(cfg, plan, n_chunk_tiles, keys_of_kind[kKindTile], longest_span, max_rows);
+            int64_t keys = cut.keys;
             if (!host_pays(cut.us, cut.whole_us, chunk_count(cut.keys), SplitCount{}, SplitCount{}))
-                return ceil_div(longest_span, kTileKeys) * kTileKeys;
-            return cut.keys;
+                keys = ceil_div(longest_span, kTileKeys) * kTileKeys;
+            return has_wave_tiles ? cheaper_next_to_decodes(keys, max_rows) : keys;
         }
         int64_t keys = pick(opt.tile_split_keys, keys_of_kind[kKindTile], tile_units_wanted, tile_floor);
         while (opt.tile_split_keys <= 0 && chunk_count(keys).rows > max_rows) keys *= 2;
+        if (opt.tile_split_keys <= 0 && n_chunk_tiles > 0 && has_wave_tiles) return cheaper_next_to_decodes(keys, max_rows);
         return keys;
     };
     int64_t tile_split = cut_chunks(ws.max_part_rows);
