@@ -8,9 +8,10 @@
 // these as 8-byte pieces that a wavefront's accumulator tiles complete to 128 contiguous bytes;
 // larger ones turn them into whole rows in LDS first.
 //
-// Two kernels.  linear_phased_kernel (more than 64 tokens): four wavefronts, one per SIMD, each with up to 128 x 128
+// Three kernels.  linear_thin_kernel (up to 16 tokens, 32 on shorter k ranges): one workgroup per compute unit, nothing cut across
+// workgroups.  linear_phased_kernel (more than 64 tokens): four wavefronts, one per SIMD, each with up to 128 x 128
 // results in accumulation registers; linear_kernel (up to 64 tokens): eight wavefronts, narrow token tiles, bound by
-// fetching the weights.  Both bring k stages of 64 (an LDS row is one full 128-byte line of its matrix row; rows of half a
+// fetching the weights.  All bring k stages of 64 (an LDS row is one full 128-byte line of its matrix row; rows of half a
 // line fetch at less than half the rate: 43 against 95 GB/s per compute unit out of L2) from global memory straight into LDS
 // (global_load_lds_dwordx4: no staging registers).  The eight 16-byte pieces of LDS row r are XOR-swizzled with
 // (r >> 1) & 7 so that the 16 lanes of a b128 operand read, which walk 16 rows at one logical piece, hit distinct banks.
@@ -76,6 +77,7 @@ __device__ __forceinline__ void lin_dma_load_16_stream(const uint16_t *base, int
 }
 // s_waitcnt with the vector-memory counter at n and the LDS counter at zero (gfx9 encoding: vmcnt in bits
 // 3:0 and 15:14, expcnt 6:4 left at its maximum, lgkmcnt 11:8)
+#define LIN_WAIT_LDS() __builtin_amdgcn_s_waitcnt(0xC07F)  // the LDS counter alone
 #define LIN_WAIT_VMCNT_AND_LDS(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (((n) >> 4) << 14) | 0x0070)
 
 // Orders a wavefront's LDS writes before the reads of other lanes that follow (and reads before later writes).  The LDS queue
@@ -566,6 +568,148 @@ __global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {
     }
 }
 
+// ---------------------------------------------------------------------------------------
+// A few tokens: a workgroup owns F features, so many that the layer is one workgroup per compute unit, and its wavefronts
+// share the k range among themselves and add up in LDS: no partial tiles in memory and no second kernel.  A wavefront takes
+// every eighth (fourth) stage of 64 k, so that the workgroup reads runs of 1 KiB of each row, brings weight rows and token rows to a
+// ring of its own by direct loads and needs no barrier in the loop.  (Operands loaded straight into registers touch sixteen rows
+// at once, which the vector-memory path of a compute unit serves at half the rate.)
+// Bound by fetching the weights; every compute unit also pulls all token rows, out of L2, which tells beyond 16 tokens on a
+// long k range: mixed like that a unit pulls 50 to 65 GB/s.  us a call (weights from memory), cut along k as before and
+// now: 8 x 4096 x 4096 11.1 and 7.0 (4.9 at 6.8 TB/s), 8 x 6144 x 4096 13.3 and 9.3 (7.4), 8 x 4096 x 14336 23.5 and 19.6 (17.3),
+// 16 x 4096 x 14336 24.1 and 22.3, 16 x 12288 x 4096 20.5 and 16.7 (14.8), 8 x 20480 x 7168 48.4 and 44.5 (43.2),
+// 8 x 28672 x 4096 36.9 and 36.0 (34.5), 32 x 6144 x 4096 15.0 and 11.4.
+// ---------------------------------------------------------------------------------------
+constexpr int kThinTokens = 32;
+template <int FROM, typename F>
+__device__ __forceinline__ void lin_count_down(F &&f) {  // f(FROM), ..., f(0), as constants
+    f(std::integral_constant<int, FROM>{});
+    if constexpr (FROM > 0) lin_count_down<FROM - 1>(f);
+}
+template <int F, int XR, int WAVES, int RING>
+__global__ __launch_bounds__(64 * WAVES, 1) void linear_thin_kernel(LinearParams p) {
+    constexpr int KS = kLinStageK;
+    constexpr int ROWS = F + XR;             // of a stage: weights, then tokens
+    constexpr int STAGE = ROWS * KS;
+    constexpr int W_LOADS = F / 8, X_LOADS = XR / 8, LOADS = W_LOADS + X_LOADS;
+    constexpr int TILES = (F + 15) / 16;     // MFMA tiles of 16 features; the last may be half used
+    constexpr int NJ = (XR + 15) / 16;       // MFMA tiles of 16 tokens
+    constexpr int STRIDE = F + 4;            // floats between the tokens of a wavefront's sums
+    static_assert(WAVES * RING * STAGE * 2 <= 160 * 1024 && NJ * 16 * STRIDE * 4 <= RING * STAGE * 2, "LDS of a compute unit; the sums fit the ring");
+    static_assert(RING * LOADS < 64, "the vector-memory counter holds 63 loads");
+    __shared__ __attribute__((aligned(16))) uint16_t smem[WAVES * RING * STAGE];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n0 = blockIdx.x * F;
+    auto row_key = [](int row) { return (row >> 1) & 7; };
+    int off[LOADS];  // rows past the matrix re-read its last row
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+        const int row = (i < W_LOADS ? i : i - W_LOADS) * 8 + lane / 8;
+        const int source = i < W_LOADS ? min(n0 + row, p.N - 1) - n0 : min(row, p.T - 1);
+        off[i] = (source * p.K + ((lane % 8) ^ row_key(row)) * 8) * 2;
+    }
+    const uint16_t *const w_base = p.w + (int64_t)n0 * p.K;
+    uint16_t *const ring = smem + wave * RING * STAGE;
+    const uint32_t ring_addr = (uint32_t)(uintptr_t)(lin_lds_ptr)(ring);
+    const int n_stages = p.K / KS;
+    // workgroups start at different places of the k range: lin_first_stage says why
+    const int first = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 3 % n_stages);
+    const int mine = (n_stages - wave + WAVES - 1) / WAVES;  // stages wave, wave + 8, ... counted from `first`
+    auto issue = [&](int i, int slot) {
+        int at = first + wave + i * WAVES;
+        if (at >= n_stages) at -= n_stages;
+        const uint32_t dst = ring_addr + (uint32_t)(slot * STAGE * 2);
+#pragma unroll
+        for (int l = 0; l < LOADS; ++l) {
+            if (l < W_LOADS) lin_dma_load_16_stream(w_base + at * KS, off[l], dst + (uint32_t)l * 1024);
+            else lin_dma_load_16(p.x + at * KS, off[l], dst + (uint32_t)l * 1024);
+        }
+    };
+    // operands of v_mfma_f32_16x16x32_bf16: lane (g, n) holds row n, k 8g .. 8g+7; tokens and features past the rows
+    // there are shadow earlier ones, and their results are not used
+    const int n = lane & 15, g = lane >> 4;
+    int a_rd[TILES][2], b_rd[NJ][2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+#pragma unroll
+        for (int a = 0; a < TILES; ++a) {
+            const int row = a * 16 + (a * 16 + 16 > F ? n & 7 : n);
+            a_rd[a][s] = row * KS + ((4 * s + g) ^ row_key(row)) * 8;
+        }
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int row = min(j * 16 + n, XR - 1);
+            b_rd[j][s] = (F + row) * KS + ((4 * s + g) ^ row_key(row)) * 8;
+        }
+    }
+    lf32x4 acc[TILES][NJ];
+#pragma unroll
+    for (int a = 0; a < TILES; ++a)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[a][j] = lf32x4{0.f, 0.f, 0.f, 0.f};
+    auto consume = [&](int slot) {
+        asm volatile("" ::: "memory");
+        const uint16_t *sp = ring + slot * STAGE;
+        lbf16x8 fa[TILES][2], fb[NJ][2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) fb[j][s] = __builtin_bit_cast(lbf16x8, *reinterpret_cast<const lu32x4 *>(sp + b_rd[j][s]));
+#pragma unroll
+            for (int a = 0; a < TILES; ++a) fa[a][s] = __builtin_bit_cast(lbf16x8, *reinterpret_cast<const lu32x4 *>(sp + a_rd[a][s]));
+        }
+        LIN_WAIT_LDS();  // in registers: the slot may be filled again
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int a = 0; a < TILES; ++a)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) acc[a][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[a][s], fb[j][s], acc[a][j], 0, 0, 0);
+    };
+#pragma unroll
+    for (int i = 0; i < RING; ++i)
+        if (i < mine) issue(i, i);
+    int slot = 0, i = 0;
+    for (; i + RING < mine; ++i) {
+        LIN_WAIT_VMCNT_AND_LDS((RING - 1) * LOADS);
+        consume(slot);
+        issue(i + RING, slot);
+        slot = slot + 1 == RING ? 0 : slot + 1;
+    }
+    lin_count_down<RING - 1>([&](auto left) {  // the last stages: nothing more to issue
+        if (i + decltype(left)::value < mine) {
+            LIN_WAIT_VMCNT_AND_LDS(decltype(left)::value * LOADS);
+            consume(slot);
+            slot = slot + 1 == RING ? 0 : slot + 1;
+            ++i;
+        }
+    });
+    // sums of this wavefront where its ring was: lane (g, n) holds token n, features 16a + 4g ..
+    float *const sums = reinterpret_cast<float *>(ring);
+#pragma unroll
+    for (int a = 0; a < TILES; ++a)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+            if (a * 16 + 4 * g < F) *reinterpret_cast<lf32x4 *>(sums + (j * 16 + n) * STRIDE + a * 16 + 4 * g) = acc[a][j];
+    __syncthreads();
+    for (int e = (int)threadIdx.x; e < p.T * (F / 2); e += 64 * WAVES) {
+        const int t = e / (F / 2), f = e % (F / 2) * 2;
+        if (n0 + f >= p.N) continue;
+        float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            const float *part = reinterpret_cast<const float *>(smem + w * RING * STAGE) + t * STRIDE + f;
+            s0 += part[0];
+            s1 += part[1];
+        }
+        typedef __attribute__((ext_vector_type(2))) float lf32x2;
+        typedef __attribute__((ext_vector_type(2))) __bf16 lbf16x2;
+        *reinterpret_cast<uint32_t *>(p.y + (int64_t)t * p.N + n0 + f) = __builtin_bit_cast(uint32_t, __builtin_convertvector(lf32x2{s0, s1}, lbf16x2));
+    }
+}
+
 // Adds the split-K pieces of every output element in piece order and rounds once to bf16.
 __global__ __launch_bounds__(256) void linear_reduce_kernel(const float *part, uint16_t *y, int64_t elems, int splits) {
     const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
@@ -645,7 +789,7 @@ static LinearPlan plan_phased(int32_t T, int32_t N, int32_t K, size_t workspace_
     return best;
 }
 
-// Up to 64 tokens: 128 or 256 features x 64 tokens of linear_kernel, cut along k so that a small batch streams the weights
+// Up to 64 tokens and not thin: 128 or 256 features x 64 tokens of linear_kernel, cut along k so that a small batch streams the weights
 // through every compute unit.  Cost in microseconds, fitted to 1,900 timings (16 layer shapes, 1 to 64 tokens, 1 to 16
 // pieces; 6 % rms, the chosen tiling 1 % slower than the best one): as above with the weights at 9.9 TB/s in a maximum that
 // is approached from above by 0.61 of the smaller term, 0.13 us per stage for a full 64 tokens, 3.6 us for the second kernel
@@ -681,7 +825,21 @@ static LinearPlan plan_small(int32_t T, int32_t N, int32_t K, size_t workspace_b
     return best;
 }
 
+// Features of a workgroup of linear_thin_kernel: as few as give a workgroup per compute unit at most; 0: not for this layer.
+// Beyond 16 tokens the token rows that every workgroup pulls grow with T x K (us cut along k and thin: 24 x 4096 x 4096 12.2 and
+// 8.6, 20 x 2560 x 8192 14.2 and 12.7, 24 x 4608 x 7168 17.2 and 16.3, 32 x 4608 x 7168 17.7 and 17.9, 24 x 4096 x 14336 24.8 and
+// 25.5, 32 x 4096 x 14336 25.5 and 28.7).  Many features on a short k range leave a wavefront a handful of stages and gain
+// nothing (8 x 9216 x 1024 9.07 and 8.99; 9 x 11136 x 3072 17.3 and 12.2, not looked at between); few features leave too many
+// compute units idle (16 x 1024 x 8192 11.0 and 10.2, 32 x 1024 x 8192 11.6 and 13.7; 16 x 1536 x 4096 10.1 and 6.4).
+static int32_t thin_features(int32_t T, int32_t N, int32_t K) {
+    if (T > kThinTokens || N < 1536 || (T > 16 && (int64_t)T * K > 200000)) return 0;
+    for (const int f : {16, 24, 32, 48, 64, 80, 96, 112, 128})
+        if (N <= f * 256) return f <= 32 || (T <= 16 && K >= 3072) ? f : 0;
+    return 0;
+}
+
 LinearPlan plan_linear(int32_t T, int32_t N, int32_t K, size_t workspace_bytes) {
+    if (const int32_t f = thin_features(T, N, K)) return LinearPlan{f, kThinTokens, (N + f - 1) / f, 1, 1, K};
     return T > kLinSmallTokens ? plan_phased(T, N, K, workspace_bytes) : plan_small(T, N, K, workspace_bytes);
 }
 
@@ -718,6 +876,35 @@ int launch_linear(const LinearPlan &pl, const void *x, const void *w, void *y, i
     if (blocks > 0x7FFFFFFF) return (int)hipErrorInvalidValue;  // more workgroups than a grid holds
     hipStream_t st = static_cast<hipStream_t>(stream);
     const dim3 grid((unsigned)blocks);
+    if (pl.token_tile == kThinTokens) {
+        if (T > kThinTokens || pl.splits != 1) return (int)hipErrorInvalidConfiguration;
+        auto launch = [&](auto f) {
+            constexpr int F = decltype(f)::value;
+            auto with = [&](auto xr) {
+                constexpr int XR = decltype(xr)::value, WAVES = F <= 64 ? 8 : 4, kStage = (F + XR) * 128 * WAVES;  // bytes, of all wavefronts
+                constexpr int RING = std::min(6, 160 * 1024 / kStage);
+                hipLaunchKernelGGL((linear_thin_kernel<F, XR, WAVES, RING>), dim3((unsigned)pl.n_tiles), dim3(64 * WAVES), 0, st, p);
+            };
+            if (T <= 8) with(std::integral_constant<int, 8>{});
+            else if (T <= 16) with(std::integral_constant<int, 16>{});
+            else if constexpr (F <= 32) {
+                if (T <= 24) with(std::integral_constant<int, 24>{});
+                else with(std::integral_constant<int, 32>{});
+            }
+        };
+        if (T > 16 && pl.feature_tile > 32) return (int)hipErrorInvalidConfiguration;
+        if (pl.feature_tile == 16) launch(std::integral_constant<int, 16>{});
+        else if (pl.feature_tile == 24) launch(std::integral_constant<int, 24>{});
+        else if (pl.feature_tile == 32) launch(std::integral_constant<int, 32>{});
+        else if (pl.feature_tile == 48) launch(std::integral_constant<int, 48>{});
+        else if (pl.feature_tile == 64) launch(std::integral_constant<int, 64>{});
+        else if (pl.feature_tile == 80) launch(std::integral_constant<int, 80>{});
+        else if (pl.feature_tile == 96) launch(std::integral_constant<int, 96>{});
+        else if (pl.feature_tile == 112) launch(std::integral_constant<int, 112>{});
+        else if (pl.feature_tile == 128) launch(std::integral_constant<int, 128>{});
+        else return (int)hipErrorInvalidConfiguration;
+        return (int)hipGetLastError();
+    }
     if (T > kLinSmallTokens) {
         if (!launch_phased(pl, p, grid, st, std::make_index_sequence<kNumPhasedShapes>{})) return (int)hipErrorInvalidConfiguration;
     } else if (pl.feature_tile == 128) {  // LDS: 6 x 24 KiB, 3 x 40 KiB

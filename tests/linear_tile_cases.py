@@ -23,4 +23,13 @@ SMALL = {
     (64, 4096, 4096): (128, 64, True, 8), (7, 1280, 4096): (128, 64, True, 16),
     (64, 32896, 64): (256, 64, True, 1), (9, 11136, 3008): (256, 64, True, 5),       # ragged last tile
     (5, 28672, 320): (128, 64, True, 1),                                             # workgroups start at all five stages
+    # nothing cut: each number of features with 1 to 8 token rows, 9 to 16, 17 to 24 and 25 to 32; fewer k stages than wavefronts, as many as
+    # their rings hold and a few more or less, many; a ragged last tile where the number of features allows one
+    (1, 4096, 64): (16, 32, True, 1), (8, 1536, 3008): (16, 32, True, 1), (9, 3968, 2624): (16, 32, True, 1), (16, 4096, 4032): (16, 32, True, 1),
+    (24, 2048, 8128): (16, 32, True, 1), (32, 4096, 1472): (16, 32, True, 1), (8, 6016, 704): (24, 32, True, 1), (15, 6016, 2112): (24, 32, True, 1),
+    (17, 4224, 1024): (24, 32, True, 1), (32, 6144, 6208): (24, 32, True, 1), (3, 8064, 1984): (32, 32, True, 1), (13, 8192, 576): (32, 32, True, 1),
+    (23, 8192, 1984): (32, 32, True, 1), (25, 6272, 1088): (32, 32, True, 1), (7, 12160, 3072): (48, 32, True, 1), (16, 8320, 3136): (48, 32, True, 1),
+    (8, 16256, 3136): (64, 32, True, 1), (10, 12416, 3200): (64, 32, True, 1), (1, 20352, 3072): (80, 32, True, 1), (16, 16640, 3200): (80, 32, True, 1),
+    (2, 24448, 3072): (96, 32, True, 1), (12, 20608, 3136): (96, 32, True, 1), (8, 28544, 3072): (112, 32, True, 1), (9, 24704, 3072): (112, 32, True, 1),
+    (5, 32640, 3072): (128, 32, True, 1), (14, 28800, 3136): (128, 32, True, 1),
 }
