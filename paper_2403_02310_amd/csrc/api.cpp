@@ -208,7 +208,7 @@ Schedule schedule_of(const sarathi_handle *h) {
     if (chunk_blocks == 0) {
         // A small decode-only batch whose blocks are all resident at once shares the memory system evenly among
         // them, so the longest decode runs at a 512th of the bandwidth for most of its life and then alone at what
-        // one block can pull (~36 GB/s): a tail of 15-20 us on 64 decodes.  With one block per compute unit the blocks
+        // one block can pull (~55 GB/s): a tail.  With one block per compute unit the blocks
         // start longest first as units fall free and each streams at twice the share; one block per unit already
         // reaches the chip's streaming rate (256 blocks x 25.5 GB/s).  Measured on 48 ... 128 decodes: -12 to -20 %;
         // from ~192 decodes on the launch is long enough for two per unit to win by 2-4 %.  Few decodes

@@ -431,7 +431,8 @@ double hybrid_launch_us(const sarathi_config &cfg, const std::vector<ChunkBin> &
 // the chosen piece is within 5 % of the best one at the median and 1.9 x (decodes only) and 1.17 x (hybrid) faster than
 // whole decodes on average; 8 decodes of 256-4096 keys: 53 -> 19 + 6 us.  A cut has to promise 5 %, and
 // below 28 us nothing is cut: two launches keep the host for about as long, and a merge would be a third.
-// (A block's rate is its compute unit's: eight wavefronts instead of four pull the same 40 GB/s, so only more blocks help.)
+// Fitted when a block pulled 40 GB/s alone; now that its loads go through LDS it pulls about 55, and the estimate fitted to that
+// chose no better (120 batches of few decodes 1.001 x, 110 hybrid ones 0.999 x).
 // Where one decode holds half of the keys or more, a plan that cuts it finer and leaves all of up to half its length whole
 // is tried first and taken if it promises the 5 %, as such batches always were (7000 and 3000 keys next to three short
 // ones then end with the 3000-key block, at 42 us).  Where it does not the general search follows: 14,000, 7000 and 6500
