@@ -8,8 +8,8 @@
 // these as 8-byte pieces that a wavefront's accumulator tiles complete to 128 contiguous bytes;
 // larger ones turn them into whole rows in LDS first.
 //
-// Three kernels.  linear_thin_kernel (up to 16 tokens, 32 on shorter k ranges): one workgroup per compute unit, nothing cut across
-// workgroups.  linear_phased_kernel (more than 64 tokens): four wavefronts, one per SIMD, each with up to 128 x 128
+// Four kernels.  linear_thin_kernel (up to 16 tokens, 32 on shorter k ranges) and linear_mid_kernel (65 to 96 tokens on some layers):
+// one workgroup per compute unit, nothing cut across workgroups.  linear_phased_kernel (more than 64 tokens otherwise): four wavefronts, one per SIMD, each with up to 128 x 128
 // results in accumulation registers; linear_kernel (up to 64 tokens): eight wavefronts, narrow token tiles, bound by
 // fetching the weights.  All bring k stages of 64 (an LDS row is one full 128-byte line of its matrix row; rows of half a
 // line fetch at less than half the rate: 43 against 95 GB/s per compute unit out of L2) from global memory straight into LDS
@@ -710,6 +710,120 @@ __global__ __launch_bounds__(64 * WAVES, 1) void linear_thin_kernel(LinearParams
     }
 }
 
+// ---------------------------------------------------------------------------------------
+// 65 to 96 tokens, where cutting k costs partial tiles and a second kernel: as in linear_thin_kernel a workgroup per compute unit
+// owns F features and the whole k range, but the token rows are too many for a ring per wavefront.  Four wavefronts share stages
+// of 128 k (F weight rows and XR token rows of two lines each); wavefront w works on k 32w .. 32w + 31 of every stage
+// with all results in registers (F / 16 x XR / 16 tiles), and the four sums meet in LDS at the end.
+// Bound by what a compute unit pulls: its weights from memory and all token rows out of L2, together at about 65 GB/s.  us a
+// call, cut along k and so: 77 x 20480 x 7168 59.9 and 53.6 (43.2 at 6.8 TB/s), 77 x 14848 x 3712 28.6 and 24.5 (16.2),
+// 77 x 7168 x 3584 18.5 and 17.4 (7.6), 77 x 8192 x 2048 13.6 and 11.2, 77 x 14336 x 8192 49.0 and 46.3, 96 x 12288 x 2048 17.2 and 15.1.
+// ---------------------------------------------------------------------------------------
+constexpr int kMidStageK = 128;
+template <int F, int XR>
+struct MidShape {
+    static constexpr int kStageBytes = (F + XR) * kMidStageK * 2;
+    static constexpr int kRing = std::min(6, 160 * 1024 / kStageBytes);
+};
+template <int F, int XR>
+__global__ __launch_bounds__(256, 1) void linear_mid_kernel(LinearParams p) {
+    constexpr int KS = kMidStageK, RING = MidShape<F, XR>::kRing, STAGE = (F + XR) * KS;
+    constexpr int NI = F / 16, NJ = XR / 16;
+    constexpr int LOADS = (F + XR) / 16;      // 1 KiB loads (four rows) of a wavefront per stage
+    static_assert(RING >= 2 && F % 16 == 0 && XR % 16 == 0 && (RING - 1) * LOADS < 64, "");
+    __shared__ __attribute__((aligned(16))) uint16_t smem[RING * STAGE];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n0 = blockIdx.x * F;
+    // load l of wavefront w moves rows 4 (4 l + w) ..; the sixteen pieces of a row are XOR-swizzled with the row's number modulo 16
+    int off[LOADS];
+#pragma unroll
+    for (int l = 0; l < LOADS; ++l) {
+        const int row = 4 * (4 * l + wave) + lane / 16, piece = (lane % 16) ^ (row & 15);
+        // F is a multiple of 16: a load is all weights or all tokens.  Rows past the matrix re-read its last row.
+        const int source = 16 * l < F ? min(n0 + row, p.N - 1) - n0 : min(row - F, p.T - 1);
+        off[l] = (source * p.K + piece * 8) * 2;
+    }
+    const uint16_t *const w_base = p.w + (int64_t)n0 * p.K;
+    const uint32_t smem_addr = (uint32_t)(uintptr_t)(lin_lds_ptr)(smem);
+    const int n_stages = p.K / KS;
+    const int first = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 3 % n_stages);
+    auto issue = [&](int stage, int slot) {
+        int at = first + stage;
+        if (at >= n_stages) at -= n_stages;
+        const uint32_t dst = smem_addr + (uint32_t)(slot * STAGE * 2 + wave * 1024);
+#pragma unroll
+        for (int l = 0; l < LOADS; ++l) {
+            if (16 * l < F) lin_dma_load_16_stream(w_base + at * KS, off[l], dst + (uint32_t)l * 4096);
+            else lin_dma_load_16(p.x + at * KS, off[l], dst + (uint32_t)l * 4096);
+        }
+    };
+    const int n = lane & 15, g = lane >> 4;
+    const int rd = n * KS + ((4 * wave + g) ^ n) * 8;  // row n of a block of sixteen, this wavefront's k
+    lf32x4 acc[NI][NJ];
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] = lf32x4{0.f, 0.f, 0.f, 0.f};
+    auto consume = [&](int slot) {
+        const uint16_t *sp = smem + slot * STAGE + rd;
+        lbf16x8 fa[NI], fb[NJ];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) fa[i] = __builtin_bit_cast(lbf16x8, *reinterpret_cast<const lu32x4 *>(sp + i * 16 * KS));
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) fb[j] = __builtin_bit_cast(lbf16x8, *reinterpret_cast<const lu32x4 *>(sp + (F + j * 16) * KS));
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int i = 0; i < NI; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+    };
+#pragma unroll
+    for (int st = 0; st < RING - 1; ++st)
+        if (st < n_stages) issue(st, st);
+    int slot = 0, st = 0;
+    for (; st + RING - 1 < n_stages; ++st) {
+        // stage st has landed, and behind the barrier everyone's part of it, and everyone has stage st-1 in registers
+        LIN_WAIT_VMCNT_AND_LDS((RING - 2) * LOADS);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        issue(st + RING - 1, slot == 0 ? RING - 1 : slot - 1);
+        consume(slot);
+        slot = slot + 1 == RING ? 0 : slot + 1;
+    }
+    for (; st < n_stages; ++st) {
+        LIN_WAIT_VMCNT_AND_LDS(0);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        consume(slot);
+        slot = slot + 1 == RING ? 0 : slot + 1;
+    }
+    // the four sums, as many token tiles at a time as LDS holds: lane (g, n) of tile (i, j) has token 16j + n, features 16i + 4g ..
+    constexpr int STRIDE = F + 4, PER_WAVE = 16 * STRIDE;  // floats of a token tile
+    constexpr int TILES = std::min(NJ, RING * STAGE * 2 / (4 * PER_WAVE * 4));
+    static_assert(TILES >= 1, "LDS holds a token tile of every wavefront");
+    float *const sums = reinterpret_cast<float *>(smem);
+#pragma unroll
+    for (int j0 = 0; j0 < NJ; j0 += TILES) {
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < TILES; ++j)
+            if (j0 + j < NJ)
+#pragma unroll
+                for (int i = 0; i < NI; ++i)
+                    *reinterpret_cast<lf32x4 *>(sums + (wave * TILES + j) * PER_WAVE + n * STRIDE + i * 16 + 4 * g) = acc[i][j0 + j < NJ ? j0 + j : 0];
+        __syncthreads();
+        const int tokens = min(TILES * 16, p.T - j0 * 16);
+        for (int e = (int)threadIdx.x; e < tokens * (F / 4); e += 256) {
+            const int t = e / (F / 4), f = e % (F / 4) * 4;
+            if (n0 + f >= p.N) continue;
+            lf32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < 4; ++w) sum += *reinterpret_cast<const lf32x4 *>(sums + (w * TILES + t / 16) * PER_WAVE + t % 16 * STRIDE + f);
+            *reinterpret_cast<lu32x2 *>(p.y + (int64_t)(j0 * 16 + t) * p.N + n0 + f) = __builtin_bit_cast(lu32x2, __builtin_convertvector(sum, lbf16x4));
+        }
+    }
+}
+
 // Adds the split-K pieces of every output element in piece order and rounds once to bf16.
 __global__ __launch_bounds__(256) void linear_reduce_kernel(const float *part, uint16_t *y, int64_t elems, int splits) {
     const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
@@ -838,7 +952,20 @@ static int32_t thin_features(int32_t T, int32_t N, int32_t K) {
     return 0;
 }
 
+// Features of a workgroup of linear_mid_kernel, or 0: not for this layer.  The token rows that every workgroup pulls grow with k and
+// are paid for by its features, and the features have to fill the compute units (us cut along k and so: 77 x 6144 x 4096, 192
+// workgroups, 18.0 and 18.7; 77 x 8192 x 7168 27.7 and 31.9; 77 x 7168 x 10240 37.1 and 46.5; 77 x 14848 x 14848 81.6 and 85.7).
+// Beyond 80 tokens the line lies lower (85 x 14336 x 8192 49.3 and 52.1, 85 x 7168 x 3584 19.1 and 18.7), and beyond 96 next to
+// nothing is left (128 x 6144 x 4096 20.1 and 24.0); 112 features leave two or three stages in LDS (77 x 28672 x 4096 42.8 and 43.4).
+static int32_t mid_features(int32_t T, int32_t N, int32_t K) {
+    if (T <= kLinSmallTokens || T > 96 || K % kMidStageK != 0) return 0;
+    for (const int f : {32, 48, 64, 80})
+        if (N <= f * 256) return N >= f * 208 && K + 1024 <= (T <= 80 ? 144 : 96) * f ? f : 0;
+    return 0;
+}
+
 LinearPlan plan_linear(int32_t T, int32_t N, int32_t K, size_t workspace_bytes) {
+    if (const int32_t f = mid_features(T, N, K)) return LinearPlan{f, T <= 80 ? 80 : 96, (N + f - 1) / f, 1, 1, K};
     if (const int32_t f = thin_features(T, N, K)) return LinearPlan{f, kThinTokens, (N + f - 1) / f, 1, 1, K};
     return T > kLinSmallTokens ? plan_phased(T, N, K, workspace_bytes) : plan_small(T, N, K, workspace_bytes);
 }
@@ -904,6 +1031,23 @@ int launch_linear(const LinearPlan &pl, const void *x, const void *w, void *y, i
         else if (pl.feature_tile == 128) launch(std::integral_constant<int, 128>{});
         else return (int)hipErrorInvalidConfiguration;
         return (int)hipGetLastError();
+    }
+    if (pl.token_tile == 80 || pl.token_tile == 96) {
+        bool known = false;
+        auto with = [&](auto f, auto xr) {
+            if (pl.feature_tile != decltype(f)::value || pl.token_tile != decltype(xr)::value || T > decltype(xr)::value) return;
+            hipLaunchKernelGGL((linear_mid_kernel<decltype(f)::value, decltype(xr)::value>), dim3((unsigned)pl.n_tiles), dim3(256), 0, st, p);
+            known = true;
+        };
+        auto rows = [&](auto f) {
+            with(f, std::integral_constant<int, 80>{});
+            with(f, std::integral_constant<int, 96>{});
+        };
+        rows(std::integral_constant<int, 32>{});
+        rows(std::integral_constant<int, 48>{});
+        rows(std::integral_constant<int, 64>{});
+        rows(std::integral_constant<int, 80>{});
+        return known ? (int)hipGetLastError() : (int)hipErrorInvalidConfiguration;
     }
     if (T > kLinSmallTokens) {
         if (!launch_phased(pl, p, grid, st, std::make_index_sequence<kNumPhasedShapes>{})) return (int)hipErrorInvalidConfiguration;

@@ -15,6 +15,11 @@ LARGE = {
     (1025, 8320, 704): (256, 192, False, 1), (577, 4992, 6080): (256, 192, False, 3), (129, 12416, 5056): (256, 192, True, 5),
     (1025, 12416, 704): (256, 256, False, 1), (450, 8320, 8128): (256, 256, False, 3), (193, 16640, 6144): (256, 256, True, 3),
     (193, 12416, 11776): (256, 256, True, 5), (129, 7168, 3008): (256, 64, False, 3),
+    # nothing cut, a workgroup per compute unit: each number of features with up to 80 and up to 96 token rows, one stage of k, as many as
+    # their rings hold, odd and even numbers of them; ragged last feature tiles
+    (65, 7168, 3584): (32, 80, True, 1), (80, 8064, 128): (32, 80, True, 1), (77, 12160, 640): (48, 80, True, 1), (66, 16256, 1664): (64, 80, True, 1),
+    (72, 20352, 8064): (80, 80, True, 1), (81, 8192, 2048): (32, 96, True, 1), (96, 11136, 3456): (48, 96, True, 1), (90, 14848, 3712): (64, 96, True, 1),
+    (85, 20352, 6528): (80, 96, True, 1), (79, 17024, 256): (80, 80, True, 1),
 }
 
 # up to 64 tokens
