@@ -37,7 +37,7 @@
 // XOR-swizzled in LDS and the two 16-byte halves of a V^T row are swapped on every other group
 // of eight channels, which makes both the staging writes and the operand reads bank-conflict free.
 //
-// Both paths share one launch: a block is either one chunk tile or one wave tile, so the
+// Both paths share one launch: a block runs chunk tiles or wave tiles, one of them or, in long launches, many from a queue, so the
 // memory-bound decodes fill the machine next to the MFMA-bound chunk tiles (the paper's reason
 // for hybrid batches, section 4.1).
 //
