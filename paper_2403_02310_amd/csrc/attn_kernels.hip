@@ -138,15 +138,12 @@ constexpr int kOneEach = 0, kQueued = 1, kRoles = 2;  // how a launch of both ki
 struct Queue {
     int32_t *counters;
     int n_items, taken, list;
-    __device__ __forceinline__ int number(int x, int count) const {
-        return ((taken - x + kSchedLists - 1) / kSchedLists + count) * kSchedLists + x;
-    }
     __device__ __forceinline__ int bump() const {
         return __hip_atomic_fetch_add(counters + list * kSchedStride, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     // the item at count `got` of the list, or kNoItem
     __device__ __forceinline__ int item(int got) const {
-        const int i = number(list, got);
+        const int i = queue_item(taken, list, got);
         return i < n_items ? i : kNoItem;
     }
     // Moves to the list that has most left; false if all are empty.  All counters are read at once: going round by
@@ -158,7 +155,7 @@ struct Queue {
             counts[x] = __hip_atomic_load(counters + x * kSchedStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
         for (int x = 0; x < kSchedLists; ++x) {
-            const int left = n_items - number(x, counts[x]);
+            const int left = n_items - queue_item(taken, x, counts[x]);
             if (left > most) most = left, list = x;
         }
         return most > 0;

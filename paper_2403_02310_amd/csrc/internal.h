@@ -26,6 +26,11 @@ constexpr int kSchedStride = 16;
 constexpr int kSchedWords = 2 * kSchedLists * kSchedStride;
 constexpr size_t kSchedBytes = sizeof(int32_t) * kSchedWords;
 constexpr int kQueueBlocks = 512;           // two per compute unit
+// Number of the item at `count` of list x of a queue whose first `taken` items are dealt out without it: the list holds, in order,
+// those of the others that are x modulo kSchedLists.
+constexpr int queue_item(int taken, int x, int count) {
+    return ((taken - x + kSchedLists - 1) / kSchedLists + count) * kSchedLists + x;
+}
 // Run-time roles: beyond this many chunk blocks (a quarter more than one per compute unit) next to decodes that stream longer
 constexpr int kChunkBlocksForRoles = 320;
 constexpr double kMinStreamUsForRoles = 80.0;

@@ -65,6 +65,8 @@ static int g_num_seqs = 0;          // shape of the call in flight, for the walk
 static int64_t g_num_tokens = 0;
 static uint64_t g_sink = 0;
 static int32_t g_lds_pad_bytes = 0; // of the last attention launch
+static int32_t g_queue_blocks = 0;
+static int g_queued_launches = 0;
 
 int launch_kv_append(const sarathi_config &cfg, const AppendMeta &m, const void *k_new, const void *v_new, void *k_cache,
                      void *v_cache, int64_t num_pages, void *) {
@@ -72,6 +74,8 @@ int launch_kv_append(const sarathi_config &cfg, const AppendMeta &m, const void 
     const uint16_t *kn = static_cast<const uint16_t *>(k_new), *vn = static_cast<const uint16_t *>(v_new);
     uint16_t *kc = static_cast<uint16_t *>(k_cache), *vc = static_cast<uint16_t *>(v_cache);
     if (m.copy_bytes) std::memcpy(m.copy_dst, m.copy_src, (m.copy_bytes + 15) / 16 * 16);
+    CHECK(m.zero_bytes % 16 == 0 && reinterpret_cast<uintptr_t>(m.zero_dst) % 16 == 0);
+    if (m.zero_bytes) std::memset(m.zero_dst, 0, m.zero_bytes);
     for (int u = 0; u < m.num_units; ++u) {
         const AppendUnit &r = m.units[u];
         const int lo = r.lo_hi & 0xFF, hi = r.lo_hi >> 8;
@@ -116,6 +120,70 @@ int static_scratch(StaticScratch *out) {
     return 0;
 }
 
+// The blocks of a queued launch, advanced one item at a time in an order drawn at random: each takes its first item by its index and
+// the others as the kernels do (own list first, then the one with most left, and with roles the other kind).  Every item has
+// to be run exactly once.
+static std::mt19937_64 g_order(7);
+static void play_queues(const AttnMeta &m, int H, int which) {
+    for (int w = 0; w < kSchedWords; ++w) CHECK(m.sched[w] == 0);
+    const bool one_launch = which == 4 || which == 5, roles = which == 5;
+    const int n_wave = (m.num_units - m.num_tile_units) * H, n_chunk = one_launch ? m.num_tile_units * H : 0;
+    const int blocks = std::min(n_wave + n_chunk, m.queue_blocks);
+    const int chunk_blocks = roles ? blocks / 2 : n_chunk;
+    CHECK(chunk_blocks <= blocks);
+    struct Queue {
+        int32_t *counters;
+        int n, taken;
+        int bump(int list) { return counters[list * kSchedStride]++; }
+        int item(int list, int got) { const int i = queue_item(taken, list, got); return i < n ? i : -1; }
+        bool move_on(int &list) {
+            int most = 0;
+            for (int x = 0; x < kSchedLists; ++x) {
+                const int left = n - queue_item(taken, x, counters[x * kSchedStride]);
+                if (left > most) most = left, list = x;
+            }
+            return most > 0;
+        }
+    } waves{m.sched, n_wave, std::min(n_wave, blocks - chunk_blocks)}, chunks{m.sched + kSchedLists * kSchedStride, n_chunk, std::min(n_chunk, chunk_blocks)};
+    std::vector<int> runs((size_t)(n_wave + n_chunk), 0);
+    struct Block { int index, wave_list, chunk_list, item; };   // item -2: none yet
+    std::vector<Block> busy;
+    for (int b = 0; b < blocks; ++b) {
+        int item = -2;
+        if (b < chunk_blocks && b < n_chunk) item = n_wave + b;
+        else if (b >= chunk_blocks && b - chunk_blocks < n_wave) item = b - chunk_blocks;
+        busy.push_back(Block{b, b % kSchedLists, b % kSchedLists, item});
+    }
+    while (!busy.empty()) {
+        const size_t at = (size_t)(g_order() % busy.size());
+        Block &b = busy[at];
+        if (b.item >= 0) CHECK(++runs[(size_t)b.item] == 1);
+        const bool after_wave = b.item == -2 ? b.index >= chunk_blocks : b.item < n_wave;
+        int next = -1;
+        if (!roles || after_wave) {
+            if (b.item != -2) next = waves.item(b.wave_list, waves.bump(b.wave_list));
+        } else {
+            next = chunks.item(b.chunk_list, chunks.bump(b.chunk_list));
+            if (next >= 0) next += n_wave;
+        }
+        while (next < 0) {
+            const bool more_waves = waves.move_on(b.wave_list), more_chunks = roles && chunks.move_on(b.chunk_list);
+            if (!more_waves && !more_chunks) break;
+            if (more_waves && (after_wave || !more_chunks)) {
+                next = waves.item(b.wave_list, waves.bump(b.wave_list));
+            } else {
+                next = chunks.item(b.chunk_list, chunks.bump(b.chunk_list));
+                if (next >= 0) next += n_wave;
+            }
+        }
+        if (next >= 0) b.item = next;
+        else { busy[at] = busy.back(); busy.pop_back(); }
+    }
+    for (int n : runs) CHECK(n == 1);
+    for (int w = 0; w < kSchedWords; ++w) m.sched[w] ^= 0x5A5A5A5A;   // nobody may count on what a launch leaves
+    g_queued_launches++;
+}
+
 // Every (column, key) pair of the batch must be covered by exactly one work unit, every unit must stay inside
 // its sequence, and every partial row / counter a unit or merge item names must lie inside its buffer (touched
 // here so that ASan sees an overrun).
@@ -123,6 +191,10 @@ int launch_attention(const sarathi_config &cfg, const AttnMeta &m, const void *,
                      float, void *, int which, void *) {
     const int H = cfg.num_kv_heads, D = cfg.head_dim;
     g_lds_pad_bytes = m.lds_pad_bytes;
+    g_queue_blocks = m.queue_blocks;
+    CHECK(which != 5 || m.queue_blocks > 0);
+    CHECK(which != 4 || m.queue_blocks == 0 || m.queue_blocks >= m.num_tile_units * H);   // every chunk tile has a block of its own
+    if (m.queue_blocks > 0 && which != 1) play_queues(m, H, which);
     for (int u = 0; u < m.num_units; ++u) {
         const uint32_t unit = m.units[u];
         const TileDesc &t = m.tiles[unit & ((1u << kUnitTileBits) - 1)];
@@ -149,7 +221,6 @@ int launch_attention(const sarathi_config &cfg, const AttnMeta &m, const void *,
         const TileDesc &t = m.tiles[ru & ((1u << kUnitTileBits) - 1)];
         CHECK(t.n_splits > 1 && (int)(ru >> kUnitTileBits) * kReduceCols < t.n_cols);
     }
-    if (which == 5) g_sink += (uint64_t)m.sched[kSchedWords - 1];
     return 0;
 }
 int launch_reduce(const sarathi_config &, const AttnMeta &m, void *, int32_t first, int32_t count, void *) {
@@ -383,6 +454,86 @@ static void drive_host_bound_cuts() {
     }
 }
 
+// Launches that hand their items out from queues, forced and by the rule, in every way such a batch is launched: the words are zero
+// when one starts (cleared by the append, by the attention call itself when it comes a second time, by the allocation-free
+// call), the options that change between an append and its attention call included.
+static void drive_queues() {
+    struct Batch {
+        int32_t hq, hkv, d, decodes, low, high;
+        std::vector<int32_t> chunks;
+        int32_t prefix;
+        bool by_rule;
+    };
+    const Batch batches[] = {{4, 1, 64, 700, 1, 300, {}, 0, false},  {4, 2, 64, 20, 40, 900, {40, 90}, 300, false}, {4, 1, 64, 9, 30, 700, {400, 333}, 500, false},
+                             {8, 2, 64, 400, 1, 200, {70, 130}, 40, false}, {8, 2, 64, 30, 100, 900, {4800}, 0, false}, {8, 8, 128, 400, 2048, 2048, {}, 0, true}};
+    const int64_t forms[][4] = {{-1, -1, 2, 0}, {1, 0, 2, 0}, {1, -1, 2, 64}, {-1, 1, 2, 64}, {1, 1, 2, 32}, {1, -1, 0, 64}, {1, 1, 1, 64}, {0, 0, 2, 64}};
+    int by_rule = 0;
+    for (const Batch &b : batches)
+        for (const auto &f : forms)
+            for (const int one_per_unit : {0, 1}) {
+                std::vector<int32_t> qs, ql, cl;
+                int32_t T = 0, max_blocks = 1;
+                auto add = [&](int32_t q, int32_t ctx) {
+                    qs.push_back(T); ql.push_back(q); cl.push_back(ctx);
+                    T += q;
+                    max_blocks = std::max(max_blocks, (ctx + 15) / 16);
+                };
+                for (int32_t q : b.chunks) add(q, q + b.prefix);
+                for (int32_t i = 0; i < b.decodes; ++i) add(1, b.low + (b.high > b.low ? i * 37 % (b.high - b.low) : 0));
+                const int32_t S = (int32_t)ql.size();
+                const sarathi_config cfg{b.hq, b.hkv, b.d, 16, 0, T, S, max_blocks};
+                sarathi_handle *h = nullptr;
+                CHECK(sarathi_create(&cfg, &h) == SARATHI_OK);
+                const char *names[] = {"item_queue", "resident_chunks", "interleave"};
+                for (int o = 0; o < 3; ++o) CHECK(sarathi_set_option(h, names[o], f[o]) == SARATHI_OK);
+                CHECK(sarathi_set_option(h, "split_keys", f[3]) == SARATHI_OK && sarathi_set_option(h, "tile_split_keys", f[3]) == SARATHI_OK);
+                if (one_per_unit) CHECK(sarathi_set_option(h, "lds_pad_kb", 96) == SARATHI_OK);
+                std::vector<int32_t> bt((size_t)S * max_blocks, 0);
+                const size_t row = (size_t)b.hkv * b.d;
+                std::vector<uint16_t> fresh((size_t)T * row), pool(row * 16);   // every sequence's pages are one page: nothing is computed here
+                char dummy[16];
+                void *ws = nullptr;
+                CHECK(posix_memalign(&ws, 256, sarathi_workspace_bytes(h)) == 0);
+                std::memset(ws, 0xFF, sarathi_workspace_bytes(h));
+                sarathi::g_num_seqs = S;
+                sarathi::g_num_tokens = T;
+                sarathi::g_queued_launches = 0;
+                auto append = [&] {
+                    CHECK(sarathi_kv_append(h, fresh.data(), fresh.data(), pool.data(), pool.data(), bt.data(), qs.data(), ql.data(), cl.data(), S, T, 1, ws,
+                                            nullptr) == SARATHI_OK);
+                };
+                auto attend = [&] {
+                    CHECK(sarathi_hybrid_attention(h, dummy, dummy, dummy, bt.data(), qs.data(), ql.data(), cl.data(), S, T, 1, 0.1f, dummy, ws, nullptr) == SARATHI_OK);
+                };
+                append();
+                attend();
+                attend();
+                if (b.by_rule && f[0] < 0 && sarathi::g_queued_launches > 0) by_rule++;
+                const bool few_chunk_blocks = b.chunks.empty() || b.chunks[0] < 1000;
+                if (f[0] == 1 && few_chunk_blocks) CHECK(sarathi::g_queued_launches == 2);
+                append();
+                append();
+                attend();
+                if (f[0] == 0) {   // queues that the append did not know of
+                    append();
+                    CHECK(sarathi_set_option(h, "item_queue", 1) == SARATHI_OK);
+                    const int before = sarathi::g_queued_launches;
+                    attend();
+                    CHECK(sarathi::g_queued_launches == before + (few_chunk_blocks || !one_per_unit ? 1 : 0));
+                    CHECK(!one_per_unit || !few_chunk_blocks || sarathi::g_queue_blocks == sarathi::kQueueBlocks / 2);
+                }
+                for (int rep = 0; rep < 2; ++rep) {
+                    const sarathi_status st = sarathi_hybrid_attention_noalloc(h, dummy, dummy, dummy, bt.data(), qs.data(), ql.data(), cl.data(), S, T, 1, 0.1f,
+                                                                               dummy, nullptr);
+                    CHECK(st == SARATHI_OK);
+                    attend();
+                }
+                CHECK(sarathi_destroy(h) == SARATHI_OK);
+                std::free(ws);
+            }
+    CHECK(by_rule > 0);
+}
+
 static void drive_checker() {
     // one chunk on a prefix and two decodes, GQA 4:2, d = 8; every buffer exactly as large as documented
     const int Hq = 4, Hkv = 2, d = 8;
@@ -426,6 +577,7 @@ int main() {
     drive_scarce_partial_rows();
     drive_decode_blocks_per_unit();
     drive_host_bound_cuts();
+    drive_queues();
     drive_checker();
     std::printf("host paths clean (sink %llu)\n", (unsigned long long)sarathi::g_sink);
     return 0;

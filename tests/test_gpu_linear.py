@@ -122,8 +122,8 @@ def test_model_shapes_sampled(hx):
         run(hx, T, N, K, seed=21, rows=rows, cols=cols)
 
 
-@pytest.mark.parametrize("T,N,K", list(linear_tile_cases.LARGE))
-def test_tiles_of_large_batches(hx, T, N, K):
+def run_guarded(hx, T, N, K):
+    """Sampled elements against the checker, every element against a float32 product, and rows behind y that must stay as they are."""
     binding, harness = hx
     print("linear case T", T, "N", N, "K", K, flush=True)
     rng = np.random.default_rng([T, N, K])
@@ -136,7 +136,7 @@ def test_tiles_of_large_batches(hx, T, N, K):
     torch.cuda.synchronize()
     assert torch.isnan(room[T:]).all() and torch.isfinite(room[:T]).all()
     got = harness.bf16_tensor_to_f64(room[:T])
-    rows = sorted(set([0, T - 1, 63, 64] + rng.integers(0, T, 12).tolist()))
+    rows = sorted(set([0, T - 1, 63 % T, 64 % T] + rng.integers(0, T, 12).tolist()))
     cols = sorted(set([0, N - 1, N - 128, 127] + rng.integers(0, N, 40).tolist()))
     w_bits = harness.device_to_bits(w[torch.as_tensor(cols, device="cuda")])
     ref = oracle.linear(x_bits, w_bits, rows=rows, cols=list(range(len(cols))))
@@ -148,6 +148,16 @@ def test_tiles_of_large_batches(hx, T, N, K):
     assert ((y - whole).abs() <= 2.0 ** -7 * whole.abs() + mag).all()
 
 
+@pytest.mark.parametrize("T,N,K", list(linear_tile_cases.LARGE))
+def test_tiles_of_large_batches(hx, T, N, K):
+    run_guarded(hx, T, N, K)
+
+
+@pytest.mark.parametrize("T,N,K", list(linear_tile_cases.SMALL))
+def test_every_element_of_small_batches(hx, T, N, K):
+    run_guarded(hx, T, N, K)
+
+
 @pytest.mark.parametrize("T,N,K", list(linear_tile_cases.SMALL))
 def test_tiles_of_small_batches(hx, T, N, K):
     rows = sorted(set([0, T - 1, T // 2])); cols = sorted(set([0, N - 1, N - 128, 127] + np.random.default_rng(N).integers(0, N, 30).tolist()))
@@ -155,7 +165,8 @@ def test_tiles_of_small_batches(hx, T, N, K):
     assert np.isfinite(got).all()
 
 
-@pytest.mark.parametrize("T,N,K", [(8, 1280, 704), (77, 384, 704), (300, 1152, 2496), (1025, 3968, 704)])
+@pytest.mark.parametrize("T,N,K", [(8, 1280, 704), (77, 384, 704), (300, 1152, 2496), (1025, 3968, 704),
+                                   (9, 3968, 2624), (77, 12160, 640)])   # ... and nothing cut, a workgroup per compute unit
 def test_output_views_that_begin_at_eight_bytes(hx, T, N, K):
     """y may be a view that begins eight bytes into its allocation: same bits as into an aligned one, nothing beside it touched."""
     binding, _ = hx
