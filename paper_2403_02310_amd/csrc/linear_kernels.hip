@@ -613,8 +613,14 @@ __global__ __launch_bounds__(64 * WAVES, 1) void linear_thin_kernel(LinearParams
     uint16_t *const ring = smem + wave * RING * STAGE;
     const uint32_t ring_addr = (uint32_t)(uintptr_t)(lin_lds_ptr)(ring);
     const int n_stages = p.K / KS;
-    // workgroups start at different places of the k range: lin_first_stage says why
-    const int first = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 3 % n_stages);
+    // Workgroups start at different places of the k range: lin_first_stage says why.  The places are kStagger stages apart, and the
+    // features of a workgroup must not be a multiple of that: with 3 and 96 features of 4096 k, workgroup b's rows lie b x 3 x 2^18
+    // bytes in and its first stage b x 3 x 2^7, so that the bits that pick the memory channel cancel (us a call with 3 and 5:
+    // 8 x 24576 x 4096 42.3 and 31.2, 8 x 10240 x 8192 28.6 and 26.0; 5 everywhere moves that to 80 features: 8 x 20480 x 8192
+    // 51.8 and 59.4).
+    constexpr int kStagger = F % 3 == 0 ? 5 : 3;
+    static_assert(F % kStagger != 0, "the start places would fall on few memory channels");
+    const int first = __builtin_amdgcn_readfirstlane((int)blockIdx.x * kStagger % n_stages);
     const int mine = (n_stages - wave + WAVES - 1) / WAVES;  // stages wave, wave + 8, ... counted from `first`
     auto issue = [&](int i, int slot) {
         int at = first + wave + i * WAVES;
