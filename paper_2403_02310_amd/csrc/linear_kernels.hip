@@ -947,14 +947,26 @@ static LinearPlan plan_small(int32_t T, int32_t N, int32_t K, size_t workspace_b
 
 // Features of a workgroup of linear_thin_kernel: as few as give a workgroup per compute unit at most; 0: not for this layer.
 // Beyond 16 tokens the token rows that every workgroup pulls grow with T x K (us cut along k and thin: 24 x 4096 x 4096 12.2 and
-// 8.6, 20 x 2560 x 8192 14.2 and 12.7, 24 x 4608 x 7168 17.2 and 16.3, 32 x 4608 x 7168 17.7 and 17.9, 24 x 4096 x 14336 24.8 and
-// 25.5, 32 x 4096 x 14336 25.5 and 28.7).  Many features on a short k range leave a wavefront a handful of stages and gain
-// nothing (8 x 9216 x 1024 9.07 and 8.99; 9 x 11136 x 3072 17.3 and 12.2, not looked at between); few features leave too many
-// compute units idle (16 x 1024 x 8192 11.0 and 10.2, 32 x 1024 x 8192 11.6 and 13.7; 16 x 1536 x 4096 10.1 and 6.4).
+// 8.6, 20 x 2560 x 8192 14.2 and 12.7, 24 x 4608 x 7168 17.8 and 16.2, 32 x 4608 x 7168 17.7 and 17.9, 24 x 4096 x 14336 24.8 and
+// 25.5, 32 x 4096 x 14336 25.5 and 28.7).  Few features leave too many compute units idle (16 x 1024 x 8192 11.0 and 10.2,
+// 32 x 1024 x 8192 11.6 and 13.7; 16 x 1536 x 4096 10.1 and 6.4).
+// Where features are few next to the compute units and k is long, a workgroup's own K (F + 0.8 T) elements are what the layer
+// waits for (beyond 16 tokens as many token rows as it loads, 24 or 32): at the same 50 GB/s a layer cut along k streams N / 190 as
+// many at once and pays 7.6 us for its second kernel (16 x 1536 x 49152 29.8 and 59.7, 8 x 1664 x 49152 30.6 and 48.2,
+// 12 x 1664 x 17152 15.8 and 20.6, 16 x 4224 x 49152 71.2 and 86.2, 17 x 1536 x 10240 13.1 and 15.7; on the other side of the line
+// 16 x 1536 x 8192 11.9 and 10.7, 16 x 4096 x 16384 25.6 and 22.5, 8 x 8192 x 28672 73.2 and 68.7, 17 x 7168 x 10240 28.2 and 27.0).
+// Of 3,170 layers of 1536 to 32,768 features and k up to 65,536 45 are 3 to 10 % slower so than cut, and 20 that are cut would be
+// 3 to 11 % faster thin; without the line 383 were slower, by up to a factor of two.
+// Beyond 8192 features the line at 3072 k is where this kernel was first looked at, not where it stops to gain (8 x 9216 x 2048 11.7
+// cut along k and 7.9 thin, 8 x 12288 x 1024 9.3 and 6.0, 16 x 24576 x 2048 18.7 and 17.0, 8 x 8320 x 192 5.4 and 5.3).
 static int32_t thin_features(int32_t T, int32_t N, int32_t K) {
     if (T > kThinTokens || N < 1536 || (T > 16 && (int64_t)T * K > 200000)) return 0;
-    for (const int f : {16, 24, 32, 48, 64, 80, 96, 112, 128})
-        if (N <= f * 256) return f <= 32 || (T <= 16 && K >= 3072) ? f : 0;
+    for (const int f : {16, 24, 32, 48, 64, 80, 96, 112, 128}) {
+        if (N > f * 256) continue;
+        const int32_t rows = T > 16 ? (T + 7) / 8 * 8 : std::max(T, 4);
+        if ((double)K * (190.0 * (f + 0.8 * rows) - N) >= (T > 16 ? 3.8e7 : 3.6e7)) return 0;
+        return f <= 32 || (T <= 16 && K >= 3072) ? f : 0;
+    }
     return 0;
 }
 

@@ -333,6 +333,14 @@ def test_linear_tile_cases_cover_every_kernel_the_planner_chooses():
                 assert (p.feature_tile, p.token_tile, p.token_tiles == 1, p.pieces > 1) in (covered if T > 64 else small), (T, N, K)
 
 
+@pytest.mark.parametrize("T,N,K,thin", [(16, 1536, 49152, False), (8, 1664, 49152, False), (12, 1664, 17152, False), (16, 4224, 49152, False),
+                                        (14, 3456, 32768, False), (17, 1536, 10240, False), (16, 1536, 4096, True), (16, 3968, 14848, True), (8, 4096, 14336, True),
+                                        (16, 12288, 16384, True), (8, 8192, 28672, True), (32, 8192, 2048, True), (24, 2048, 8128, True)])
+def test_a_few_tokens_are_cut_along_k_where_workgroups_would_wait_for_long_ranges(T, N, K, thin):
+    p = binding.plan_linear(T, N, K)
+    assert ((p.token_tile, p.pieces) == (32, 1)) == thin and (thin or p.pieces > 1), (p.token_tile, p.pieces)
+
+
 def test_plan_linear_refuses_what_linear_refuses():
     out = binding.LinearPlan()
     assert binding.lib.sarathi_plan_linear(0, 128, 64, 0, ctypes.byref(out)) == binding.EINVAL
