@@ -82,8 +82,6 @@ struct Plan {
     int32_t num_part_rows = 0;
     int32_t split_keys = 0;
     int32_t tile_split_keys = 0;
-    int64_t tile_unit_steps = 0;      // 32-key steps summed over the chunk-tile units
-    int32_t longest_tile_unit_steps = 0;  // 32-key steps of the longest chunk-tile unit
     int64_t wave_keys = 0;            // keys summed over the wave tiles
     int64_t shared_wave_keys = 0;     // those of sequences with several wave tiles, which read the same keys
     bool even_decode_pieces = false;  // few decodes, cut into pieces of nearly one length

@@ -697,14 +697,6 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
     emit_units(plan, 0, n_chunk_tiles, tile_split, 0, scratch, bucket);
     plan.num_tile_units = (int32_t)plan.units.size();
     plan.num_tile_reduce_units = (int32_t)plan.reduce_units.size();
-    plan.tile_unit_steps = 0;
-    for (size_t ti = 0; ti < n_chunk_tiles; ++ti)
-        plan.tile_unit_steps += ceil_div(plan.tiles[ti].n_keys - plan.tiles[ti].key_lo, kTileKeys) + plan.tiles[ti].n_splits - 1;
-    plan.longest_tile_unit_steps = 0;  // units are sorted longest first
-    if (plan.num_tile_units > 0) {
-        const uint32_t u = plan.units[0];
-        plan.longest_tile_unit_steps = steps_of_split(plan.tiles[u & ((1u << kUnitTileBits) - 1)], (int32_t)(u >> kUnitTileBits));
-    }
     plan.wave_keys = keys_of_kind[kKindWave];
     const size_t wave_base = plan.units.size();
     const int32_t split_chunk_tiles = plan.num_split_tiles;
