@@ -220,15 +220,12 @@ Schedule schedule_of(const sarathi_handle *h) {
         if (one && s.lds_pad == 0) s.lds_pad = kOneBlockPerUnitLdsPad;
     }
     const bool one_launch = chunk_blocks > 0 && wave_blocks > 0 && h->opt.interleave != 0;
-    // The time the decodes need to stream their keys and values.
-    const double wave_us = (double)pl.wave_keys * h->cfg.num_kv_heads * h->cfg.head_dim * 4.0 / 6.5e6;
-    // Roles pay where chunk blocks would otherwise pile up two to a compute unit for a part of the launch, and the launch is long
-    // enough for what blocks then wait for counters (3 to 8 us).  us, static and with roles: 512 chunk blocks next to 1024 decodes
-    // 1645 and 1626, 608 next to 300 decodes (420 us) 539 and 504, 504 next to 300 decodes 592 and 524, 840 next to 128
-    // decodes (700 us) 1074 and 910; but 264 blocks next to 150 decodes (150 us) 196 and 205, 272 blocks next to 13 decodes (20 us)
-    // 57 and 71, 256 next to 300 short ones (19 us) 196 and 228.
+    // The time the decodes need to stream their keys and values, and the longest block alone.
+    const double key_us = h->cfg.head_dim * 4.0;
+    const double wave_us = (double)pl.wave_keys * h->cfg.num_kv_heads * key_us / 6.5e6, longest_us = (double)pl.longest_wave_keys * key_us / 68.0e3;
+    const bool shared = 2 * pl.shared_wave_keys > pl.wave_keys;
     if (one_launch)
-        s.roles = h->opt.resident_chunks == 1 || (h->opt.resident_chunks < 0 && chunk_blocks > kChunkBlocksForRoles && wave_us > kMinStreamUsForRoles);
+        s.roles = h->opt.resident_chunks == 1 || (h->opt.resident_chunks < 0 && roles_pay(chunk_blocks, wave_blocks, wave_us, longest_us, shared));
     // A queue evens out the XCDs (3.5 % of a long launch) and costs an item's block 1.5 us, of two on a compute unit.  us, a
     // block per item and queued: 1024 decodes, 8192 items, 1546 and 1518; 512 decodes, 4096 items, 759 and 748; 100 long
     // ones 1240 and 1218; but 256 decodes, 2048 items, 216.5 and 219.5; 1024 short ones, 8192 items, 157 and 162.

@@ -377,6 +377,7 @@ struct HybridBatch {
     double wave_us;       // all decode keys at 6.5 TB/s
     double wave_block_us; // the longest decode block's
     int64_t wave_blocks;
+    bool shared;          // most keys are read by several wave tiles
 };
 double hybrid_launch_us(const sarathi_config &cfg, const std::vector<ChunkBin> &bins, const HybridBatch &b, int64_t split_keys, int64_t max_rows) {
     const double scale = cfg.head_dim == 128 ? 1.0 : 0.69;
@@ -404,7 +405,7 @@ double hybrid_launch_us(const sarathi_config &cfg, const std::vector<ChunkBin> &
         return us <= decode_us ? us : decode_us + (us - decode_us) / next_to_decodes * after;
     };
     double chunk_us;
-    const bool roles = blocks > kChunkBlocksForRoles && b.wave_us > kMinStreamUsForRoles;
+    const bool roles = roles_pay(blocks, b.wave_blocks, b.wave_us, b.wave_block_us, b.shared);
     if (roles) {
         chunk_us = std::max(two_phases(block_steps, 0.91, 0.76), two_phases(work / 256.0, 0.91, 0.38) + 0.55 * 0.76 * scale * block_steps);
     } else if (blocks <= 512) {
@@ -620,7 +621,7 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
         const double key_us = cfg.head_dim * 4.0;
         const int64_t wave_block_keys = std::min(longest_wave_span, wave_split + wave_split / 2);
         HybridBatch b{(double)keys_of_kind[kKindWave] * cfg.num_kv_heads * key_us / 6.5e6, (double)wave_block_keys * key_us / 68.0e3,
-                      (int64_t)(plan.tiles.size() - n_chunk_tiles) * cfg.num_kv_heads};
+                      (int64_t)(plan.tiles.size() - n_chunk_tiles) * cfg.num_kv_heads, 2 * plan.shared_wave_keys > keys_of_kind[kKindWave]};
         if (b.wave_blocks <= 512) b.wave_block_us = std::min(b.wave_block_us, std::max(b.wave_us, 10.0));  // few decodes are cut below
         const std::vector<ChunkBin> &bins = chunk_bins(plan, n_chunk_tiles, longest_span);
         const double as_is = hybrid_launch_us(cfg, bins, b, keys, max_rows);
@@ -701,14 +702,17 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
     const size_t wave_base = plan.units.size();
     const int32_t split_chunk_tiles = plan.num_split_tiles;
     emit_units(plan, n_chunk_tiles, plan.tiles.size(), wave_split, wave_whole, scratch, bucket);
+    plan.longest_wave_keys = 0;  // units are sorted longest first
+    if (plan.units.size() > wave_base) {
+        const uint32_t u = plan.units[wave_base];
+        plan.longest_wave_keys = steps_of_split(plan.tiles[u & ((1u << kUnitTileBits) - 1)], (int32_t)(u >> kUnitTileBits)) * kTileKeys;
+    }
     // Few decodes in pieces of nearly one length: the longest piece (the first unit), were all as long as it, would be at most
     // 1.35 times the keys there are.
     plan.even_decode_pieces = false;
     if (few_cut && plan.num_split_tiles > split_chunk_tiles) {
-        const uint32_t u = plan.units[wave_base];
-        const int64_t longest = steps_of_split(plan.tiles[u & ((1u << kUnitTileBits) - 1)], (int32_t)(u >> kUnitTileBits));
         const int64_t n_units = (int64_t)(plan.units.size() - wave_base);
-        plan.even_decode_pieces = 20 * longest * kTileKeys * n_units <= 27 * keys_of_kind[kKindWave];
+        plan.even_decode_pieces = 20 * (int64_t)plan.longest_wave_keys * n_units <= 27 * keys_of_kind[kKindWave];
     }
     pair_column_tiles(plan, wave_base, cfg.num_kv_heads, scratch);
 }

@@ -65,6 +65,7 @@ static int g_num_seqs = 0;          // shape of the call in flight, for the walk
 static int64_t g_num_tokens = 0;
 static uint64_t g_sink = 0;
 static int32_t g_lds_pad_bytes = 0; // of the last attention launch
+static int g_which = 0;             // and its kind
 static int32_t g_queue_blocks = 0;
 static int g_queued_launches = 0;
 
@@ -191,6 +192,7 @@ int launch_attention(const sarathi_config &cfg, const AttnMeta &m, const void *,
                      float, void *, int which, void *) {
     const int H = cfg.num_kv_heads, D = cfg.head_dim;
     g_lds_pad_bytes = m.lds_pad_bytes;
+    g_which = which;
     g_queue_blocks = m.queue_blocks;
     CHECK(which != 5 || m.queue_blocks > 0);
     CHECK(which != 4 || m.queue_blocks == 0 || m.queue_blocks >= m.num_tile_units * H);   // every chunk tile has a block of its own
@@ -534,6 +536,43 @@ static void drive_queues() {
     CHECK(by_rule > 0);
 }
 
+// Which launches of both kinds of tile take their roles at run time: those whose chunk blocks fill every slot next to decodes that take
+// long to stream, or one of which is long; not those whose chunk blocks leave slots to the decodes from the start, short
+// decodes, or column tiles that share keys.
+static void drive_roles_by_rule() {
+    struct Batch {
+        int32_t hq, hkv, d;
+        std::vector<int32_t> chunks, prefixes;
+        int32_t decodes, keys;
+        bool roles;
+    };
+    const Batch batches[] = {{64, 8, 128, {512, 512}, {911, 2840}, 1024, 2300, true}, {56, 8, 128, {1024, 512, 384}, {9475, 3210, 11117}, 128, 8700, true},
+                             {64, 8, 128, {700, 700}, {800, 100}, 10, 12000, true},   {64, 8, 128, {1919}, {111}, 15, 3800, true},
+                             {64, 8, 128, {285, 1984}, {431, 0}, 3, 3241, true},      {64, 8, 128, {1119}, {1}, 1, 900, false},
+                             {32, 8, 128, {1492}, {0}, 52, 4500, false},              {64, 8, 128, {1186}, {584}, 350, 200, false},
+                             {58, 2, 64, {1833}, {0}, 678, 5000, false},              {32, 8, 128, {512}, {1871}, 64, 2100, false}};
+    for (const Batch &b : batches) {
+        std::vector<int32_t> qs, ql, cl;
+        int32_t T = 0;
+        for (size_t i = 0; i < b.chunks.size(); ++i) { qs.push_back(T); ql.push_back(b.chunks[i]); cl.push_back(b.chunks[i] + b.prefixes[i]); T += b.chunks[i]; }
+        for (int32_t i = 0; i < b.decodes; ++i) { qs.push_back(T); ql.push_back(1); cl.push_back(b.keys); T += 1; }
+        const int32_t S = (int32_t)ql.size(), blocks = 1024;
+        const sarathi_config cfg{b.hq, b.hkv, b.d, 16, 0, T, S, blocks};
+        sarathi_handle *h = nullptr;
+        CHECK(sarathi_create(&cfg, &h) == SARATHI_OK);
+        std::vector<int32_t> bt((size_t)S * blocks, 0);
+        void *ws = nullptr;
+        CHECK(posix_memalign(&ws, 256, sarathi_workspace_bytes(h)) == 0);
+        char dummy[16];
+        sarathi::g_num_seqs = S;
+        sarathi::g_num_tokens = T;
+        CHECK(sarathi_hybrid_attention(h, dummy, dummy, dummy, bt.data(), qs.data(), ql.data(), cl.data(), S, T, 1, 0.1f, dummy, ws, nullptr) == SARATHI_OK);
+        CHECK(sarathi::g_which == (b.roles ? 5 : 4));  // kinds of launch: internal.h
+        CHECK(sarathi_destroy(h) == SARATHI_OK);
+        std::free(ws);
+    }
+}
+
 static void drive_checker() {
     // one chunk on a prefix and two decodes, GQA 4:2, d = 8; every buffer exactly as large as documented
     const int Hq = 4, Hkv = 2, d = 8;
@@ -578,6 +617,7 @@ int main() {
     drive_decode_blocks_per_unit();
     drive_host_bound_cuts();
     drive_queues();
+    drive_roles_by_rule();
     drive_checker();
     std::printf("host paths clean (sink %llu)\n", (unsigned long long)sarathi::g_sink);
     return 0;
