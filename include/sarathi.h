@@ -109,9 +109,9 @@ const char *sarathi_last_error(const sarathi_handle *handle);
  * "interleave" (batches holding both prefill chunks and decodes: 0 = chunk-tile kernel then
  * wave-tile kernel on the caller's stream, 1 = chunk-tile kernel and the merge of its split tiles
  * on a second stream next to the wave-tile kernel, 2 = one launch holding both kinds of block),
- * "resident_chunks" (one-launch mode: one half of the blocks, one to a compute unit as the hardware places them, works off the
- * chunk tiles and the other half the 16-column tiles, each taking from the other kind when its own is finished; -1 =
- * automatic, 0 = never, 1 = wherever there are more items than blocks resident at once),
+ * "resident_chunks" (one-launch mode: blocks choose between chunk and wave tiles when they start so
+ * that a compute unit runs at most one chunk block while decode work remains; -1 = automatic, 0 =
+ * never, 1 = always),
  * "stream_kv" (the decodes' K/V loads carry the non-temporal hint, which pays where K/V is read once;
  * -1 = automatic: unless most keys are read by several 16-column tiles, 0 = never, 1 = always),
  * "window" (sliding-window attention as in the paper's Table 1 for Mistral-7B: with window W > 0 the
@@ -121,7 +121,7 @@ const char *sarathi_last_error(const sarathi_handle *handle);
  * that blocks start longest first as units fall free, which shortens the tail of small batches; 2 = as many as fit;
  * -1 = automatic: one for up to 1024 blocks, unless few decodes were cut into pieces of nearly one length),
  * "item_queue" (blocks take decodes / 16-column tiles from a queue instead of one block per tile: -1 = automatic, in long
- * launches, 0 = only where "resident_chunks" has them do so, 1 = wherever there are more of them than blocks resident at once),
+ * launches, 0 = only where "resident_chunks" has them do so, 1 = always),
  * "inline_append" (0/1: sarathi_kv_append sends up to 224 page records in its kernel's arguments instead of
  * letting the blocks read them from the pinned buffer), "lds_pad_kb" (diagnostic: KiB of unused LDS per
  * attention block, which lowers the number of blocks a compute unit holds),

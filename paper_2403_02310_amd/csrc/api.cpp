@@ -233,9 +233,6 @@ Schedule schedule_of(const sarathi_handle *h) {
     const bool queue = h->opt.item_queue == 1 || (h->opt.item_queue < 0 && queue_pays);
     if (s.roles || (queue && wave_blocks > 0 && (!one_launch || chunk_blocks <= kQueueBlocks)))
         s.queue_blocks = s.lds_pad > kTwoBlocksLdsPad ? kQueueBlocks / 2 : kQueueBlocks;
-    // Where every item has a block that is resident at once, counters only cost (us with forced roles, queued and a block per item:
-    // 1190 tokens next to 89 decodes, 503 items of 64 channels, 50.8 and 39.2; 400 tokens next to 60 decodes 47.7 and 43.6).
-    if (s.queue_blocks >= wave_blocks + (one_launch ? chunk_blocks : 0)) s.queue_blocks = 0, s.roles = false;
     if (!s.roles && one_launch && s.queue_blocks < chunk_blocks) s.queue_blocks = 0;  // every chunk tile has a block of its own
     return s;
 }
