@@ -251,6 +251,37 @@ def test_randomized_batches_shapes_and_options(hx):
     print("worst max abs %.3e, worst row rel %.3e" % tuple(worst), flush=True)
 
 
+QUEUE_OPTIONS = [{"item_queue": 1}, {"item_queue": 1, "interleave": 0}, {"item_queue": 1, "interleave": 1}, {"item_queue": 1, "window": 77},
+                 {"item_queue": 1, "resident_chunks": 0, "split_keys": 32}, {"resident_chunks": 1, "window": 333, "tile_split_keys": 64},
+                 {"item_queue": 1, "resident_chunks": 1, "split_keys": 32}, {"item_queue": 1, "tile_min_cols": 1 << 20},
+                 {"item_queue": 1, "decode_blocks_per_cu": 1, "plan_at_append": 0}, {"item_queue": 1, "stream_kv": 0, "tile_split_keys": 96}]
+
+
+@pytest.mark.parametrize("opts", QUEUE_OPTIONS, ids=str)
+def test_queues_with_other_options(hx, opts):
+    """Forced queues in every kind of launch, under windows and through both entry points: draws of head shape, chunks and
+    decodes, every output row against the checker, and the allocation-free call's as well."""
+    rng = np.random.default_rng([20240311, QUEUE_OPTIONS.index(opts)])
+    for case in range(4):
+        shape = RANDOM_SHAPES[int(rng.integers(len(RANDOM_SHAPES)))]
+        n_chunks, n_dec = int(rng.integers(0, 4)), int(rng.choice([1, 30, 130]))
+        max_ctx = int(rng.choice([100, 900, 4000]))
+        print("case", case, shape, "chunks", n_chunks, "decodes", n_dec, "max_ctx", max_ctx, opts, flush=True)
+        b = wl.random_hybrid(9500 + case, shape, n_chunks, n_dec, max_chunk=min(300, max_ctx), max_ctx=max_ctx)
+        h = hx.make_handle(b)
+        for k, v in opts.items():
+            h.set_option(k, v)
+        st = hx.setup_and_run(b, 0x7FC1, handle=h)
+        k_all = np.concatenate([st["kv_host"][i][0] for i in range(b.num_seqs)])
+        v_all = np.concatenate([st["kv_host"][i][1] for i in range(b.num_seqs)])
+        ref = oracle.hybrid_attention(b.q_bits(0), k_all, v_all, b.kv_start, b.q_start, b.q_len, b.ctx_len, b.sm_scale,
+                                      window=opts.get("window", 0))
+        compare(hx.bf16_tensor_to_f64(st["out"]), ref, "queue case %d" % case)
+        st["out"].zero_()
+        h.hybrid_attention_noalloc(st["q"], st["k_cache"], st["v_cache"], st["bt"], b.q_start, b.q_len, b.ctx_len, b.sm_scale, st["out"])
+        compare(hx.bf16_tensor_to_f64(st["out"]), ref, "queue case %d, allocation-free" % case)
+
+
 @pytest.mark.parametrize("shape", ["gqa4_d128", "gqa7_d128", "mqa4_d64"])
 @pytest.mark.parametrize("window", [1, 17, 64, 300])
 def test_sliding_window(hx, shape, window):
@@ -350,7 +381,7 @@ def test_crafted_value_patterns(hx, case):
 
 
 def test_run_time_roles_repeat_on_one_workspace(hx):
-    """Blocks that pick chunk or wave tiles when they start (per-unit flags and queue heads in the workspace):
+    """Blocks that prefer chunk or wave tiles and take them from queues (counters in the workspace):
     several launches in a row on one handle and workspace, each against the checker and equal bit for bit."""
     s = SHAPES["gqa4_d128"]
     b = wl._make("roles", s, [200, 150, 1, 1, 1, 9, 1], [900, 150, 700, 33, 1200, 64, 300], 83)
@@ -372,7 +403,7 @@ def test_run_time_roles_repeat_on_one_workspace(hx):
 
 
 def test_run_time_roles_do_not_depend_on_what_the_workspace_held(hx):
-    """The scheduling words of the run-time role assignment live in the caller's workspace; whatever an earlier
+    """The scheduling words (queue counters) live in the caller's workspace; whatever an earlier
     user of that memory left there (all-ones bytes here, then the leftovers of a launch, then all-ones again)
     must not change the result."""
     s = SHAPES["gqa4_d128"]
