@@ -92,8 +92,9 @@ sarathi_status sarathi_destroy(sarathi_handle *handle);
 /* Bytes of device scratch the caller must pass as `workspace` (256-byte aligned) to the two
  * device entry points: batch metadata, the work lists, scheduling words and the split-KV partial results.
  * Nothing is expected of its contents (no region has to be zero on entry).  Between a sarathi_kv_append and the
- * sarathi_hybrid_attention of the same iteration the metadata region holds that iteration's plan: do not
- * overwrite it in between (the attention call would read a stale plan). */
+ * sarathi_hybrid_attention of the same iteration it holds that iteration's plan and the scheduling words of its launch,
+ * which the append has cleared: write nowhere into it in between (the attention call would read a stale plan, or its blocks
+ * would skip work).  A second attention call on the same append clears the words itself. */
 size_t sarathi_workspace_bytes(const sarathi_handle *handle);
 
 /* Text of the last error on this handle (includes hipGetErrorString where relevant). */
@@ -109,9 +110,9 @@ const char *sarathi_last_error(const sarathi_handle *handle);
  * "interleave" (batches holding both prefill chunks and decodes: 0 = chunk-tile kernel then
  * wave-tile kernel on the caller's stream, 1 = chunk-tile kernel and the merge of its split tiles
  * on a second stream next to the wave-tile kernel, 2 = one launch holding both kinds of block),
- * "resident_chunks" (one-launch mode: blocks choose between chunk and wave tiles when they start so
- * that a compute unit runs at most one chunk block while decode work remains; -1 = automatic, 0 =
- * never, 1 = always),
+ * "resident_chunks" (one-launch mode: one half of the blocks, one to a compute unit as the hardware places them, works off the
+ * chunk tiles and the other half the 16-column tiles, each taking from the other kind when its own is finished; -1 =
+ * automatic, 0 = never, 1 = always),
  * "stream_kv" (the decodes' K/V loads carry the non-temporal hint, which pays where K/V is read once;
  * -1 = automatic: unless most keys are read by several 16-column tiles, 0 = never, 1 = always),
  * "window" (sliding-window attention as in the paper's Table 1 for Mistral-7B: with window W > 0 the
@@ -123,8 +124,8 @@ const char *sarathi_last_error(const sarathi_handle *handle);
  * "item_queue" (blocks take decodes / 16-column tiles from a queue instead of one block per tile: -1 = automatic, in long
  * launches, 0 = only where "resident_chunks" has them do so, 1 = always),
  * "inline_append" (0/1: sarathi_kv_append sends up to 224 page records in its kernel's arguments instead of
- * letting the blocks read them from the pinned buffer), "lds_pad_kb" (diagnostic: KiB of unused LDS per
- * attention block, which lowers the number of blocks a compute unit holds),
+ * letting the blocks read them from the pinned buffer), "lds_pad_kb" (diagnostic: 0 to 96 KiB of unused LDS per
+ * attention block, of which a block gets the 95 at most that fit next to its own 64; 16 or more leave one block to a compute unit),
  * "time_kernels" (0/1/2, see sarathi_get_kernel_times), "time_every" (n >= 1: only every n-th launch of a
  * kind is bracketed, so that a timed run carries few events; default 1).
  * Unknown names return SARATHI_EINVAL. */
@@ -178,8 +179,8 @@ sarathi_status sarathi_kv_append(sarathi_handle *handle,
  * in a fixed order by a second small kernel, so results are bitwise reproducible run to
  * run and do not depend on which physical pages hold the data.  A call enqueues kernels only: a small
  * one that moves the batch metadata from the handle's pinned buffer into the workspace (not needed when the
- * sarathi_kv_append of the same iteration has already brought it), a fill of the scheduling words when blocks
- * take their role at run time, the attention launch, and the merge when a key range was cut.
+ * sarathi_kv_append of the same iteration has already brought it), a fill of the scheduling words when blocks take their
+ * items from queues and that append has not cleared them, the attention launch, and the merge when a key range was cut.
  */
 sarathi_status sarathi_hybrid_attention(sarathi_handle *handle,
                                         const void *q,

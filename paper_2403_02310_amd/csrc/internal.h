@@ -142,9 +142,8 @@ struct Options {
     int64_t item_queue = -1;        // blocks take wave tiles from a queue: -1 = in long launches, 0 = never (unless roles do), 1 = always
     int64_t inline_append = 1;      // KV append: up to 224 page records travel in the kernel's arguments (else all are read from the pinned buffer)
     int64_t lds_pad_kb = 0;         // diagnostic only: KiB of unused LDS added to every attention block
-    int64_t resident_chunks = -1;   // one-launch mode: blocks take their role (chunk or wave tiles) when they start, so that
-                                    // a compute unit holds at most one chunk block while decode work remains
-                                    // (-1 = when there are more chunk blocks than compute units, 0 = never, 1 = always)
+    int64_t resident_chunks = -1;   // one-launch mode: half of the blocks prefer chunk tiles and half wave tiles, one of each to a
+                                    // compute unit (-1 = where roles_pay says so, 0 = never, 1 = always)
 };
 
 WorkspaceLayout make_workspace_layout(const sarathi_config &cfg);

@@ -367,7 +367,8 @@ ChunkCut cheapest_chunk_cut(const sarathi_config &cfg, const Plan &plan, size_t 
 // timings of 290 batches (1 to 3 chunks of 64-1024 tokens behind 0-12,288 keys next to 1-600 decodes of up to 16,384 keys,
 // five head shapes, seven cuts each; the estimate errs by 10 % rms):
 //   the decodes take 2.3 + the larger of (their bytes at 6.5 TB/s, the longest block's at 68 GB/s) + a quarter of the
-//   smaller + 0.15 of the chunks' work spread over the compute units;
+//   smaller + 0.15 of the chunks' work spread over the compute units (68 is what fits these launches; cheapest_wave_cut keeps
+//   the 40 of its own fit, which chooses as well);
 //   a chunk block takes 0.91 us per 32-key step next to a decode block and 0.55 once they have ended, between that and 0.67 and
 //   0.76 where there are 256 to 512 chunk blocks, and 1.4 steps besides (0.69 of all that with 64 channels); beyond
 //   512 blocks, or one per compute unit where blocks take roles, the launch is as long as the work dealt out evenly + 0.55 of
@@ -614,9 +615,11 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
     int64_t longest_wave_span = 0;
     for (size_t ti = n_chunk_tiles; ti < plan.tiles.size(); ++ti)
         longest_wave_span = std::max<int64_t>(longest_wave_span, plan.tiles[ti].n_keys - plan.tiles[ti].key_lo);
-    // What the rules below chose, or a cut that hybrid_launch_us finds 6 % cheaper.  (220 batches beyond 32 us: 0.955 x the
-    // time on average, none more than 1.09 x; 512 tokens behind 9000 next to 64 decodes, 32 and 8 heads: 177 us in pieces
-    // of 3072 keys, 142 in halves.)
+    // What the rules below chose, or a cut that hybrid_launch_us finds 6 % cheaper.  (512 tokens behind 9000 next to 64 decodes,
+    // 32 and 8 heads: 177 us in pieces of 3072 keys, 142 in halves.  Of 1500 drawn batches 161 are cut differently, at 0.876 x
+    // the time on average; 14 of them are more than 3 % slower, at worst 201 tokens behind 4332 next to one decode, 32 and 32
+    // heads, 44.7 and 52.4 us.  Were 10 % to be promised, 6 would be, and the average 0.879 x.)  Forced roles and separate
+    // launches get the same cuts: 90 batches with such options are on average within 2 % with and without them.
     auto cheaper_next_to_decodes = [&](int64_t keys, int64_t max_rows) {
         const double key_us = cfg.head_dim * 4.0;
         const int64_t wave_block_keys = std::min(longest_wave_span, wave_split + wave_split / 2);
