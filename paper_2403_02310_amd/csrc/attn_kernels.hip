@@ -24,7 +24,8 @@
 // against 90 to 106 GB/s for one compute unit out of its caches, 36 against 52 from memory while 64 of them stream.  That path
 // is what decodes share with the chunk tiles of the same launch.  Straight into operands, and through LDS: 512 tokens behind
 // 1871 next to 64 decodes, 32 and 8 heads, 124.1 and 107.6 us a call; 256 decodes 224.0 and 216.7; 512 decodes of 64 channels, 58
-// and 2 heads, 173 and 123.  (The first two figures include the streaming hint's new rule, the last one is without the hint.)
+// and 2 heads, 173 and 123.  (The first two with the streaming hint, the last one without.  Next to chunk
+// tiles neither gains alone: 124.6 us with neither, 121.7 with the hint, 124.9 through LDS, 110.8 with both on another part.)
 //
 // Chunk-tile path (prefill chunks).  A workgroup of four wavefronts owns 128 columns of one
 // sequence (32 per wave) and walks the key range in 32-key tiles staged once per workgroup in
