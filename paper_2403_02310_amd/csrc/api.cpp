@@ -229,7 +229,14 @@ Schedule schedule_of(const sarathi_handle *h) {
     // A queue evens out the XCDs (3.5 % of a long launch) and costs an item's block 1.5 us, of two on a compute unit.  us, a
     // block per item and queued: 1024 decodes, 8192 items, 1546 and 1518; 512 decodes, 4096 items, 759 and 748; 100 long
     // ones 1240 and 1218; but 256 decodes, 2048 items, 216.5 and 219.5; 1024 short ones, 8192 items, 157 and 162.
-    const bool queue_pays = 0.035 * wave_us > 0.003 * (double)wave_blocks + 3.0;
+    // Decodes of nearly one length run in rounds.  Where the third one fills less than half of the slots, the queue gives both blocks of
+    // the compute units that are first an item and the others none (us: 136 of 4090 to 4096 keys, 1088 items, 373.6 and 388.0,
+    // 144 395.4 and 410.7, 152 412.2 and 423.2; 168, beyond the half, 465.6 and 447.1, 104 291.2 and 282.3, 200 551.0 and 530.9; 136 of
+    // 3000 to 4096 keys 313.2 and 323.3, of 1000 to 6000 295.2 and 295.7).
+    const int64_t wave_units = (int64_t)pl.units.size() - pl.num_tile_units;
+    const bool thin_third_round = chunk_blocks == 0 && 2 * wave_blocks > 4 * kQueueBlocks && 2 * wave_blocks <= 5 * kQueueBlocks &&
+                                  4 * (int64_t)pl.longest_wave_keys * wave_units <= 5 * pl.wave_keys;
+    const bool queue_pays = 0.035 * wave_us > 0.003 * (double)wave_blocks + 3.0 && !thin_third_round;
     const bool queue = h->opt.item_queue == 1 || (h->opt.item_queue < 0 && queue_pays);
     if (s.roles || (queue && wave_blocks > 0 && (!one_launch || chunk_blocks <= kQueueBlocks)))
         s.queue_blocks = s.lds_pad > kTwoBlocksLdsPad ? kQueueBlocks / 2 : kQueueBlocks;

@@ -573,6 +573,35 @@ static void drive_roles_by_rule() {
     }
 }
 
+// Which launches of decodes alone hand their items out from queues by the rule: long ones, but not those of nearly one length whose
+// third round would fill less than half of the slots.
+static void drive_queue_by_rule() {
+    struct Batch {
+        int32_t decodes, low, high;
+        bool queued;
+    };
+    const Batch batches[] = {{104, 4096, 4096, true}, {136, 4096, 4096, false}, {152, 3000, 4096, false}, {152, 1000, 6000, true},
+                             {160, 4096, 4096, false}, {168, 4096, 4096, true}, {300, 4096, 4096, true}, {300, 200, 600, false}, {64, 500, 2000, false}};
+    for (const Batch &b : batches) {
+        const int32_t S = b.decodes, blocks = 400;
+        const sarathi_config cfg{32, 8, 128, 16, 0, S, S, blocks};
+        std::vector<int32_t> q_start((size_t)S), q_len((size_t)S, 1), ctx((size_t)S), bt((size_t)S * blocks, 0);
+        for (int32_t i = 0; i < S; ++i) {
+            q_start[(size_t)i] = i;
+            ctx[(size_t)i] = b.low + (int32_t)((int64_t)(b.high - b.low) * i / std::max(1, S - 1));
+        }
+        sarathi_handle *h = nullptr;
+        CHECK(sarathi_create(&cfg, &h) == SARATHI_OK);
+        char dummy[16];
+        sarathi::g_num_seqs = S;
+        sarathi::g_num_tokens = S;
+        CHECK(sarathi_hybrid_attention_noalloc(h, dummy, dummy, dummy, bt.data(), q_start.data(), q_len.data(), ctx.data(), S, S, 1, 0.1f, dummy,
+                                               nullptr) == SARATHI_OK);
+        CHECK((sarathi::g_queue_blocks > 0) == b.queued);
+        CHECK(sarathi_destroy(h) == SARATHI_OK);
+    }
+}
+
 static void drive_checker() {
     // one chunk on a prefix and two decodes, GQA 4:2, d = 8; every buffer exactly as large as documented
     const int Hq = 4, Hkv = 2, d = 8;
@@ -618,6 +647,7 @@ int main() {
     drive_host_bound_cuts();
     drive_queues();
     drive_roles_by_rule();
+    drive_queue_by_rule();
     drive_checker();
     std::printf("host paths clean (sink %llu)\n", (unsigned long long)sarathi::g_sink);
     return 0;
