@@ -220,9 +220,9 @@ Schedule schedule_of(const sarathi_handle *h) {
         if (one && s.lds_pad == 0) s.lds_pad = kOneBlockPerUnitLdsPad;
     }
     const bool one_launch = chunk_blocks > 0 && wave_blocks > 0 && h->opt.interleave != 0;
-    // The time the decodes need to stream their keys and values, and the longest block alone.
+    // The time the decodes need to stream their keys and values, and the longest block next to a chunk block.
     const double key_us = h->cfg.head_dim * 4.0;
-    const double wave_us = (double)pl.wave_keys * h->cfg.num_kv_heads * key_us / 6.5e6, longest_us = (double)pl.longest_wave_keys * key_us / 68.0e3;
+    const double wave_us = (double)pl.wave_keys * h->cfg.num_kv_heads * key_us / 6.5e6, longest_us = (double)pl.longest_wave_keys * key_us / kNextToChunks;
     const bool shared = 2 * pl.shared_wave_keys > pl.wave_keys;
     if (one_launch)
         s.roles = h->opt.resident_chunks == 1 || (h->opt.resident_chunks < 0 && roles_pay(chunk_blocks, wave_blocks, wave_us, longest_us, shared));

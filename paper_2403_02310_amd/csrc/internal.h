@@ -86,26 +86,27 @@ struct Plan {
 };
 
 // Whether the blocks of a launch of both kinds of tile take their role at run time: `stream_us` is the time the decodes' keys and
-// values need at the chip's rate, `longest_us` what the longest decode block needs alone, `shared` says that most keys are
-// read by several wave tiles.
+// values need at the chip's rate, `longest_us` what the longest decode block needs next to a chunk block (kNextToChunks bytes
+// a us), `shared` says that most keys are read by several wave tiles.
 //
 // A block per tile starts the chunk tiles first; 512 of them fill every slot, and until the last ones run nothing streams and the
-// longest decode has not begun.  Roles keep one slot of a compute unit for decodes, at 3 to 8 us for the counters and a tail of
-// their own.  570 batches of 257 to 1600 chunk blocks next to decodes of 4 to 400 us, a block per tile over roles on average:
+// longest decode has not begun.  Roles keep one slot of a compute unit for decodes, at 3 to 8 us for the counters, 8 ns per decode
+// block for its claim and a tail of their own.  570 batches of 257 to 1600 chunk blocks next to decodes of 4 to 400 us, a block
+// per tile over roles on average:
 //   chunk blocks      decodes of 10-20 us  20-40  40-60  60-80  80-120  120-200  longer
 //   257 to 320                       0.68   0.73   0.83   0.84    0.88     0.94    0.95
 //   400 to 512                       0.86   0.88   0.92   0.91    0.93     0.99    0.99
 //   512 to 700                       0.90   0.97   0.98   1.00    1.07     1.04    1.01
 //   700 to 1000                      0.94   0.97   1.10   1.07    1.11     1.04    1.03
 //   1000 to 1600                     0.95   1.00   1.10   1.14    1.14     1.16    1.10
-// and beyond 512 wherever one decode is long (1984 and 285 tokens next to 3 decodes, 64 and 8 heads, 113.3 and 102.5 us; 1919
-// next to 15 of up to 4630 keys, 56 and 8, 106.7 and 92.9).  Tiles that read the same keys meet in L2 only where they run
-// next to each other: 58 and 2 heads 363 and 439, 388 and 447.
-// Claims cost 8 ns per decode block (1186 tokens next to 350 decodes of up to 347 keys, 64 and 8 heads, 110.7 and 118.1 us).
+// and beyond 512 wherever one decode is long (1984 and 285 tokens next to 3 decodes, 64 and 8 heads, 113.3 and 102.5 us; 1241
+// behind 412 next to 20 of up to 3400 keys, 56 and 8, 95.8 and 75.9), but not next to many short ones (1186 tokens next to 350 of up to
+// 347 keys 110.7 and 118.1).  Tiles that read the same keys meet in L2 only where they run next to each other: 58 and 2 heads
+// 363 and 439, 388 and 447.  Of 960 batches the rule takes the slower way by more than 5 % in 21.
+constexpr double kNextToChunks = 27.2e3;
 inline bool roles_pay(int64_t chunk_blocks, int64_t wave_blocks, double stream_us, double longest_us, bool shared) {
-    const double decode_us = stream_us > longest_us ? stream_us + 0.25 * longest_us : longest_us + 0.25 * stream_us;
-    const double gain_us = decode_us - 0.008 * (double)wave_blocks;
-    return !shared && chunk_blocks >= kQueueBlocks && gain_us > 24.0 && gain_us * (double)(chunk_blocks - 440) > 5000.0;
+    const double gain_us = stream_us + longest_us - 0.008 * (double)wave_blocks;
+    return !shared && chunk_blocks >= kQueueBlocks && gain_us > 50.0 && gain_us * (double)(chunk_blocks - 440) > 8000.0;
 }
 
 // Byte offsets of the regions inside the caller's workspace (all 256-byte aligned).

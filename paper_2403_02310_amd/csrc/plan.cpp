@@ -406,7 +406,7 @@ double hybrid_launch_us(const sarathi_config &cfg, const std::vector<ChunkBin> &
         return us <= decode_us ? us : decode_us + (us - decode_us) / next_to_decodes * after;
     };
     double chunk_us;
-    const bool roles = roles_pay(blocks, b.wave_blocks, b.wave_us, b.wave_block_us, b.shared);
+    const bool roles = roles_pay(blocks, b.wave_blocks, b.wave_us, b.wave_block_us * (68.0e3 / kNextToChunks), b.shared);
     if (roles) {
         chunk_us = std::max(two_phases(block_steps, 0.91, 0.76), two_phases(work / 256.0, 0.91, 0.38) + 0.55 * 0.76 * scale * block_steps);
     } else if (blocks <= 512) {

@@ -548,7 +548,8 @@ static void drive_roles_by_rule() {
     };
     const Batch batches[] = {{64, 8, 128, {512, 512}, {911, 2840}, 1024, 2300, true}, {56, 8, 128, {1024, 512, 384}, {9475, 3210, 11117}, 128, 8700, true},
                              {64, 8, 128, {700, 700}, {800, 100}, 10, 12000, true},   {64, 8, 128, {1919}, {111}, 15, 3800, true},
-                             {64, 8, 128, {285, 1984}, {431, 0}, 3, 3241, true},      {64, 8, 128, {1119}, {1}, 1, 900, false},
+                             {64, 8, 128, {285, 1984}, {431, 0}, 3, 3241, true},     {56, 8, 128, {1241}, {412}, 20, 3377, true},
+                                  {64, 8, 128, {1119}, {1}, 1, 900, false},
                              {32, 8, 128, {1492}, {0}, 52, 4500, false},              {64, 8, 128, {1186}, {584}, 350, 200, false},
                              {58, 2, 64, {1833}, {0}, 678, 5000, false},              {32, 8, 128, {512}, {1871}, 64, 2100, false}};
     for (const Batch &b : batches) {
