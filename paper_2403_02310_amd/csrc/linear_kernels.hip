@@ -975,10 +975,12 @@ static int32_t thin_features(int32_t T, int32_t N, int32_t K) {
 // workgroups, 18.0 and 18.7; 77 x 8192 x 7168 27.7 and 31.9; 77 x 7168 x 10240 37.1 and 46.5; 77 x 14848 x 14848 81.6 and 85.7).
 // Beyond 80 tokens the line lies lower (85 x 14336 x 8192 49.3 and 52.1, 85 x 7168 x 3584 19.1 and 18.7), and beyond 96 next to
 // nothing is left (128 x 6144 x 4096 20.1 and 24.0); 112 features leave two or three stages in LDS (77 x 28672 x 4096 42.8 and 43.4).
+// 64 features with 96 token rows lose on their way in and out what they gain in the loop until k is long enough (81 x 14848 x 512 7.1
+// and 7.4, 81 x 13824 x 1024 10.0 and 10.4, 96 x 16384 x 1024 10.8 and 10.8, 81 x 13824 x 2048 17.4 and 15.9).
 static int32_t mid_features(int32_t T, int32_t N, int32_t K) {
     if (T <= kLinSmallTokens || T > 96 || K % kMidStageK != 0) return 0;
     for (const int f : {32, 48, 64, 80})
-        if (N <= f * 256) return N >= f * 208 && K + 1024 <= (T <= 80 ? 144 : 96) * f ? f : 0;
+        if (N <= f * 256) return N >= f * 208 && K + 1024 <= (T <= 80 ? 144 : 96) * f && (T <= 80 || f != 64 || K > 1024) ? f : 0;
     return 0;
 }
 

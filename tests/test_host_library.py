@@ -341,6 +341,12 @@ def test_a_few_tokens_are_cut_along_k_where_workgroups_would_wait_for_long_range
     assert ((p.token_tile, p.pieces) == (32, 1)) == thin and (thin or p.pieces > 1), (p.token_tile, p.pieces)
 
 
+@pytest.mark.parametrize("T,N,K,uncut", [(81, 14848, 512, False), (96, 13824, 1024, False), (81, 13824, 2048, True), (77, 14848, 512, True),
+                                         (96, 12288, 512, True), (96, 20480, 1024, True), (90, 14848, 3712, True)])
+def test_81_to_96_tokens_on_short_ranges_of_64_features_run_in_larger_tiles(T, N, K, uncut):
+    assert (binding.plan_linear(T, N, K).token_tile in (80, 96)) == uncut
+
+
 def test_plan_linear_refuses_what_linear_refuses():
     out = binding.LinearPlan()
     assert binding.lib.sarathi_plan_linear(0, 128, 64, 0, ctypes.byref(out)) == binding.EINVAL
