@@ -2,7 +2,7 @@
 // 2.1 and 3.1),  y[t][n] = sum_k x[t][k] * w[n][k],  bf16 in, fp32 accumulation, bf16 out.
 //
 // Both operands are contiguous along the contraction index k, which is the per-lane operand
-// shape of v_mfma_f32_32x32x16_bf16 (a lane holds one row and 8 consecutive k).  The weight tile
+// shape of v_mfma_f32_32x32x16_bf16 and v_mfma_f32_16x16x32_bf16 (a lane holds one row and 8 consecutive k).  The weight tile
 // is the A operand (rows = output features) and the token tile the B operand (columns = tokens),
 // so an accumulator lane holds ONE token and runs of 4 consecutive features.  Small batches write
 // these as 8-byte pieces that a wavefront's accumulator tiles complete to 128 contiguous bytes;
@@ -86,6 +86,15 @@ __device__ __forceinline__ void lin_wavefront_lds_order() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// c += a b^T (16 rows x 16 columns x 32 k) in place.  Inline assembly, because it ties the result to the accumulation registers of c:
+// through the builtin the compiler gives each of up to 256 results new registers and copies them back, 234 to 658 moves per
+// two stages, and spills in the key loop of the largest shape (2048 x 8192 x 7168: 522 us).  The compiler does not see that this
+// is a matrix instruction, so the caller keeps the distances that the hardware does not: other instructions read c from 8 wait
+// states on, and the instruction reads a, b and c from 2 wait states after a vector instruction wrote them.
+__device__ __forceinline__ void lin_mfma_in_place(lf32x4 &c, const lbf16x8 &a, const lbf16x8 &b) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
 
 struct LinearParams {
@@ -297,24 +306,26 @@ __global__ __launch_bounds__(kLinThreads, 1) void linear_kernel(LinearParams p) 
 }
 
 // ---------------------------------------------------------------------------------------
-// More than 64 tokens: four wavefronts in a 2 x 2 grid, one per SIMD.  A wavefront owns (A0 + A1) x (B0 + B1) MFMA tiles
+// More than 64 tokens: four wavefronts in a 2 x 2 grid, one per SIMD.  A wavefront owns (A0 + A1) x (B0 + B1) blocks
 // of 32 features x 32 tokens (4 x 4 in the largest shape: all 256 accumulation registers), so that a 256 x 256 tile reads
-// 8 operands from LDS per 16 MFMAs; eight wavefronts of 64 x 128 read 12, which together with the incoming stages is all
-// the LDS port delivers at full MFMA rate (384 + 128 of 512 clocks), and they were bound by it.
+// 8 operands of 1 KiB from LDS per 16 x 32 x 32 x 16 multiply-adds; eight wavefronts of 64 x 128 read 12 (195-205 us on 2048 x 8192 x 7168).
+// A block is four v_mfma_f32_16x16x32_bf16 rather than two v_mfma_f32_32x32x16_bf16 per 32 k: both issue at the matrix pipes' rate (16.3
+// and 32.3 clocks), but the smaller draws less power per multiply-add, and on N(0,1) values power sets the clock: 2181 against
+// 1869 TFLOP/s where nothing else runs, 1.91 against 1.67 GHz here (2048 x 8192 x 7168 180 -> 162 us, 2048 x 14336 x 8192 372 -> 346;
+// on zeros both 132).
 //
 // A stage is worked off in phases: half A0 of the wavefront's weight rows x half B0 of its token rows, A0 x B1, A1 x B1,
 // A1 x B0, each over the stage's 64 k.  While a phase's MFMAs issue, the operands of the half that a later phase needs are
 // read into registers (8 reads per 16 MFMAs), and the barrier at the head of the next phase then frees that half's LDS for
 // the stage RING stages on.  So LDS is refilled half by half and a fetch has 1.75 stages (RING = 2) to land; waiting for
 // whole stages gives it less than one of the two that 128 KiB hold, and the loop then waits for memory: 2048 x 8192 x 7168
-// on all-zero data 158 us by whole stages, 121 us by halves.  On N(0,1) data the matrix pipes' power sets the clock:
-// 195-205 us before (eight wavefronts, whole stages), 174-182 us now = 1.3-1.38 PFLOP/s; its MFMAs alone take 146 us.
+// on all-zero data 158 us by whole stages, 121 us by halves (with the 32 x 32 instruction, as the figures below).  The matrix pipes
+// are busy for 71 to 76 % of the cycles.
 // One wavefront per SIMD leaves nobody to cover a wait, so a phase is laid out by hand: slot m issues its share of reads and
-// fetches, then MFMA m, and a scheduling barrier keeps the compiler from moving them (343 instructions per 128 MFMAs).
+// fetches, then MFMA m, and a scheduling barrier keeps the compiler from moving them (213 other instructions per 256 MFMAs).
 // Accumulators go out through LDS as whole rows (16-byte stores, 128 to 256 contiguous bytes per token and wavefront): 5 us
 // less per tile than 8-byte stores from the accumulator layout.  The way out still takes 8.2 us for 256 x 256: each piece is
-// a predicated read, a wait and a store in a row, and that shape (256 + 256 registers) spills 43 registers there, none in
-// the key loop; the other shapes spill none.
+// a predicated read, a wait and a store in a row.  No shape spills.
 // ---------------------------------------------------------------------------------------
 template <int A0, int A1, int B0, int B1, int RING, bool STREAM>
 __global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {
@@ -377,14 +388,14 @@ __global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {
 
     // ---- operands: wavefront (wn, wt) owns features 32 NI wn .. and tokens 32 NJ wt .. of the tile
     const int wn = wave & 1, wt = wave >> 1;
-    const int r = lane & 31, g = lane >> 5;
-    int piece[4];  // element offset of k16 step s inside a 32-row block for this lane
+    const int n = lane & 15, g = lane >> 4;
+    int piece[4];  // element offset of operand s (k 32 (s / 2) .., rows 16 (s % 2) ..) inside a 32-row block for this lane
 #pragma unroll
-    for (int s = 0; s < 4; ++s) piece[s] = r * KS + ((2 * s + g) ^ row_key(r)) * 8;
+    for (int s = 0; s < 4; ++s) piece[s] = (s % 2 * 16 + n) * KS + ((s / 2 * 4 + g) ^ row_key(n)) * 8;
     constexpr int BX = B0 > B1 ? B0 : B1;
     lbf16x8 fa[2][A0 > A1 ? A0 : A1][4];  // weight operands of halves A0, A1
     lbf16x8 fb[2][BX][4];                 // token operands: B0 and B1 swap sets from stage to stage
-    // read q (k16 step q / nb, block q % nb) of half h from ring slot `slot`; tokens go to set `set`
+    // read q (operand q / nb, block q % nb) of half h from ring slot `slot`; tokens go to set `set`
     auto read = [&](auto ht, auto set, int q, int slot) {
         constexpr int h = decltype(ht)::value;
         constexpr int nb = kBlocks[h] > 0 ? kBlocks[h] : 1;
@@ -394,18 +405,22 @@ __global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {
         if (h == HA0 || h == HA1) fa[h == HA1 ? 1 : 0][b][s] = v;
         else fb[decltype(set)::value][b][s] = v;
     };
-    lf32x16 acc[NI][NJ];
+    lf32x4 acc[NI][NJ][4];  // of a 32 x 32 block: features 16 (q / 2) .., tokens 16 (q % 2) ..
 #pragma unroll
     for (int i = 0; i < NI; ++i)
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+            for (int q = 0; q < 4; ++q) {
+                acc[i][j][q] = lf32x4{0.f, 0.f, 0.f, 0.f};
+                asm volatile("" : "+a"(acc[i][j][q]));  // zeros in place before the first barrier, far from the first MFMA
+            }
     auto mfma = [&](int a, int na, int nb, int b_first, const lbf16x8 (&b_ops)[BX][4], int m) {
-        const int s = m / (na * nb), e = m % (na * nb);
+        const int kh = m / (na * nb * 4), e = m / 4 % (na * nb);
         const int j = e / na, i = (j & 1) ? na - 1 - e % na : e % na;  // consecutive MFMAs share an operand
-        lf32x16 &c = acc[(a ? A0 : 0) + i][b_first + j];
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a][i][s], b_ops[j][s], c, 0, 0, 0);
+        const int fi = m % 4 / 2, tj = fi ^ (m & 1);
+        lf32x4 &c = acc[(a ? A0 : 0) + i][b_first + j][fi * 2 + tj];
+        lin_mfma_in_place(c, fa[a][i][kh * 2 + fi], b_ops[j][kh * 2 + tj]);
     };
     using S0 = std::integral_constant<int, 0>;
     using S1 = std::integral_constant<int, 1>;
@@ -449,7 +464,7 @@ __global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {
     // Loads younger than half rh when the phase starts: RING stages less rh and less ih, which is issued next.
     auto phase = [&](auto at, auto bt, auto bset, auto rht, auto rset, int rslot, auto iht, int istage, int islot) {
         constexpr int a = decltype(at)::value, b = decltype(bt)::value, rh = decltype(rht)::value, ih = decltype(iht)::value;
-        constexpr int na = a ? A1 : A0, nb = b ? B1 : B0, NM = na * nb * 4;
+        constexpr int na = a ? A1 : A0, nb = b ? B1 : B0, NM = na * nb * 8;
         constexpr int reads = 4 * kBlocks[rh], loads = 2 * kBlocks[ih];
         constexpr int span = NM * 3 / 4;
         LIN_PHASE_HEAD(RING * LOADS - 2 * kBlocks[rh] - 2 * kBlocks[ih]);
@@ -470,7 +485,7 @@ __global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {
     // refills what the other one read.  Loads younger than what it reads: RING - 1 stages.
     auto phase_one_half = [&](auto at, auto bset, auto rset, int rslot, int istage, int islot) {
         constexpr int a = decltype(at)::value;
-        constexpr int na = a ? A1 : A0, NM = na * B0 * 4;
+        constexpr int na = a ? A1 : A0, NM = na * B0 * 8;
         constexpr int reads = a ? 4 * (B0 + A0) : 4 * A1, loads = a ? 2 * A1 : 2 * (A0 + B0);
         LIN_PHASE_HEAD((RING - 1) * LOADS);
 #pragma unroll
@@ -519,9 +534,10 @@ __global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {
     if (st < n_stages) stage(st, S0{});
 
     // ---- output.  The padding loads have landed and every wavefront is done with the operands: LDS (16 KiB per wavefront)
-    // turns 32 tokens at a time into rows; 16-byte piece c of row r sits at c ^ (r & 15).  Accumulator element e of lane
-    // (r, g) of tile (i, j) is feature 32i + 8(e/4) + 4g + e%4, token 32j + r.
+    // turns 32 tokens at a time into rows; 16-byte piece c of row r sits at c ^ (r & 15).  Element e of lane (g, n) of
+    // accumulator q of block (i, j) is feature 32i + 16(q/2) + 4g + e, token 32j + 16(q%2) + n.
     LIN_PHASE_HEAD(0);
+    asm volatile("s_nop 7\n\ts_nop 7" ::: "memory");  // sixteen wait states between the last MFMA and the first read of its results
 #undef LIN_PHASE_HEAD
     const int f_wave = n0 + wn * 32 * NI, t_wave = t0 + wt * 32 * NJ;
     char *const out = reinterpret_cast<char *>(smem) + wave * 16384;
@@ -536,10 +552,9 @@ __global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {
 #pragma unroll
             for (int i = 0; i < NI; ++i)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const lf32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-                    *reinterpret_cast<lu32x2 *>(buf + r * 256 + ((i * 4 + q) ^ (r & 15)) * 16 + g * 8) = __builtin_bit_cast(lu32x2, __builtin_convertvector(v, lbf16x4));
-                }
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<lu32x2 *>(buf + (q % 2 * 16 + n) * 256 + ((i * 4 + q / 2 * 2 + g / 2) ^ n) * 16 + g % 2 * 8) =
+                        __builtin_bit_cast(lu32x2, __builtin_convertvector(acc[i][j][q], lbf16x4));
             lin_wavefront_lds_order();
 #pragma unroll
             for (int u = 0; u < PIECES / 2; ++u) {
@@ -554,8 +569,7 @@ __global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {
             for (int i = 0; i < NI; ++i)
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    *reinterpret_cast<lf32x4 *>(out + r * 512 + ((i * 8 + 2 * q + g) ^ (r & 15)) * 16) =
-                        lf32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+                    *reinterpret_cast<lf32x4 *>(out + (q % 2 * 16 + n) * 512 + ((i * 8 + q / 2 * 4 + g) ^ n) * 16) = acc[i][j][q];
             lin_wavefront_lds_order();
 #pragma unroll
             for (int u = 0; u < PIECES / 2; ++u) {
