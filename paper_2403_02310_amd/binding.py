@@ -76,6 +76,12 @@ if not os.path.exists(LIB_PATH):
     raise ImportError("libsarathi.so is not built: run `python -c 'import __graft_entry__ as g; g.build()'` "
                       "(or python -m paper_2403_02310_amd.build) first; there is no fallback path")
 
+try:
+    from . import _marshal
+except ImportError as e:
+    raise ImportError("_marshal.so is not built or does not load: run `python -m paper_2403_02310_amd.build` first; there is no "
+                      "fallback path") from e
+
 lib = ctypes.CDLL(LIB_PATH)
 _i32p = ctypes.POINTER(ctypes.c_int32)
 _vp = ctypes.c_void_p
@@ -117,33 +123,12 @@ lib.sarathi_linear.restype = ctypes.c_int
 lib.sarathi_linear.argtypes = [_vp, _vp, _vp, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, _vp, ctypes.c_size_t, _vp]
 
 
-def _with_addresses(name: str):
-    """The same C function for ``Handle``'s own calls, whose length arrays arrive as addresses of int32 arrays (``_addr``).
-    A function object of its own: ``lib``'s keep taking int32 pointers and refuse anything else."""
-    f = lib[name]
-    f.restype = getattr(lib, name).restype
-    f.argtypes = [_vp if t is _i32p else t for t in getattr(lib, name).argtypes]
-    return f
-
-
-_kv_append = _with_addresses("sarathi_kv_append")
-_hybrid_attention = _with_addresses("sarathi_hybrid_attention")
-_hybrid_attention_noalloc = _with_addresses("sarathi_hybrid_attention_noalloc")
-
-
 def _i32(a) -> np.ndarray:
     return np.ascontiguousarray(a, dtype=np.int32)
 
 
 def _ptr(a: Optional[np.ndarray]):
     return None if a is None else a.ctypes.data_as(_i32p)
-
-
-def _addr(a: np.ndarray) -> int:
-    """Address of a contiguous int32 array that the caller keeps alive for the call.  As a plain integer: building a
-    ctypes pointer from an array takes 2.4 us, and the three length arrays of the two calls of an iteration made up half
-    of the 28 us it kept the host busy (small batches are bound by that)."""
-    return a.__array_interface__["data"][0]
 
 
 def _dev(t) -> Optional[int]:
@@ -157,13 +142,35 @@ def _dev(t) -> Optional[int]:
     return t.data_ptr()
 
 
+def _current_stream() -> int:
+    """Handle of torch's current stream on the current device."""
+    import torch
+    if torch.cuda.is_initialized():  # the same without making a Stream object
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
+
+
+def _check_block_table(block_table, max_blocks: int, num_seqs: int) -> None:
+    """The C ABI takes a bare pointer and walks it with the handle's row width; a tensor of another width
+    would be read with the wrong stride, so the marshalling layer, which still sees the shape, refuses it."""
+    shape = getattr(block_table, "shape", None)
+    if shape is None:
+        return
+    if len(shape) != 2 or int(shape[1]) != max_blocks or int(shape[0]) < num_seqs:
+        raise ValueError("block_table must be [>= %d, %d] (the handle's max_blocks_per_seq), got %s"
+                         % (num_seqs, max_blocks, tuple(shape)))
+
+
+_marshal.setup(*(ctypes.cast(f, _vp).value for f in (lib.sarathi_kv_append, lib.sarathi_hybrid_attention, lib.sarathi_hybrid_attention_noalloc)),
+               np.ndarray, _i32, _current_stream, _check_block_table)
 
 
 class Handle:
@@ -232,52 +239,32 @@ class Handle:
             items = list(items)[: info.num_items]
         return info, items
 
-    def _check_block_table(self, block_table, num_seqs: int) -> None:
-        """The C ABI takes a bare pointer and walks it with the handle's row width; a tensor of another width
-        would be read with the wrong stride, so the marshalling layer, which still sees the shape, refuses it."""
-        shape = getattr(block_table, "shape", None)
-        if shape is None:
-            return
-        if len(shape) != 2 or int(shape[1]) != int(self.config.max_blocks_per_seq) or int(shape[0]) < num_seqs:
-            raise ValueError("block_table must be [>= %d, %d] (the handle's max_blocks_per_seq), got %s"
-                             % (num_seqs, self.config.max_blocks_per_seq, tuple(shape)))
-        if hasattr(block_table, "is_contiguous") and not block_table.is_contiguous():
-            raise ValueError("block_table must be contiguous")
+    def _workspace_or(self, workspace):
+        if workspace is not None:
+            return workspace
+        return self.workspace if self.workspace is not None else self.ensure_workspace()
+
+    def _address(self) -> Optional[int]:
+        return self._h.value if self._h is not None else None
 
     def kv_append(self, k_new, v_new, k_cache, v_cache, block_table, q_start, q_len, ctx_len,
                   num_pages: Optional[int] = None, num_tokens: Optional[int] = None, workspace=None, stream=None):
-        qs, ql, cl = _i32(q_start), _i32(q_len), _i32(ctx_len)
-        n = int(ql.sum()) if num_tokens is None else num_tokens
-        pages = int(k_cache.shape[0]) if num_pages is None else num_pages
-        ws = workspace if workspace is not None else self.ensure_workspace()
-        self._check_block_table(block_table, len(ql))
-        self._check(_kv_append(self._h, _dev(k_new), _dev(v_new), _dev(k_cache), _dev(v_cache),
-                               _dev(block_table), _addr(qs), _addr(ql), _addr(cl), len(ql), n, pages,
-                               _dev(ws), _stream(stream)))
+        self._check(_marshal.kv_append(self._address(), self.config.max_blocks_per_seq, k_new, v_new, k_cache, v_cache, block_table,
+                                       q_start, q_len, ctx_len, num_pages, num_tokens, self._workspace_or(workspace), stream))
 
     def hybrid_attention(self, q, k_cache, v_cache, block_table, q_start, q_len, ctx_len, sm_scale: float, out,
                          num_pages: Optional[int] = None, num_tokens: Optional[int] = None, workspace=None,
                          stream=None):
-        qs, ql, cl = _i32(q_start), _i32(q_len), _i32(ctx_len)
-        n = int(ql.sum()) if num_tokens is None else num_tokens
-        pages = int(k_cache.shape[0]) if num_pages is None else num_pages
-        ws = workspace if workspace is not None else self.ensure_workspace()
-        self._check_block_table(block_table, len(ql))
-        self._check(_hybrid_attention(self._h, _dev(q), _dev(k_cache), _dev(v_cache), _dev(block_table),
-                                      _addr(qs), _addr(ql), _addr(cl), len(ql), n, pages, float(sm_scale),
-                                      _dev(out), _dev(ws), _stream(stream)))
+        self._check(_marshal.attention(self._address(), self.config.max_blocks_per_seq, q, k_cache, v_cache, block_table,
+                                       q_start, q_len, ctx_len, num_pages, num_tokens, float(sm_scale), out, stream,
+                                       self._workspace_or(workspace)))
         return out
 
     def hybrid_attention_noalloc(self, q, k_cache, v_cache, block_table, q_start, q_len, ctx_len, sm_scale: float, out,
                                  num_pages: Optional[int] = None, num_tokens: Optional[int] = None, stream=None):
         """``sarathi_hybrid_attention_noalloc``: no workspace, the library's built-in scratch."""
-        qs, ql, cl = _i32(q_start), _i32(q_len), _i32(ctx_len)
-        n = int(ql.sum()) if num_tokens is None else num_tokens
-        pages = int(k_cache.shape[0]) if num_pages is None else num_pages
-        self._check_block_table(block_table, len(ql))
-        self._check(_hybrid_attention_noalloc(self._h, _dev(q), _dev(k_cache), _dev(v_cache), _dev(block_table),
-                                              _addr(qs), _addr(ql), _addr(cl), len(ql), n, pages, float(sm_scale),
-                                              _dev(out), _stream(stream)))
+        self._check(_marshal.attention(self._address(), self.config.max_blocks_per_seq, q, k_cache, v_cache, block_table,
+                                       q_start, q_len, ctx_len, num_pages, num_tokens, float(sm_scale), out, stream))
         return out
 
 

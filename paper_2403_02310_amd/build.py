@@ -4,11 +4,13 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsarathi.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 SOURCES = ["api.cpp", "linear_api.cpp", "plan.cpp", "scheduler.cpp", "attn_kernels.hip", "linear_kernels.hip"]
 
 
@@ -24,7 +26,18 @@ def build_library(verbose: bool = False) -> str:
         sys.stderr.write(log + "\n")
     if res.returncode != 0:
         raise RuntimeError("hipcc failed building libsarathi.so")
+    build_marshal()
     return LIB
+
+
+def build_marshal() -> str:
+    """The Python module that marshals the library's calls (host code only)."""
+    res = subprocess.run(["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-Wextra", "-I", sysconfig.get_paths()["include"],
+                          "-o", MARSHAL, os.path.join(CSRC, "marshal.cpp")], capture_output=True, text=True)
+    if res.returncode != 0:
+        sys.stderr.write(res.stdout + res.stderr)
+        raise RuntimeError("g++ failed building _marshal.so")
+    return MARSHAL
 
 
 def build_sanitized_host(out_dir: str) -> str:

@@ -1,0 +1,92 @@
+"""The native argument marshalling hands the C calls what the objects hold, in every form that they may come in."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2403_02310_amd import binding
+
+vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
+APPEND = ctypes.CFUNCTYPE(ctypes.c_int, *[vp] * 9, i32, i32, i64, vp, vp)
+ATTENTION = ctypes.CFUNCTYPE(ctypes.c_int, *[vp] * 8, i32, i32, i64, ctypes.c_float, vp, vp, vp)
+NOALLOC = ctypes.CFUNCTYPE(ctypes.c_int, *[vp] * 8, i32, i32, i64, ctypes.c_float, vp, vp)
+MAX_BLOCKS = 5
+
+
+@pytest.fixture
+def calls():
+    """Calls as the C side sees them: the arguments, lengths read out of memory."""
+    got = []
+
+    def record(kind, first_length):
+        def f(*args):
+            n = args[first_length + 3]
+            lengths = [list((i32 * n).from_address(args[first_length + j])) for j in range(3)]
+            got.append((kind, args[:first_length], lengths, args[first_length + 3:]))
+            return -3
+        return f
+    fns = [APPEND(record("append", 6)), ATTENTION(record("attention", 5)), NOALLOC(record("noalloc", 5))]
+    tail = (np.ndarray, binding._i32, lambda: 77, binding._check_block_table)
+    binding._marshal.setup(*(ctypes.cast(f, vp).value for f in fns), *tail)
+    yield got
+    binding._marshal.setup(*(ctypes.cast(f, vp).value for f in (binding.lib.sarathi_kv_append, binding.lib.sarathi_hybrid_attention,
+                                                               binding.lib.sarathi_hybrid_attention_noalloc)),
+                           np.ndarray, binding._i32, binding._current_stream, binding._check_block_table)
+
+
+def tensors():
+    bf = lambda *s: torch.zeros(*s, dtype=torch.bfloat16)  # noqa: E731
+    return {"q": bf(4, 2, 64), "k_new": bf(4, 1, 64), "v_new": bf(4, 1, 64), "k": bf(7, 1, 16, 64), "v": bf(7, 1, 64, 16),
+            "table": torch.zeros(3, MAX_BLOCKS, dtype=torch.int32), "out": bf(4, 2, 64), "ws": bf(512)}
+
+
+LENGTHS = [[0, 2, 3], [2, 1, 1], [2, 9, 30]]
+FORMS = [lambda a: np.array(a, np.int32), list, tuple, lambda a: np.array(a, np.int64), lambda a: np.array(a, ">i4"),
+         lambda a: np.repeat(np.array(a, np.int32), 2)[::2], lambda a: torch.tensor(a), lambda a: np.array(a, np.uint32)]
+
+
+@pytest.mark.parametrize("form", range(len(FORMS)))
+def test_lengths_of_every_form(calls, form):
+    t = tensors()
+    qs, ql, cl = (FORMS[form](a) for a in LENGTHS)
+    m = binding._marshal
+    assert m.kv_append(11, MAX_BLOCKS, t["k_new"], t["v_new"], t["k"], t["v"], t["table"], qs, ql, cl, None, None, t["ws"], None) == -3
+    assert m.attention(11, MAX_BLOCKS, t["q"], t["k"], t["v"], t["table"], qs, ql, cl, None, None, 0.5, t["out"], 9, t["ws"]) == -3
+    assert m.attention(11, MAX_BLOCKS, t["q"], t["k"], t["v"], t["table"], qs, ql, cl, 6, 3, 0.25, t["out"], None) == -3
+    at = lambda *names: tuple(t[n].data_ptr() for n in names)  # noqa: E731
+    assert calls == [
+        ("append", (11, *at("k_new", "v_new", "k", "v", "table")), LENGTHS, (3, 4, 7, *at("ws"), 77)),
+        ("attention", (11, *at("q", "k", "v", "table")), LENGTHS, (3, 4, 7, 0.5, *at("out", "ws"), 9)),
+        ("noalloc", (11, *at("q", "k", "v", "table")), LENGTHS, (3, 3, 6, 0.25, *at("out"), 77)),
+    ]
+
+
+def test_addresses_none_and_streams(calls):
+    class Stream:
+        cuda_stream = 123
+    qs, ql, cl = LENGTHS
+    m = binding._marshal
+    m.kv_append(None, MAX_BLOCKS, None, 1 << 63, 4096, True, 8192, qs, ql, cl, 2 ** 40, 2 ** 31 + 5, 256, Stream())
+    assert calls == [("append", (None, None, 1 << 63, 4096, 1, 8192), LENGTHS, (3, -2 ** 31 + 5, 2 ** 40, 256, 123))]
+
+
+def test_refusals(calls):
+    t = tensors()
+    m = binding._marshal
+
+    def attend(**over):
+        a = {**t, "lengths": LENGTHS[1], "scale": 0.5, "stream": None, **over}
+        return m.attention(11, MAX_BLOCKS, a["q"], a["k"], a["v"], a["table"], LENGTHS[0], a["lengths"], LENGTHS[2], None, None, a["scale"], a["out"],
+                           a["stream"], a["ws"])
+    wide, short = torch.zeros(3, MAX_BLOCKS + 1, dtype=torch.int32), torch.zeros(2, MAX_BLOCKS, dtype=torch.int32)
+    for bad in (dict(table=wide), dict(table=short), dict(table=wide[:, :MAX_BLOCKS]), dict(table=torch.zeros(3, dtype=torch.int32)),
+                dict(q=t["q"].transpose(0, 1)), dict(k=t["k"][:, :, ::2])):
+        with pytest.raises(ValueError):
+            attend(**bad)
+    for bad, error in ((dict(k=4096), AttributeError), (dict(lengths=object()), TypeError), (dict(q=object()), AttributeError), (dict(q=1.5), AttributeError)):
+        with pytest.raises(error):
+            attend(**bad)
+    assert calls == []
+    attend()
+    assert len(calls) == 1
