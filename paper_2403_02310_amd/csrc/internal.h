@@ -129,7 +129,7 @@ struct Options {
     int64_t split_keys = 0;         // keys per wavefront of a wave-tile block (a block covers four times as many); 0 = automatic
     int64_t target_items = 1536;    // automatic choice aims for about this many wavefronts of wave-tile work per KV head
     int64_t tile_split_keys = 0;    // keys per split of the 128-column chunk tiles, 0 = automatic
-    int64_t tile_min_cols = 64;     // sequences with fewer columns (q_len*G) use wave tiles only
+    int64_t tile_min_cols = 0;      // sequences with fewer columns (q_len*G) use wave tiles only; 0 = 64, or all do where the batch is small
     int64_t plan_at_append = 1;     // sarathi_kv_append also plans and uploads the attention metadata of its batch
     int64_t interleave = 2;         // batches with both kinds of tile: 0 = two launches in sequence, 1 = chunk kernel on a
                                     // second stream next to the wave kernel, 2 = one launch holding both kinds of block

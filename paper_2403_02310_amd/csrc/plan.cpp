@@ -26,6 +26,7 @@ constexpr int32_t kMaxSplitUnits = 8192;
 constexpr int32_t kMaxPartRows = 32768;
 constexpr int32_t kMinWaveKeys = 1024;   // automatic choice: keys per wavefront of a wave-tile block before the tile is split
 constexpr int32_t kMinTileSplitKeys = 1024;  // next to decodes
+constexpr int32_t kChunkMinCols = 64;        // automatic choice: sequences with fewer columns run as wave tiles in any batch
 
 WorkspaceLayout make_workspace_layout(const sarathi_config &cfg) {
     WorkspaceLayout w{};
@@ -432,7 +433,9 @@ double hybrid_launch_us(const sarathi_config &cfg, const std::vector<ChunkBin> &
 // Against timings of 20 decode-only and 17 hybrid batches (1 to 64 decodes of 256 to 32,768 keys, seven pieces each):
 // the chosen piece is within 5 % of the best one at the median and 1.9 x (decodes only) and 1.17 x (hybrid) faster than
 // whole decodes on average; 8 decodes of 256-4096 keys: 53 -> 19 + 6 us.  A cut has to promise 5 %, and
-// below 28 us nothing is cut: two launches keep the host for about as long, and a merge would be a third.
+// below 18 us (28 next to chunk tiles) nothing is cut: the merge is one launch more, 3 us a pass (us a pass, whole and cut: a decode of
+// 3072 keys of 64 channels 20.0 and 13.8, of 2048, estimated at 16, 15.3 and 13.9, of 1536 13.0 and 14.0; of 1536 of 128 channels, 22.7, 16.5
+// and 14.1, of 1024, 16.2, 12.9 and 13.7; next to 191 tokens two of 1293, 56 and 8 heads, 16.3 and 19.2).
 // Fitted when a block pulled 40 GB/s alone; now that its loads go through LDS it pulls about 55, and the estimate fitted to that
 // chose no better (120 batches of few decodes 1.001 x, 110 hybrid ones 0.999 x).
 // Where one decode holds half of the keys or more, a plan that cuts it finer and leaves all of up to half its length whole
@@ -508,11 +511,49 @@ WaveCut cheapest_wave_cut(const sarathi_config &cfg, const Plan &plan, size_t n_
             if (c < std::min(0.95 * as_is, best.us)) best = WaveCut{keys, uncut, true, c, as_is};
         }
     };
-    if (as_is >= 28.0) {
+    if (as_is >= (n_chunk_tiles == 0 ? 18.0 : 28.0)) {
         if (whole > 0) search(whole);
         if (!best.few) search(0);
     }
     return best;
+}
+
+// Whether a batch's short prefill chunks run as wave tiles like its decodes: eight times the blocks, each with an eighth of the columns and
+// its keys quartered among its wavefronts, where 128-column tiles leave the chip idle and walk all keys in a row.  A chunk
+// tile alone on its compute unit takes 0.52 us per 32 keys (0.33 with 64 channels); a wave block reads its keys, which its
+// neighbours read as well, at 95 GB/s out of L2, at half of that next to a second block, and every tile costs the host 0.03 us.
+// The line in keys is where cut chunk tiles take as long.  us a pass (append, attention), chunk tiles and wave tiles: 64 tokens
+// behind 512, 32 and 8 heads, 18.6 and 11.1; 256 behind 512 22.1 and 18.5, behind 2048 27.3 and 36.2; 64 behind 2048 19.6 and 20.0; 64
+// tokens of 64 channels, 4 heads and one, behind 512 14.7 and 9.6, behind 2048 14.2 and 16.2; 256 behind none, 56 and 8 heads, 14.4 and
+// 18.5; 64 behind none, 58 and 2 heads of 64, 9.4 and 11.1.  Chunks of more than 1024 columns keep chunk tiles: with few KV heads they would
+// gain as well (256 tokens behind 512, 16 and 2 heads, 21.5 and 12.6), but only as long as the batch holds little else.
+bool chunks_as_wave_tiles(const sarathi_config &cfg, const Options &opt, const WorkspaceLayout &ws, const int32_t *q_len, const int32_t *ctx_len,
+                          int32_t num_seqs) {
+    if (opt.tile_split_keys > 0 || opt.resident_chunks == 1 || opt.interleave != 2) return false;  // asks for chunk tiles
+    const int64_t G = cfg.num_q_heads / cfg.num_kv_heads;
+    int64_t tiles = 0, chunk_tiles = 0, span = 0, other_span = 0;  // spans: of the chunks, of the others
+    for (int32_t s = 0; s < num_seqs; ++s) {
+        const int64_t n = ceil_div((int64_t)q_len[s] * G, kWaveCols);
+        const int64_t keys = opt.window > 0 ? std::min<int64_t>(ctx_len[s], opt.window + q_len[s]) : ctx_len[s];
+        tiles += n;
+        if ((int64_t)q_len[s] * G < kChunkMinCols) {
+            other_span = std::max(other_span, keys);
+            continue;
+        }
+        chunk_tiles += n;
+        span = std::max(span, keys);
+        if (n > 64 || tiles * cfg.num_kv_heads > 512) return false;
+    }
+    if (chunk_tiles == 0 || tiles * cfg.num_kv_heads > 512) return false;
+    const bool alone = tiles * cfg.num_kv_heads <= 256;
+    const double chunk_us = (double)span / kTileKeys * (cfg.head_dim == 128 ? 0.52 : 0.33);
+    const double wave_us = (double)span * cfg.head_dim * 4.0 / (alone ? 95.0e3 : 47.5e3) + 0.03 * (double)chunk_tiles;
+    // Decodes that run longer hide the chunks either way, and next to them two blocks to a compute unit take each other's rate (88
+    // tokens behind 527 next to 14 decodes of up to 2655 keys, 56 and 8 heads, 30.5 and 35.1; 44 next to 8 of 2328 17.0 and 18.7).
+    const double other_us = (double)other_span * cfg.head_dim * 4.0 / 55.0e3;
+    if (span > (alone ? 1792 : 896) || std::max(wave_us, std::min(other_us, alone ? 8.0 : 1.0e9)) + 1.0 >= chunk_us) return false;
+    // a plan that travels in kernel arguments has to fit one launch so
+    return ws.meta_per_launch == 0 || attn_meta_bytes((size_t)tiles, (size_t)tiles, 0) <= ws.meta_per_launch;
 }
 
 }  // namespace
@@ -530,6 +571,8 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
     plan.most_pieces = 0;
     plan.shared_wave_keys = 0;
     const int32_t G = cfg.num_q_heads / cfg.num_kv_heads;
+    int64_t min_cols = opt.tile_min_cols;
+    if (min_cols <= 0) min_cols = chunks_as_wave_tiles(cfg, opt, ws, q_len, ctx_len, num_seqs) ? INT64_MAX : kChunkMinCols;
 
     // Tiles: chunk tiles first, then wave tiles (two passes keep each kind contiguous).
     int64_t keys_of_kind[2] = {0, 0};
@@ -538,7 +581,7 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
         const int32_t kind = pass == 0 ? kKindTile : kKindWave;
         for (int32_t s = 0; s < num_seqs; ++s) {
             const int64_t n_cols = (int64_t)q_len[s] * G;
-            const bool chunk = n_cols >= opt.tile_min_cols;   // prefill chunk: 128-column LDS-staged tiles
+            const bool chunk = n_cols >= min_cols;   // prefill chunk: 128-column LDS-staged tiles
             if (chunk != (kind == kKindTile)) continue;
             const int32_t prefix = ctx_len[s] - q_len[s];
             const int32_t width = chunk ? kTileCols : kWaveCols;

@@ -302,6 +302,23 @@ def test_sliding_window(hx, shape, window):
         compare(out, ref, "window %d %s" % (window, opts))
 
 
+@pytest.mark.parametrize("heads,q_len,ctx_len,window", [
+    ((32, 8, 128), [64], [1792], 0), ((32, 8, 128), [256], [896], 0), ((14, 2, 128), [33, 1, 40, 1], [700, 300, 40, 512], 0),
+    ((58, 2, 64), [31, 1], [1500, 200], 0), ((14, 2, 128), [37, 1, 18], [1300, 555, 9001], 500),
+])
+def test_short_chunks_as_wave_tiles(hx, heads, q_len, ctx_len, window):
+    """What small batches of short chunks run as: 16-column tiles, cut along the keys or not, ends inside tiles and pages."""
+    b = wl._make("short_chunks", wl.AttnShape(*heads), q_len, ctx_len, 87)
+    ref = oracle.attention_for_batch(b, window=window)
+    for opts in ({}, {"split_keys": 32}, {"tile_min_cols": 64}):
+        h = hx.make_handle(b)
+        h.set_option("window", window)
+        for k, v in opts.items():
+            h.set_option(k, v)
+        print("heads", heads, "q_len", q_len, "options", opts, flush=True)
+        compare(hx.bf16_tensor_to_f64(hx.setup_and_run(b, 0x7FC1, handle=h)["out"]), ref, "short chunks %s %s" % (heads, opts))
+
+
 def test_window_longer_than_every_context_changes_nothing(hx):
     s = SHAPES["gqa4_d128"]
     b = wl._make("window_inactive", s, [200, 1, 1], [700, 300, 1], 85)

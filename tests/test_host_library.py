@@ -124,6 +124,24 @@ def test_plan_coverage_with_forced_options():
     _coverage_check(b, tile_min_cols=1 << 20, split_keys=1 << 20)
 
 
+@pytest.mark.parametrize("heads,q_len,ctx_len,window,chunk_tiles", [
+    ((32, 8, 128), [64], [1792], 0, False), ((32, 8, 128), [64], [1793], 0, True),               # keys, a block per compute unit
+    ((32, 8, 128), [128], [1000], 0, False), ((32, 8, 128), [129], [1000], 0, True),             # beyond 256 blocks fewer keys
+    ((32, 8, 128), [256], [896], 0, False), ((32, 8, 128), [256], [897], 0, True), ((32, 8, 128), [257], [700], 0, True),  # 512 blocks
+    ((32, 8, 128), [64], [96], 0, True), ((4, 1, 64), [64], [1500], 0, False), ((4, 1, 64), [64], [192], 0, True),
+    ((32, 8, 128), [64] + [1] * 4, [576] + [500] * 4, 0, False), ((32, 8, 128), [64] + [1] * 4, [576] + [3000] * 4, 0, False),
+    ((32, 8, 128), [64] + [1] * 4, [400] + [3000] * 4, 0, True), ((56, 8, 128), [88] + [1] * 14, [615] + [2655] * 14, 0, True),
+    ((32, 8, 128), [64], [9000], 500, False), ((32, 8, 128), [16, 17], [400, 1000], 0, False), ((16, 2, 128), [15], [700], 0, False),
+    ((16, 2, 128), [128], [700], 0, False), ((16, 2, 128), [129], [700], 0, True),                                        # columns
+])
+def test_short_chunks_of_small_batches_run_as_wave_tiles(heads, q_len, ctx_len, window, chunk_tiles):
+    b = wl._make("short_chunks", wl.AttnShape(*heads), q_len, ctx_len, 5)
+    assert (_coverage_check(b, window=window).num_tile_items > 0) == chunk_tiles
+    assert _coverage_check(b, window=window, tile_min_cols=64).num_tile_items > 0
+    for asks in ({"tile_split_keys": 64}, {"resident_chunks": 1}, {"interleave": 0}):
+        assert _coverage_check(b, window=window, **asks).num_tile_items > 0
+
+
 @pytest.mark.parametrize("window", [1, 33, 500, 4096])
 def test_plan_coverage_under_a_sliding_window(window):
     """Pieces start at the 32-key tile that holds the first key of the tile's first row's window."""
