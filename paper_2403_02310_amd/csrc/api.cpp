@@ -248,7 +248,8 @@ Schedule schedule_of(const sarathi_handle *h) {
 // `sched_clear`: the scheduling words are zero already.
 // `instrumented` = false: the allocation-free entry point, which records no timing events and never forks a
 // second stream (both create runtime objects on first use).
-sarathi_status enqueue_attention(sarathi_handle *h, char *dev, float *part_ml, float *part_o, int32_t *sched,
+// `in_arguments`: `dev` is host memory instead, and the plan travels in the attention launch's arguments.
+sarathi_status enqueue_attention(sarathi_handle *h, char *dev, bool in_arguments, float *part_ml, float *part_o, int32_t *sched,
                                  const int32_t *block_table, const void *q, const void *k_cache, const void *v_cache,
                                  int64_t num_pages, float sm_scale, void *out, hipStream_t s, bool instrumented, bool sched_clear) {
     const Plan &pl = h->plan;
@@ -272,6 +273,7 @@ sarathi_status enqueue_attention(sarathi_handle *h, char *dev, float *part_ml, f
     m.part_o = part_o;
     m.sched = sched;
     m.window = (int32_t)h->opt.window;
+    m.plan_bytes = in_arguments ? mo.reduce : 0;
     const Schedule sched_plan = schedule_of(h);
     m.lds_pad_bytes = sched_plan.lds_pad;
     m.queue_blocks = sched_plan.queue_blocks;
@@ -632,7 +634,7 @@ extern "C" sarathi_status sarathi_hybrid_attention(sarathi_handle *h, const void
         if (e != hipSuccess) return hip_fail(h, "launch upload(metadata)", e);
         if ((st = guard.release()) != SARATHI_OK) return st;
     }
-    return enqueue_attention(h, dev, reinterpret_cast<float *>(ws + h->ws.part_ml), reinterpret_cast<float *>(ws + h->ws.part_o),
+    return enqueue_attention(h, dev, false, reinterpret_cast<float *>(ws + h->ws.part_ml), reinterpret_cast<float *>(ws + h->ws.part_o),
                              reinterpret_cast<int32_t *>(ws + h->ws.sched), block_table, q, k_cache, v_cache, num_pages, sm_scale,
                              out, s, /*instrumented=*/true, sched_clear);
 }
@@ -670,8 +672,12 @@ extern "C" sarathi_status sarathi_hybrid_attention_noalloc(sarathi_handle *h, co
     if (e != hipSuccess) return hip_fail(h, "hipGetSymbolAddress(scratch)", e);
     std::memset(h->noalloc_meta.data(), 0, o.total);
     pack_attn_meta(h->noalloc_meta.data(), h->plan, o);
-    e = (hipError_t)launch_upload_args(sc.meta, h->noalloc_meta.data(), o.total, stream);
-    if (e != hipSuccess) return hip_fail(h, "launch upload(metadata in kernel arguments)", e);
-    return enqueue_attention(h, sc.meta, sc.part_ml, sc.part_o, sc.sched, block_table, q, k_cache, v_cache, num_pages, sm_scale,
+    // A small plan that no merge and no queue reads goes with the attention launch itself.
+    const bool with_launch = o.total <= kPlanArgBytes && h->plan.reduce_units.empty() && schedule_of(h).queue_blocks == 0;
+    if (!with_launch) {
+        e = (hipError_t)launch_upload_args(sc.meta, h->noalloc_meta.data(), o.total, stream);
+        if (e != hipSuccess) return hip_fail(h, "launch upload(metadata in kernel arguments)", e);
+    }
+    return enqueue_attention(h, with_launch ? h->noalloc_meta.data() : sc.meta, with_launch, sc.part_ml, sc.part_o, sc.sched, block_table, q, k_cache, v_cache, num_pages, sm_scale,
                              out, static_cast<hipStream_t>(stream), /*instrumented=*/false, /*sched_clear=*/false);
 }

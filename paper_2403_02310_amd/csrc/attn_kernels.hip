@@ -64,6 +64,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstddef>
 #include <cstdint>
 #include <cstring>
 #include <mutex>
@@ -102,6 +103,25 @@ struct AttnParams {
     int32_t *sched;          // scheduling words (see internal.h)
     int32_t window;          // sliding window: a query at position p sees keys p-window+1 .. p; 0 = all keys up to p
 };
+
+// Arguments of a launch that carries its plan along and reads it where the arguments are: what the allocation-free call does with a
+// small plan, instead of a launch of its own that puts it into memory (64 tokens next to three decodes, 4 heads and one, 14.2 -> 11.0 us a
+// pass, the host's time for two launches).  Instantiations of their own: 4 KiB of arguments keep the host 1 us longer.
+constexpr uint32_t kPlanArgWords = (uint32_t)kPlanArgBytes / 4;
+struct AttnArgs {
+    AttnParams base;
+    uint32_t units_off;  // bytes from the plan's start to its work units
+    uint32_t plan[kPlanArgWords];
+};
+static_assert(sizeof(AttnArgs) <= 4096, "kernel arguments are limited to 4 KiB");
+__device__ __forceinline__ AttnParams attn_params(const AttnParams &p) { return p; }
+__device__ __forceinline__ AttnParams attn_params(const AttnArgs &a) {
+    AttnParams p = a.base;
+    const uintptr_t plan = (uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(AttnArgs, plan);
+    p.tiles = reinterpret_cast<const TileDesc *>(plan);
+    p.units = reinterpret_cast<const uint32_t *>(plan + a.units_off);
+    return p;
+}
 
 // What one work unit (tile, split) covers.
 struct UnitRange {
@@ -1120,16 +1140,18 @@ __device__ __forceinline__ void chunk_item(const AttnParams &p, int item, uint16
 
 // Chunk tiles: one block per (unit, KV head); one wavefront per SIMD so that the pipelined
 // loop has the registers it needs, the matrix pipe / vector ALU overlap comes from inside the wave.
-template <int D>
-__global__ __launch_bounds__(256, 2) void attn_chunk_kernel(AttnParams p) {
+template <int D, typename Args>
+__global__ __launch_bounds__(256, 2) void attn_chunk_kernel(Args args) {
+    const AttnParams p = attn_params(args);
     __shared__ __attribute__((aligned(16))) uint16_t smem[ChunkSmem<D>::kTotalElems];
     chunk_item<D>(p, (int)blockIdx.x, smem);
 }
 
 // Wave tiles (decodes, tiny chunks): one item per block or, QUEUED, the first gridDim.x items by the blocks in order and the
 // others from the queue.
-template <int D, bool STREAM, bool QUEUED>
-__global__ __launch_bounds__(256, 2) void attn_wave_kernel(AttnParams p) {
+template <int D, bool STREAM, bool QUEUED, typename Args>
+__global__ __launch_bounds__(256, 2) void attn_wave_kernel(Args args) {
+    const AttnParams p = attn_params(args);
     __shared__ __attribute__((aligned(16))) uint16_t smem[WaveSmem<D>::kTotalElems];
     const int block = (int)blockIdx.x;
     if constexpr (!QUEUED) {
@@ -1154,8 +1176,9 @@ __global__ __launch_bounds__(256, 2) void attn_wave_kernel(AttnParams p) {
 // unit; two chunk blocks on one unit leave it without a memory stream.  So one block per compute unit (the first
 // half of the grid, which the hardware spreads over the units before it gives any of them a second block) works off the chunk
 // tiles and the other the wave tiles, each kind longest first, and a block whose queue is empty takes from the other one.
-template <int D, int MODE, bool STREAM>
-__global__ __launch_bounds__(256, 2) void attn_hybrid_kernel(AttnParams p) {
+template <int D, int MODE, bool STREAM, typename Args>
+__global__ __launch_bounds__(256, 2) void attn_hybrid_kernel(Args args) {
+    const AttnParams p = attn_params(args);
     constexpr int kSmemElems = ChunkSmem<D>::kTotalElems > WaveSmem<D>::kTotalElems ? ChunkSmem<D>::kTotalElems : WaveSmem<D>::kTotalElems;
     __shared__ __attribute__((aligned(16))) uint16_t smem[kSmemElems];
     const int n_chunk = p.num_tile_units * p.num_kv_heads;
@@ -1608,6 +1631,16 @@ int launch_attention(const sarathi_config &cfg, const AttnMeta &m, const void *q
     p.scale_log2 = sm_scale * 1.4426950408889634f;
     p.sched = m.sched;
     p.window = m.window;
+    if (m.plan_bytes > 0 && (m.plan_bytes > kPlanArgBytes || m.queue_blocks > 0)) return (int)hipErrorInvalidConfiguration;
+    // launch(arguments) of a launch of a block per item
+    auto with_plan = [&](auto launch) {
+        if (m.plan_bytes == 0) return launch(p);
+        AttnArgs args;
+        args.base = p;
+        args.units_off = (uint32_t)(reinterpret_cast<const char *>(m.units) - reinterpret_cast<const char *>(m.tiles));
+        std::memcpy(args.plan, m.tiles, m.plan_bytes);
+        launch(args);
+    };
     const bool stream_kv = m.stream_kv != 0;
     // unused LDS that lowers the blocks per compute unit; all it can take next to the blocks' own 64 KiB already leaves one
     const unsigned dyn_lds = (unsigned)std::min<int32_t>(m.lds_pad_bytes, 95 * 1024);
@@ -1622,7 +1655,11 @@ int launch_attention(const sarathi_config &cfg, const AttnMeta &m, const void *q
         const dim3 grid(std::min(chunk_blocks + wave_blocks, in_flight));
         auto launch = [&](auto d, auto mode) {
             with_stream([&](auto hint) {
-                hipLaunchKernelGGL((attn_hybrid_kernel<decltype(d)::value, decltype(mode)::value, decltype(hint)::value>), grid, dim3(256), dyn_lds, st, p);
+                auto go = [&](const auto &args) {
+                    hipLaunchKernelGGL((attn_hybrid_kernel<decltype(d)::value, decltype(mode)::value, decltype(hint)::value, std::decay_t<decltype(args)>>), grid,
+                                       dim3(256), dyn_lds, st, args);
+                };
+                if constexpr (decltype(mode)::value == kOneEach) with_plan(go); else go(p);
             });
         };
         auto pick_mode = [&](auto d) {
@@ -1635,16 +1672,23 @@ int launch_attention(const sarathi_config &cfg, const AttnMeta &m, const void *q
         return (int)hipGetLastError();
     }
     if (chunk_blocks && (which & 1)) {
-        if (cfg.head_dim == 128)
-            hipLaunchKernelGGL(attn_chunk_kernel<128>, dim3(chunk_blocks), dim3(256), dyn_lds, st, p);
-        else
-            hipLaunchKernelGGL(attn_chunk_kernel<64>, dim3(chunk_blocks), dim3(256), dyn_lds, st, p);
+        with_plan([&](const auto &args) {
+            using Args = std::decay_t<decltype(args)>;
+            if (cfg.head_dim == 128)
+                hipLaunchKernelGGL((attn_chunk_kernel<128, Args>), dim3(chunk_blocks), dim3(256), dyn_lds, st, args);
+            else
+                hipLaunchKernelGGL((attn_chunk_kernel<64, Args>), dim3(chunk_blocks), dim3(256), dyn_lds, st, args);
+        });
     }
     if (wave_blocks && (which & 2)) {
         const dim3 grid(std::min(wave_blocks, in_flight));
         auto launch = [&](auto d, auto queued) {
             with_stream([&](auto hint) {
-                hipLaunchKernelGGL((attn_wave_kernel<decltype(d)::value, decltype(hint)::value, decltype(queued)::value>), grid, dim3(256), dyn_lds, st, p);
+                auto go = [&](const auto &args) {
+                    hipLaunchKernelGGL((attn_wave_kernel<decltype(d)::value, decltype(hint)::value, decltype(queued)::value, std::decay_t<decltype(args)>>), grid,
+                                       dim3(256), dyn_lds, st, args);
+                };
+                if constexpr (!decltype(queued)::value) with_plan(go); else go(p);
             });
         };
         auto pick_queued = [&](auto d) {

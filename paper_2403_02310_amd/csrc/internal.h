@@ -194,6 +194,8 @@ struct AppendMeta {
 int launch_kv_append(const sarathi_config &cfg, const AppendMeta &m, const void *k_new, const void *v_new,
                      void *k_cache, void *v_cache, int64_t num_pages, void *stream);
 
+constexpr size_t kPlanArgBytes = 3840;   // of a plan, in the arguments of the attention launch itself
+
 struct AttnMeta {
     const TileDesc *tiles;       // dev
     const uint32_t *units;       // dev
@@ -212,6 +214,8 @@ struct AttnMeta {
     int32_t window;              // sliding window in keys, 0 = none
     int32_t stream_kv;           // 1: the wave tiles' K/V loads carry the streaming hint
     int32_t lds_pad_bytes = 0;   // diagnostic: dynamic LDS added to the attention launches (fewer blocks per compute unit)
+    size_t plan_bytes = 0;       // not 0: tiles and, behind them, units are so many bytes of ordinary host memory, up to kPlanArgBytes, which
+                                 // travel in the attention launch's arguments (no queues, no merge)
 };
 
 // which: bit 0 = the chunk-tile kernel, bit 1 = the wave-tile kernel, 4 = both kinds in one launch (with queue_blocks at least

@@ -118,3 +118,18 @@ def _oracle_for_queries(batch, st, q_copy):
     k = np.concatenate([st["kv_host"][i][0] for i in range(batch.num_seqs)])
     v = np.concatenate([st["kv_host"][i][1] for i in range(batch.num_seqs)])
     return oracle.hybrid_attention(batch.q_bits(q_copy), k, v, batch.kv_start, batch.q_start, batch.q_len, batch.ctx_len, batch.sm_scale)
+
+
+@pytest.mark.parametrize("interleave", [2, 0])
+@pytest.mark.parametrize("heads", [(8, 2, 128), (4, 1, 64)])
+@pytest.mark.parametrize("chunks,decodes", [((), 1), ((), 73), ((), 74), ((300,), 0), ((300,), 3), ((300, 33), 60), ((300, 33), 61), ((300, 33), 62)])
+def test_noalloc_plan_in_the_launch_arguments_or_in_memory(chunks, decodes, heads, interleave):
+    """3840 bytes of plan travel with the attention launch (73 tiles of 52 bytes; the chunks have ten and two), more in launches of
+    their own: bit for bit the outputs of the workspace entry point, which reads the plan from memory."""
+    from paper_2403_02310_amd import harness as hx
+    q_len = list(chunks) + [1] * decodes
+    ctx_len = [q + 40 for q in chunks] + [17 + 5 * i % 700 for i in range(decodes)]
+    batch = wl._make("plan_in_arguments", wl.AttnShape(*heads), q_len, ctx_len, 93)
+    h, st, base, out2 = _both(hx, batch, {"interleave": interleave})
+    np.testing.assert_array_equal(hx.device_to_bits(out2), base)
+    compare(hx.bf16_tensor_to_f64(out2), oracle.attention_for_batch(batch), "plan in arguments")
