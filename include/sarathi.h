@@ -321,7 +321,8 @@ sarathi_status sarathi_linear(const void *x, const void *w, void *y, int32_t num
  * sizing studies. */
 typedef struct {
     int32_t feature_tile, token_tile;    /* output features x tokens of a workgroup's tile */
-    int32_t feature_tiles, token_tiles;  /* how many of them */
+    int32_t feature_tiles, token_tiles;  /* how many of them; feature tiles that end short of out_features are those of full rounds of
+                                          * workgroups, and the features behind them run with a tiling of their own in a second launch */
     int32_t pieces;                      /* of the k range; more than one: fp32 partial tiles and a second kernel */
     int32_t k_per_piece;
 } sarathi_linear_plan;

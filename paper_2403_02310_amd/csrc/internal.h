@@ -264,5 +264,17 @@ struct LinearPlan {
 LinearPlan plan_linear(int32_t T, int32_t N, int32_t K, size_t workspace_bytes);
 int launch_linear(const LinearPlan &pl, const void *x, const void *w, void *y, int32_t T, int32_t N, int32_t K,
                   void *workspace, void *stream);
+// The same with a tiling of their own for the first features and for the rest, launched one after the other where that is faster.
+struct LinearParts {
+    int32_t first_features;  // of part[0]; N: there is no second part
+    LinearPlan part[2];
+    size_t workspace_bytes(int32_t T, int32_t N) const {
+        const size_t a = part[0].splits > 1 ? sizeof(float) * (size_t)part[0].splits * (size_t)T * (size_t)first_features : 0;
+        const size_t b = first_features < N && part[1].splits > 1 ? sizeof(float) * (size_t)part[1].splits * (size_t)T * (size_t)(N - first_features) : 0;
+        return a > b ? a : b;
+    }
+};
+LinearParts plan_linear_parts(int32_t T, int32_t N, int32_t K, size_t workspace_bytes);
+int launch_linear_parts(const LinearParts &parts, const void *x, const void *w, void *y, int32_t T, int32_t N, int32_t K, void *workspace, void *stream);
 
 }  // namespace sarathi

@@ -21,15 +21,14 @@ bool shape_ok(int32_t T, int32_t N, int32_t K) {
 
 extern "C" size_t sarathi_linear_workspace_bytes(int32_t num_tokens, int32_t out_features, int32_t in_features) {
     if (!shape_ok(num_tokens, out_features, in_features) || num_tokens == 0) return 0;
-    const LinearPlan pl = plan_linear(num_tokens, out_features, in_features, SIZE_MAX);
-    return pl.splits > 1 ? sizeof(float) * (size_t)pl.splits * (size_t)num_tokens * (size_t)out_features : 0;
+    return plan_linear_parts(num_tokens, out_features, in_features, SIZE_MAX).workspace_bytes(num_tokens, out_features);
 }
 
 extern "C" sarathi_status sarathi_plan_linear(int32_t num_tokens, int32_t out_features, int32_t in_features,
                                               size_t workspace_bytes, sarathi_linear_plan *out) {
     if (!out || num_tokens == 0) return SARATHI_EINVAL;
     if (!shape_ok(num_tokens, out_features, in_features)) return SARATHI_ESHAPE;
-    const LinearPlan pl = plan_linear(num_tokens, out_features, in_features, workspace_bytes);
+    const LinearPlan pl = plan_linear_parts(num_tokens, out_features, in_features, workspace_bytes).part[0];
     *out = sarathi_linear_plan{pl.feature_tile, pl.token_tile, pl.n_tiles, pl.t_tiles, pl.splits, pl.k_per_split};
     return SARATHI_OK;
 }
@@ -40,7 +39,7 @@ extern "C" sarathi_status sarathi_linear(const void *x, const void *w, void *y, 
     if (!shape_ok(num_tokens, out_features, in_features)) return SARATHI_ESHAPE;
     if (num_tokens == 0) return SARATHI_OK;
     if (!x || !w || !y) return SARATHI_EINVAL;
-    const LinearPlan pl = plan_linear(num_tokens, out_features, in_features, workspace ? workspace_bytes : 0);
-    const hipError_t e = (hipError_t)launch_linear(pl, x, w, y, num_tokens, out_features, in_features, workspace, stream);
+    const LinearParts parts = plan_linear_parts(num_tokens, out_features, in_features, workspace ? workspace_bytes : 0);
+    const hipError_t e = (hipError_t)launch_linear_parts(parts, x, w, y, num_tokens, out_features, in_features, workspace, stream);
     return e == hipSuccess ? SARATHI_OK : SARATHI_EHIP;
 }

@@ -100,9 +100,10 @@ __device__ __forceinline__ void lin_mfma_in_place(lf32x4 &c, const lbf16x8 &a, c
 struct LinearParams {
     const uint16_t *x;   // [T, K]
     const uint16_t *w;   // [N, K]
-    uint16_t *y;         // [T, N]
+    uint16_t *y;         // [T, N], rows y_stride apart (linear_phased_kernel; the others: N)
     float *part;         // [splits, T, N] when splits > 1
     int32_t T, N, K;
+    int32_t y_stride;
     int32_t n_tiles, t_tiles, splits;
     int32_t k_per_split;  // multiple of 64
 };
@@ -561,7 +562,7 @@ __global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {
                 const int row = (u * 64 + lane) / PIECES, c = (u * 64 + lane) % PIECES;
                 const lu32x4 v = *reinterpret_cast<const lu32x4 *>(buf + row * 256 + (c ^ (row & 15)) * 16);
                 const int t = t_wave + j * 32 + row, f = f_wave + c * 8;
-                if (t < p.T && f < p.N) *reinterpret_cast<lu32x4_at8 *>(p.y + (int64_t)t * p.N + f) = v;
+                if (t < p.T && f < p.N) *reinterpret_cast<lu32x4_at8 *>(p.y + (int64_t)t * p.y_stride + f) = v;
             }
         } else {
             constexpr int PIECES = 8 * NI;                // the same, fp32
@@ -844,8 +845,8 @@ __global__ __launch_bounds__(256, 1) void linear_mid_kernel(LinearParams p) {
     }
 }
 
-// Adds the split-K pieces of every output element in piece order and rounds once to bf16.
-__global__ __launch_bounds__(256) void linear_reduce_kernel(const float *part, uint16_t *y, int64_t elems, int splits) {
+// Adds the split-K pieces of every output element in piece order and rounds once to bf16.  Rows of N (a multiple of 4), in y `y_stride` apart.
+__global__ __launch_bounds__(256) void linear_reduce_kernel(const float *part, uint16_t *y, int64_t elems, int splits, int32_t N, int32_t y_stride) {
     const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
     if (i >= elems) return;
     lf32x4 sum = *reinterpret_cast<const lf32x4 *>(part + i);
@@ -859,7 +860,12 @@ __global__ __launch_bounds__(256) void linear_reduce_kernel(const float *part, u
         for (int j = 0; j < 4; ++j)
             if (s + j < splits) sum += v[j];
     }
-    *reinterpret_cast<lu32x2 *>(y + i) = __builtin_bit_cast(lu32x2, __builtin_convertvector(sum, lbf16x4));
+    int64_t at = i;
+    if (N != y_stride) {  // features of a wider row: so few that 32 bits hold their number
+        const uint32_t row = (uint32_t)i / (uint32_t)N;
+        at = (int64_t)row * y_stride + ((uint32_t)i - row * (uint32_t)N);
+    }
+    *reinterpret_cast<lu32x2 *>(y + at) = __builtin_bit_cast(lu32x2, __builtin_convertvector(sum, lbf16x4));
 }
 
 }  // namespace
@@ -886,12 +892,14 @@ constexpr size_t kNumPhasedShapes = sizeof(kPhasedShapes) / sizeof(kPhasedShapes
 //   the padded product at 2.26 PFLOP/s, and the weights at 8.05 TB/s,
 // plus 0.53 of the other two (none hides the others entirely), 4.3 us per launch, and for pieces of k their fp32 partial
 // tiles, written and read back at 6.2 TB/s, and 1.2 us for the second kernel.
-static LinearPlan plan_phased(int32_t T, int32_t N, int32_t K, size_t workspace_bytes) {
+// `limit`: a cost from which on no plan is wanted; `cost` is then at least that.
+static LinearPlan plan_phased(int32_t T, int32_t N, int32_t K, size_t workspace_bytes, double *cost = nullptr, double limit = 1.0e12) {
     const int64_t k_stages = K / kLinStageK;
     const int64_t per_split_bytes = (int64_t)T * N * 4;
     const double memory_us = 2.0 * N * K / 8.05e6;
     LinearPlan best{};
     double best_cost = -1.0;
+    if (cost) *cost = limit;
     for (const PhasedShape &sh : kPhasedShapes) {
         const int64_t n_tiles = (N + sh.features() - 1) / sh.features();
         const int64_t t_tiles = (T + sh.tokens() - 1) / sh.tokens();
@@ -899,6 +907,7 @@ static LinearPlan plan_phased(int32_t T, int32_t N, int32_t K, size_t workspace_
         const double stage_us = t_tiles == 1 ? sh.stage_us_one_tile : sh.stage_us;
         const double out_us = 8.2 * sh.features() * sh.tokens() / 65536.0;
         const double product_us = 2.0 * (double)tiles * sh.features() * sh.tokens() * K / 2.26e9;
+        if (4.3 + product_us >= limit) continue;
         for (int64_t s = 1; s <= 16 && (s == 1 || (s * 4 <= k_stages && tiles * s <= 1024)); ++s) {
             if (s > 1 && (size_t)(s * per_split_bytes) > workspace_bytes) break;
             const int64_t stages = (k_stages + s - 1) / s;
@@ -920,6 +929,7 @@ static LinearPlan plan_phased(int32_t T, int32_t N, int32_t K, size_t workspace_
             }
         }
     }
+    if (cost && best_cost >= 0.0) *cost = std::min(best_cost, limit);
     return best;
 }
 
@@ -1004,6 +1014,38 @@ LinearPlan plan_linear(int32_t T, int32_t N, int32_t K, size_t workspace_bytes) 
     return T > kLinSmallTokens ? plan_phased(T, N, K, workspace_bytes) : plan_small(T, N, K, workspace_bytes);
 }
 
+// More tiles than compute units: the features of the full rounds of one shape as they are, and the others, whose round would be partly
+// filled, with the tiling that suits them, in a launch of their own; taken where the two costs together are below the one.
+// us a call, one tiling and two: 2048 x 14336 x 8192 (448 tiles of 256 x 256) 346 and 323, 1156 x 14336 x 8192 (375 of 192 x 256) 256
+// and 217, 562 x 24192 x 3840 117 and 99, 1284 x 28672 x 4096 267 and 243, 576 x 28672 x 4096, estimated 2 % dearer, 128 and 126.  Of 320
+// drawn layers estimated between 1 % dearer and a third cheaper seven were more than 1 % slower so, at most 3.4 %, and the average 6.7 % faster
+// (8 % by the estimate's own line, which errs on the side of one tiling).  Up to 96 tokens one token tile covers the batch.
+LinearParts plan_linear_parts(int32_t T, int32_t N, int32_t K, size_t workspace_bytes) {
+    LinearParts best{N, {plan_linear(T, N, K, workspace_bytes), LinearPlan{}}};
+    if (T <= 96 || (int64_t)best.part[0].n_tiles * best.part[0].t_tiles <= 128) return best;
+    double bar;
+    plan_phased(T, N, K, workspace_bytes, &bar);
+    const double feature_us = 2.0 * T * (double)K / 2.26e9, k_stages = K / kLinStageK;
+    for (const PhasedShape &sh : kPhasedShapes) {
+        const int64_t n_tiles = (N + sh.features() - 1) / sh.features(), t_tiles = (T + sh.tokens() - 1) / sh.tokens();
+        const int64_t rounds = n_tiles * t_tiles / 256;
+        if (rounds == 0 || t_tiles == 1) continue;
+        const int32_t whole = (int32_t)(rounds * 256 / t_tiles), first = whole * sh.features();
+        if (whole == 0 || first >= N) continue;
+        const double compute_us = (double)rounds * (k_stages * sh.stage_us + 8.2 * sh.features() * sh.tokens() / 65536.0);
+        const double product_us = 2.0 * whole * (double)t_tiles * sh.features() * sh.tokens() * K / 2.26e9, memory_us = 2.0 * first * K / 8.05e6;
+        const double longest = std::max(compute_us, std::max(product_us, memory_us));
+        const double first_us = 4.3 + longest + 0.53 * (compute_us + product_us + memory_us - longest);
+        if (first_us + 1.53 * (N - first) * feature_us >= bar) continue;  // (the least that the rest can cost)
+        double rest_us;
+        const LinearPlan rest = plan_phased(T, N - first, K, workspace_bytes, &rest_us, bar - first_us);
+        if (first_us + rest_us >= bar) continue;
+        bar = first_us + rest_us;
+        best = LinearParts{first, {LinearPlan{sh.features(), sh.tokens(), whole, (int32_t)t_tiles, 1, K}, rest}};
+    }
+    return best;
+}
+
 // Launches the shape of the table that the plan names; false if it names none of them.
 template <size_t I>
 static bool launch_phased_shape(const LinearPlan &pl, const LinearParams &p, dim3 grid, hipStream_t st) {
@@ -1023,14 +1065,14 @@ static bool launch_phased(const LinearPlan &pl, const LinearParams &p, dim3 grid
     return (launch_phased_shape<I>(pl, p, grid, st) || ...);
 }
 
-int launch_linear(const LinearPlan &pl, const void *x, const void *w, void *y, int32_t T, int32_t N, int32_t K,
-                  void *workspace, void *stream) {
+static int launch_part(const LinearPlan &pl, const void *x, const void *w, void *y, int32_t T, int32_t N, int32_t K, int32_t y_stride,
+                       void *workspace, void *stream) {
     LinearParams p;
     p.x = static_cast<const uint16_t *>(x);
     p.w = static_cast<const uint16_t *>(w);
     p.y = static_cast<uint16_t *>(y);
     p.part = static_cast<float *>(workspace);
-    p.T = T; p.N = N; p.K = K;
+    p.T = T; p.N = N; p.K = K; p.y_stride = y_stride;
     p.n_tiles = pl.n_tiles; p.t_tiles = pl.t_tiles; p.splits = pl.splits; p.k_per_split = pl.k_per_split;
     const int64_t items = (int64_t)pl.n_tiles * pl.t_tiles * pl.splits;
     const int64_t blocks = (items + kLinXcds - 1) / kLinXcds * kLinXcds;
@@ -1095,8 +1137,20 @@ int launch_linear(const LinearPlan &pl, const void *x, const void *w, void *y, i
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || pl.splits == 1) return (int)e;
     const int64_t elems = (int64_t)T * N;
-    hipLaunchKernelGGL(linear_reduce_kernel, dim3((unsigned)((elems / 4 + 255) / 256)), dim3(256), 0, st, p.part, p.y, elems, pl.splits);
+    hipLaunchKernelGGL(linear_reduce_kernel, dim3((unsigned)((elems / 4 + 255) / 256)), dim3(256), 0, st, p.part, p.y, elems, pl.splits, N, y_stride);
     return (int)hipGetLastError();
+}
+
+int launch_linear(const LinearPlan &pl, const void *x, const void *w, void *y, int32_t T, int32_t N, int32_t K, void *workspace, void *stream) {
+    return launch_part(pl, x, w, y, T, N, K, N, workspace, stream);
+}
+
+int launch_linear_parts(const LinearParts &parts, const void *x, const void *w, void *y, int32_t T, int32_t N, int32_t K, void *workspace, void *stream) {
+    const int32_t first = parts.first_features;
+    const int e = launch_part(parts.part[0], x, w, y, T, first, K, N, workspace, stream);
+    if (e != (int)hipSuccess || first >= N) return e;
+    // the workspace is free again when the first part's launches have ended, in the order of the stream
+    return launch_part(parts.part[1], x, static_cast<const uint16_t *>(w) + (int64_t)first * K, static_cast<uint16_t *>(y) + first, T, N - first, K, N, workspace, stream);
 }
 
 }  // namespace sarathi

@@ -71,6 +71,21 @@ def test_linear_matches_checker(hx, T, N, K):
     run(hx, T, N, K, seed=T + N + K)
 
 
+@pytest.mark.parametrize("T,N,K,workspace", [(700, 24704, 704, "full"), (1300, 11264, 1984, "none"), (1025, 13184, 1984, "full"),
+                                             (1025, 13184, 1984, "half"), (577, 26240, 3008, "full")])
+def test_features_of_full_rounds_and_the_rest_as_two_launches(hx, T, N, K, workspace):
+    """More tiles than compute units: a tiling for the full rounds and one for the rest, cut along k or not; the rows and columns
+    around the seam, the ends, and every element written."""
+    binding, _ = hx
+    p = binding.plan_linear(T, N, K, None if workspace == "full" else 0)
+    seam = p.feature_tile * p.feature_tiles
+    assert 0 < seam < N or workspace != "full"
+    rows = sorted({0, 1, 63, 64, 127, 255, 256, T // 2, T - 2, T - 1})
+    cols = sorted({c for at in (0, 64, 128, seam, N // 2, N) for c in range(at - 24, at + 24) if 0 <= c < N})
+    got = run(hx, T, N, K, seed=T + N + K, workspace=workspace, rows=rows, cols=cols)
+    assert np.isfinite(got).all()
+
+
 @pytest.mark.parametrize("workspace", ["full", "half", "none"])
 def test_split_k_pieces_agree(hx, workspace):
     """A small batch on a long k range is cut into pieces; with less or no workspace fewer or none: same result to rounding."""

@@ -365,6 +365,21 @@ def test_81_to_96_tokens_on_short_ranges_of_64_features_run_in_larger_tiles(T, N
     assert (binding.plan_linear(T, N, K).token_tile in (80, 96)) == uncut
 
 
+@pytest.mark.parametrize("T,N,K,first,pieces_of_rest", [
+    (700, 24704, 704, 21760, 0), (1300, 11264, 1984, 6912, 0), (1025, 13184, 1984, 13056, 7), (577, 26240, 3008, 26112, 10), (2048, 14336, 8192, 8192, 0),
+    (2048, 8192, 7168, 8192, 0), (96, 65664, 704, 65664, 0), (577, 12416, 704, 12416, 0),      # full rounds, one token tile, fewer tiles than units
+])
+def test_features_behind_the_full_rounds_get_a_tiling_of_their_own(T, N, K, first, pieces_of_rest):
+    p = binding.plan_linear(T, N, K)
+    assert min(N, p.feature_tile * p.feature_tiles) == first
+    ws = binding.linear_workspace_bytes(T, N, K)
+    assert ws == 4 * pieces_of_rest * T * (N - first)
+    if first < N:
+        tiles = p.feature_tiles * p.token_tiles   # full rounds, as nearly as whole feature tiles fill them
+        assert p.pieces == 1 and tiles >= 128 and -tiles % 256 < p.token_tiles
+        assert binding.plan_linear(T, N, K, 0).pieces == 1
+
+
 def test_plan_linear_refuses_what_linear_refuses():
     out = binding.LinearPlan()
     assert binding.lib.sarathi_plan_linear(0, 128, 64, 0, ctypes.byref(out)) == binding.EINVAL
