@@ -106,18 +106,20 @@ struct AttnParams {
 
 // Arguments of a launch that carries its plan along and reads it where the arguments are: what the allocation-free call does with a
 // small plan, instead of a launch of its own that puts it into memory (64 tokens next to three decodes, 4 heads and one, 14.2 -> 11.0 us a
-// pass, the host's time for two launches).  Instantiations of their own: 4 KiB of arguments keep the host 1 us longer.
-constexpr uint32_t kPlanArgWords = (uint32_t)kPlanArgBytes / 4;
+// pass, the host's time for two launches).  Instantiations of their own, and two sizes: 4 KiB of arguments keep the host 0.5 us longer.
+constexpr size_t kSmallPlanArgBytes = 960;
+template <size_t BYTES>
 struct AttnArgs {
     AttnParams base;
     uint32_t units_off;  // bytes from the plan's start to its work units
-    uint32_t plan[kPlanArgWords];
+    uint32_t plan[BYTES / 4];
 };
-static_assert(sizeof(AttnArgs) <= 4096, "kernel arguments are limited to 4 KiB");
+static_assert(sizeof(AttnArgs<kPlanArgBytes>) <= 4096, "kernel arguments are limited to 4 KiB");
 __device__ __forceinline__ AttnParams attn_params(const AttnParams &p) { return p; }
-__device__ __forceinline__ AttnParams attn_params(const AttnArgs &a) {
+template <size_t BYTES>
+__device__ __forceinline__ AttnParams attn_params(const AttnArgs<BYTES> &a) {
     AttnParams p = a.base;
-    const uintptr_t plan = (uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(AttnArgs, plan);
+    const uintptr_t plan = (uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(AttnArgs<BYTES>, plan);
     p.tiles = reinterpret_cast<const TileDesc *>(plan);
     p.units = reinterpret_cast<const uint32_t *>(plan + a.units_off);
     return p;
@@ -1381,15 +1383,17 @@ struct AppendParams {
     uint32_t zero_blocks;
 };
 
-// Small batches carry their records in the kernel's arguments (the argument block is on the device when the
+// Small batches carry their records in the kernel's arguments, of two sizes, since the host copies them at each launch (64 tokens and 3 decodes
+// in 384 bytes of records instead of 3584: 11.1 -> 10.6 us a pass; the argument block is on the device when the
 // blocks start; a record in pinned host memory is a read across the host link at the head of every block's
 // chain of dependent loads: record -> block-table entry -> stores).
-constexpr int kInlineAppendUnits = 224;
+constexpr int kInlineAppendUnits = 224, kFewAppendUnits = 24;
+template <int UNITS>
 struct AppendParamsInline {
     AppendParams base;
-    AppendUnit units[kInlineAppendUnits];
+    AppendUnit units[UNITS];
 };
-static_assert(sizeof(AppendParamsInline) <= 4096, "kernel arguments are limited to 4 KiB");
+static_assert(sizeof(AppendParamsInline<kInlineAppendUnits>) <= 4096, "kernel arguments are limited to 4 KiB");
 
 template <int D>
 __device__ __forceinline__ void kv_append_block(const AppendParams &p, const AppendUnit *units) {
@@ -1466,8 +1470,8 @@ template <int D>
 __global__ __launch_bounds__(D) void kv_append_kernel(AppendParams p) {
     kv_append_block<D>(p, p.units);
 }
-template <int D>
-__global__ __launch_bounds__(D) void kv_append_inline_kernel(AppendParamsInline p) {
+template <int D, int UNITS>
+__global__ __launch_bounds__(D) void kv_append_inline_kernel(AppendParamsInline<UNITS> p) {
     kv_append_block<D>(p.base, p.units);
 }
 
@@ -1497,13 +1501,18 @@ int launch_kv_append(const sarathi_config &cfg, const AppendMeta &m, const void 
     const unsigned blocks = p.copy_blocks + p.zero_blocks + (unsigned)m.num_units * (unsigned)cfg.num_kv_heads;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (m.units_host && m.num_units <= kInlineAppendUnits) {
-        AppendParamsInline pi;
-        pi.base = p;
-        std::memcpy(pi.units, m.units_host, sizeof(AppendUnit) * (size_t)m.num_units);
-        if (cfg.head_dim == 128)
-            hipLaunchKernelGGL(kv_append_inline_kernel<128>, dim3(blocks), dim3(128), 0, st, pi);
-        else
-            hipLaunchKernelGGL(kv_append_inline_kernel<64>, dim3(blocks), dim3(64), 0, st, pi);
+        auto launch = [&](auto units) {
+            constexpr int U = decltype(units)::value;
+            AppendParamsInline<U> pi;
+            pi.base = p;
+            std::memcpy(pi.units, m.units_host, sizeof(AppendUnit) * (size_t)m.num_units);
+            if (cfg.head_dim == 128)
+                hipLaunchKernelGGL((kv_append_inline_kernel<128, U>), dim3(blocks), dim3(128), 0, st, pi);
+            else
+                hipLaunchKernelGGL((kv_append_inline_kernel<64, U>), dim3(blocks), dim3(64), 0, st, pi);
+        };
+        if (m.num_units <= kFewAppendUnits) launch(std::integral_constant<int, kFewAppendUnits>{});
+        else launch(std::integral_constant<int, kInlineAppendUnits>{});
         return (int)hipGetLastError();
     }
     if (cfg.head_dim == 128)
@@ -1635,11 +1644,13 @@ int launch_attention(const sarathi_config &cfg, const AttnMeta &m, const void *q
     // launch(arguments) of a launch of a block per item
     auto with_plan = [&](auto launch) {
         if (m.plan_bytes == 0) return launch(p);
-        AttnArgs args;
-        args.base = p;
-        args.units_off = (uint32_t)(reinterpret_cast<const char *>(m.units) - reinterpret_cast<const char *>(m.tiles));
-        std::memcpy(args.plan, m.tiles, m.plan_bytes);
-        launch(args);
+        auto carry = [&](auto args) {
+            args.base = p;
+            args.units_off = (uint32_t)(reinterpret_cast<const char *>(m.units) - reinterpret_cast<const char *>(m.tiles));
+            std::memcpy(args.plan, m.tiles, m.plan_bytes);
+            launch(args);
+        };
+        if (m.plan_bytes <= kSmallPlanArgBytes) carry(AttnArgs<kSmallPlanArgBytes>{}); else carry(AttnArgs<kPlanArgBytes>{});
     };
     const bool stream_kv = m.stream_kv != 0;
     // unused LDS that lowers the blocks per compute unit; all it can take next to the blocks' own 64 KiB already leaves one
