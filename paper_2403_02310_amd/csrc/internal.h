@@ -253,8 +253,8 @@ int launch_upload_args(void *dst, const void *host_src, size_t bytes, void *stre
 
 // ---- linear layer (linear_kernels.hip) ----
 struct LinearPlan {
-    int32_t feature_tile; // output features per workgroup tile: 256, 192 or 128; 16 to 128 with 32 tokens, 32 to 80 with 80 or 96
-    int32_t token_tile;   // tokens per workgroup tile: 256, 192, 128, 96, 80, 64 or 32
+    int32_t feature_tile; // output features per workgroup tile: 256, 192 or 128; 16 to 128 with 32 tokens, 16 to 96 with 48, 64, 80 or 96
+    int32_t token_tile;   // tokens per workgroup tile: 256, 192, 128, 96, 80, 64, 48 or 32
     int32_t n_tiles;      // feature tiles
     int32_t t_tiles;      // token tiles
     int32_t splits;       // pieces of the k range (1 = none); pieces write fp32 partial tiles

@@ -8,9 +8,9 @@
 // these as 8-byte pieces that a wavefront's accumulator tiles complete to 128 contiguous bytes;
 // larger ones turn them into whole rows in LDS first.
 //
-// Four kernels.  linear_thin_kernel (up to 16 tokens, 32 on shorter k ranges) and linear_mid_kernel (65 to 96 tokens on some layers):
-// one workgroup per compute unit, nothing cut across workgroups.  linear_phased_kernel (more than 64 tokens otherwise): four wavefronts, one per SIMD, each with up to 128 x 128
-// results in accumulation registers; linear_kernel (up to 64 tokens): eight wavefronts, narrow token tiles, bound by
+// Four kernels.  linear_thin_kernel (up to 16 tokens, 32 on shorter k ranges) and linear_mid_kernel (17 to 96 tokens where k ranges are
+// short next to the features): one workgroup per compute unit, nothing cut across workgroups.  linear_phased_kernel (more than 64 tokens otherwise): four wavefronts, one per SIMD, each with up to 128 x 128
+// results in accumulation registers; linear_kernel (up to 64 tokens otherwise): eight wavefronts, narrow token tiles, bound by
 // fetching the weights.  All bring k stages of 64 (an LDS row is one full 128-byte line of its matrix row; rows of half a
 // line fetch at less than half the rate: 43 against 95 GB/s per compute unit out of L2) from global memory straight into LDS
 // (global_load_lds_dwordx4: no staging registers).  The eight 16-byte pieces of LDS row r are XOR-swizzled with
@@ -732,13 +732,14 @@ __global__ __launch_bounds__(64 * WAVES, 1) void linear_thin_kernel(LinearParams
 }
 
 // ---------------------------------------------------------------------------------------
-// 65 to 96 tokens, where cutting k costs partial tiles and a second kernel: as in linear_thin_kernel a workgroup per compute unit
+// 17 to 96 tokens, where cutting k costs partial tiles and a second kernel: as in linear_thin_kernel a workgroup per compute unit
 // owns F features and the whole k range, but the token rows are too many for a ring per wavefront.  Four wavefronts share stages
 // of 128 k (F weight rows and XR token rows of two lines each); wavefront w works on k 32w .. 32w + 31 of every stage
 // with all results in registers (F / 16 x XR / 16 tiles), and the four sums meet in LDS at the end.
 // Bound by what a compute unit pulls: its weights from memory and all token rows out of L2, together at about 65 GB/s.  us a
 // call, cut along k and so: 77 x 20480 x 7168 59.9 and 53.6 (43.2 at 6.8 TB/s), 77 x 14848 x 3712 28.6 and 24.5 (16.2),
-// 77 x 7168 x 3584 18.5 and 17.4 (7.6), 77 x 8192 x 2048 13.6 and 11.2, 77 x 14336 x 8192 49.0 and 46.3, 96 x 12288 x 2048 17.2 and 15.1.
+// 77 x 7168 x 3584 18.5 and 17.4 (7.6), 77 x 8192 x 2048 13.6 and 11.2, 77 x 14336 x 8192 49.0 and 46.3, 96 x 12288 x 2048 17.2 and 15.1;
+// with fewer tokens fewer token rows: 36 x 20480 x 7168 53.6 and 45.5, 45 x 7168 x 3584 17.0 and 13.4, 63 x 15360 x 2944 24.0 and 19.8.
 // ---------------------------------------------------------------------------------------
 constexpr int kMidStageK = 128;
 template <int F, int XR>
@@ -933,7 +934,7 @@ static LinearPlan plan_phased(int32_t T, int32_t N, int32_t K, size_t workspace_
     return best;
 }
 
-// Up to 64 tokens and not thin: 128 or 256 features x 64 tokens of linear_kernel, cut along k so that a small batch streams the weights
+// Up to 64 tokens otherwise: 128 or 256 features x 64 tokens of linear_kernel, cut along k so that a small batch streams the weights
 // through every compute unit.  Cost in microseconds, fitted to 1,900 timings (16 layer shapes, 1 to 64 tokens, 1 to 16
 // pieces; 6 % rms, the chosen tiling 1 % slower than the best one): as above with the weights at 9.9 TB/s in a maximum that
 // is approached from above by 0.61 of the smaller term, 0.13 us per stage for a full 64 tokens, 3.6 us for the second kernel
@@ -1008,9 +1009,26 @@ static int32_t mid_features(int32_t T, int32_t N, int32_t K) {
     return 0;
 }
 
+// The same for 17 to 64 tokens where linear_thin_kernel does not take them.  Cut along k pays 4 us for its second kernel, this for the token rows, K
+// of them per workgroup, so the line falls with the tokens and rises where k is short.  us a call, cut and so: 20 x 14336 x 8192 41.6 and 37.0,
+// 20 x 12288 x 2048 13.9 and 10.9, 32 x 20480 x 7168 52.2 and 45.4, 32 x 8192 x 7168 23.2 and 22.5, 32 x 14848 x 14848 72.4 and 70.4; 48 of them
+// 74.1 and 77.0, 48 x 4096 x 4096 14.5 and 11.4, 48 x 6144 x 4096 16.6 and 14.6, 48 x 14336 x 8192 44.1 and 40.1, 48 x 8192 x 7168 24.3 and 24.5,
+// 48 x 7168 x 10240 32.1 and 34.3, 33 x 4608 x 7168 18.0 and 20.5; 64 x 8192 x 2048 12.8 and 10.1, 64 x 6144 x 4096 18.0 and 16.6, 64 x 20480 x 7168
+// 55.3 and 49.4, 64 x 10240 x 8192 35.6 and 40.2.  16 features with 64 token rows (64 x 4096 x 4096 15.8 and 12.8) and 112 features (48 x 28672 x
+// 4096 38.1 and 38.2) are left as they were.  Of 160 drawn layers that run so none is slower, 1.165 x faster on average.
+static int32_t few_features(int32_t T, int32_t N, int32_t K) {
+    if (T <= 16 || T > kLinSmallTokens || K % kMidStageK != 0) return 0;
+    const int64_t k_per_feature = T <= 32 ? 260 : T <= 48 ? 215 : 180, on_short_ranges = T <= 48 ? 330 : 215;
+    if (256 * ((int64_t)K + 1024) > N * (K <= 4096 ? std::max(k_per_feature, on_short_ranges) : k_per_feature)) return 0;
+    for (const int f : {16, 32, 48, 64, 80, 96})
+        if (N <= f * 256) return N >= f * 160 && (f > 16 || T <= 48) ? f : 0;
+    return 0;
+}
+
 LinearPlan plan_linear(int32_t T, int32_t N, int32_t K, size_t workspace_bytes) {
     if (const int32_t f = mid_features(T, N, K)) return LinearPlan{f, T <= 80 ? 80 : 96, (N + f - 1) / f, 1, 1, K};
     if (const int32_t f = thin_features(T, N, K)) return LinearPlan{f, kThinTokens, (N + f - 1) / f, 1, 1, K};
+    if (const int32_t f = few_features(T, N, K)) return LinearPlan{f, T <= 48 ? 48 : 64, (N + f - 1) / f, 1, 1, K};
     return T > kLinSmallTokens ? plan_phased(T, N, K, workspace_bytes) : plan_small(T, N, K, workspace_bytes);
 }
 
@@ -1108,17 +1126,24 @@ static int launch_part(const LinearPlan &pl, const void *x, const void *w, void 
         else return (int)hipErrorInvalidConfiguration;
         return (int)hipGetLastError();
     }
-    if (pl.token_tile == 80 || pl.token_tile == 96) {
+    if (pl.token_tile == 48 || pl.token_tile == 80 || pl.token_tile == 96 || (pl.token_tile == 64 && pl.feature_tile < 128)) {
         bool known = false;
         auto with = [&](auto f, auto xr) {
             if (pl.feature_tile != decltype(f)::value || pl.token_tile != decltype(xr)::value || T > decltype(xr)::value) return;
             hipLaunchKernelGGL((linear_mid_kernel<decltype(f)::value, decltype(xr)::value>), dim3((unsigned)pl.n_tiles), dim3(256), 0, st, p);
             known = true;
         };
+        auto few_rows = [&](auto f) {
+            with(f, std::integral_constant<int, 48>{});
+            with(f, std::integral_constant<int, 64>{});
+        };
         auto rows = [&](auto f) {
+            few_rows(f);
             with(f, std::integral_constant<int, 80>{});
             with(f, std::integral_constant<int, 96>{});
         };
+        with(std::integral_constant<int, 16>{}, std::integral_constant<int, 48>{});
+        few_rows(std::integral_constant<int, 96>{});
         rows(std::integral_constant<int, 32>{});
         rows(std::integral_constant<int, 48>{});
         rows(std::integral_constant<int, 64>{});

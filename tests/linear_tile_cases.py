@@ -37,4 +37,10 @@ SMALL = {
     (8, 16256, 3136): (64, 32, True, 1), (10, 12416, 3200): (64, 32, True, 1), (1, 20352, 3072): (80, 32, True, 1), (16, 16640, 3200): (80, 32, True, 1),
     (2, 24448, 3072): (96, 32, True, 1), (12, 20608, 3136): (96, 32, True, 1), (8, 28544, 3072): (112, 32, True, 1), (9, 24704, 3072): (112, 32, True, 1),
     (5, 32640, 3072): (128, 32, True, 1), (14, 28800, 3136): (128, 32, True, 1),
+    # nothing cut either: each number of features with up to 48 and up to 64 token rows; one stage of k, as many as their rings hold, odd and even
+    # numbers of them; ragged last feature tiles
+    (33, 4096, 128): (16, 48, True, 1), (48, 3968, 3968): (16, 48, True, 1), (36, 8064, 1920): (32, 48, True, 1), (47, 8192, 2176): (32, 48, True, 1),
+    (17, 12160, 2048): (48, 48, True, 1), (24, 16256, 6528): (64, 48, True, 1), (32, 20352, 896): (80, 48, True, 1), (20, 24448, 640): (96, 48, True, 1),
+    (64, 8064, 640): (32, 64, True, 1), (49, 12160, 1152): (48, 64, True, 1), (63, 16256, 3072): (64, 64, True, 1), (50, 20352, 128): (80, 64, True, 1),
+    (64, 24448, 2176): (96, 64, True, 1),
 }
