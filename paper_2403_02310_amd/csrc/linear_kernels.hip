@@ -547,6 +547,16 @@ __global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {
     for (int j = 0; j < NJ; ++j) {
         __builtin_amdgcn_sched_barrier(0);
         lin_wavefront_lds_order();  // the reads of the strip that the same LDS held before
+        // The strip's results and the lane's index become values that the compiler cannot have read before: copies of all accumulators, or
+        // places of all strips, made in front of the first one, would not fit the registers, and what is stored away for
+        // that is stored next to the last MFMAs, which the compiler does not know to wait for.
+        int strip_lane = lane;
+        asm volatile("" : "+v"(strip_lane));
+        const int n = strip_lane & 15, g = strip_lane >> 4;
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) asm volatile("" : "+a"(acc[i][j][q]));
         if (final_rows) {
             constexpr int PIECES = 4 * NI;                // of a token's row of this wavefront, bf16
             char *const buf = out + (j & 1) * 8192;
@@ -559,7 +569,7 @@ __global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {
             lin_wavefront_lds_order();
 #pragma unroll
             for (int u = 0; u < PIECES / 2; ++u) {
-                const int row = (u * 64 + lane) / PIECES, c = (u * 64 + lane) % PIECES;
+                const int row = (u * 64 + strip_lane) / PIECES, c = (u * 64 + strip_lane) % PIECES;
                 const lu32x4 v = *reinterpret_cast<const lu32x4 *>(buf + row * 256 + (c ^ (row & 15)) * 16);
                 const int t = t_wave + j * 32 + row, f = f_wave + c * 8;
                 if (t < p.T && f < p.N) *reinterpret_cast<lu32x4_at8 *>(p.y + (int64_t)t * p.y_stride + f) = v;
@@ -574,7 +584,7 @@ __global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {
             lin_wavefront_lds_order();
 #pragma unroll
             for (int u = 0; u < PIECES / 2; ++u) {
-                const int row = (u * 64 + lane) / PIECES, c = (u * 64 + lane) % PIECES;
+                const int row = (u * 64 + strip_lane) / PIECES, c = (u * 64 + strip_lane) % PIECES;
                 const lf32x4 v = *reinterpret_cast<const lf32x4 *>(out + row * 512 + (c ^ (row & 15)) * 16);
                 const int t = t_wave + j * 32 + row, f = f_wave + c * 4;
                 if (t < p.T && f < p.N) *reinterpret_cast<lf32x4 *>(p.part + ((int64_t)wi.split * p.T + t) * p.N + f) = v;
