@@ -533,18 +533,18 @@ bool chunks_as_wave_tiles(const sarathi_config &cfg, const Options &opt, const W
     const int64_t G = cfg.num_q_heads / cfg.num_kv_heads;
     int64_t tiles = 0, chunk_tiles = 0, span = 0, other_span = 0;  // spans: of the chunks, of the others
     for (int32_t s = 0; s < num_seqs; ++s) {
-        const int64_t n = ceil_div((int64_t)q_len[s] * G, kWaveCols);
+        const int64_t n = ((int64_t)q_len[s] * G + kWaveCols - 1) / kWaveCols;
         const int64_t keys = opt.window > 0 ? std::min<int64_t>(ctx_len[s], opt.window + q_len[s]) : ctx_len[s];
         tiles += n;
+        if (n > 64 || tiles * cfg.num_kv_heads > 512) return false;
         if ((int64_t)q_len[s] * G < kChunkMinCols) {
             other_span = std::max(other_span, keys);
             continue;
         }
         chunk_tiles += n;
         span = std::max(span, keys);
-        if (n > 64 || tiles * cfg.num_kv_heads > 512) return false;
     }
-    if (chunk_tiles == 0 || tiles * cfg.num_kv_heads > 512) return false;
+    if (chunk_tiles == 0) return false;
     const bool alone = tiles * cfg.num_kv_heads <= 256;
     const double chunk_us = (double)span / kTileKeys * (cfg.head_dim == 128 ? 0.52 : 0.33);
     const double wave_us = (double)span * cfg.head_dim * 4.0 / (alone ? 95.0e3 : 47.5e3) + 0.03 * (double)chunk_tiles;
