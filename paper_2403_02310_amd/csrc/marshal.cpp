@@ -6,6 +6,8 @@
 #include <Python.h>
 
 #include <cstdint>
+#include <cstring>
+#include <vector>
 
 namespace {
 
@@ -54,17 +56,33 @@ bool device(PyObject *t, void **out) {
     return ok;
 }
 
+// "i", or "=i" and "<i" as unaligned arrays and ctypes arrays have it (the host's bytes are little-endian).
+static_assert(__BYTE_ORDER__ == __ORDER_LITTLE_ENDIAN__, "'<' names the host's byte order");
+bool is_int32(const Py_buffer &view) {
+    if (view.itemsize != 4 || !view.format) return false;
+    const char *f = view.format;
+    if (*f == '@' || *f == '=' || *f == '<') ++f;
+    return (*f == 'i' || *f == 'l') && f[1] == 0;
+}
+
 // int32 lengths, contiguous: an array of that kind as it is, anything else through as_i32.
 struct Lengths {
     Py_buffer view{};
     bool held = false;
+    std::vector<int32_t> aligned;  // the lengths, if the buffer holds them at an odd address
     ~Lengths() {
         if (held) PyBuffer_Release(&view);
     }
     bool take(PyObject *a) {
         held = PyObject_GetBuffer(a, &view, PyBUF_C_CONTIGUOUS | PyBUF_FORMAT) == 0;
         if (!held) return false;
-        if (view.ndim >= 1 && view.itemsize == 4 && view.format && view.format[0] == 'i' && view.format[1] == 0) return true;
+        if (view.ndim >= 1 && is_int32(view)) {
+            if (reinterpret_cast<uintptr_t>(view.buf) % alignof(int32_t) != 0) {
+                aligned.resize(static_cast<size_t>(view.len) / sizeof(int32_t));
+                std::memcpy(aligned.data(), view.buf, aligned.size() * sizeof(int32_t));
+            }
+            return true;
+        }
         PyBuffer_Release(&view);
         held = false;
         return false;
@@ -81,7 +99,7 @@ struct Lengths {
         if (!ok && !PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, "lengths must convert to int32");
         return ok;
     }
-    const int32_t *data() const { return static_cast<const int32_t *>(view.buf); }
+    const int32_t *data() const { return aligned.empty() ? static_cast<const int32_t *>(view.buf) : aligned.data(); }
     int32_t count() const { return static_cast<int32_t>(view.shape[0]); }
     int64_t sum() const {
         int64_t s = 0;

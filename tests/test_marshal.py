@@ -62,6 +62,23 @@ def test_lengths_of_every_form(calls, form):
     ]
 
 
+def unaligned(a):
+    v = np.frombuffer(bytearray(4 * len(a) + 1), dtype=np.int32, offset=1, count=len(a))
+    v[:] = a
+    return v
+
+
+@pytest.mark.parametrize("form", [lambda a: (i32 * len(a))(*a), lambda a: np.array((i32 * len(a))(*a)), unaligned, lambda a: unaligned(a + [7])[:len(a)],
+                                  lambda a: memoryview(np.array(a, np.int32)), lambda a: np.array([(x, 1) for x in a], [("a", "i4"), ("b", "i1")])["a"]])
+@pytest.mark.parametrize("which", range(3))
+def test_int32_lengths_whose_buffers_name_their_type_otherwise(calls, form, which):
+    """Unaligned arrays and ctypes arrays describe int32 as "=i" and "<i"."""
+    t = tensors()
+    lengths = [form(a) if j == which else a for j, a in enumerate(LENGTHS)]
+    binding._marshal.attention(11, MAX_BLOCKS, t["q"], t["k"], t["v"], t["table"], *lengths, None, None, 0.5, t["out"], 9)
+    assert [c[2] for c in calls] == [LENGTHS]
+
+
 def test_addresses_none_and_streams(calls):
     class Stream:
         cuda_stream = 123
