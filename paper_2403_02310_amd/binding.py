@@ -169,6 +169,19 @@ def _check_block_table(block_table, max_blocks: int, num_seqs: int) -> None:
                          % (num_seqs, max_blocks, tuple(shape)))
 
 
+def _taken_as(ctype):
+    """``value -> int``: the conversion of a ctypes call to one argument of that type, its ``ArgumentError`` included."""
+    return ctypes.PYFUNCTYPE(ctype, ctype)(lambda value: value)
+
+
+def _address(value) -> Optional[int]:
+    if isinstance(value, (str, bytes)):  # a pointer to the text, which the call would outlive
+        raise ctypes.ArgumentError("address expected, got %s" % type(value).__name__)
+    return _as_pointer(value)
+
+
+_as_pointer = _taken_as(_vp)
+_marshal.conversions(_taken_as(ctypes.c_int32), _taken_as(ctypes.c_int64), _address)
 _marshal.setup(*(ctypes.cast(f, _vp).value for f in (lib.sarathi_kv_append, lib.sarathi_hybrid_attention, lib.sarathi_hybrid_attention_noalloc)),
                np.ndarray, _i32, _current_stream, _check_block_table)
 

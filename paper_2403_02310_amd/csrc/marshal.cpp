@@ -20,39 +20,48 @@ using NoallocFn = int (*)(void *, const void *, const void *, const void *, cons
 AppendFn append_fn;
 AttentionFn attention_fn;
 NoallocFn noalloc_fn;
-PyObject *ndarray_type, *as_i32, *current_stream, *refuse_table;  // registered by binding.py, kept for the life of the process
+// registered by binding.py, kept for the life of the process
+PyObject *ndarray_type, *as_i32, *current_stream, *refuse_table;
+PyObject *as_c_int32, *as_c_int64, *as_c_address;
 PyObject *s_is_contiguous, *s_data_ptr, *s_shape, *s_cuda_stream;
 
-// An int as the C call takes it (wrapped to 64 bits); sets an error otherwise.
-bool as_int(PyObject *o, uint64_t *out) {
-    *out = PyLong_AsUnsignedLongLongMask(o);
-    return !(*out == (uint64_t)-1 && PyErr_Occurred());
+// An int as the C call takes it (wrapped to 64 bits), None and what is no int through `convert`, which takes and refuses what a
+// ctypes call does; sets an error otherwise.
+bool as_int(PyObject *o, PyObject *convert, uint64_t *out) {
+    PyObject *made = nullptr;
+    if (!PyLong_Check(o)) {
+        if (!(made = PyObject_CallOneArg(convert, o))) return false;
+        o = made;
+    }
+    const bool none = o == Py_None;  // a null address
+    *out = none ? 0 : PyLong_AsUnsignedLongLongMask(o);
+    Py_XDECREF(made);
+    return none || !(*out == (uint64_t)-1 && PyErr_Occurred());
+}
+bool as_address(PyObject *o, void **out) {
+    uint64_t v = 0;
+    if (o != Py_None && !as_int(o, as_c_address, &v)) return false;
+    *out = reinterpret_cast<void *>(v);
+    return true;
 }
 
 // Address of a device tensor (contiguous), of an int, or null for None.
 bool device(PyObject *t, void **out) {
     *out = nullptr;
-    if (t == Py_None) return true;
-    PyObject *address = nullptr;
-    if (PyLong_Check(t)) {
-        Py_INCREF(t);
-        address = t;
-    } else {
-        PyObject *c = PyObject_CallMethodNoArgs(t, s_is_contiguous);
-        if (!c) return false;
-        const int yes = PyObject_IsTrue(c);
-        Py_DECREF(c);
-        if (yes < 0) return false;
-        if (!yes) {
-            PyErr_SetString(PyExc_ValueError, "device tensors must be contiguous");
-            return false;
-        }
-        if (!(address = PyObject_CallMethodNoArgs(t, s_data_ptr))) return false;
+    if (t == Py_None || PyLong_Check(t)) return as_address(t, out);
+    PyObject *c = PyObject_CallMethodNoArgs(t, s_is_contiguous);
+    if (!c) return false;
+    const int yes = PyObject_IsTrue(c);
+    Py_DECREF(c);
+    if (yes < 0) return false;
+    if (!yes) {
+        PyErr_SetString(PyExc_ValueError, "device tensors must be contiguous");
+        return false;
     }
-    uint64_t v;
-    const bool ok = as_int(address, &v);
+    PyObject *address = PyObject_CallMethodNoArgs(t, s_data_ptr);
+    if (!address) return false;
+    const bool ok = as_address(address, out);
     Py_DECREF(address);
-    *out = reinterpret_cast<void *>(v);
     return ok;
 }
 
@@ -131,10 +140,8 @@ bool stream_of(PyObject *s, void **out) {
     else if (PyLong_Check(s)) Py_INCREF(s), v = s;
     else v = PyObject_GetAttr(s, s_cuda_stream);
     if (!v) return false;
-    uint64_t a = 0;
-    const bool ok = v == Py_None || as_int(v, &a);
+    const bool ok = as_address(v, out);
     Py_DECREF(v);
-    *out = reinterpret_cast<void *>(a);
     return ok;
 }
 
@@ -149,16 +156,18 @@ struct Batch {
         num_seqs = q_len.count();
         uint64_t v;
         if (tokens == Py_None) num_tokens = static_cast<int32_t>(q_len.sum());
-        else if (as_int(tokens, &v)) num_tokens = static_cast<int32_t>(v);
+        else if (as_int(tokens, as_c_int32, &v)) num_tokens = static_cast<int32_t>(v);
         else return false;
         if (pages == Py_None) {
             PyObject *shape = PyObject_GetAttr(k_cache, s_shape);
             PyObject *first = shape ? PySequence_GetItem(shape, 0) : nullptr;
-            const bool ok = first && as_int(first, &v);
+            PyObject *whole = first ? PyNumber_Long(first) : nullptr;
+            const bool ok = whole && as_int(whole, as_c_int64, &v);
+            Py_XDECREF(whole);
             Py_XDECREF(first);
             Py_XDECREF(shape);
             if (!ok) return false;
-        } else if (!as_int(pages, &v)) return false;
+        } else if (!as_int(pages, as_c_int64, &v)) return false;
         num_pages = static_cast<int64_t>(v);
         return table_fits(block_table, max_blocks, num_seqs) && device(block_table, &table);
     }
@@ -208,12 +217,19 @@ PyObject *attention(PyObject *, PyObject *const *a, Py_ssize_t n) {
     return PyLong_FromLong(st);
 }
 
+void keep(PyObject **const *places, PyObject *const *objects, int n) {
+    for (int i = 0; i < n; ++i) {
+        Py_INCREF(objects[i]);
+        Py_XSETREF(*places[i], objects[i]);
+    }
+}
+
 // (address of sarathi_kv_append, .._hybrid_attention, .._hybrid_attention_noalloc, numpy.ndarray, as_i32, current_stream, refuse_table)
 PyObject *setup(PyObject *, PyObject *const *a, Py_ssize_t n) {
     if (!arity(n, 7)) return nullptr;
-    uint64_t f[3];
+    void *f[3];
     for (int i = 0; i < 3; ++i)
-        if (!as_int(a[i], &f[i])) return nullptr;
+        if (!as_address(a[i], &f[i])) return nullptr;
     if (!PyType_Check(a[3])) {
         PyErr_SetString(PyExc_TypeError, "the array type expected");
         return nullptr;
@@ -221,17 +237,23 @@ PyObject *setup(PyObject *, PyObject *const *a, Py_ssize_t n) {
     append_fn = reinterpret_cast<AppendFn>(f[0]);
     attention_fn = reinterpret_cast<AttentionFn>(f[1]);
     noalloc_fn = reinterpret_cast<NoallocFn>(f[2]);
-    PyObject **const keep[] = {&ndarray_type, &as_i32, &current_stream, &refuse_table};
-    for (int i = 0; i < 4; ++i) {
-        Py_INCREF(a[3 + i]);
-        Py_XSETREF(*keep[i], a[3 + i]);
-    }
+    PyObject **const places[] = {&ndarray_type, &as_i32, &current_stream, &refuse_table};
+    keep(places, a + 3, 4);
+    Py_RETURN_NONE;
+}
+
+// (as_c_int32, as_c_int64, as_c_address)
+PyObject *conversions(PyObject *, PyObject *const *a, Py_ssize_t n) {
+    if (!arity(n, 3)) return nullptr;
+    PyObject **const places[] = {&as_c_int32, &as_c_int64, &as_c_address};
+    keep(places, a, 3);
     Py_RETURN_NONE;
 }
 
 PyMethodDef methods[] = {
     {"kv_append", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(kv_append)), METH_FASTCALL, nullptr},
     {"attention", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(attention)), METH_FASTCALL, nullptr},
+    {"conversions", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(conversions)), METH_FASTCALL, nullptr},
     {"setup", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(setup)), METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr},
 };

@@ -88,6 +88,57 @@ def test_addresses_none_and_streams(calls):
     assert calls == [("append", (None, None, 1 << 63, 4096, 1, 8192), LENGTHS, (3, -2 ** 31 + 5, 2 ** 40, 256, 123))]
 
 
+def call(t, **over):
+    """attention(..) with one argument replaced."""
+    a = {**t, "pages": None, "tokens": None, "stream": 9, **over}
+    return binding._marshal.attention(11, MAX_BLOCKS, a["q"], a["k"], a["v"], a["table"], *LENGTHS, a["pages"], a["tokens"], 0.5, a["out"], a["stream"])
+
+
+class Tensor:
+    """What marshalling asks a tensor for."""
+
+    def __init__(self, address=4096, shape=(7, 1)):
+        self.address, self.shape = address, shape
+
+    def is_contiguous(self):
+        return True
+
+    def data_ptr(self):
+        return self.address
+
+
+class Stream:
+    def __init__(self, handle):
+        self.cuda_stream = handle
+
+
+class Parameter:
+    def __init__(self, value):
+        self._as_parameter_ = value
+
+
+@pytest.mark.parametrize("over,at,value", [
+    (dict(tokens=i32(6)), (3, 1), 6), (dict(tokens=np.int64(6)), (3, 1), 6), (dict(tokens=torch.tensor(6)), (3, 1), 6), (dict(tokens=Parameter(6)), (3, 1), 6),
+    (dict(tokens=Parameter(i32(-6))), (3, 1), -6), (dict(pages=i64(2 ** 40)), (3, 2), 2 ** 40), (dict(pages=np.int32(5)), (3, 2), 5), (dict(pages=True), (3, 2), 1),
+    (dict(k=Tensor(shape=(7.5, 1))), (3, 2), 7), (dict(k=Tensor(shape=(np.int64(7), 1))), (3, 2), 7), (dict(k=Tensor(shape=["7", 1])), (3, 2), 7),
+    (dict(q=Tensor(None)), (1, 1), None), (dict(q=Tensor(vp(64))), (1, 1), 64), (dict(q=Tensor(Parameter(64))), (1, 1), 64),
+    (dict(stream=Stream(None)), (3, 5), None), (dict(stream=Stream(vp(64))), (3, 5), 64), (dict(stream=Stream(True)), (3, 5), 1),
+])
+def test_integers_and_addresses_in_what_a_ctypes_call_takes(calls, over, at, value):
+    call(tensors(), **over)
+    assert calls[0][at[0]][at[1]] == value
+
+
+@pytest.mark.parametrize("over", [
+    dict(tokens=6.0), dict(tokens="6"), dict(tokens=i64(6)), dict(tokens=np.float32(6)), dict(pages=i32(7)), dict(pages=7.0), dict(pages=b"7"), dict(q=Tensor(np.int64(64))),
+    dict(q=Tensor(64.0)), dict(q=Tensor(i64(64))), dict(stream=Stream(np.int64(5))), dict(stream=Stream(5.0)), dict(stream=Stream(i32(5))),
+])
+def test_integers_and_addresses_that_a_ctypes_call_refuses(calls, over):
+    with pytest.raises(ctypes.ArgumentError):
+        call(tensors(), **over)
+    assert calls == []
+
+
 def test_refusals(calls):
     t = tensors()
     m = binding._marshal
