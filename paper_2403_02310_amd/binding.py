@@ -127,6 +127,15 @@ def _i32(a) -> np.ndarray:
     return np.ascontiguousarray(a, dtype=np.int32)
 
 
+def _lengths(q_start, q_len, ctx_len):
+    """The three arrays of a batch, none of which ends before q_len does: the C calls read as many of each."""
+    qs, ql, cl = _i32(q_start), _i32(q_len), _i32(ctx_len)
+    if qs.size < len(ql) or ql.size < len(ql) or cl.size < len(ql):
+        raise ValueError("q_start, q_len and ctx_len need one for each sequence of q_len (%d), got %d, %d and %d"
+                         % (len(ql), qs.size, ql.size, cl.size))
+    return qs, ql, cl
+
+
 def _ptr(a: Optional[np.ndarray]):
     return None if a is None else a.ctypes.data_as(_i32p)
 
@@ -239,7 +248,7 @@ class Handle:
 
     # ---- entry points ----------------------------------------------------
     def plan(self, q_start, q_len, ctx_len, num_tokens: Optional[int] = None, with_items: bool = True):
-        qs, ql, cl = _i32(q_start), _i32(q_len), _i32(ctx_len)
+        qs, ql, cl = _lengths(q_start, q_len, ctx_len)
         n = int(ql.sum()) if num_tokens is None else num_tokens
         info = PlanInfo()
         self._check(lib.sarathi_plan_hybrid_attention(self._h, _ptr(qs), _ptr(ql), _ptr(cl), len(ql), n,
@@ -285,7 +294,7 @@ class PreparedBatch:
     """Host length arrays converted once, for callers that time repeated iterations."""
 
     def __init__(self, q_start, q_len, ctx_len):
-        self.q_start, self.q_len, self.ctx_len = _i32(q_start), _i32(q_len), _i32(ctx_len)
+        self.q_start, self.q_len, self.ctx_len = _lengths(q_start, q_len, ctx_len)
         self.num_seqs = len(self.q_len)
         self.num_tokens = int(self.q_len.sum())
         self.p_q_start, self.p_q_len, self.p_ctx_len = _ptr(self.q_start), _ptr(self.q_len), _ptr(self.ctx_len)

@@ -110,9 +110,10 @@ struct Lengths {
     }
     const int32_t *data() const { return aligned.empty() ? static_cast<const int32_t *>(view.buf) : aligned.data(); }
     int32_t count() const { return static_cast<int32_t>(view.shape[0]); }
+    Py_ssize_t all() const { return view.len / 4; }
     int64_t sum() const {
         int64_t s = 0;
-        for (Py_ssize_t i = 0; i < view.len / 4; ++i) s += data()[i];
+        for (Py_ssize_t i = 0; i < all(); ++i) s += data()[i];
         return s;
     }
 };
@@ -154,6 +155,11 @@ struct Batch {
     bool get(int64_t max_blocks, PyObject *block_table, PyObject *qs, PyObject *ql, PyObject *cl, PyObject *pages, PyObject *tokens, PyObject *k_cache) {
         if (!q_start.get(qs) || !q_len.get(ql) || !ctx_len.get(cl)) return false;
         num_seqs = q_len.count();
+        if (q_start.all() < num_seqs || q_len.all() < num_seqs || ctx_len.all() < num_seqs) {
+            PyErr_Format(PyExc_ValueError, "q_start, q_len and ctx_len need one for each sequence of q_len (%d), got %zd, %zd and %zd", (int)num_seqs,
+                         q_start.all(), q_len.all(), ctx_len.all());
+            return false;
+        }
         uint64_t v;
         if (tokens == Py_None) num_tokens = static_cast<int32_t>(q_len.sum());
         else if (as_int(tokens, as_c_int32, &v)) num_tokens = static_cast<int32_t>(v);

@@ -139,6 +139,28 @@ def test_integers_and_addresses_that_a_ctypes_call_refuses(calls, over):
     assert calls == []
 
 
+@pytest.mark.parametrize("form", [list, lambda a: np.array(a, np.int32), unaligned])
+def test_lengths_that_end_before_the_batch_are_refused(calls, form):
+    """The C call reads as many of each as q_len has; more are taken, as buffers of a full batch are handed over."""
+    t, m = tensors(), binding._marshal
+    for j in (0, 2):
+        for short in ([], LENGTHS[j][:2]):
+            lengths = [form(short if i == j else a) for i, a in enumerate(LENGTHS)]
+            with pytest.raises(ValueError, match="one for each sequence"):
+                m.attention(11, MAX_BLOCKS, t["q"], t["k"], t["v"], t["table"], *lengths, None, None, 0.5, t["out"], 9)
+            with pytest.raises(ValueError, match="one for each sequence"):
+                m.kv_append(11, MAX_BLOCKS, t["k_new"], t["v_new"], t["k"], t["v"], t["table"], *lengths, None, None, t["ws"], 9)
+    assert calls == []
+    m.attention(11, MAX_BLOCKS, t["q"], t["k"], t["v"], t["table"], form(LENGTHS[0] + [9]), form(LENGTHS[1]), form(LENGTHS[2] + [9, 9]), None, None, 0.5, t["out"], 9)
+    m.attention(11, MAX_BLOCKS, t["q"], t["k"], t["v"], t["table"], form(LENGTHS[0]), np.array(LENGTHS[1])[:, None], np.array([LENGTHS[2]]), None, None, 0.5, t["out"], 9)
+    assert [c[2] for c in calls] == [LENGTHS, LENGTHS]
+    h = binding.Handle(2, 1, 64, max_tokens=64, max_seqs=8, max_blocks_per_seq=MAX_BLOCKS)
+    for call_with in (h.plan, binding.PreparedBatch):
+        for j in (0, 2):
+            with pytest.raises(ValueError, match="one for each sequence"):
+                call_with(*(form(a[:2] if i == j else a) for i, a in enumerate(LENGTHS)))
+
+
 def test_refusals(calls):
     t = tensors()
     m = binding._marshal
