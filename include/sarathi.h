@@ -323,11 +323,15 @@ typedef struct {
     int32_t feature_tile, token_tile;    /* output features x tokens of a workgroup's tile */
     int32_t feature_tiles, token_tiles;  /* how many of them; feature tiles that end short of out_features are those of full rounds of
                                           * workgroups, and the features behind them run with a tiling of their own in a second launch */
-    int32_t pieces;                      /* of the k range; more than one: fp32 partial tiles and a second kernel */
+    int32_t pieces;                      /* of the k range, in this launch; more than one: fp32 partial tiles and a second kernel */
     int32_t k_per_piece;
 } sarathi_linear_plan;
 sarathi_status sarathi_plan_linear(int32_t num_tokens, int32_t out_features, int32_t in_features, size_t workspace_bytes,
                                    sarathi_linear_plan *out);
+/* The same for the features behind the first tiling's (feature_tile * feature_tiles of sarathi_plan_linear); all zero where that covers
+ * the layer.  The call uses a workspace if either tiling has pieces. */
+sarathi_status sarathi_plan_linear_rest(int32_t num_tokens, int32_t out_features, int32_t in_features, size_t workspace_bytes,
+                                        sarathi_linear_plan *out);
 
 #ifdef __cplusplus
 }

@@ -69,7 +69,7 @@ class LinearPlan(ctypes.Structure):
 EXPORTED = ["sarathi_create", "sarathi_destroy", "sarathi_workspace_bytes", "sarathi_last_error",
             "sarathi_set_option", "sarathi_kv_append", "sarathi_hybrid_attention",
             "sarathi_plan_hybrid_attention", "sarathi_build_stall_free_batch", "sarathi_get_kernel_times",
-            "sarathi_linear", "sarathi_linear_workspace_bytes", "sarathi_plan_linear",
+            "sarathi_linear", "sarathi_linear_workspace_bytes", "sarathi_plan_linear", "sarathi_plan_linear_rest",
             "sarathi_hybrid_attention_noalloc"]
 
 if not os.path.exists(LIB_PATH):
@@ -117,8 +117,9 @@ lib.sarathi_build_stall_free_batch.argtypes = [ctypes.c_int32, ctypes.c_int32,
                                                ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.POINTER(Batch)]
 lib.sarathi_linear_workspace_bytes.restype = ctypes.c_size_t
 lib.sarathi_linear_workspace_bytes.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_int32]
-lib.sarathi_plan_linear.restype = ctypes.c_int
-lib.sarathi_plan_linear.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, ctypes.c_size_t, ctypes.POINTER(LinearPlan)]
+for _f in (lib.sarathi_plan_linear, lib.sarathi_plan_linear_rest):
+    _f.restype = ctypes.c_int
+    _f.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, ctypes.c_size_t, ctypes.POINTER(LinearPlan)]
 lib.sarathi_linear.restype = ctypes.c_int
 lib.sarathi_linear.argtypes = [_vp, _vp, _vp, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, _vp, ctypes.c_size_t, _vp]
 
@@ -346,15 +347,26 @@ def linear_workspace_bytes(num_tokens: int, out_features: int, in_features: int)
     return int(lib.sarathi_linear_workspace_bytes(num_tokens, out_features, in_features))
 
 
-def plan_linear(num_tokens: int, out_features: int, in_features: int, workspace_bytes: Optional[int] = None) -> LinearPlan:
-    """Tiling ``linear`` would launch with that much workspace (None: as much as it asks for)."""
+def _plan_linear(f, num_tokens: int, out_features: int, in_features: int, workspace_bytes: Optional[int]) -> LinearPlan:
     if workspace_bytes is None:
         workspace_bytes = linear_workspace_bytes(num_tokens, out_features, in_features)
     out = LinearPlan()
-    st = lib.sarathi_plan_linear(num_tokens, out_features, in_features, workspace_bytes, ctypes.byref(out))
+    st = f(num_tokens, out_features, in_features, workspace_bytes, ctypes.byref(out))
     if st != 0:
-        raise SarathiError(st, "sarathi_plan_linear(T=%d, N=%d, K=%d) failed" % (num_tokens, out_features, in_features))
+        raise SarathiError(st, "%s(T=%d, N=%d, K=%d) failed" % (f.__name__, num_tokens, out_features, in_features))
     return out
+
+
+def plan_linear(num_tokens: int, out_features: int, in_features: int, workspace_bytes: Optional[int] = None) -> LinearPlan:
+    """Tiling ``linear`` would launch with that much workspace (None: as much as it asks for); where it ends short of
+    ``out_features``, ``plan_linear_rest`` has the others'."""
+    return _plan_linear(lib.sarathi_plan_linear, num_tokens, out_features, in_features, workspace_bytes)
+
+
+def plan_linear_rest(num_tokens: int, out_features: int, in_features: int, workspace_bytes: Optional[int] = None) -> Optional[LinearPlan]:
+    """Tiling of the features behind the first tiling's, a launch of its own; None where there are none."""
+    p = _plan_linear(lib.sarathi_plan_linear_rest, num_tokens, out_features, in_features, workspace_bytes)
+    return p if p.feature_tiles > 0 else None
 
 
 def linear(x, w, y, workspace=None, stream=None) -> None:

@@ -24,13 +24,23 @@ extern "C" size_t sarathi_linear_workspace_bytes(int32_t num_tokens, int32_t out
     return plan_linear_parts(num_tokens, out_features, in_features, SIZE_MAX).workspace_bytes(num_tokens, out_features);
 }
 
-extern "C" sarathi_status sarathi_plan_linear(int32_t num_tokens, int32_t out_features, int32_t in_features,
-                                              size_t workspace_bytes, sarathi_linear_plan *out) {
+static sarathi_status plan_part(int part, int32_t num_tokens, int32_t out_features, int32_t in_features, size_t workspace_bytes,
+                                sarathi_linear_plan *out) {
     if (!out || num_tokens == 0) return SARATHI_EINVAL;
     if (!shape_ok(num_tokens, out_features, in_features)) return SARATHI_ESHAPE;
-    const LinearPlan pl = plan_linear_parts(num_tokens, out_features, in_features, workspace_bytes).part[0];
+    const LinearPlan pl = plan_linear_parts(num_tokens, out_features, in_features, workspace_bytes).part[part];
     *out = sarathi_linear_plan{pl.feature_tile, pl.token_tile, pl.n_tiles, pl.t_tiles, pl.splits, pl.k_per_split};
     return SARATHI_OK;
+}
+
+extern "C" sarathi_status sarathi_plan_linear(int32_t num_tokens, int32_t out_features, int32_t in_features,
+                                              size_t workspace_bytes, sarathi_linear_plan *out) {
+    return plan_part(0, num_tokens, out_features, in_features, workspace_bytes, out);
+}
+
+extern "C" sarathi_status sarathi_plan_linear_rest(int32_t num_tokens, int32_t out_features, int32_t in_features,
+                                                   size_t workspace_bytes, sarathi_linear_plan *out) {
+    return plan_part(1, num_tokens, out_features, in_features, workspace_bytes, out);
 }
 
 extern "C" sarathi_status sarathi_linear(const void *x, const void *w, void *y, int32_t num_tokens,

@@ -380,8 +380,38 @@ def test_features_behind_the_full_rounds_get_a_tiling_of_their_own(T, N, K, firs
         assert binding.plan_linear(T, N, K, 0).pieces == 1
 
 
+@pytest.mark.parametrize("T,N,K,rest", [(1025, 13184, 1984, (128, 64, 7)), (577, 26240, 3008, (128, 64, 10)), (2048, 14336, 8192, (192, 256, 1)), (2048, 8192, 7168, None)])
+def test_plan_linear_rest_is_the_second_tiling(T, N, K, rest):
+    p = binding.plan_linear_rest(T, N, K)
+    assert (p and (p.feature_tile, p.token_tile, p.pieces)) == rest
+
+
+def test_the_two_tilings_cover_the_features_and_ask_for_the_workspace():
+    rng = np.random.default_rng(3)
+    two = 0
+    for _ in range(600):
+        T, N, K = int(np.exp(rng.uniform(0, np.log(2500)))), 128 * int(rng.integers(1, 240)), 64 * int(rng.integers(1, 230))
+        for ws in (None, 0, 1 << 22):
+            first, rest = binding.plan_linear(T, N, K, ws), binding.plan_linear_rest(T, N, K, ws)
+            covered = first.feature_tile * first.feature_tiles
+            assert (covered < N) == (rest is not None)
+            need = 0
+            for p, features in ((first, min(N, covered)),) + (((rest, N - covered),) if rest else ()):
+                assert p.feature_tile * (p.feature_tiles - 1) < features <= p.feature_tile * p.feature_tiles
+                assert p.token_tile * (p.token_tiles - 1) < T <= p.token_tile * p.token_tiles
+                assert p.k_per_piece * (p.pieces - 1) < K <= p.k_per_piece * p.pieces
+                need = max(need, 4 * p.pieces * T * features if p.pieces > 1 else 0)
+            if ws is None:
+                assert binding.linear_workspace_bytes(T, N, K) == need
+                two += rest is not None
+            else:
+                assert need <= ws
+    assert two > 20
+
+
 def test_plan_linear_refuses_what_linear_refuses():
     out = binding.LinearPlan()
-    assert binding.lib.sarathi_plan_linear(0, 128, 64, 0, ctypes.byref(out)) == binding.EINVAL
-    assert binding.lib.sarathi_plan_linear(4, 100, 64, 0, ctypes.byref(out)) == binding.ESHAPE
-    assert binding.lib.sarathi_plan_linear(4, 128, 64, 0, None) == binding.EINVAL
+    for plan in (binding.lib.sarathi_plan_linear, binding.lib.sarathi_plan_linear_rest):
+        assert plan(0, 128, 64, 0, ctypes.byref(out)) == binding.EINVAL
+        assert plan(4, 100, 64, 0, ctypes.byref(out)) == binding.ESHAPE
+        assert plan(4, 128, 64, 0, None) == binding.EINVAL
