@@ -1067,7 +1067,7 @@ LinearParts plan_linear_parts(int32_t T, int32_t N, int32_t K, size_t workspace_
         if (first_us + 1.53 * (N - first) * feature_us >= bar) continue;  // (the least that the rest can cost)
         double rest_us;
         const LinearPlan rest = plan_phased(T, N - first, K, workspace_bytes, &rest_us, bar - first_us);
-        if (first_us + rest_us >= bar) continue;
+        if (rest.n_tiles == 0 || first_us + rest_us >= bar) continue;  // (none below the limit, whatever the two sums round to)
         bar = first_us + rest_us;
         best = LinearParts{first, {LinearPlan{sh.features(), sh.tokens(), whole, (int32_t)t_tiles, 1, K}, rest}};
     }
