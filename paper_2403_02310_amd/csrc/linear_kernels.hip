@@ -92,7 +92,8 @@ __device__ __forceinline__ void lin_wavefront_lds_order() {
 // through the builtin the compiler gives each of up to 256 results new registers and copies them back, 234 to 658 moves per
 // two stages, and spills in the key loop of the largest shape (2048 x 8192 x 7168: 522 us).  The compiler does not see that this
 // is a matrix instruction, so the caller keeps the distances that the hardware does not: other instructions read c from 8 wait
-// states on, and the instruction reads a, b and c from 2 wait states after a vector instruction wrote them.
+// states on, and the instruction reads a, b and c from 2 wait states after a vector instruction wrote them.  Whether the registers that the
+// compiler chose leave them so is looked up in its assembly (tests/test_device_code.py): a copy or a spill in between gives wrong sums.
 __device__ __forceinline__ void lin_mfma_in_place(lf32x4 &c, const lbf16x8 &a, const lbf16x8 &b) {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
