@@ -408,15 +408,6 @@ __global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {
         else fb[decltype(set)::value][b][s] = v;
     };
     lf32x4 acc[NI][NJ][4];  // of a 32 x 32 block: features 16 (q / 2) .., tokens 16 (q % 2) ..
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                acc[i][j][q] = lf32x4{0.f, 0.f, 0.f, 0.f};
-                asm volatile("" : "+a"(acc[i][j][q]));  // zeros in place before the first barrier, far from the first MFMA
-            }
     auto mfma = [&](int a, int na, int nb, int b_first, const lbf16x8 (&b_ops)[BX][4], int m) {
         const int kh = m / (na * nb * 4), e = m / 4 % (na * nb);
         const int j = e / na, i = (j & 1) ? na - 1 - e % na : e % na;  // consecutive MFMAs share an operand
@@ -450,6 +441,17 @@ __global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {
 #pragma unroll
         for (int i = 0; i < half_loads(HA1); ++i) issue(TA1{}, i, st, st);
     }
+    // Zeros in place while the loads are on their way, before the first barrier and far from the first MFMA (in front of the loads
+    // they kept them back for a clock quad each).
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                acc[i][j][q] = lf32x4{0.f, 0.f, 0.f, 0.f};
+                asm volatile("" : "+a"(acc[i][j][q]));
+            }
     LIN_PHASE_HEAD(RING * LOADS - 2 * A0);
 #pragma unroll
     for (int q = 0; q < 4 * A0; ++q) read(TA0{}, S0{}, q, 0);
