@@ -555,6 +555,7 @@ __global__ __launch_bounds__(256, 1) void linear_phased_kernel(LinearParams p) {
         // that is stored next to the last MFMAs, which the compiler does not know to wait for.
         int strip_lane = lane;
         asm volatile("" : "+v"(strip_lane));
+        strip_lane &= 63;  // known to the compiler again: rows and pieces without signed divisions
         const int n = strip_lane & 15, g = strip_lane >> 4;
 #pragma unroll
         for (int i = 0; i < NI; ++i)
