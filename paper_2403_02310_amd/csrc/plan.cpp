@@ -531,7 +531,7 @@ bool chunks_as_wave_tiles(const sarathi_config &cfg, const Options &opt, const W
                           int32_t num_seqs) {
     if (opt.tile_split_keys > 0 || opt.resident_chunks == 1 || opt.interleave != 2) return false;  // asks for chunk tiles
     const int64_t G = cfg.num_q_heads / cfg.num_kv_heads;
-    int64_t tiles = 0, chunk_tiles = 0, span = 0, other_span = 0;  // spans: of the chunks, of the others
+    int64_t tiles = 0, chunk_tiles = 0, span = 0, other_span = 0, other_keys = 0;  // spans: of the chunks, of the others
     for (int32_t s = 0; s < num_seqs; ++s) {
         const int64_t n = ((int64_t)q_len[s] * G + kWaveCols - 1) / kWaveCols;
         const int64_t keys = opt.window > 0 ? std::min<int64_t>(ctx_len[s], opt.window + q_len[s]) : ctx_len[s];
@@ -539,6 +539,7 @@ bool chunks_as_wave_tiles(const sarathi_config &cfg, const Options &opt, const W
         if (n > 64 || tiles * cfg.num_kv_heads > 512) return false;
         if ((int64_t)q_len[s] * G < kChunkMinCols) {
             other_span = std::max(other_span, keys);
+            other_keys += n * keys;
             continue;
         }
         chunk_tiles += n;
@@ -551,6 +552,18 @@ bool chunks_as_wave_tiles(const sarathi_config &cfg, const Options &opt, const W
     // Decodes that run longer hide the chunks either way, and next to them two blocks to a compute unit take each other's rate (88
     // tokens behind 527 next to 14 decodes of up to 2655 keys, 56 and 8 heads, 30.5 and 35.1; 44 next to 8 of 2328 17.0 and 18.7).
     const double other_us = (double)other_span * cfg.head_dim * 4.0 / 55.0e3;
+    // Decodes that stream for longer than the chunk tiles take hide those, and wave tiles take from their rate (us a pass: 121 tokens
+    // behind 813 next to 167 decodes that stream 4.0 times as long, 4 heads and one of 64 channels, 47.5 and 53.6; 50 behind 552 next to
+    // 6, 3.9 times, 32 and 8 heads, 47.2 and 57.9; of 190 drawn batches beyond 1.5 times 26 are more than 3 % slower as wave tiles, and the
+    // average is 1.02 x faster; of 59 between 1.0 and 1.5 times 4, and 1.11 x).
+    const double stream_us = (double)other_keys * cfg.num_kv_heads * cfg.head_dim * 4.0 / 6.5e6;
+    if (stream_us > 1.5 * chunk_us) return false;
+    // Decodes that are cut next to chunk tiles too (25 us at a block's rate) bring a merge along, with which those are cut at no further
+    // launch, while wave tiles of long contexts are cut into eight times as many pieces (61 tokens behind 1395 next to 5 decodes of up to
+    // 7618 keys, 32 and 8 heads, 25.4 and 36.6; 228 behind 893 next to 80 of up to 4965, 4 heads and one of 64 channels, 17.9 and 20.4; 52
+    // behind 964 next to 14 of up to 2934, 32 and 8 heads, 33.1 and 24.5; behind 1445 next to two of up to 3716, which hardly stream, 19.5 and 16.6;
+    // allocation-free, where the host pays for each piece, 65 behind 1 and 48 behind 1639 next to 34 of up to 10,291, 4 heads and one of 64, 20.6 and 27.0).
+    if (span > 1100 && (double)other_span * cfg.head_dim * 4.0 / 40.0e3 >= 25.0 && (ws.meta_per_launch != 0 || stream_us > 0.15 * chunk_us)) return false;
     if (span > (alone ? 1792 : 896) || std::max(wave_us, std::min(other_us, alone ? 8.0 : 1.0e9)) + 1.0 >= chunk_us) return false;
     // a plan that travels in kernel arguments has to fit one launch so
     return ws.meta_per_launch == 0 || attn_meta_bytes((size_t)tiles, (size_t)tiles, 0) <= ws.meta_per_launch;

@@ -142,6 +142,21 @@ def test_short_chunks_of_small_batches_run_as_wave_tiles(heads, q_len, ctx_len, 
         assert _coverage_check(b, window=window, **asks).num_tile_items > 0
 
 
+@pytest.mark.parametrize("heads,q_len,ctx_len,chunk_tiles", [
+    ((32, 8, 128), [61] + [1] * 5, [1456] + [7618, 6000, 4000, 3000, 2802], True),       # decodes that are cut, 1456 keys
+    ((32, 8, 128), [61] + [1] * 5, [1100] + [7618, 6000, 4000, 3000, 2802], False),      # up to 1100
+    ((32, 8, 128), [61] + [1] * 5, [1456] + [1900] * 5, False),                          # decodes that stay whole
+    ((32, 8, 128), [43] + [1] * 2, [1488] + [3716, 631], False),                         # and hardly stream
+    ((4, 1, 64), [228] + [1] * 80, [1121] + [4965] + [1156] * 79, True),
+    ((4, 1, 64), [121] + [1] * 167, [934] + [5862] * 167, True),                         # decodes stream four times as long as the chunk
+    ((32, 8, 128), [49] + [1] * 11, [569] + [2151] * 11, True), ((32, 8, 128), [49] + [1] * 10, [569] + [2151] * 10, False),   # 1.6 and 1.5 times
+])
+def test_short_chunks_stay_chunk_tiles_next_to_long_decodes(heads, q_len, ctx_len, chunk_tiles):
+    """Where the decodes hide the chunks, or are cut and merged anyway, as chunk tiles of long contexts then are."""
+    b = wl._make("short_chunks", wl.AttnShape(*heads), q_len, ctx_len, 6)
+    assert (_coverage_check(b).num_tile_items > 0) == chunk_tiles
+
+
 @pytest.mark.parametrize("window", [1, 33, 500, 4096])
 def test_plan_coverage_under_a_sliding_window(window):
     """Pieces start at the 32-key tile that holds the first key of the tile's first row's window."""
