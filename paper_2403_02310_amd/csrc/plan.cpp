@@ -435,7 +435,12 @@ double hybrid_launch_us(const sarathi_config &cfg, const std::vector<ChunkBin> &
 // whole decodes on average; 8 decodes of 256-4096 keys: 53 -> 19 + 6 us.  A cut has to promise 5 %, and
 // below 18 us (28 next to chunk tiles) nothing is cut: the merge is one launch more, 3 us a pass (us a pass, whole and cut: a decode of
 // 3072 keys of 64 channels 20.0 and 13.8, of 2048, estimated at 16, 15.3 and 13.9, of 1536 13.0 and 14.0; of 1536 of 128 channels, 22.7, 16.5
-// and 14.1, of 1024, 16.2, 12.9 and 13.7; next to 191 tokens two of 1293, 56 and 8 heads, 16.3 and 19.2).
+// and 14.1, of 1024, 16.2, 12.9 and 13.7; next to 191 tokens two of 1293, 56 and 8 heads, 16.3 and 19.2).  From 18 to 28 us the host decides:
+// it is done with an iteration whose decodes are cut after 12.8 us and 0.03 for each of their tiles, in an allocation-free call, where the
+// cut also costs the launches that put the plan into memory, after 15.8 us and 0.09, and whole they take 0.85 and 0.8 of the estimate (us a
+// pass, whole and cut: 4 heads and one of 64 channels, 168 decodes 21.9 and 18.3, 212 18.5 and 21.8, 348 18.5 and 24.3; allocation-free one
+// decode of 32 and 8 heads estimated at 19.7 14.9 and 15.9, at 26.9 18.3 and 15.0; 50 tiles of 64 channels at 18.8 17.4 and 20.3.  The dearest of
+// 330 drawn batches: 39 decodes of 32 and 8 heads at 23.8, allocation-free, stay whole, 20.6 and 18.3).
 // Fitted when a block pulled 40 GB/s alone; now that its loads go through LDS it pulls about 55, and the estimate fitted to that
 // chose no better (120 batches of few decodes 1.001 x, 110 hybrid ones 0.999 x).
 // Where one decode holds half of the keys or more, a plan that cuts it finer and leaves all of up to half its length whole
@@ -449,7 +454,7 @@ struct WaveCut {
     double us, as_is_us;  // of the launch and its merge by the estimate, cut so and by the rule for many decodes
 };
 WaveCut cheapest_wave_cut(const sarathi_config &cfg, const Plan &plan, size_t n_chunk_tiles, int64_t wave_keys, int64_t tile_split, int64_t wave_split,
-                          int64_t max_rows, bool chunks_made_do) {
+                          int64_t max_rows, bool chunks_made_do, bool plan_in_arguments) {
     const int64_t n_wave_tiles = (int64_t)(plan.tiles.size() - n_chunk_tiles);
     const double key_us = cfg.head_dim * 4.0;  // bytes of a key and its value, one KV head
     double chunk_steps = 0.0;
@@ -511,7 +516,8 @@ WaveCut cheapest_wave_cut(const sarathi_config &cfg, const Plan &plan, size_t n_
             if (c < std::min(0.95 * as_is, best.us)) best = WaveCut{keys, uncut, true, c, as_is};
         }
     };
-    if (as_is >= (n_chunk_tiles == 0 ? 18.0 : 28.0)) {
+    const double host_us = (plan_in_arguments ? 15.8 : 12.8) + (plan_in_arguments ? 0.09 : 0.03) * (double)n_wave_tiles;
+    if (as_is >= 28.0 || (n_chunk_tiles == 0 && as_is >= 18.0 && host_us < (plan_in_arguments ? 0.8 : 0.85) * as_is)) {
         if (whole > 0) search(whole);
         if (!best.few) search(0);
     }
@@ -712,7 +718,8 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
     int64_t wave_whole = 0;
     bool few_cut = false;
     if (opt.split_keys <= 0 && has_wave_tiles && (int64_t)(plan.tiles.size() - n_chunk_tiles) * cfg.num_kv_heads <= 512) {
-        WaveCut w = cheapest_wave_cut(cfg, plan, n_chunk_tiles, keys_of_kind[kKindWave], tile_split, wave_split, ws.max_part_rows, false);
+        WaveCut w = cheapest_wave_cut(cfg, plan, n_chunk_tiles, keys_of_kind[kKindWave], tile_split, wave_split, ws.max_part_rows, false,
+                                      ws.meta_per_launch != 0);
         auto wave_count = [&]() { return count_splits(plan, n_chunk_tiles, plan.tiles.size(), w.keys, w.whole); };
         const int64_t wave_rows = wave_count().rows;
         if (w.few && wave_rows + chunk_count(tile_split).rows > ws.max_part_rows) {
@@ -722,7 +729,7 @@ void plan_attention(const sarathi_config &cfg, const Options &opt, const Workspa
             // (512 tokens behind 3871 next to 9000 and 3000 keys: 89 us, 136 with both cuts doubled until they fit).
             if (opt.tile_split_keys <= 0) tile_split = cut_chunks(ws.max_part_rows - wave_rows);
             w = cheapest_wave_cut(cfg, plan, n_chunk_tiles, keys_of_kind[kKindWave], tile_split, wave_split,
-                                  std::max<int64_t>(0, ws.max_part_rows - chunk_count(tile_split).rows), true);
+                                  std::max<int64_t>(0, ws.max_part_rows - chunk_count(tile_split).rows), true, ws.meta_per_launch != 0);
         }
         if (w.few && host_pays(w.us, w.as_is_us, chunk_count(tile_split), wave_count(), chunk_count(tile_split))) {
             wave_split = w.keys;

@@ -157,6 +157,17 @@ def test_short_chunks_stay_chunk_tiles_next_to_long_decodes(heads, q_len, ctx_le
     assert (_coverage_check(b).num_tile_items > 0) == chunk_tiles
 
 
+@pytest.mark.parametrize("heads,n,keys,cut", [
+    ((4, 1, 64), 60, 2500, True), ((4, 1, 64), 212, 2500, False), ((4, 1, 64), 348, 2200, False),   # the host's time for the pieces
+    ((4, 1, 64), 348, 4200, True),                                                                   # estimated at 28 us and more
+    ((16, 2, 128), 40, 1250, True), ((32, 8, 128), 1, 1300, True), ((32, 8, 128), 1, 1024, False),
+])
+def test_decodes_are_cut_where_the_host_is_done_sooner(heads, n, keys, cut):
+    ctx_len = [keys] + [max(1, keys // 7)] * (n - 1)
+    b = wl._make("few_decodes", wl.AttnShape(*heads), [1] * n, ctx_len, 7)
+    assert (_coverage_check(b).num_reduce_items > 0) == cut
+
+
 @pytest.mark.parametrize("window", [1, 33, 500, 4096])
 def test_plan_coverage_under_a_sliding_window(window):
     """Pieces start at the 32-key tile that holds the first key of the tile's first row's window."""
