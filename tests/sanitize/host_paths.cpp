@@ -68,6 +68,7 @@ static int32_t g_lds_pad_bytes = 0; // of the last attention launch
 static int g_which = 0;             // and its kind
 static int32_t g_queue_blocks = 0;
 static int g_queued_launches = 0;
+static size_t g_plan_bytes = 0;     // of the plan in the last attention launch's arguments
 
 int launch_kv_append(const sarathi_config &cfg, const AppendMeta &m, const void *k_new, const void *v_new, void *k_cache,
                      void *v_cache, int64_t num_pages, void *) {
@@ -188,9 +189,21 @@ static void play_queues(const AttnMeta &m, int H, int which) {
 // Every (column, key) pair of the batch must be covered by exactly one work unit, every unit must stay inside
 // its sequence, and every partial row / counter a unit or merge item names must lie inside its buffer (touched
 // here so that ASan sees an overrun).
-int launch_attention(const sarathi_config &cfg, const AttnMeta &m, const void *, const void *, const void *, int64_t,
+int launch_attention(const sarathi_config &cfg, const AttnMeta &given, const void *, const void *, const void *, int64_t,
                      float, void *, int which, void *) {
     const int H = cfg.num_kv_heads, D = cfg.head_dim;
+    // A plan in the launch's arguments: the kernels see so many bytes and nothing behind them.
+    AttnMeta m = given;
+    std::vector<char> arguments(m.plan_bytes);
+    g_plan_bytes = m.plan_bytes;
+    if (m.plan_bytes > 0) {
+        CHECK(m.plan_bytes <= kPlanArgBytes && m.queue_blocks == 0 && m.num_reduce_units == 0);
+        const size_t units = (size_t)(reinterpret_cast<const char *>(m.units) - reinterpret_cast<const char *>(m.tiles));
+        std::memcpy(arguments.data(), m.tiles, m.plan_bytes);
+        m.tiles = reinterpret_cast<const TileDesc *>(arguments.data());
+        m.units = reinterpret_cast<const uint32_t *>(arguments.data() + units);
+        CHECK(units + sizeof(uint32_t) * (size_t)m.num_units <= m.plan_bytes);
+    }
     g_lds_pad_bytes = m.lds_pad_bytes;
     g_which = which;
     g_queue_blocks = m.queue_blocks;
@@ -435,6 +448,8 @@ static void drive_host_bound_cuts() {
     Batch batches[] = {{4, 1, 64, {130}, {130}, false},
                        {32, 8, 128, std::vector<int32_t>(8, 1), {500, 1000, 1500, 2000, 2500, 3000, 3500, 4000}, true},
                        {64, 8, 128, {625, 1, 1}, {912, 3403, 3440}, true},
+                       {64, 8, 128, {1}, {1200}, false},   // whole it takes one launch, cut four
+                       {32, 8, 128, {1}, {1750}, true},
                        {8, 2, 128, {300, 1, 37, 1, 1, 200}, {1300, 555, 37, 1, 7000, 900}, true}};
     for (int32_t i = 0; i < 54; ++i) {
         batches[0].q_len.push_back(1);
@@ -603,6 +618,40 @@ static void drive_queue_by_rule() {
     }
 }
 
+// Which allocation-free calls carry their plan in the attention launch's arguments: those whose tiles fit, with nothing cut and no queue.
+static void drive_plans_in_arguments() {
+    struct Batch {
+        int32_t chunk, decodes, keys;
+        int64_t queue;
+        size_t bytes;   // of tiles and units; 0: in memory
+    };
+    const Batch batches[] = {{0, 1, 40, -1, 52},      {0, 18, 40, -1, 936},    {0, 19, 40, -1, 988}, {0, 73, 40, -1, 3796}, {0, 74, 40, -1, 0},
+                             {300, 60, 40, -1, 3640}, {300, 63, 40, -1, 3796}, {300, 64, 40, -1, 0}, {0, 18, 40, 1, 0},     {0, 2, 7000, -1, 0}};
+    for (const Batch &b : batches)
+        for (const int64_t interleave : {2, 1, 0}) {
+            const int32_t S = b.decodes + (b.chunk > 0), T = b.decodes + b.chunk, blocks = 500;
+            const sarathi_config cfg{8, 2, 128, 16, 0, T, S, blocks};
+            std::vector<int32_t> qs, ql, cl, bt((size_t)S * blocks, 0);
+            if (b.chunk > 0) { qs.push_back(0); ql.push_back(b.chunk); cl.push_back(b.chunk + 40); }
+            for (int32_t i = 0; i < b.decodes; ++i) { qs.push_back(b.chunk + i); ql.push_back(1); cl.push_back(b.keys); }
+            sarathi_handle *h = nullptr;
+            CHECK(sarathi_create(&cfg, &h) == SARATHI_OK);
+            CHECK(sarathi_set_option(h, "interleave", interleave) == SARATHI_OK && sarathi_set_option(h, "item_queue", b.queue) == SARATHI_OK);
+            char dummy[16];
+            void *ws = nullptr;
+            CHECK(posix_memalign(&ws, 256, sarathi_workspace_bytes(h)) == 0);
+            sarathi::g_num_seqs = S;
+            sarathi::g_num_tokens = T;
+            CHECK(sarathi_hybrid_attention_noalloc(h, dummy, dummy, dummy, bt.data(), qs.data(), ql.data(), cl.data(), S, T, 1, 0.1f, dummy,
+                                                   nullptr) == SARATHI_OK);
+            CHECK(sarathi::g_plan_bytes == b.bytes);
+            CHECK(sarathi_hybrid_attention(h, dummy, dummy, dummy, bt.data(), qs.data(), ql.data(), cl.data(), S, T, 1, 0.1f, dummy, ws, nullptr) == SARATHI_OK);
+            CHECK(sarathi::g_plan_bytes == 0);
+            CHECK(sarathi_destroy(h) == SARATHI_OK);
+            std::free(ws);
+        }
+}
+
 static void drive_checker() {
     // one chunk on a prefix and two decodes, GQA 4:2, d = 8; every buffer exactly as large as documented
     const int Hq = 4, Hkv = 2, d = 8;
@@ -649,6 +698,7 @@ int main() {
     drive_queues();
     drive_roles_by_rule();
     drive_queue_by_rule();
+    drive_plans_in_arguments();
     drive_checker();
     std::printf("host paths clean (sink %llu)\n", (unsigned long long)sarathi::g_sink);
     return 0;

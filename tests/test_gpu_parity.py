@@ -81,6 +81,12 @@ def test_edge_lengths(hx):
     _check_batch(hx, b)
 
 
+@pytest.mark.parametrize("decodes", [1, 24, 25, 224, 225])
+def test_append_records_in_either_argument_block_or_in_memory(hx, decodes):
+    """A decode is one record: up to 24 of them in a small argument block, up to 224 in a large one, more in memory."""
+    _check_batch(hx, wl._make("append_records", wl.AttnShape(4, 2, 64), [1] * decodes, [1 + 7 * i % 90 for i in range(decodes)], 79))
+
+
 def test_long_decode_uses_splits_and_matches(hx):
     """Decodes of very different lengths: by default each is one block whose four wavefronts quarter the keys and
     merge in LDS; a decode beyond 6144 keys, and any decode under a forced small split size, is also split across

@@ -122,10 +122,11 @@ def _oracle_for_queries(batch, st, q_copy):
 
 @pytest.mark.parametrize("interleave", [2, 0])
 @pytest.mark.parametrize("heads", [(8, 2, 128), (4, 1, 64)])
-@pytest.mark.parametrize("chunks,decodes", [((), 1), ((), 73), ((), 74), ((300,), 0), ((300,), 3), ((300, 33), 60), ((300, 33), 61), ((300, 33), 62)])
+@pytest.mark.parametrize("chunks,decodes", [((), 1), ((), 18), ((), 19), ((), 73), ((), 74), ((300,), 0), ((300,), 3), ((300, 33), 60), ((300, 33), 61), ((300, 33), 62)])
 def test_noalloc_plan_in_the_launch_arguments_or_in_memory(chunks, decodes, heads, interleave):
-    """3840 bytes of plan travel with the attention launch (73 tiles of 52 bytes; the chunks have ten and two), more in launches of
-    their own: bit for bit the outputs of the workspace entry point, which reads the plan from memory."""
+    """3840 bytes of plan travel with the attention launch (73 tiles of 52 bytes; the chunks have ten and two; up to 18 of them in a smaller
+    argument block), more in launches of their own: bit for bit the outputs of the workspace entry point, which reads the plan from
+    memory.  (Which call takes which path is checked on the CPU, in tests/sanitize/host_paths.cpp.)"""
     from paper_2403_02310_amd import harness as hx
     q_len = list(chunks) + [1] * decodes
     ctx_len = [q + 40 for q in chunks] + [17 + 5 * i % 700 for i in range(decodes)]
