@@ -106,7 +106,8 @@ const char *sarathi_last_error(const sarathi_handle *handle);
  * wave-tile work per KV head the automatic choice aims for), "tile_split_keys" (keys per split of the 128-column chunk tiles, 0 =
  * automatic), "tile_min_cols" (sequences with at least this many columns q_len*G use chunk
  * tiles; unless it is set, 64, or none do in a small batch of short chunks, where 16-column tiles are faster), "plan_at_append" (0/1: sarathi_kv_append also plans and uploads the attention
- * metadata of its batch so that the following attention call needs no copy of its own),
+ * metadata of its batch so that the following attention call needs no copy of its own; the allocation-free call does not read it, so
+ * a program that makes no other attention calls saves the time with 0),
  * "interleave" (batches holding both prefill chunks and decodes: 0 = chunk-tile kernel then
  * wave-tile kernel on the caller's stream, 1 = chunk-tile kernel and the merge of its split tiles
  * on a second stream next to the wave-tile kernel, 2 = one launch holding both kinds of block),

@@ -312,19 +312,19 @@ __global__ __launch_bounds__(kLinThreads, 1) void linear_kernel(LinearParams p) 
 // of 32 features x 32 tokens (4 x 4 in the largest shape: all 256 accumulation registers), so that a 256 x 256 tile reads
 // 8 operands of 1 KiB from LDS per 16 x 32 x 32 x 16 multiply-adds; eight wavefronts of 64 x 128 read 12 (195-205 us on 2048 x 8192 x 7168).
 // A block is four v_mfma_f32_16x16x32_bf16 rather than two v_mfma_f32_32x32x16_bf16 per 32 k: both issue at the matrix pipes' rate (16.3
-// and 32.3 clocks), but the smaller draws less power per multiply-add, and on N(0,1) values power sets the clock: 2181 against
-// 1869 TFLOP/s where nothing else runs, 1.91 against 1.67 GHz here (2048 x 8192 x 7168 180 -> 162 us, 2048 x 14336 x 8192 372 -> 346;
-// on zeros both 132).
+// and 32.3 clocks), but the smaller draws less power per multiply-add, and on N(0,1) values power sets the clock: 1.93 to 2.10
+// against 1.65 to 1.78 PFLOP/s where nothing else runs, 1.88 against 1.64 GHz here (2048 x 8192 x 7168 180 -> 160 us, 2048 x 14336 x
+// 8192 372 -> 346; on zeros both instructions 2.46 PFLOP/s at 2.4 GHz).
 //
 // A stage is worked off in phases: half A0 of the wavefront's weight rows x half B0 of its token rows, A0 x B1, A1 x B1,
 // A1 x B0, each over the stage's 64 k.  While a phase's MFMAs issue, the operands of the half that a later phase needs are
-// read into registers (8 reads per 16 MFMAs), and the barrier at the head of the next phase then frees that half's LDS for
+// read into registers (8 reads per 32 MFMAs), and the barrier at the head of the next phase then frees that half's LDS for
 // the stage RING stages on.  So LDS is refilled half by half and a fetch has 1.75 stages (RING = 2) to land; waiting for
 // whole stages gives it less than one of the two that 128 KiB hold, and the loop then waits for memory: 2048 x 8192 x 7168
 // on all-zero data 158 us by whole stages, 121 us by halves (with the 32 x 32 instruction, as the figures below).  The matrix pipes
-// are busy for 71 to 76 % of the cycles.
+// are busy for 75 % of the cycles (78 % with that).
 // One wavefront per SIMD leaves nobody to cover a wait, so a phase is laid out by hand: slot m issues its share of reads and
-// fetches, then MFMA m, and a scheduling barrier keeps the compiler from moving them (213 other instructions per 256 MFMAs).
+// fetches, then MFMA m, and a scheduling barrier keeps the compiler from moving them (204 other instructions per 256 MFMAs).
 // Accumulators go out through LDS as whole rows (16-byte stores, 128 to 256 contiguous bytes per token and wavefront): 5 us
 // less per tile than 8-byte stores from the accumulator layout.  The way out still takes 8.2 us for 256 x 256: each piece is
 // a predicated read, a wait and a store in a row.  No shape spills.
@@ -900,9 +900,11 @@ constexpr PhasedShape kPhasedShapes[] = {
 };
 constexpr size_t kNumPhasedShapes = sizeof(kPhasedShapes) / sizeof(kPhasedShapes[0]);
 
-// More than 64 tokens.  Cost of a tiling in microseconds, fitted to 3,600 timings (the 13 layer shapes of four models, 15
-// token counts from 40 to 2048, every tile shape and piece count that could compete; a tiling's time is met within 7 % rms,
-// the chosen one is 2 % slower than the best measured on average): the largest of
+// More than 64 tokens.  Cost of a tiling in microseconds, fitted to 3,600 timings of the kernels with the 32 x 32 x 16 instruction (the 13
+// layer shapes of four models, 15 token counts from 40 to 2048, every tile shape and piece count that could compete; met within 7 % rms).
+// The present kernels take 0.94 of it, within 6.5 % rms of that (2,809 timings, 260 layers of 65 to 2048 tokens, tilings up to a quarter dearer
+// than the chosen one), and the chosen tiling is 1.4 % slower than the best of those on average, 13.6 % at most (554 x 4608 x 7168).
+// The largest of
 //   rounds of workgroups (one per compute unit) x (stages per piece x stage time + the tile's way out, 8.2 us for 256 x 256),
 //   the padded product at 2.26 PFLOP/s, and the weights at 8.05 TB/s,
 // plus 0.53 of the other two (none hides the others entirely), 4.3 us per launch, and for pieces of k their fp32 partial
@@ -1049,9 +1051,9 @@ LinearPlan plan_linear(int32_t T, int32_t N, int32_t K, size_t workspace_bytes) 
 // More tiles than compute units: the features of the full rounds of one shape as they are, and the others, whose round would be partly
 // filled, with the tiling that suits them, in a launch of their own; taken where the two costs together are below the one.
 // us a call, one tiling and two: 2048 x 14336 x 8192 (448 tiles of 256 x 256) 346 and 323, 1156 x 14336 x 8192 (375 of 192 x 256) 256
-// and 217, 562 x 24192 x 3840 117 and 99, 1284 x 28672 x 4096 267 and 243, 576 x 28672 x 4096, estimated 2 % dearer, 128 and 126.  Of 320
-// drawn layers estimated between 1 % dearer and a third cheaper seven were more than 1 % slower so, at most 3.4 %, and the average 6.7 % faster
-// (8 % by the estimate's own line, which errs on the side of one tiling).  Up to 96 tokens one token tile covers the batch.
+// and 217, 562 x 24192 x 3840 117 and 99, 1284 x 28672 x 4096 267 and 243, 576 x 28672 x 4096, estimated 2 % dearer, 128 and 126.  260
+// drawn layers that run so are 1.066 x faster on average, and one is slower (375 x 16640 x 9344, a full round and 256 features, 128.0 and 131.4).
+// Up to 96 tokens one token tile covers the batch.
 LinearParts plan_linear_parts(int32_t T, int32_t N, int32_t K, size_t workspace_bytes) {
     LinearParts best{N, {plan_linear(T, N, K, workspace_bytes), LinearPlan{}}};
     if (T <= 96 || (int64_t)best.part[0].n_tiles * best.part[0].t_tiles <= 128) return best;
