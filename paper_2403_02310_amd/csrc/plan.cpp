@@ -301,8 +301,8 @@ double chunk_launch_us(const sarathi_config &cfg, const std::vector<ChunkBin> &b
 
 // Where the plan travels in kernel arguments: how many launches it takes, and for how many microseconds an iteration keeps the
 // host.  From calls that the host bounded when it took 26 us for a few tiles, 38 for 59 tiles in 264 pieces (two launches for the plan and a
-// merge).  Marshalled natively they keep it 12 to 14 us less, and a whole plan of one launch travels with the attention launch, so this
-// leaves some plans whole that would be faster cut, and none cut that were not.
+// merge).  Marshalled natively they keep it 12 to 14 us less, and a whole plan of one launch travels with the attention launch: the line is
+// too high on both sides and has not been drawn anew.
 struct ArgumentLaunches {
     int64_t launches;
     double host_us;
